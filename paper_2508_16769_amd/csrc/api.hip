@@ -146,14 +146,10 @@ int dr_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const floa
     return launch_spmm_bwd_adaptive(At, edge_class, dH, xr_idx, D, cls, dXr, accumulate, as_stream(stream));
 }
 
-static size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-
 size_t dr_csr_transpose_workspace_bytes(int64_t n_rows, int64_t n_cols, int64_t nnz) {
     (void)n_rows;
     if (n_cols < 0 || nnz < 0) return 0;
-    // cursor[n_cols] | edge key[nnz] | edge row[nnz] | block sums | counter and list of the rows of more than 64 entries
-    return align256(4 * (size_t)(n_cols + 1)) + 2 * align256(4 * (size_t)(nnz + 1)) +
-           align256(4 * ((size_t)(n_cols + 1) / 1024 + 2)) + align256(4 * ((size_t)n_cols + 64));
+    return csr_transpose_workspace(n_cols, nnz);
 }
 
 int dr_csr_transpose(const dr_csr* A, int32_t* t_rowptr, int32_t* t_colidx, float* t_vals, void* workspace,
@@ -168,14 +164,14 @@ int dr_csr_transpose(const dr_csr* A, int32_t* t_rowptr, int32_t* t_colidx, floa
     DRC_REQUIRE(aligned(workspace, 256), "dr_csr_transpose: workspace must be 256-byte aligned");
     if (workspace_bytes < need)
         return fail(DR_ERR_WORKSPACE, "dr_csr_transpose: workspace has %zu bytes, needs %zu", workspace_bytes, need);
-    return launch_csr_transpose(A, t_rowptr, t_colidx, t_vals, workspace, as_stream(stream));
+    const TransposeJob job{A, t_rowptr, t_colidx, t_vals, workspace};
+    return launch_csr_transposes(&job, 1, as_stream(stream));
 }
 
 size_t dr_csr_normalize_workspace_bytes(int mode, int64_t n_rows, int64_t n_cols, int64_t nnz) {
     (void)n_rows;
-    (void)nnz;
-    if (mode != DR_NORM_SYM || n_cols < 0) return 0;
-    return align256(4 * (size_t)(n_cols + 1));
+    if (n_cols < 0 || nnz < 0) return 0;
+    return csr_normalize_workspace(mode, n_cols, nnz);
 }
 
 int dr_csr_normalize(int mode, int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* rowptr,

@@ -63,8 +63,15 @@ int launch_spmm_fwd_adaptive(const dr_csr* A, const float* xr_vals, const uint16
 int launch_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const float* dH, const uint16_t* xr_idx, int D,
                              const dr_degree_classes* c, float* dXr, int accumulate, hipStream_t s);
 int launch_edge_classes(const dr_csr* At, const int32_t* a_rowptr, const dr_degree_classes* c, uint8_t* out, hipStream_t s);
-int launch_csr_transpose(const dr_csr* A, int32_t* t_rowptr, int32_t* t_colidx, float* t_vals, void* ws,
-                         hipStream_t s);
+struct TransposeJob {             // one relation of a set that is transposed by the same launches (each with its own workspace)
+    const dr_csr* A;
+    int32_t *t_rowptr, *t_colidx;
+    float* t_vals;                // may be null (pattern only)
+    void* ws;                     // csr_transpose_workspace() bytes, 256-byte aligned
+};
+size_t csr_transpose_workspace(int64_t n_cols, int64_t nnz);
+int launch_csr_transposes(const TransposeJob* jobs, int n, hipStream_t s);
+size_t csr_normalize_workspace(int mode, int64_t n_cols, int64_t nnz);
 int launch_csr_normalize(int mode, int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* rowptr,
                          const int32_t* colidx, float* vals_out, void* ws, hipStream_t s);
 int launch_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t* rowptr,

@@ -221,12 +221,14 @@ int drc::heteroconv_bind(dr_heteroconv* c, const dr_csr* near, const dr_csr* pin
         spmm_plan_destroy(c->near_plan);
         c->near_plan = nullptr;
     }
+    TransposeJob jobs[3];
     for (int i = 0; i < 3; ++i) {
         const dr_csr& A = c->A[i];
         DRC_REQUIRE(c->t_ws[i] != nullptr, "heteroconv_bind: context without transpose workspace");
-        DRC_TRY(dr_csr_transpose(&A, c->t_rp[i], c->t_ci[i], c->t_v[i], c->t_ws[i], c->t_wsb[i], s));
+        jobs[i] = TransposeJob{&c->A[i], c->t_rp[i], c->t_ci[i], c->t_v[i], c->t_ws[i]};
         c->At[i] = dr_csr{A.n_cols, A.n_rows, A.nnz, c->t_rp[i], c->t_ci[i], c->t_v[i]};
     }
+    DRC_TRY(launch_csr_transposes(jobs, 3, s));
     return DR_OK;
 }
 

@@ -1,0 +1,56 @@
+"""Stable transpose and edge values at the sizes where the column partition changes shape: bucket and tile edges, runs of
+empty rows longer than a wavefront, one column that holds everything, more columns than one bucket's workgroup owns."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+def _pattern(rng, M, N, E, law):
+    """CSR pattern with E entries; integers only, so the comparison is exact."""
+    if law == "one_row":
+        rows = np.full(E, M // 2)
+    elif law == "tail_rows":                      # long runs of empty rows in front of and between the rows that hold entries
+        rows = rng.choice(np.array([0, M // 3, M - 1]), E)
+    else:
+        rows = rng.integers(0, M, E)
+    cols = np.full(E, N - 1) if law == "one_col" else rng.integers(0, N, E)
+    if law == "skewed_cols":                      # half of all entries in 3 columns
+        hot = rng.random(E) < 0.5
+        cols[hot] = rng.choice(np.array([0, N // 2, N - 1]), int(hot.sum()))
+    rows = np.sort(rows, kind="stable")
+    rp = np.zeros(M + 1, np.int32)
+    np.cumsum(np.bincount(rows, minlength=M), out=rp[1:])
+    return rp, cols.astype(np.int32)
+
+
+@pytest.mark.parametrize("M,N,E,law", [
+    (1, 1, 1, "uniform"), (3, 64, 63, "uniform"), (3, 65, 65, "uniform"), (700, 4096, 4095, "uniform"),
+    (700, 4097, 4097, "skewed_cols"), (5000, 1, 3000, "uniform"), (5000, 333, 9000, "tail_rows"), (1, 90_000, 8193, "one_row"),
+    (40_000, 65_537, 300_001, "skewed_cols"), (9_000, 2_000, 70_000, "one_col"), (100_000, 1_300_000, 2_100_000, "uniform"),
+    (60_000, 2_200_001, 400_000, "skewed_cols"),
+])
+def test_transpose_and_values_exact(M, N, E, law):
+    import torch
+    import paper_2508_16769_amd as P
+    say(f"setup M={M} N={N} E={E} {law}")
+    rng = np.random.default_rng(M + 7 * N + 11 * E)
+    rp, ci = _pattern(rng, M, N, E, law)
+    d_rp, d_ci = torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda()
+    deg_in, deg_out = np.diff(rp).astype(np.float64), np.bincount(ci, minlength=N).astype(np.float64)
+    rows = np.repeat(np.arange(M), np.diff(rp))
+    for mode in (P.DR_NORM_MEAN, P.DR_NORM_SYM):
+        vals = torch.empty(E, dtype=torch.float32, device="cuda")
+        ws = torch.empty(max(256, P.dr_csr_normalize_workspace_bytes(mode, M, N, E)), dtype=torch.uint8, device="cuda")
+        P.dr_csr_normalize(mode, M, N, d_rp, d_ci, vals, ws)
+        want = 1.0 / deg_in[rows] if mode == P.DR_NORM_MEAN else 1.0 / np.sqrt(deg_in[rows] * deg_out[ci])
+        assert np.array_equal(vals.cpu().numpy(), want.astype(np.float32))
+    ids = torch.arange(E, dtype=torch.int32, device="cuda").view(torch.float32)      # the values name the entries
+    At = P.device_transpose(P.Csr(M, N, d_rp, d_ci, ids))
+    t_rp, t_ci, _ = oracle.csr_transpose(M, N, rp, ci, np.ones(E, np.float64))
+    assert np.array_equal(At.rowptr.cpu().numpy(), t_rp)
+    assert np.array_equal(At.colidx.cpu().numpy(), t_ci)
+    assert np.array_equal(At.vals.view(torch.int32).cpu().numpy(), np.argsort(ci, kind="stable"))
