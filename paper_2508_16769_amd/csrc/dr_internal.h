@@ -53,6 +53,25 @@ int launch_topk(const float* X, int64_t n, int D, int k, float* vals, uint16_t* 
 // the same rows selected at two widths in one pass over X (vals2 == nullptr: only the first)
 int launch_topk2(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, int k2, float* vals2, uint16_t* idx2,
                  hipStream_t s);
+// DR-SpMM.  A job is one relation; jobs of one call may share launches and run side by side.
+constexpr int kMaxSegs = 24;     // relations per launch (their descriptors travel as kernel arguments)
+struct SpmmFwdJob {
+    const dr_csr* A;
+    const float* xs_vals;
+    const uint16_t* xs_idx;
+    int k;
+    float* H;
+};
+struct SpmmBwdJob {
+    const dr_csr* At;
+    const float* dH;
+    const uint16_t* xs_idx;
+    int k;
+    float* dXs;
+    int accumulate;
+};
+int launch_spmm_fwds(const SpmmFwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
+int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
 int launch_spmm_fwd(const dr_csr* A, const float* xs_vals, const uint16_t* xs_idx, int D, int k, float* H,
                     hipStream_t s);
 int launch_spmm_bwd(const dr_csr* At, const float* dH, const uint16_t* xs_idx, int D, int k, float* dXs,

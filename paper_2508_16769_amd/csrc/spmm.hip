@@ -1,18 +1,20 @@
-// DR-SpMM forward (paper Section 3.2 / Alg. 1) and backward (Section 3.3 / Alg. 2) for one relation.
+// DR-SpMM forward (paper Section 3.2 / Alg. 1) and backward (Section 3.3 / Alg. 2).
 //
-// Work decomposition (both directions).  A workgroup is ONE wavefront and owns kRW consecutive CSR rows;
-// there are no workgroup barriers to wait at, and the hardware dispatcher balances the (uneven) blocks.
+// Work decomposition (both directions).  A wavefront owns RW consecutive CSR rows; the four wavefronts of a workgroup
+// work independently except on very long rows, and the hardware dispatcher balances the (uneven) workgroups.
 //   * The wavefront is split into 8 groups of 8 lanes; a group owns one row at a time and walks that
 //     row's edges in storage order, so 8 rows are in flight per wavefront (the wave64 counterpart of the
 //     paper's "partition the warp into parts, one neighbour each") and every row sum has one fixed
 //     order: results are reproducible bit for bit.
-//   * The block's rows are ranked by degree, longest first, and a group that finishes a row takes the
+//   * The wavefront's rows are ranked by degree, longest first, and a group that finishes a row takes the
 //     next undealt one (a counter in LDS): the long rows start early, the short ones fill the gaps, and
 //     the per-group totals come out balanced -- the paper's degree classes, resolved per block at run
 //     time.  Which group sums a row does not change the order of that row's sum.
 //   * Rows with more than kSolo edges are not given to one group: all 8 groups stride over their edges
-//     into per-group partial sums that are then added in a fixed order (high-fanout nets, the tail of
-//     the power-law `near` degrees).
+//     into per-group partial sums that are then added in a fixed order (the tail of the power-law `near` degrees).
+//   * Rows with more than kLong edges (high-fanout nets) are left to the end and then walked by all 32 groups of the
+//     workgroup: one wavefront alone takes some 20 us per thousand edges, which on a 250 000-cell graph was as long as
+//     all the rest of the launch (0.127 ms with 180 such nets against 0.064 ms for the relation's transpose, k = 8).
 //   * Edge records (source column, edge value) are staged into LDS in sorted-row order with independent
 //     coalesced loads.  A group then consumes its rows as ONE stream of records across row boundaries,
 //     so the gather pipeline never drains between rows (rows have only a handful of edges).
@@ -25,6 +27,8 @@
 //     of the whole layer step).
 //   * Workgroup ids are remapped so each XCD walks a contiguous range of row blocks: neighbouring rows of
 //     the spatially local `near` relation gather overlapping source rows, which then hit in that XCD's L2.
+//   * One launch serves several relations (and several sub-graphs): the workgroups of an XCD take its share of the first
+//     relation's blocks, then of the next one's.  Small relations fill the chip together instead of one after the other.
 //
 //   * Cache policy: what is read or written exactly once (the CSR records, the saved-index window, the
 //     dense output rows) uses non-temporal loads and stores, so that the streams do not evict the gathered
@@ -46,52 +50,57 @@ namespace drc {
 
 constexpr int kLPE = 8;          // lanes per row group
 constexpr int kNG = kWave / kLPE;  // groups per wavefront
-constexpr int kRW = 32;          // rows per wavefront-workgroup
-constexpr int kSolo = 32;        // rows with more edges are walked by all 8 groups together
+constexpr int kWPB = 4;          // wavefronts per workgroup
+constexpr int kSolo = 32;        // rows with more edges are walked by all 8 groups of the wavefront together
+constexpr int kLong = 256;       // rows with more edges are walked by all wavefronts of the workgroup together
 constexpr int kCap = 256;        // edge records staged in LDS per pass (rows never straddle passes); 2 KB keeps
-                                 // a forward workgroup below 7 KB of LDS, i.e. 23 workgroups per CU
+                                 // a forward workgroup below 27 KB of LDS, i.e. six of them per CU
 constexpr int kStageIters = kCap / kWave;
 constexpr int kBufPad = 4;       // row buffers are D + 4 words apart: group g starts 4 banks after group g-1
 constexpr unsigned kValid = 0x80000000u, kLast = 0x40000000u, kRowMask = 0x0000ffffu;
 
-struct WavePlan {
-    int* sRp;      // [kRW + 1] row pointers of the block
-    int* sOrder;   // [kRW]     slot -> local row; solo rows by degree, descending
-    int* sStart;   // [kRW + 1] slot -> offset of the row's records in sorted-row order
-    int2* sRec;    // [kCap]    staged (column, value bits) records
-    int* sNext;    // [1]       next undealt slot of the current pass
+template <int RW> struct WavePlan {
+    int* sRp;      // [RW + 1] row pointers of the wavefront's rows
+    int* sOrder;   // [RW]     slot -> local row; solo rows by degree, descending
+    int* sStart;   // [RW + 1] slot -> offset of the row's records in sorted-row order
+    int2* sRec;    // [kCap]   staged (column, value bits) records
+    int* sNext;    // [1]      next undealt slot of the current pass
     int n_solo;
-    unsigned long long coop_mask, zero_mask;
+    unsigned long long coop_mask, zero_mask, long_mask;
 };
 
-__host__ __device__ constexpr int plan_ints() { return (kRW + 1) + kRW + (kRW + 1) + 2 + 2 /*pad*/ + 2 * kCap; }
+template <int RW> __host__ __device__ constexpr int plan_ints() { return 2 * kCap + (RW + 1) + RW + (RW + 1) + 2; }   // even: 3 RW + 4 + 2 kCap
 
-__device__ __forceinline__ void lds_fence() { __syncthreads(); }   // one wavefront per workgroup: orders LDS traffic
+// Orders the LDS accesses of one wavefront for the compiler (the hardware keeps them in program order).
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
-__device__ __forceinline__ WavePlan make_plan(int* base, const int32_t* __restrict__ rowptr, int r0, int nr) {
-    WavePlan p;
-    p.sRp = base;
-    p.sOrder = p.sRp + (kRW + 1);
-    p.sStart = p.sOrder + kRW;
-    p.sNext = p.sStart + (kRW + 1);
-    int* r = p.sNext + 2;
-    r += (reinterpret_cast<uintptr_t>(r) & 7) ? 1 : 0;   // 8-byte alignment for int2
-    p.sRec = reinterpret_cast<int2*>(r);
+template <int RW>
+__device__ __forceinline__ WavePlan<RW> make_plan(int* base, const int32_t* __restrict__ rowptr, int r0, int nr) {
+    WavePlan<RW> p;
+    p.sRec = reinterpret_cast<int2*>(base);
+    p.sRp = base + 2 * kCap;
+    p.sOrder = p.sRp + (RW + 1);
+    p.sStart = p.sOrder + RW;
+    p.sNext = p.sStart + (RW + 1);
 
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
     const int rp_lo = rowptr[r0 + min(lane, nr)];
     const int rp_hi = rowptr[r0 + min(lane + 1, nr)];
     if (lane <= nr) p.sRp[lane] = rp_lo;
     const int deg = (lane < nr) ? (rp_hi - rp_lo) : -1;
     const bool solo = deg >= 1 && deg <= kSolo;
-    p.coop_mask = __ballot(deg > kSolo);
+    p.long_mask = __ballot(deg > kLong);
+    p.coop_mask = __ballot(deg > kSolo && deg <= kLong);
     p.zero_mask = __ballot(deg == 0);
     p.n_solo = __popcll(__ballot(solo));
     // rank of every solo row among the solo rows: degree descending, row ascending
     const int key = solo ? deg : -1;
     int rank = 0;
 #pragma unroll
-    for (int j = 0; j < kRW; ++j) {
+    for (int j = 0; j < RW; ++j) {
         const int kj = __shfl(key, j, kWave);
         rank += (kj > key || (kj == key && j < lane)) ? 1 : 0;
     }
@@ -114,10 +123,10 @@ __device__ __forceinline__ WavePlan make_plan(int* base, const int32_t* __restri
 }
 
 // End slot of the pass that starts at slot sa: as many whole solo rows as fit kCap records (at least one).
-__device__ __forceinline__ int pass_end(const WavePlan& p, int sa) {
-    const int lane = threadIdx.x;
+template <int RW> __device__ __forceinline__ int pass_end(const WavePlan<RW>& p, int sa) {
+    const int lane = threadIdx.x & (kWave - 1);
     const int base = p.sStart[sa];
-    const bool fits = lane > sa && lane <= p.n_solo && p.sStart[lane] - base <= kCap;
+    const bool fits = lane > sa && lane <= p.n_solo && p.sStart[min(lane, p.n_solo)] - base <= kCap;
     return sa + __popcll(__ballot(fits));
 }
 
@@ -130,10 +139,11 @@ __device__ __forceinline__ int tag_class(int col, const uint8_t* __restrict__ ec
     return ecls ? (col | ((int)__builtin_nontemporal_load(ecls + e) << 30)) : col;
 }
 
-__device__ __forceinline__ void stage_solo(const WavePlan& p, const int32_t* __restrict__ colidx,
+template <int RW>
+__device__ __forceinline__ void stage_solo(const WavePlan<RW>& p, const int32_t* __restrict__ colidx,
                                            const float* __restrict__ avals, int sa, int sb,
                                            const uint8_t* __restrict__ ecls = nullptr) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
     const int base = p.sStart[sa];
     const int total = p.sStart[sb] - base;
     int2 r[kStageIters];
@@ -158,10 +168,11 @@ __device__ __forceinline__ void stage_solo(const WavePlan& p, const int32_t* __r
 }
 
 // Stages records [c0, c0 + n) of one long row (n <= kCap, n >= 1).
-__device__ __forceinline__ void stage_chunk(const WavePlan& p, const int32_t* __restrict__ colidx,
+template <int RW>
+__device__ __forceinline__ void stage_chunk(const WavePlan<RW>& p, const int32_t* __restrict__ colidx,
                                             const float* __restrict__ avals, int c0, int n,
                                             const uint8_t* __restrict__ ecls = nullptr) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
     int2 r[kStageIters];
 #pragma unroll
     for (int j = 0; j < kStageIters; ++j) {
@@ -186,7 +197,8 @@ struct Stream {
     // Every member is assigned on every path (selects, no branches): with a member written on one side of a branch
     // only, the compiler keeps the record in scratch memory and stores through a selected address, and a scratch
     // access is a vector-memory operation -- waiting for it drains the gathers in flight.
-    __device__ __forceinline__ void take_slot(const WavePlan& p, int li, int sa, int npass, int base) {
+    template <int RW>
+    __device__ __forceinline__ void take_slot(const WavePlan<RW>& p, int li, int sa, int npass, int base) {
         const bool ok = li < npass;
         const int s = sa + (ok ? li : 0);
         const int c = p.sStart[s] - base, e = p.sStart[s + 1] - base, r = p.sOrder[s];
@@ -195,16 +207,17 @@ struct Stream {
         row = ok ? r : row;
         done = ok ? done : 1;
     }
-    __device__ __forceinline__ void next_row(const WavePlan& p, int sa, int npass, int base) {
-        const int lane = threadIdx.x;
+    template <int RW>
+    __device__ __forceinline__ void next_row(const WavePlan<RW>& p, int sa, int npass, int base) {
+        const int lane = threadIdx.x & (kWave - 1);
         int li = 0;
         if ((lane & (kLPE - 1)) == 0) li = atomicAdd(p.sNext, 1);
         li = __shfl(li, lane & ~(kLPE - 1), kWave);
         take_slot(p, li, sa, npass, base);
     }
     // returns the meta word of the record just taken and advances
-    template <bool STRIDED>
-    __device__ __forceinline__ unsigned advance(const WavePlan& p, int sa, int npass, int base) {
+    template <bool STRIDED, int RW>
+    __device__ __forceinline__ unsigned advance(const WavePlan<RW>& p, int sa, int npass, int base) {
         unsigned m = kValid | (unsigned)row;
         if constexpr (STRIDED) {
             cur += kNG;
@@ -318,8 +331,8 @@ struct DegreeK {
     __device__ __forceinline__ int width_of_class(int c, int k1) const { return c == 0 ? k1 : (c == 1 ? k2 : k3); }
 };
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT>
-__device__ __forceinline__ void fwd_issue(FwdBatch<KPL, EPI>& b, Stream& st, const WavePlan& plan,
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+__device__ __forceinline__ void fwd_issue(FwdBatch<KPL, EPI>& b, Stream& st, const WavePlan<RW>& plan,
                                           const float* __restrict__ xs_vals, const uint16_t* __restrict__ xs_idx,
                                           int D, int k, int t, int g, int sa, int npass, int base, const DegreeK& dk) {
 #pragma unroll
@@ -329,9 +342,10 @@ __device__ __forceinline__ void fwd_issue(FwdBatch<KPL, EPI>& b, Stream& st, con
         const uint32_t col = valid ? (uint32_t)rec.x : 0u;   // exhausted lanes gather source row 0
         b.a[q] = __int_as_float(rec.y);
         int kk = k;                                          // pairs of the gathered row this destination takes
-        if constexpr (ADAPT) kk = dk.width(plan.sRp[st.row + 1] - plan.sRp[st.row], k);   // a prefix of the rank order
+        // (strided: one row, whose width the caller has put into k1 and k2 = k3 = k1)
+        if constexpr (ADAPT) kk = STRIDED ? dk.k3 : dk.width(plan.sRp[st.row + 1] - plan.sRp[st.row], k);   // a prefix of the rank order
         b.p[q].template load<ADAPT>(xs_vals, xs_idx, col * (uint32_t)k, t, kk, D);
-        b.meta[q] = valid ? st.template advance<STRIDED>(plan, sa, npass, base) : 0u;
+        b.meta[q] = valid ? st.template advance<STRIDED, RW>(plan, sa, npass, base) : 0u;
     }
 }
 
@@ -347,19 +361,19 @@ __device__ __forceinline__ void fwd_consume(const FwdBatch<KPL, EPI>& b, float* 
     }
 }
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT>
-__device__ __forceinline__ void fwd_run(Stream& st, const WavePlan& plan, const float* __restrict__ xs_vals,
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+__device__ __forceinline__ void fwd_run(Stream& st, const WavePlan<RW>& plan, const float* __restrict__ xs_vals,
                                         const uint16_t* __restrict__ xs_idx, float* buf, float* __restrict__ Hblk,
                                         int D, int k, int t, int g, int sa, int npass, int base, int vec_store,
                                         const DegreeK& dk) {
     if constexpr (KPL != 0) {
         FwdBatch<KPL, EPI> A, B;
-        fwd_issue<KPL, EPI, STRIDED, ADAPT>(A, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
+        fwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
         for (;;) {
-            fwd_issue<KPL, EPI, STRIDED, ADAPT>(B, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
+            fwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(B, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
             fwd_consume(A, buf, Hblk, D, t, vec_store);
             if (!__any(B.meta[0] & kValid)) break;
-            fwd_issue<KPL, EPI, STRIDED, ADAPT>(A, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
+            fwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, plan, xs_vals, xs_idx, D, k, t, g, sa, npass, base, dk);
             fwd_consume(B, buf, Hblk, D, t, vec_store);
             if (!__any(A.meta[0] & kValid)) break;
         }
@@ -374,33 +388,61 @@ __device__ __forceinline__ void fwd_run(Stream& st, const WavePlan& plan, const 
                     const int c = xs_idx[rb + q];
                     buf[c] = fmaf(a, xs_vals[rb + q], buf[c]);
                 }
-                const unsigned m = st.template advance<STRIDED>(plan, sa, npass, base);
+                const unsigned m = st.template advance<STRIDED, RW>(plan, sa, npass, base);
                 if (m & kLast) flush_row(Hblk + (size_t)(m & kRowMask) * D, buf, D, t, vec_store);
             }
         }
     }
 }
 
-template <int KPL, int EPI, bool ADAPT>
-__global__ __launch_bounds__(kWave) void spmm_fwd_kernel(
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx, const float* __restrict__ avals,
-    const float* __restrict__ xs_vals, const uint16_t* __restrict__ xs_idx, float* __restrict__ H,
-    int M, int D, int k, int n_tiles, int per_xcd, int vec_store, DegreeK dk) {
+struct SpmmFwdSeg {              // one relation of a launch
+    const int32_t *rowptr, *colidx;
+    const float *avals, *xs_vals;
+    const uint16_t* xs_idx;
+    float* H;
+    int M, k, vec_store;
+    int n_blocks, per_xcd, first;      // workgroups of this relation, per XCD, and where they start in an XCD's sequence
+};
+struct SpmmFwdArgs { SpmmFwdSeg s[kMaxSegs]; int n, D; };
+
+// wavefronts per SIMD the registers are budgeted for (six fit the LDS as well)
+constexpr int fwd_waves(int kpl, bool adapt) { return kpl == 16 || kpl == -8 ? 4 : (adapt || kpl < 0 || kpl > 1 ? 5 : 6); }
+
+template <int KPL, int EPI, int RW, bool ADAPT>
+__global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_kernel(SpmmFwdArgs args, DegreeK dk) {
     static_assert(!ADAPT || KPL != 0, "the adaptive-K forward needs a path that can mask pairs");
     extern __shared__ float4 smem4[];
-    float* rowbuf = reinterpret_cast<float*>(smem4);                 // [kNG][D], 16-byte aligned
-    const int tile_id = xcd_contiguous_tile(blockIdx.x, per_xcd);
-    if (tile_id >= n_tiles) return;
-    const int r0 = tile_id * kRW;
-    const int nr = min(kRW, M - r0);
-    const int lane = threadIdx.x;
+    __shared__ unsigned long long sLong[kWPB];
+    const int local = blockIdx.x / kNumXcd, xcd = blockIdx.x % kNumXcd;
+    int sg = 0;
+    while (sg + 1 < args.n && local >= args.s[sg + 1].first) ++sg;
+    const SpmmFwdSeg& s = args.s[sg];
+    const int blk = xcd * s.per_xcd + local - s.first;
+    if (blk >= s.n_blocks) return;
+    const int32_t* __restrict__ rowptr = s.rowptr;
+    const int32_t* __restrict__ colidx = s.colidx;
+    const float* __restrict__ avals = s.avals;
+    const float* __restrict__ xs_vals = s.xs_vals;
+    const uint16_t* __restrict__ xs_idx = s.xs_idx;
+    const int D = args.D, k = s.k, vec_store = s.vec_store;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r0 = min((blk * kWPB + wave) * RW, s.M);
+    const int nr = min(RW, s.M - r0);
     const int g = lane / kLPE, t = lane % kLPE;
     const int ldb = D + kBufPad;
+    const int wave_words = kNG * ldb + plan_ints<RW>();
+    float* const base0 = reinterpret_cast<float*>(smem4);
+    float* rowbuf = base0 + wave * wave_words;                       // [kNG][ldb], 16-byte aligned
     float* buf = rowbuf + g * ldb;
-    float* Hblk = H + (size_t)r0 * D;
+    float* Hblk = s.H + (size_t)r0 * D;
 
     for (int i = lane; i < kNG * ldb; i += kWave) rowbuf[i] = 0.0f;
-    WavePlan plan = make_plan(reinterpret_cast<int*>(rowbuf + kNG * ldb), rowptr, r0, nr);
+    WavePlan<RW> plan = make_plan<RW>(reinterpret_cast<int*>(rowbuf + kNG * ldb), rowptr, r0, nr);
+    if (lane == 0) sLong[wave] = plan.long_mask;
+    __syncthreads();
+    unsigned long long any_long = 0;
+#pragma unroll
+    for (int w = 0; w < kWPB; ++w) any_long |= sLong[w];
 
     // ---- rows without edges: zeros ----
     for (unsigned long long m = plan.zero_mask; m; m &= m - 1) {
@@ -411,25 +453,24 @@ __global__ __launch_bounds__(kWave) void spmm_fwd_kernel(
     // ---- long rows: all groups stride over the row, partial sums added in a fixed order ----
     for (unsigned long long m = plan.coop_mask; m; m &= m - 1) {
         const int row = __ffsll((long long)m) - 1;
-        const int e0 = plan.sRp[row], e1 = plan.sRp[row + 1];
-        for (int c0 = e0; c0 < e1; c0 += kCap) {
-            const int n = min(kCap, e1 - c0);
-            lds_fence();
-            stage_chunk(plan, colidx, avals, c0, n);
-            lds_fence();
-            Stream st{g, n, row, g >= n ? 1 : 0};
-            fwd_run<KPL, EPI, true, ADAPT>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dk);
-        }
+        const int e0 = plan.sRp[row], n = plan.sRp[row + 1] - e0;    // n <= kLong = kCap: one staged chunk
+        DegreeK dkr = dk;
+        if constexpr (ADAPT) dkr.k3 = dk.width(n, k);
+        lds_fence();
+        stage_chunk(plan, colidx, avals, e0, n);
+        lds_fence();
+        Stream st{g, n, row, g >= n ? 1 : 0};
+        fwd_run<KPL, EPI, true, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dkr);
         lds_fence();
         float* out = Hblk + (size_t)row * D;
         for (int c = lane; c < D; c += kWave) {
-            float s = 0.0f;
+            float sum = 0.0f;
 #pragma unroll
             for (int q = 0; q < kNG; ++q) {
-                s += rowbuf[q * ldb + c];
+                sum += rowbuf[q * ldb + c];
                 rowbuf[q * ldb + c] = 0.0f;
             }
-            __builtin_nontemporal_store(s, out + c);
+            __builtin_nontemporal_store(sum, out + c);
         }
         lds_fence();
     }
@@ -443,78 +484,153 @@ __global__ __launch_bounds__(kWave) void spmm_fwd_kernel(
         lds_fence();
         Stream st{0, 0, 0, 0};
         st.take_slot(plan, g, sa, sb - sa, plan.sStart[sa]);     // first 8 rows of the pass: one per group
-        fwd_run<KPL, EPI, false, ADAPT>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, sa, sb - sa, plan.sStart[sa],
-                                        vec_store, dk);
+        fwd_run<KPL, EPI, false, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, sa, sb - sa, plan.sStart[sa],
+                                            vec_store, dk);
         sa = sb;
+    }
+
+    // ---- very long rows of the whole workgroup: each wavefront takes a quarter of the row ----
+    if (!any_long) return;
+    for (int w = 0; w < kWPB; ++w) {
+        for (unsigned long long m = sLong[w]; m; m &= m - 1) {
+            const int row = (blk * kWPB + w) * RW + __ffsll((long long)m) - 1;
+            const int e0 = rowptr[row], e1 = rowptr[row + 1];
+            DegreeK dkr = dk;
+            if constexpr (ADAPT) dkr.k3 = dk.width(e1 - e0, k);
+            const int per = (e1 - e0 + kWPB - 1) / kWPB;
+            const int w0 = min(e0 + wave * per, e1), w1 = min(w0 + per, e1);
+            for (int c0 = w0; c0 < w1; c0 += kCap) {
+                const int n = min(kCap, w1 - c0);
+                lds_fence();
+                stage_chunk(plan, colidx, avals, c0, n);
+                lds_fence();
+                Stream st{g, n, 0, g >= n ? 1 : 0};
+                fwd_run<KPL, EPI, true, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dkr);
+            }
+            __syncthreads();
+            float* out = s.H + (size_t)row * D;
+            for (int c = threadIdx.x; c < D; c += kWPB * kWave) {
+                float sum = 0.0f;
+                for (int q = 0; q < kWPB; ++q)
+#pragma unroll
+                    for (int p = 0; p < kNG; ++p) {
+                        float* b = base0 + q * wave_words + p * ldb + c;
+                        sum += *b;
+                        *b = 0.0f;
+                    }
+                __builtin_nontemporal_store(sum, out + c);
+            }
+            __syncthreads();
+        }
     }
 }
 
-int launch_spmm_fwd(const dr_csr* A, const float* xs_vals, const uint16_t* xs_idx, int D, int k, float* H,
-                    hipStream_t s) {
-    const int M = (int)A->n_rows;
-    if (A->nnz == 0) return launch_fill_u32(reinterpret_cast<uint32_t*>(H), (size_t)M * D, 0u, s);
-    const int n_tiles = (M + kRW - 1) / kRW;
-    const int per_xcd = (n_tiles + kNumXcd - 1) / kNumXcd;
-    const int vec_store = (D % 4 == 0 && aligned(H, 16)) ? 1 : 0;
+// Rows per wavefront: 32 fill the groups evenly (a group that finishes takes the next row); with few rows in all, 8 --
+// one per group -- put four times as many wavefronts on the chip and cut the serial chain of a wavefront to one row per
+// group.  The line: as long as 8 rows per wavefront still fit the chip at once (256 compute units x 24 wavefronts).
+static bool few_rows(int64_t rows) { return rows <= 8ll * 24 * 256; }
+
+static int fwd_kind(const SpmmFwdJob& j) {
+    const int k = j.k;
     int kpl = 0;
     if (k % kLPE == 0) {
         const int q = k / kLPE;
         if (q == 1) kpl = 1;
-        else if (q == 2 && aligned(xs_vals, 8) && aligned(xs_idx, 4)) kpl = 2;
-        else if ((q == 4 || q == 8 || q == 16) && aligned(xs_vals, 16) && aligned(xs_idx, 8)) kpl = q;
+        else if (q == 2 && aligned(j.xs_vals, 8) && aligned(j.xs_idx, 4)) kpl = 2;
+        else if ((q == 4 || q == 8 || q == 16) && aligned(j.xs_vals, 16) && aligned(j.xs_idx, 8)) kpl = q;
     }
     if (kpl == 0 && k <= 4 * kLPE) kpl = -((k + kLPE - 1) / kLPE);   // strided scalar pairs, masked past k
-    const size_t lds = sizeof(float) * (size_t)kNG * (D + kBufPad) + sizeof(int) * (size_t)plan_ints();
-    dim3 grid((unsigned)(per_xcd * kNumXcd)), block(kWave);
-#define DRC_LAUNCH_FWD(V, E)                                                                                              \
-    hipLaunchKernelGGL((spmm_fwd_kernel<V, E, false>), grid, block, lds, s, A->rowptr, A->colidx, A->vals, xs_vals, xs_idx, \
-                       H, M, D, k, n_tiles, per_xcd, vec_store, DegreeK{})
-    switch (kpl) {
-        case 1: DRC_LAUNCH_FWD(1, 4); break;
-        case 2: DRC_LAUNCH_FWD(2, 3); break;
-        case 4: DRC_LAUNCH_FWD(4, 2); break;
-        case 8: DRC_LAUNCH_FWD(8, 1); break;
-        case 16: DRC_LAUNCH_FWD(16, 1); break;
-        case -1: DRC_LAUNCH_FWD(-1, 4); break;
-        case -2: DRC_LAUNCH_FWD(-2, 3); break;
-        case -3: DRC_LAUNCH_FWD(-3, 2); break;
-        case -4: DRC_LAUNCH_FWD(-4, 2); break;
-        default: DRC_LAUNCH_FWD(0, 1); break;
+    return kpl;
+}
+
+template <int KPL, int EPI, bool ADAPT>
+static void launch_fwd_kernel(SpmmFwdArgs& a, DegreeK dk, hipStream_t s) {
+    int64_t rows = 0;
+    for (int i = 0; i < a.n; ++i) rows += a.s[i].M;
+    const bool few = few_rows(rows);
+    const int rw = few ? 8 : 32;
+    int first = 0;
+    for (int i = 0; i < a.n; ++i) {
+        SpmmFwdSeg& g = a.s[i];
+        g.n_blocks = (g.M + kWPB * rw - 1) / (kWPB * rw);
+        g.per_xcd = (g.n_blocks + kNumXcd - 1) / kNumXcd;
+        g.first = first;
+        first += g.per_xcd;
     }
-#undef DRC_LAUNCH_FWD
+    const size_t lds = sizeof(float) * kWPB * ((size_t)kNG * (a.D + kBufPad) + (few ? plan_ints<8>() : plan_ints<32>()));
+    const dim3 grid((unsigned)(first * kNumXcd)), block(kWPB * kWave);
+    if (few) hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 8, ADAPT>), grid, block, lds, s, a, dk);
+    else hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 32, ADAPT>), grid, block, lds, s, a, dk);
+}
+
+// Several relations at once: those whose width takes the same kernel share a launch.
+int launch_spmm_fwds(const SpmmFwdJob* jobs, int n, int D, hipStream_t s) {
+    unsigned long long done = 0;
+    for (int i = 0; i < n; ++i) {
+        if (done >> i & 1) continue;
+        const SpmmFwdJob& j = jobs[i];
+        if (j.A->n_rows == 0) continue;
+        if (j.A->nnz == 0) {
+            DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(j.H), (size_t)j.A->n_rows * D, 0u, s));
+            continue;
+        }
+        const int kind = fwd_kind(j);
+        SpmmFwdArgs a{};
+        a.D = D;
+        for (int r = i; r < n && a.n < kMaxSegs; ++r) {
+            const SpmmFwdJob& q = jobs[r];
+            if ((done >> r & 1) || q.A->nnz == 0 || fwd_kind(q) != kind) continue;
+            done |= 1ull << r;
+            SpmmFwdSeg& g = a.s[a.n++];
+            g = SpmmFwdSeg{q.A->rowptr, q.A->colidx, q.A->vals, q.xs_vals, q.xs_idx, q.H, (int)q.A->n_rows, q.k,
+                           (D % 4 == 0 && aligned(q.H, 16)) ? 1 : 0, 0, 0, 0};
+        }
+        switch (kind) {
+            case 1: launch_fwd_kernel<1, 4, false>(a, DegreeK{}, s); break;
+            case 2: launch_fwd_kernel<2, 3, false>(a, DegreeK{}, s); break;
+            case 4: launch_fwd_kernel<4, 2, false>(a, DegreeK{}, s); break;
+            case 8: launch_fwd_kernel<8, 1, false>(a, DegreeK{}, s); break;
+            case 16: launch_fwd_kernel<16, 1, false>(a, DegreeK{}, s); break;
+            case -1: launch_fwd_kernel<-1, 4, false>(a, DegreeK{}, s); break;
+            case -2: launch_fwd_kernel<-2, 3, false>(a, DegreeK{}, s); break;
+            case -3: launch_fwd_kernel<-3, 2, false>(a, DegreeK{}, s); break;
+            case -4: launch_fwd_kernel<-4, 2, false>(a, DegreeK{}, s); break;
+            default: launch_fwd_kernel<0, 1, false>(a, DegreeK{}, s); break;
+        }
+    }
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
 
+int launch_spmm_fwd(const dr_csr* A, const float* xs_vals, const uint16_t* xs_idx, int D, int k, float* H, hipStream_t s) {
+    const SpmmFwdJob j{A, xs_vals, xs_idx, k, H};
+    return launch_spmm_fwds(&j, 1, D, s);
+}
+
 int launch_spmm_fwd_adaptive(const dr_csr* A, const float* xr_vals, const uint16_t* xr_idx, int D, const dr_degree_classes* c,
                              float* H, hipStream_t s) {
-    const int M = (int)A->n_rows, k = c->k1;
-    if (A->nnz == 0) return launch_fill_u32(reinterpret_cast<uint32_t*>(H), (size_t)M * D, 0u, s);
-    const int n_tiles = (M + kRW - 1) / kRW;
-    const int per_xcd = (n_tiles + kNumXcd - 1) / kNumXcd;
-    const int vec_store = (D % 4 == 0 && aligned(H, 16)) ? 1 : 0;
-    const size_t lds = sizeof(float) * (size_t)kNG * (D + kBufPad) + sizeof(int) * (size_t)plan_ints();
+    const int k = c->k1;
+    if (A->nnz == 0) return launch_fill_u32(reinterpret_cast<uint32_t*>(H), (size_t)A->n_rows * D, 0u, s);
     const DegreeK dk{c->t1, c->t2, c->k2, c->k3};
-    dim3 grid((unsigned)(per_xcd * kNumXcd)), block(kWave);
-#define DRC_LAUNCH_FWD_A(V, E)                                                                                            \
-    hipLaunchKernelGGL((spmm_fwd_kernel<V, E, true>), grid, block, lds, s, A->rowptr, A->colidx, A->vals, xr_vals, xr_idx, \
-                       H, M, D, k, n_tiles, per_xcd, vec_store, dk)
+    SpmmFwdArgs a{};
+    a.D = D;
+    a.n = 1;
+    a.s[0] = SpmmFwdSeg{A->rowptr, A->colidx, A->vals, xr_vals, xr_idx, H, (int)A->n_rows, k, (D % 4 == 0 && aligned(H, 16)) ? 1 : 0, 0, 0, 0};
     // widths that fill the lanes evenly keep the vector loads of the uniform kernel (pairs past the destination's
     // width are redirected after the load); the others take the strided scalar pairs
     const bool vec = (k == 8) || (k == 16 && aligned(xr_vals, 8) && aligned(xr_idx, 4)) ||
                      ((k == 32 || k == 64) && aligned(xr_vals, 16) && aligned(xr_idx, 8));
     switch (vec ? k / kLPE + 100 : (k + kLPE - 1) / kLPE) {
-        case 101: DRC_LAUNCH_FWD_A(1, 4); break;
-        case 102: DRC_LAUNCH_FWD_A(2, 3); break;
-        case 104: DRC_LAUNCH_FWD_A(4, 2); break;
-        case 108: DRC_LAUNCH_FWD_A(8, 1); break;
-        case 1: DRC_LAUNCH_FWD_A(-1, 4); break;
-        case 2: DRC_LAUNCH_FWD_A(-2, 3); break;
-        case 3: DRC_LAUNCH_FWD_A(-3, 2); break;
-        case 4: DRC_LAUNCH_FWD_A(-4, 2); break;
-        default: DRC_LAUNCH_FWD_A(-8, 1); break;   // k1 <= 64 (checked by the caller)
+        case 101: launch_fwd_kernel<1, 4, true>(a, dk, s); break;
+        case 102: launch_fwd_kernel<2, 3, true>(a, dk, s); break;
+        case 104: launch_fwd_kernel<4, 2, true>(a, dk, s); break;
+        case 108: launch_fwd_kernel<8, 1, true>(a, dk, s); break;
+        case 1: launch_fwd_kernel<-1, 4, true>(a, dk, s); break;
+        case 2: launch_fwd_kernel<-2, 3, true>(a, dk, s); break;
+        case 3: launch_fwd_kernel<-3, 2, true>(a, dk, s); break;
+        case 4: launch_fwd_kernel<-4, 2, true>(a, dk, s); break;
+        default: launch_fwd_kernel<-8, 1, true>(a, dk, s); break;   // k1 <= 64 (checked by the caller)
     }
-#undef DRC_LAUNCH_FWD_A
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
@@ -542,8 +658,8 @@ __device__ __forceinline__ void load_ci(int (&ci)[KPL + 1], const uint16_t* sIdx
 
 constexpr unsigned kClassShift = 16;   // adaptive-K backward: degree class of the record's destination in meta bits 16-17
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT>
-__device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int (&ci)[KPL + 1], const WavePlan& plan,
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+__device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int (&ci)[KPL + 1], const WavePlan<RW>& plan,
                                           const uint16_t* sIdx, const float* __restrict__ dH, int D, int k, int t, int g,
                                           int sa, int npass, int base, const DegreeK& dk) {
 #pragma unroll
@@ -567,7 +683,7 @@ __device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int
         }
         unsigned m = 0;
         if (valid) {
-            m = st.template advance<STRIDED>(plan, sa, npass, base) | (cls << kClassShift);
+            m = st.template advance<STRIDED, RW>(plan, sa, npass, base) | (cls << kClassShift);
             if (!STRIDED && (m & kLast) && !st.done) load_ci<KPL>(ci, sIdx, st.row, t);
         }
         b.meta[q] = m;
@@ -601,41 +717,72 @@ __device__ __forceinline__ void bwd_consume(const BwdBatch<KPL, EPI>& b, float (
     }
 }
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT>
-__device__ __forceinline__ void bwd_run(Stream& st, int (&ci)[KPL + 1], float (&acc)[KPL], const WavePlan& plan,
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+__device__ __forceinline__ void bwd_run(Stream& st, int (&ci)[KPL + 1], float (&acc)[KPL], const WavePlan<RW>& plan,
                                         const uint16_t* sIdx, const float* __restrict__ dH, float* __restrict__ Gblk,
                                         int D, int k, int s0, int t, int g, int sa, int npass, int base,
                                         int accumulate, const DegreeK& dk) {
     BwdBatch<KPL, EPI> A, B;
-    bwd_issue<KPL, EPI, STRIDED, ADAPT>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
+    bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
     for (;;) {
-        bwd_issue<KPL, EPI, STRIDED, ADAPT>(B, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
+        bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(B, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
         bwd_consume<KPL, EPI, ADAPT>(A, acc, Gblk, k, s0, t, accumulate, dk);
         if (!__any(B.meta[0] & kValid)) break;
-        bwd_issue<KPL, EPI, STRIDED, ADAPT>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
+        bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
         bwd_consume<KPL, EPI, ADAPT>(B, acc, Gblk, k, s0, t, accumulate, dk);
         if (!__any(A.meta[0] & kValid)) break;
     }
 }
 
-template <int KPL, int EPI, bool ADAPT>
-__global__ __launch_bounds__(kWave) void spmm_bwd_kernel(
-    const int32_t* __restrict__ t_rowptr, const int32_t* __restrict__ t_colidx, const float* __restrict__ t_vals,
-    const float* __restrict__ dH, const uint16_t* __restrict__ xs_idx, float* __restrict__ dXs,
-    int N, int D, int k, int n_tiles, int per_xcd, int accumulate, const uint8_t* __restrict__ ecls, DegreeK dk) {
-    extern __shared__ float4 smem4[];
-    constexpr int kWin = kLPE * KPL;                                       // compact slots per pass over the block
-    float* part = reinterpret_cast<float*>(smem4);                         // [kNG][kWin] long-row partials
-    uint16_t* sIdx = reinterpret_cast<uint16_t*>(part + kNG * kWin);       // [kRW][kWin] saved columns of the window
-    const int tile_id = xcd_contiguous_tile(blockIdx.x, per_xcd);
-    if (tile_id >= n_tiles) return;
-    const int r0 = tile_id * kRW;
-    const int nr = min(kRW, N - r0);
-    const int lane = threadIdx.x;
-    const int g = lane / kLPE, t = lane % kLPE;
-    float* Gblk = dXs + (size_t)r0 * k;
+struct SpmmBwdSeg {              // one transposed relation of a launch
+    const int32_t *rowptr, *colidx;
+    const float *avals, *dH;
+    const uint16_t* xs_idx;
+    float* dXs;
+    const uint8_t* ecls;
+    int N, k, accumulate;
+    int n_blocks, per_xcd, first;
+};
+struct SpmmBwdArgs { SpmmBwdSeg s[kMaxSegs]; int n, D; };
 
-    WavePlan plan = make_plan(reinterpret_cast<int*>(sIdx + kRW * kWin), t_rowptr, r0, nr);
+template <int KPL, int RW> constexpr int bwd_wave_words() {     // LDS words of one wavefront
+    return kNG * kLPE * KPL + RW * kLPE * KPL / 2 + plan_ints<RW>();
+}
+
+template <int KPL, int EPI, int RW, bool ADAPT>
+__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk) {
+    extern __shared__ float4 smem4[];
+    __shared__ unsigned long long sLong[kWPB];
+    constexpr int kWin = kLPE * KPL;                                       // compact slots per pass over the block
+    constexpr int kWords = bwd_wave_words<KPL, RW>();
+    const int local = blockIdx.x / kNumXcd, xcd = blockIdx.x % kNumXcd;
+    int sg = 0;
+    while (sg + 1 < args.n && local >= args.s[sg + 1].first) ++sg;
+    const SpmmBwdSeg& s = args.s[sg];
+    const int blk = xcd * s.per_xcd + local - s.first;
+    if (blk >= s.n_blocks) return;
+    const int32_t* __restrict__ t_rowptr = s.rowptr;
+    const int32_t* __restrict__ t_colidx = s.colidx;
+    const float* __restrict__ t_vals = s.avals;
+    const float* __restrict__ dH = s.dH;
+    const uint16_t* __restrict__ xs_idx = s.xs_idx;
+    const uint8_t* __restrict__ ecls = ADAPT ? s.ecls : nullptr;
+    const int D = args.D, k = s.k, accumulate = s.accumulate;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* const base0 = reinterpret_cast<float*>(smem4);
+    float* part = base0 + wave * kWords;                                   // [kNG][kWin] long-row partials
+    uint16_t* sIdx = reinterpret_cast<uint16_t*>(part + kNG * kWin);       // [RW][kWin] saved columns of the window
+    const int r0 = min((blk * kWPB + wave) * RW, s.N);
+    const int nr = min(RW, s.N - r0);
+    const int g = lane / kLPE, t = lane % kLPE;
+    float* Gblk = s.dXs + (size_t)r0 * k;
+
+    WavePlan<RW> plan = make_plan<RW>(reinterpret_cast<int*>(part + kNG * kWin + RW * kWin / 2), t_rowptr, r0, nr);
+    if (lane == 0) sLong[wave] = plan.long_mask;
+    __syncthreads();
+    unsigned long long any_long = 0;
+#pragma unroll
+    for (int w = 0; w < kWPB; ++w) any_long |= sLong[w];
 
     for (int s0 = 0; s0 < k; s0 += kWin) {
         // saved columns of this window for every row of the block (0 beyond k)
@@ -658,30 +805,27 @@ __global__ __launch_bounds__(kWave) void spmm_bwd_kernel(
         // ---- long rows ----
         for (unsigned long long m = plan.coop_mask; m; m &= m - 1) {
             const int row = __ffsll((long long)m) - 1;
-            const int e0 = plan.sRp[row], e1 = plan.sRp[row + 1];
+            const int e0 = plan.sRp[row], n = plan.sRp[row + 1] - e0;      // n <= kLong = kCap: one staged chunk
             int ci[KPL + 1];
             float acc[KPL];
             load_ci<KPL>(ci, sIdx, row, t);
 #pragma unroll
             for (int u = 0; u < KPL; ++u) acc[u] = 0.f;
-            for (int c0 = e0; c0 < e1; c0 += kCap) {
-                const int n = min(kCap, e1 - c0);
-                lds_fence();
-                stage_chunk(plan, t_colidx, t_vals, c0, n, ADAPT ? ecls : nullptr);
-                lds_fence();
-                Stream st{g, n, row, g >= n ? 1 : 0};
-                bwd_run<KPL, EPI, true, ADAPT>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk);
-            }
+            lds_fence();
+            stage_chunk(plan, t_colidx, t_vals, e0, n, ecls);
+            lds_fence();
+            Stream st{g, n, row, g >= n ? 1 : 0};
+            bwd_run<KPL, EPI, true, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk);
 #pragma unroll
             for (int u = 0; u < KPL; ++u) part[g * kWin + t + kLPE * u] = acc[u];
             lds_fence();
             for (int w = lane; w < kWin; w += kWave) {
                 if (s0 + w < k) {
-                    float s = 0.f;
+                    float sum = 0.f;
 #pragma unroll
-                    for (int q = 0; q < kNG; ++q) s += part[q * kWin + w];
+                    for (int q = 0; q < kNG; ++q) sum += part[q * kWin + w];
                     float* o = Gblk + (size_t)row * k + s0 + w;
-                    *o = accumulate ? (*o + s) : s;
+                    *o = accumulate ? (*o + sum) : sum;
                 }
             }
             lds_fence();
@@ -692,7 +836,7 @@ __global__ __launch_bounds__(kWave) void spmm_bwd_kernel(
             const int sb = pass_end(plan, sa);
             lds_fence();
             if (lane == 0) *plan.sNext = kNG;
-            stage_solo(plan, t_colidx, t_vals, sa, sb, ADAPT ? ecls : nullptr);
+            stage_solo(plan, t_colidx, t_vals, sa, sb, ecls);
             lds_fence();
             Stream st{0, 0, 0, 0};
             st.take_slot(plan, g, sa, sb - sa, plan.sStart[sa]);
@@ -702,60 +846,134 @@ __global__ __launch_bounds__(kWave) void spmm_bwd_kernel(
 #pragma unroll
             for (int u = 0; u < KPL; ++u) { ci[u] = 0; acc[u] = 0.f; }
             if (!st.done) load_ci<KPL>(ci, sIdx, st.row, t);
-            bwd_run<KPL, EPI, false, ADAPT>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, sa, sb - sa, plan.sStart[sa],
-                                            accumulate, dk);
+            bwd_run<KPL, EPI, false, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, sa, sb - sa, plan.sStart[sa],
+                                                accumulate, dk);
             sa = sb;
+        }
+
+        // ---- very long rows of the whole workgroup: each wavefront takes a quarter of the row ----
+        if (!any_long) continue;
+        for (int w = 0; w < kWPB; ++w) {
+            for (unsigned long long m = sLong[w]; m; m &= m - 1) {
+                const int row = (blk * kWPB + w) * RW + __ffsll((long long)m) - 1;
+                const int e0 = t_rowptr[row], e1 = t_rowptr[row + 1];
+                const int per = (e1 - e0 + kWPB - 1) / kWPB;
+                const int w0 = min(e0 + wave * per, e1), w1 = min(w0 + per, e1);
+                int ci[KPL + 1];
+                float acc[KPL];
+#pragma unroll
+                for (int u = 0; u < KPL; ++u) {
+                    const int slot = s0 + t + kLPE * u;
+                    ci[u] = slot < k ? xs_idx[(size_t)row * k + slot] : 0;
+                    acc[u] = 0.f;
+                }
+                ci[KPL] = xs_idx[(size_t)row * k];                          // (adaptive K: one window, s0 = 0)
+                for (int c0 = w0; c0 < w1; c0 += kCap) {
+                    const int n = min(kCap, w1 - c0);
+                    lds_fence();
+                    stage_chunk(plan, t_colidx, t_vals, c0, n, ecls);
+                    lds_fence();
+                    Stream st{g, n, 0, g >= n ? 1 : 0};
+                    bwd_run<KPL, EPI, true, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk);
+                }
+#pragma unroll
+                for (int u = 0; u < KPL; ++u) part[g * kWin + t + kLPE * u] = acc[u];
+                __syncthreads();
+                for (int i = threadIdx.x; i < kWin; i += kWPB * kWave) {
+                    if (s0 + i < k) {
+                        float sum = 0.f;
+                        for (int q = 0; q < kWPB; ++q)
+#pragma unroll
+                            for (int p = 0; p < kNG; ++p) sum += base0[q * kWords + p * kWin + i];
+                        float* o = s.dXs + (size_t)row * k + s0 + i;
+                        *o = accumulate ? (*o + sum) : sum;
+                    }
+                }
+                __syncthreads();
+            }
         }
     }
 }
 
-static int launch_bwd_any(const dr_csr* At, const float* dH, const uint16_t* xs_idx, int D, int k, float* dXs, int accumulate,
-                          const uint8_t* ecls, DegreeK dk, hipStream_t s) {
-    const int N = (int)At->n_rows;
-    if (At->nnz == 0) {
-        if (accumulate) return DR_OK;
-        return launch_fill_u32(reinterpret_cast<uint32_t*>(dXs), (size_t)N * k, 0u, s);
+template <int KPL, int EPI, bool ADAPT>
+static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s) {
+    int64_t rows = 0;
+    for (int i = 0; i < a.n; ++i) rows += a.s[i].N;
+    const bool few = few_rows(rows);
+    const int rw = few ? 8 : 32;
+    int first = 0;
+    for (int i = 0; i < a.n; ++i) {
+        SpmmBwdSeg& g = a.s[i];
+        g.n_blocks = (g.N + kWPB * rw - 1) / (kWPB * rw);
+        g.per_xcd = (g.n_blocks + kNumXcd - 1) / kNumXcd;
+        g.first = first;
+        first += g.per_xcd;
     }
-    const int n_tiles = (N + kRW - 1) / kRW;
-    const int per_xcd = (n_tiles + kNumXcd - 1) / kNumXcd;
-    int kpl = 8;
-    if (k <= 8) kpl = 1;
-    else if (k <= 16) kpl = 2;
-    else if (k <= 32) kpl = 4;
-    dim3 grid((unsigned)(per_xcd * kNumXcd)), block(kWave);
-    const size_t lds = sizeof(float) * (size_t)kNG * (kLPE * kpl) + sizeof(uint16_t) * (size_t)kRW * (kLPE * kpl) +
-                       sizeof(int) * (size_t)plan_ints();
-#define DRC_LAUNCH_BWD(V, E, A)                                                                                            \
-    hipLaunchKernelGGL((spmm_bwd_kernel<V, E, A>), grid, block, lds, s, At->rowptr, At->colidx, At->vals, dH, xs_idx, dXs, \
-                       N, D, k, n_tiles, per_xcd, accumulate ? 1 : 0, ecls, dk)
-    if (ecls) {
-        switch (kpl) {
-            case 1: DRC_LAUNCH_BWD(1, 4, true); break;
-            case 2: DRC_LAUNCH_BWD(2, 4, true); break;
-            case 4: DRC_LAUNCH_BWD(4, 2, true); break;
-            default: DRC_LAUNCH_BWD(8, 1, true); break;   // k <= 64: one window of slots (checked by the caller)
+    const size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8>() : bwd_wave_words<KPL, 32>());
+    const dim3 grid((unsigned)(first * kNumXcd)), block(kWPB * kWave);
+    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT>), grid, block, lds, s, a, dk);
+    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT>), grid, block, lds, s, a, dk);
+}
+
+static int bwd_kind(int k) { return k <= 8 ? 1 : (k <= 16 ? 2 : (k <= 32 ? 4 : 8)); }
+
+// Several transposed relations at once (no job reads what another writes); equal kernels share a launch.
+int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s) {
+    unsigned long long done = 0;
+    for (int i = 0; i < n; ++i) {
+        if (done >> i & 1) continue;
+        const SpmmBwdJob& j = jobs[i];
+        if (j.At->n_rows == 0) continue;
+        if (j.At->nnz == 0) {
+            if (!j.accumulate) DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(j.dXs), (size_t)j.At->n_rows * j.k, 0u, s));
+            continue;
         }
-    } else {
-        switch (kpl) {
-            case 1: DRC_LAUNCH_BWD(1, 4, false); break;
-            case 2: DRC_LAUNCH_BWD(2, 4, false); break;
-            case 4: DRC_LAUNCH_BWD(4, 2, false); break;
-            default: DRC_LAUNCH_BWD(8, 1, false); break;
+        const int kind = bwd_kind(j.k);
+        SpmmBwdArgs a{};
+        a.D = D;
+        for (int r = i; r < n && a.n < kMaxSegs; ++r) {
+            const SpmmBwdJob& q = jobs[r];
+            if ((done >> r & 1) || q.At->nnz == 0 || bwd_kind(q.k) != kind) continue;
+            done |= 1ull << r;
+            a.s[a.n++] = SpmmBwdSeg{q.At->rowptr, q.At->colidx, q.At->vals, q.dH, q.xs_idx, q.dXs, nullptr, (int)q.At->n_rows, q.k,
+                                    q.accumulate ? 1 : 0, 0, 0, 0};
+        }
+        switch (kind) {
+            case 1: launch_bwd_kernel<1, 4, false>(a, DegreeK{}, s); break;
+            case 2: launch_bwd_kernel<2, 4, false>(a, DegreeK{}, s); break;
+            case 4: launch_bwd_kernel<4, 2, false>(a, DegreeK{}, s); break;
+            default: launch_bwd_kernel<8, 1, false>(a, DegreeK{}, s); break;
         }
     }
-#undef DRC_LAUNCH_BWD
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
 
 int launch_spmm_bwd(const dr_csr* At, const float* dH, const uint16_t* xs_idx, int D, int k, float* dXs,
                     int accumulate, hipStream_t s) {
-    return launch_bwd_any(At, dH, xs_idx, D, k, dXs, accumulate, nullptr, DegreeK{}, s);
+    const SpmmBwdJob j{At, dH, xs_idx, k, dXs, accumulate};
+    return launch_spmm_bwds(&j, 1, D, s);
 }
 
 int launch_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const float* dH, const uint16_t* xr_idx, int D,
                              const dr_degree_classes* c, float* dXr, int accumulate, hipStream_t s) {
-    return launch_bwd_any(At, dH, xr_idx, D, c->k1, dXr, accumulate, edge_class, DegreeK{c->t1, c->t2, c->k2, c->k3}, s);
+    if (At->nnz == 0) {
+        if (accumulate) return DR_OK;
+        return launch_fill_u32(reinterpret_cast<uint32_t*>(dXr), (size_t)At->n_rows * c->k1, 0u, s);
+    }
+    const DegreeK dk{c->t1, c->t2, c->k2, c->k3};
+    SpmmBwdArgs a{};
+    a.D = D;
+    a.n = 1;
+    a.s[0] = SpmmBwdSeg{At->rowptr, At->colidx, At->vals, dH, xr_idx, dXr, edge_class, (int)At->n_rows, c->k1, accumulate ? 1 : 0, 0, 0, 0};
+    switch (bwd_kind(c->k1)) {
+        case 1: launch_bwd_kernel<1, 4, true>(a, dk, s); break;
+        case 2: launch_bwd_kernel<2, 4, true>(a, dk, s); break;
+        case 4: launch_bwd_kernel<4, 2, true>(a, dk, s); break;
+        default: launch_bwd_kernel<8, 1, true>(a, dk, s); break;   // k <= 64: one window of slots (checked by the caller)
+    }
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
 }
 
 // class (0 low, 1 medium, 2 high) of the destination of every stored entry of At, from the forward row pointers
