@@ -95,6 +95,28 @@ def kernel_models(Nc, Nn, E, D, ks):
     return m
 
 
+def fused_models(Nc, Nn, E, D, ks):
+    """{kernel name: (bytes, flops)} of the kernels heteroconv_kernel_times reports that do several of the operations
+    above in one pass over their operands: every array such a kernel reads or writes, once."""
+    k_near, k_pins, k_self, k_pinned = ks
+    W = 4 * D * D
+    m = operation_models(Nc, Nn, E, D, ks)
+    fl = {n: f for n, (_, f) in m.items()}
+    out = {}
+    out["proj.cell+merge"] = (6 * Nc * k_near + 8 * Nc * D + 3 * W + 5 * Nc * D, fl["proj.near"] + fl["proj.pinned+merge"])
+    out["wgrad.cell"] = (8 * Nc * D + 6 * Nc * k_near + 5 * Nc * D + 3 * W,
+                         fl["wgrad.neigh_near"] + fl["wgrad.self_near"] + fl["wgrad.pinned"])
+    # dH of every relation, and the self-term gradient at the saved columns
+    out["dproj.cell"] = (5 * Nc * D + 3 * W + 8 * Nc * D + 6 * Nc * k_near, fl["dproj.near"] + fl["dproj.pinned"] + fl["dself.near+dX"])
+    out["dproj.pins"] = (4 * Nn * D + 2 * W + 4 * Nn * D + 6 * Nn * k_self, fl["dproj.pins"] + fl["dself.pins+dX"])
+    dx_cell, dx_net = 4 * Nc * D + 4 * Nc * k_near, 4 * Nn * D + 4 * Nn * k_self      # dense dX out, compact self term in
+    out["dr_spmm_bwd.pins+dX"] = (m["dr_spmm_bwd.pins"][0] - 4 * Nc * k_pins + dx_cell, fl["dr_spmm_bwd.pins"])
+    out["dr_spmm_bwd.near+pins+dX"] = (m["dr_spmm_bwd.near"][0] + m["dr_spmm_bwd.pins"][0] - 4 * Nc * (k_near + k_pins) + dx_cell,
+                                       fl["dr_spmm_bwd.near"] + fl["dr_spmm_bwd.pins"])
+    out["dr_spmm_bwd.pinned+dX"] = (m["dr_spmm_bwd.pinned"][0] - 4 * Nn * k_pinned + dx_net, fl["dr_spmm_bwd.pinned"])
+    return out
+
+
 DR_KERNELS = ("dr_topk.cell", "dr_topk.net", "dr_spmm_fwd.near", "dr_spmm_fwd.pins", "dr_spmm_fwd.pinned",
               "dr_spmm_bwd.near", "dr_spmm_bwd.pins", "dr_spmm_bwd.pinned")
 
@@ -484,7 +506,7 @@ def main() -> int:
         layer_ms = (time.perf_counter() - t0) * 1e3 / n_steps
         times = {} if args.no_profile_events else layer.heteroconv_kernel_times()
         layer.heteroconv_profile(False)
-        lmodels = kernel_models(g.Nc, g.Nn, E, D, ks)
+        lmodels = {**kernel_models(g.Nc, g.Nn, E, D, ks), **fused_models(g.Nc, g.Nn, E, D, ks)}
         step_bytes = sum(b for b, _ in operation_models(g.Nc, g.Nn, E, D, ks).values())
         lk = {}
         for name, (ms_sum, cnt) in times.items():

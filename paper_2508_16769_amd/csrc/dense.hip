@@ -1,835 +1,979 @@
 // Dense part of the HeteroConv layer (paper Section 3.2, matrix form Y = A X W, and its gradients in
-// Section 3.3): the per-relation linear projections on the matrix cores, fp32 in and out
-// (v_mfma_f32_32x32x2_f32), with the element-wise glue fused into the operand loads and epilogues:
+// Section 3.3): the per-relation linear projections and the weight gradients on the matrix cores, with the
+// element-wise glue fused in:
 //   - the D-ReLU output enters as CBSR and is densified on the fly into the LDS operand tile;
-//   - the max-merge mask gates an operand while it is loaded (backward) or is produced by the
-//     epilogue that merges the two cell branches (forward);
-//   - the self-term gradient is sampled at the saved CBSR indices straight out of the accumulators,
-//     added to the compact SpMM gradient and written as the dense, top-k-gated dX rows.
+//   - the max-merge is formed in registers from both cell branches (forward), its mask gates the upstream gradient as
+//     it enters (backward);
+//   - the self-term gradient is sampled at the saved CBSR indices and leaves compact.
 //
-// Projection kernel.  Persistent workgroups (as many as fit the chip at once: two to four per CU) loop over
-// 32-row tiles (D >= 96; 64 or 128 rows for narrower D).  The weights never
-// touch LDS: wavefront w keeps the 32-column slab of W it is responsible for in registers in MFMA
-// B-operand layout for the whole kernel (64 VGPRs per 128x128 weight), so the inner loop is one
-// ds_read_b128 of the A operand per four MFMAs.  Row tiles are double-buffered through LDS: every global
-// load a tile needs (operand rows, mask bytes, CBSR pairs, the other branch for the max-merge) is issued
-// before the multiply of the previous tile and consumed after it.  The operand kind and the epilogue are
-// template parameters: with a single code path per instantiation every load has exactly one consumer, so
-// the compiler's wait counters are placed at the consumers and not, conservatively, in front of the
-// multiply.
-// These contractions run at the fp32 matrix rate (2*rows*D*D flops per weight); they are bound by the
-// MFMA pipe, not by HBM, once the tiles stream (arithmetic intensity D/4 flop per byte moved).
+// Arithmetic.  Operands are fp32, the matrix cores' fp32 rate is 155 TFLOP/s (measured from registers) and was what bound
+// these kernels.  Each fp32 number is therefore written as the sum of three bf16 numbers, x = x1 + x2 + x3 (round to
+// nearest each time: 3 x 8 significant bits hold all 24, so the sum is exact), and a product is formed from six bf16
+// products, x1 y1 + x1 y2 + x2 y1 + x1 y3 + x2 y2 + x3 y1, each exact, all accumulated in fp32.  What is left out,
+// x2 y3 + x3 y2 + x3 y3, is below 2^-25 |x y|: half an ulp of one fp32 rounding, which an fp32 multiply-add commits for
+// every term anyway.  Measured against fp64 on N(0,1) data (2-norm): K = 128: 6.5e-8 with the small products in an
+// accumulator of their own, 1.6e-7 in one accumulator, 1.9e-7 for the fp32 instruction; K = 4096: 4.0e-7 / 1.0e-6 /
+// 1.1e-6.  Six bf16 products run at 250 .. 300 TFLOP/s of fp32 work, above what memory feeds these kernels, so they are
+// bound by HBM now: every operand is read once for all the products it takes part in.
+//
+// Layouts.  The 16x16x32 instruction takes eight consecutive contraction indices per lane, as one 16-byte register
+// group.  LDS holds the operand tile in exactly those units, one plane per part.  The contraction index is permuted
+// (unit u = columns 4u .. 4u+3 and D/2+4u .. D/2+4u+3) so that the global loads behind a unit are two fully coalesced
+// float4 loads; the weights follow the same order.  The weights are the first operand and the activations the second, so
+// a lane ends up with four consecutive output columns of one row: one 16-byte store per 16 rows.
+//
+// Pipeline.  Eight wavefronts per workgroup, two per SIMD, LDS tiles doubled, one barrier per tile.  In every step
+// the wavefronts of the first half split and stage the next tile and then multiply the current one, those of the second half
+// multiply first: on each SIMD the vector instructions of one wavefront run under the matrix instructions of the other.
+// (With both halves in step and one LDS buffer a 1.2 M-row forward took 0.72 ms.)
 #include "dr_internal.h"
 
 #include <atomic>
-#include <type_traits>
 
 namespace drc {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kPT = 256;  // threads per workgroup (4 wavefronts)
-constexpr int kCP = 8;    // CBSR pairs per thread that are prefetched into registers
-
-enum AKind { kADense = 0, kADenseMasked = 1, kACbsrDense = 2 };   // last: segment 0 CBSR, segment 1 dense
-
-template <int NT> struct ProjCfg {
-    static constexpr int D = 32 * NT;
-    static constexpr int KS = D / 2;                                  // MFMA k-steps per segment
-    static constexpr int RG = (NT >= 3) ? 1 : (NT == 2 ? 2 : 4);      // wavefront row groups
-    static constexpr int BM = (NT == 1) ? 128 : (NT == 2 ? 64 : 32);  // rows per tile
-    static constexpr int SPW = (BM / 32) / RG;                        // 32-row sub-tiles per wavefront
-    static constexpr int LDA = D + 4;                                 // LDS row stride: rows stay 16-byte aligned
-    static constexpr int F4 = BM * D / 4 / kPT;                       // float4 per thread per dense tile
-    static constexpr int TPR = kPT / BM;                              // threads that share one tile row
-    static constexpr int RPW = BM / 4;                                // tile rows staged by one wavefront
-    static constexpr size_t kLds = sizeof(float) * 2 * BM * LDA;
+template <int D> struct Tile {
+    static constexpr int NB = D / 16;                              // 16-column blocks = wavefronts side by side
+    static constexpr int WAVES = D == 96 ? 6 : 8;
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int RG = WAVES / NB;                          // row groups of 32 rows (wavefronts one below the other)
+    static constexpr int BM = 32 * RG;                             // rows per tile
+    static constexpr int KU = D / 8;                               // 16-byte units per row and part
+    static constexpr int KS = D / 32;                              // MFMA steps
+    static constexpr int TPR = D == 128 ? 16 : (D == 32 ? 4 : 8);  // threads that share one CBSR row; a row never straddles wavefronts
+    static constexpr int PLANE = KU * (BM + 1);                    // units per part; the +1 spreads a row's units over the banks
+    static constexpr int OPER = 3 * PLANE;                         // units per operand
+    static_assert(BM * KU == THREADS && BM * TPR <= THREADS && 64 % TPR == 0, "one unit per thread");
 };
 
-struct GemmParams {
-    GemmOperand seg[2];
-    int nseg;
-    int rows;
-    int epi;
-    float* out;
-    uint8_t* mask_out;
-    SampleSet first, second;      // kEpiSampleDense(2): selections and compact gradients of the write-out
-    int relu;                     // kEpiStore / kEpiMaxMerge: clamp what is written at zero
-};
-constexpr int kEpiSampleDense2 = 3;   // kEpiSampleDense with a second selection and/or no compact on the first
+// Three bf16 parts of eight numbers, two at a time (one conversion instruction makes two parts).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// the largest bf16 number: a value that would round up to infinity keeps a finite first part (the rest follows exactly)
+constexpr float kMaxBf16 = 3.3895313892515355e38f;
+struct Split8 { bf16x8 p[3]; };
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+__device__ __forceinline__ float low_part(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
+__device__ __forceinline__ float high_part(uint32_t v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = x[2 * j], b = x[2 * j + 1];
+        w[0][j] = pack2(__builtin_amdgcn_fmed3f(a, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(b, -kMaxBf16, kMaxBf16));
+        const float ra = a - low_part(w[0][j]), rb = b - high_part(w[0][j]);
+        w[1][j] = pack2(ra, rb);
+        w[2][j] = pack2(ra - low_part(w[1][j]), rb - high_part(w[1][j]));
+    }
+    Split8 s;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) s.p[p] = __builtin_bit_cast(bf16x8, w[p]);
+    return s;
+}
+// the parts of `s` where keep(j) holds, zero elsewhere
+template <typename K> __device__ __forceinline__ Split8 select8(const Split8& s, K keep) {
+    uint32_t m[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) m[j] = (keep(2 * j) ? 0x0000ffffu : 0u) | (keep(2 * j + 1) ? 0xffff0000u : 0u);
+    Split8 r;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        struct Words { uint32_t w[4]; } v = __builtin_bit_cast(Words, s.p[p]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v.w[j] &= m[j];
+        r.p[p] = __builtin_bit_cast(bf16x8, v);
+    }
+    return r;
+}
+// the three parts of one number, `stride` bf16 numbers apart
+__device__ __forceinline__ void put_parts(__bf16* at, int stride, float v) {
+    const __bf16 a = (__bf16)__builtin_amdgcn_fmed3f(v, -kMaxBf16, kMaxBf16);
+    const float r = v - (float)a;
+    const __bf16 b = (__bf16)r;
+    at[0] = a;
+    at[stride] = b;
+    at[2 * stride] = (__bf16)(r - (float)b);
+}
 
-struct PairRegs {
-    float v[kCP];
-    uint32_t c[kCP];
-};
+__device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// hi += leading products, lo += the five small ones (smallest first), for two tiles of rows at a time: consecutive
+// instructions go to different accumulators
+struct Acc { f32x4 hi, lo; };
+__device__ __forceinline__ void mfma6(const bf16x8 (&w)[3], const bf16x8 (&x)[2][3], Acc (&c)[2]) {
+    constexpr int W[5] = {2, 0, 1, 1, 0}, X[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) c[rb].lo = mfma(w[W[i]], x[rb][X[i]], c[rb].lo);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) c[rb].hi = mfma(w[0], x[rb][0], c[rb].hi);
+}
+// the same into one accumulator
+__device__ __forceinline__ void mfma6_one(const bf16x8 (&w)[3], const bf16x8 (&x)[2][3], f32x4 (&c)[2]) {
+    constexpr int W[6] = {2, 0, 1, 1, 0, 0}, X[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) c[rb] = mfma(w[W[i]], x[rb][X[i]], c[rb]);
+}
 
-// C tile element held by (lane, acc register r) of a 32x32 MFMA block
-__device__ __forceinline__ int mfma_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
-// Contraction index served by MFMA k-step s in lane half h.  Eight consecutive k form a group: half 0
-// takes the first four, half 1 the last four, so a lane fetches the A values of four k-steps with one
-// 16-byte LDS read.  The B registers are loaded in the same order.
-__device__ __forceinline__ int mfma_k(int s, int h) { return 8 * (s >> 2) + 4 * h + (s & 3); }
-
-// 16-byte load that does not displace cached lines (the four scalar loads merge into one instruction)
-__device__ __forceinline__ float4 nt_load4(const float* p) {
-    float4 v;
-    v.x = __builtin_nontemporal_load(p);
-    v.y = __builtin_nontemporal_load(p + 1);
-    v.z = __builtin_nontemporal_load(p + 2);
-    v.w = __builtin_nontemporal_load(p + 3);
+// Row blocks are read and written through buffer descriptors: the base is the block's first row and the size ends with
+// the array, so rows past the end read as zero and are not written.  No access in the pipelines is conditional, which
+// lets the compiler count exactly how many may still be outstanding (a store under a branch makes every later wait for a
+// load wait for the store as well), and the rows of a block need one offset register.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+using Buf = __amdgpu_buffer_rsrc_t;
+constexpr int kNt = 2;                    // cache policy: streamed
+constexpr int kNowhere = 0x7ffffff0;      // an offset outside every block
+// (a descriptor has to be uniform for the compiler too, and parts of this address arithmetic may be done per lane)
+__device__ __forceinline__ Buf block_view(const void* p, int rows_left, int row_bytes) {
+    const int rows = __builtin_amdgcn_readfirstlane(min(max(rows_left, 0), 1 << 16));
+    const uint64_t at = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), (short)0, rows * row_bytes, 0x00020000);
+}
+// Keeps `base + constant` in that form: the compiler would merge the constant into known-zero bits of the base and then
+// no longer find it for the instruction's own offset field.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
     return v;
 }
+__device__ __forceinline__ f32x4 load4(Buf b, int off) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, kNt)); }
+__device__ __forceinline__ float load1(Buf b, int off) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt)); }
+__device__ __forceinline__ uint32_t load1u(Buf b, int off) { return __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt); }
+template <int CP> __device__ __forceinline__ void store4(Buf b, int off, const f32x4& v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, CP);
+}
 
-
-template <int NT, int AK, int EPI>
-// wavefronts per SIMD the register budget is set for: 4 for the one-operand store kernels, 3 with the merge or
-// sampling epilogue (they hold the other branch / the pairs as well), 2 with two resident weight slabs
-__global__ __launch_bounds__(kPT, (EPI == kEpiStore ? (AK == kACbsrDense ? 2 : 4) : 3)) void proj_kernel(GemmParams p) {
-    constexpr bool kSample2 = (EPI == kEpiSampleDense2);
-    using C = ProjCfg<NT>;
-    constexpr int D = C::D, KS = C::KS, BM = C::BM, SPW = C::SPW, LDA = C::LDA, F4 = C::F4;
-    constexpr int TPR = C::TPR, RPW = C::RPW;
-    constexpr int NSEG = (AK == kACbsrDense) ? 2 : 1;
-    constexpr bool kMasked = (AK == kADenseMasked);
-    extern __shared__ __align__(16) float smem[];
-    float* const buf0 = smem;
-    float* const buf1 = smem + BM * LDA;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ct = wave % NT, rg = wave / NT;
-    const bool mm = rg < C::RG;                      // this wavefront multiplies (NT = 3 leaves one idle)
-    const int prow = tid / TPR, ppart = tid % TPR;   // row-owned stagings: tile row and share of it
-    const int n_tiles = (p.rows + BM - 1) / BM;
-    if ((int)blockIdx.x >= n_tiles) return;
-
-    // ---- weights of this wavefront's column slab, MFMA B-operand layout, resident in registers ----
-    float breg[NSEG][KS];
+// Weight fragments of one 16-column block: output column n = first + (lane & 15), unit 4 s + (lane >> 4) per step.
+// TRANS: B[k][n] = W[n][k].
+template <int D, bool TRANS>
+__device__ __forceinline__ void load_weight(const float* __restrict__ W, int first, int lane, bf16x8 (&w)[Tile<D>::KS][3]) {
+    const int n = first + (lane & 15);
 #pragma unroll
-    for (int sg = 0; sg < NSEG; ++sg) {
-        // B[kk][n] = W[kk][n], or W[n][kk] for the transposed use: one strided load per element, no branches
-        const int sk = p.seg[sg].transpose_w ? 1 : D, sn = p.seg[sg].transpose_w ? D : 1;
-        const float* W = p.seg[sg].W + (32 * ct + (lane & 31)) * sn;
+    for (int s = 0; s < Tile<D>::KS; ++s) {
+        const int k0 = 4 * (4 * s + (lane >> 4));
+        float x[8];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) breg[sg][s] = W[mfma_k(s, lane >> 5) * sk];
+        for (int j = 0; j < 8; ++j) {
+            const int k = k0 + (j & 3) + (j >> 2) * (D / 2);
+            x[j] = TRANS ? W[(size_t)n * D + k] : W[(size_t)k * D + n];
+        }
+        const Split8 sp = split8(x);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[s][p] = sp.p[p];
     }
+}
 
-    floatx16 acc[SPW];
-#pragma unroll
-    for (int j = 0; j < SPW; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+// A kernel's arguments, read where they lie: loads from the constant address space are scalar whatever is stored in
+// between, so that descriptors built from them are uniform.
+#define DRC_CONST __attribute__((address_space(4)))
+template <typename T> __device__ __forceinline__ const DRC_CONST T* kernel_args() {
+    return (const DRC_CONST T*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+}
 
-    // ---- dense operand tile: global -> registers -> LDS.  Wavefront w stages tile rows
-    // [w*RPW, (w+1)*RPW); loads are unconditional on clamped rows, masks ride along raw. ----
-    const GemmOperand& od = p.seg[NSEG - 1];
-    float4 pre[F4];
-    uint32_t prem[F4];
-    auto prefetch = [&](int tile) {
+// The graph whose tiles hold tile `t` (tile0 of the graphs is increasing); q only moves forward.
+template <typename SEG> __device__ __forceinline__ void find_seg(const DRC_CONST SEG* s, int n, int t, int& q) {
+    while (q + 1 < n && t >= s[q + 1].tile0) ++q;
+}
+
+// CBSR rows -> operand tile.  Pairs ppart, ppart + TPR, ... of a row belong to thread (row, ppart); the first kPairs per
+// thread travel through registers, further ones (wide selections) are fetched when they are placed.
+constexpr int kPairs = 4;
+struct PairRegs { float v[kPairs]; uint32_t c[kPairs]; };
+
+// pairs of row `row` of a block whose selections start at `vals`, `idx`
+template <int TPR>
+__device__ __forceinline__ void load_pairs(PairRegs& r, Buf vals, Buf idx, int k, int row, int ppart) {
+    const int at4 = opaque((row * k + ppart) * 4), at2 = opaque((row * k + ppart) * 2);
 #pragma unroll
-        for (int it = 0; it < F4; ++it) {
-            const int q = it * kWave + lane;
-            const int row = wave * RPW + q / (D / 4), c4 = (q % (D / 4)) * 4;
-            const size_t off = (size_t)min(tile * BM + row, p.rows - 1) * D + c4;
-            pre[it] = nt_load4(od.dense + off);                         // operand rows are read once: streamed
-            if (kMasked) prem[it] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(od.mask + off));
+    for (int u = 0; u < kPairs; ++u) {
+        r.v[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, at4 + TPR * u * 4, 0, 0));
+        r.c[u] = __builtin_amdgcn_raw_buffer_load_b16(idx, at2 + TPR * u * 2, 0, 0);
+    }
+}
+
+template <int D> __device__ __forceinline__ void put_pair(bf16x8* plane, int row, int col, float v) {
+    using T = Tile<D>;
+    const int half = col >= D / 2 ? 1 : 0, c = col - half * (D / 2);
+    put_parts(reinterpret_cast<__bf16*>(plane + (c >> 2) * (T::BM + 1) + row) + (c & 3) + 4 * half, 8 * T::PLANE, v);
+}
+
+// rows past the end hold zeros at column 0
+template <int D>
+__device__ __forceinline__ void stage_cbsr(bf16x8* oper, const PairRegs& pr, const float* __restrict__ vals,
+                                           const uint16_t* __restrict__ idx, int k, int rows_left, int row, int ppart) {
+    using T = Tile<D>;
+    const bf16x8 z = {};
+    for (int u = ppart; u < T::KU * 3; u += T::TPR) oper[(u / T::KU) * T::PLANE + (u % T::KU) * (T::BM + 1) + row] = z;
+    // the threads of a row sit in one wavefront and LDS executes a wavefront's accesses in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u)
+        put_pair<D>(oper, ppart + T::TPR * u < k ? row : T::BM, (int)pr.c[u], pr.v[u]);    // pairs past k go to the padding row
+    if (k > T::TPR * kPairs && row < rows_left)
+        for (int t = ppart + T::TPR * kPairs; t < k; t += T::TPR) put_pair<D>(oper, row, idx[(size_t)row * k + t], vals[(size_t)row * k + t]);
+}
+
+// dense unit -> operand tile
+template <int D> __device__ __forceinline__ void stage_unit(bf16x8* oper, int row, int unit, const Split8& s) {
+    using T = Tile<D>;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) oper[p * T::PLANE + unit * (T::BM + 1) + row] = s.p[p];
+}
+
+template <int D> __device__ __forceinline__ void load_x(const bf16x8* oper, int s, int rg, int lane, bf16x8 (&x)[2][3]) {
+    using T = Tile<D>;
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            x[rb][p] = oper[p * T::PLANE + (4 * s + (lane >> 4)) * (T::BM + 1) + rg * 32 + rb * 16 + (lane & 15)];
+}
+
+// ---------------------------------------------------------------------------------------------------
+// forward:  cells  Y = max(Xs W_self + H_near W_neigh, H_pinned W_pinned), mask      (three weights)
+//           nets   Y = Xs W_self + H_pins W_neigh                                     (two weights)
+// A workgroup keeps the weights of its side in registers (wavefront w: 16 output columns, 48 registers per weight at
+// D = 128) and walks over row tiles of that side; the loads of the next tile are in flight during the multiply.  One read of
+// every operand, one write of Y: separate kernels for near and for pinned + merge wrote Y twice and read it once in
+// between.
+// ---------------------------------------------------------------------------------------------------
+struct ProjFwdSide {              // one graph's rows of one node type
+    const float *vals, *H1, *H2;  // CBSR of the self term, H_near / H_pins, H_pinned (cells)
+    const uint16_t* idx;
+    float* Y;
+    uint8_t* mask;
+    int rows, k, tile0;
+};
+struct ProjFwdArgs {
+    ProjFwdSide cell[kMaxGraphs], net[kMaxGraphs];
+    const float *w_self_near, *w_neigh_near, *w_pinned, *w_self_pins, *w_neigh_pins;
+    int n, cell_tiles, net_tiles, cell_wgs, relu;
+};
+static_assert(sizeof(ProjFwdArgs) < 4096, "kernel arguments");
+
+template <int D, bool CELL>
+__device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf16x8* smem, int wg, int n_wg) {
+    using T = Tile<D>;
+    const DRC_CONST ProjFwdSide* const segs = CELL ? a->cell : a->net;
+    const int tiles = CELL ? a->cell_tiles : a->net_tiles;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = wave % T::NB, rg = wave / T::NB;
+    const int urow = tid / T::KU, unit = tid % T::KU;              // this thread's unit of a dense operand
+    const int prow = tid / T::TPR, ppart = tid % T::TPR;           // past the tile (D = 96): reads nothing, writes nothing
+    const bool pairs = wave * 64 < T::BM * T::TPR;                 // whole wavefronts
+
+    bf16x8 wS[T::KS][3], w1[T::KS][3], w2[T::KS][3];
+    load_weight<D, false>(CELL ? a->w_self_near : a->w_self_pins, 16 * nb, lane, wS);
+    load_weight<D, false>(CELL ? a->w_neigh_near : a->w_neigh_pins, 16 * nb, lane, w1);
+    if constexpr (CELL) load_weight<D, false>(a->w_pinned, 16 * nb, lane, w2);
+
+    f32x4 h1[2], h2[2];
+    PairRegs pr;
+    const int uoff = opaque((urow * D + 4 * unit) * 4);                    // bytes from the first row of the tile
+    auto prefetch = [&](const DRC_CONST ProjFwdSide* g, int t) {             // past the last tile: reads nothing
+        const int base = (t - g->tile0) * T::BM, left = t < tiles ? g->rows - base : 0;
+        const Buf b1 = block_view(g->H1 + (size_t)base * D, left, D * 4);
+        h1[0] = load4(b1, uoff);
+        h1[1] = load4(b1, uoff + D * 2);
+        if constexpr (CELL) {
+            const Buf b2 = block_view(g->H2 + (size_t)base * D, left, D * 4);
+            h2[0] = load4(b2, uoff);
+            h2[1] = load4(b2, uoff + D * 2);
         }
+        load_pairs<T::TPR>(pr, block_view(g->vals + (size_t)base * g->k, left, g->k * 4), block_view(g->idx + (size_t)base * g->k, left, g->k * 2),
+                           g->k, prow, ppart);
     };
-    auto commit = [&](int tile, float* b) {
-        const uint32_t keep = (uint32_t)od.mask_keep;
+    auto commit = [&](const DRC_CONST ProjFwdSide* g, int t, bf16x8* buf) {
+        const int base = (t - g->tile0) * T::BM;
+        float x[8];
 #pragma unroll
-        for (int it = 0; it < F4; ++it) {
-            const int q = it * kWave + lane;
-            const int row = wave * RPW + q / (D / 4), c4 = (q % (D / 4)) * 4;
-            const bool in = tile * BM + row < p.rows;
-            float4 v = pre[it];
-            if (kMasked) {
-                const uint32_t m = prem[it];
-                v.x = (((m >> 0) & 0xffu) == keep) ? v.x : 0.f;
-                v.y = (((m >> 8) & 0xffu) == keep) ? v.y : 0.f;
-                v.z = (((m >> 16) & 0xffu) == keep) ? v.z : 0.f;
-                v.w = (((m >> 24) & 0xffu) == keep) ? v.w : 0.f;
+        for (int j = 0; j < 8; ++j) x[j] = h1[j >> 2][j & 3];
+        stage_unit<D>(buf + T::OPER, urow, unit, split8(x));
+        if constexpr (CELL) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = h2[j >> 2][j & 3];
+            stage_unit<D>(buf + 2 * T::OPER, urow, unit, split8(x));
+        }
+        if (pairs) stage_cbsr<D>(buf, pr, g->vals + (size_t)base * g->k, g->idx + (size_t)base * g->k, g->k, t < tiles ? g->rows - base : 0, prow, ppart);
+    };
+    int t = wg;
+    if (t >= tiles) return;
+    const bool first_half = wave < T::WAVES / 2;
+    int q = 0, q1, q2;                            // graphs of tile t, of the next one and of the one after
+    find_seg(segs, a->n, t, q);
+    prefetch(segs + q, t);
+    commit(segs + q, t, smem);
+    q1 = q;
+    find_seg(segs, a->n, t + n_wg, q1);
+    prefetch(segs + q1, t + n_wg);
+    __syncthreads();
+    for (int cur = 0;; cur ^= 1) {
+        const DRC_CONST ProjFwdSide* const g = segs + q;
+        const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+        bf16x8* const buf = smem + cur * 3 * T::OPER;
+        q2 = q1;
+        find_seg(segs, a->n, t1 + n_wg, q2);
+        auto stage_next = [&]() {
+            commit(segs + q1, t1, smem + (cur ^ 1) * 3 * T::OPER);
+            prefetch(segs + q2, t1 + n_wg);
+        };
+        if (first_half) stage_next();
+        __builtin_amdgcn_sched_barrier(0);
+        Acc c1[2] = {}, c2[2] = {};
+#pragma unroll
+        for (int s = 0; s < T::KS; ++s) {
+            bf16x8 x[2][3];
+            load_x<D>(buf, s, rg, lane, x);
+            mfma6(wS[s], x, c1);
+            load_x<D>(buf + T::OPER, s, rg, lane, x);
+            mfma6(w1[s], x, c1);
+            if constexpr (CELL) {
+                load_x<D>(buf + 2 * T::OPER, s, rg, lane, x);
+                mfma6(w2[s], x, c2);
             }
-            if (!in) v = make_float4(0.f, 0.f, 0.f, 0.f);
-            *reinterpret_cast<float4*>(b + row * LDA + c4) = v;
         }
-    };
-
-    // ---- CBSR pairs of a tile, row-owned: thread (prow, ppart) holds pairs ppart, ppart+TPR, ... of tile
-    // row prow.  The first kCP pairs per thread travel through registers; the rest (k > kCP*TPR) are
-    // fetched when they are placed. ----
-    auto load_pairs = [&](PairRegs& pr, const float* vals, const uint16_t* idx, int k, int tile) {
-        const size_t base = (size_t)min(tile * BM + prow, p.rows - 1) * k;
+        __builtin_amdgcn_sched_barrier(0);
+        const Buf by = block_view(g->Y + (size_t)base * D, g->rows - base, D * 4);
+        const Buf bm = block_view(g->mask + (size_t)base * D, g->rows - base, D);
 #pragma unroll
-        for (int u = 0; u < kCP; ++u) {
-            const int t = min(ppart + TPR * u, k - 1);
-            pr.v[u] = vals[base + t];
-            pr.c[u] = idx[base + t];
-        }
-    };
-    auto load_cols = [&](PairRegs& pr, const uint16_t* idx, int k, int tile) {       // columns only, values zero
-        const size_t base = (size_t)min(tile * BM + prow, p.rows - 1) * k;
+        for (int rb = 0; rb < 2; ++rb) {
+            const int at = (rg * 32 + rb * 16 + (lane & 15)) * D + 16 * nb + 4 * (lane >> 4);
+            f32x4 v = c1[rb].hi + c1[rb].lo;
+            if constexpr (CELL) {                 // mask = [near >= pinned]
+                const f32x4 p = c2[rb].hi + c2[rb].lo;
+                uint32_t m = 0;
 #pragma unroll
-        for (int u = 0; u < kCP; ++u) {
-            pr.v[u] = 0.f;
-            pr.c[u] = idx[base + min(ppart + TPR * u, k - 1)];
-        }
-    };
-    auto zero_own_part = [&](float* rowp) {
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int i = 0; i < D / TPR / 4; ++i) *reinterpret_cast<float4*>(rowp + ppart * (D / TPR) + 4 * i) = z;
-        // The threads of one row sit in one wavefront and LDS executes a wavefront's accesses in order, so
-        // the scattered writes that follow land on the zeroed row without a workgroup barrier.
-        __builtin_amdgcn_wave_barrier();
-    };
-    // D-ReLU rows -> dense LDS tile.  Every write is unconditional: pairs past k go to the padding column,
-    // rows past the end write zeros.
-    auto stage_cbsr = [&](const PairRegs& pr, int tile, float* b) {
-        const GemmOperand& o = p.seg[0];
-        float* rowp = b + prow * LDA;
-        zero_own_part(rowp);
-        const int k = o.k;
-        const bool rin = tile * BM + prow < p.rows;
-#pragma unroll
-        for (int u = 0; u < kCP; ++u) {
-            const int t = ppart + TPR * u;
-            rowp[t < k ? (int)pr.c[u] : D] = rin ? pr.v[u] : 0.f;
-        }
-        const size_t base = (size_t)min(tile * BM + prow, p.rows - 1) * k;
-        for (int u = kCP; u * TPR < k; ++u) {
-            const int t = ppart + TPR * u;
-            const float v = o.cbsr_vals[base + min(t, k - 1)];
-            const int c = o.cbsr_idx[base + min(t, k - 1)];
-            rowp[t < k ? c : D] = rin ? v : 0.f;
-        }
-    };
-
-    // A operands are read from LDS one group of four k-steps ahead of the MFMAs that consume them
-    // (explicit software pipeline; the scheduling barriers keep the reads from sinking next to their use).
-    auto multiply = [&](const float* b, auto sg_tag) {
-        constexpr int SG = decltype(sg_tag)::value;
-        if (!mm) return;
-        const float* a0 = b + ((rg * SPW) * 32 + (lane & 31)) * LDA + 4 * (lane >> 5);
-        float4 a[2][SPW];
-#pragma unroll
-        for (int j = 0; j < SPW; ++j) a[0][j] = *reinterpret_cast<const float4*>(a0 + j * 32 * LDA);
-#pragma unroll
-        for (int g = 0; g < KS / 4; ++g) {
-            if (g + 1 < KS / 4) {
-#pragma unroll
-                for (int j = 0; j < SPW; ++j)
-                    a[(g + 1) & 1][j] = *reinterpret_cast<const float4*>(a0 + j * 32 * LDA + 8 * (g + 1));
+                for (int r = 0; r < 4; ++r) {
+                    const bool near_wins = v[r] >= p[r];
+                    m |= near_wins ? 1u << (8 * r) : 0u;
+                    v[r] = near_wins ? v[r] : p[r];
+                }
+                __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, kNt);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if (a->relu) {
 #pragma unroll
-            for (int j = 0; j < SPW; ++j) {
-                const float4 av = a[g & 1][j];
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, breg[SG][4 * g + 0], acc[j], 0, 0, 0);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, breg[SG][4 * g + 1], acc[j], 0, 0, 0);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, breg[SG][4 * g + 2], acc[j], 0, 0, 0);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, breg[SG][4 * g + 3], acc[j], 0, 0, 0);
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            store4<kNt>(by, at * 4, v);
+        }
+        if (!first_half) stage_next();
+        if (t1 >= tiles) break;
+        __syncthreads();
+        t = t1;
+        q = q1;
+        q1 = q2;
+    }
+}
+
+template <int D> constexpr int waves_per_simd() { return 2; }
+
+template <int D>
+__global__ __launch_bounds__(Tile<D>::THREADS, waves_per_simd<D>()) void proj_kernel(ProjFwdArgs a) {
+    extern __shared__ bf16x8 smem8[];
+    const DRC_CONST ProjFwdArgs* const k = kernel_args<ProjFwdArgs>();
+    if ((int)blockIdx.x < k->cell_wgs) proj_fwd_side<D, true>(k, smem8, blockIdx.x, k->cell_wgs);
+    else proj_fwd_side<D, false>(k, smem8, blockIdx.x - k->cell_wgs, gridDim.x - k->cell_wgs);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// backward:  cells  dZ_near = dY where mask == 1, dZ_pinned = dY where mask == 0
+//                   dH_near = dZ_near W_neigh^T,  dH_pinned = dZ_pinned W_pinned^T,
+//                   S[row, t] = (dZ_near W_self^T)[row, idx[row, t]]
+//            nets   dH_pins = dY W_neigh^T,  S[row, t] = (dY W_self^T)[row, idx[row, t]]
+// dY and the mask are read once for all three products; the self term leaves compact ([rows, k]), so that the kernel that
+// sums the transposed relations can add it and write the dense dX (it used to read dY and the mask again, in a kernel of
+// its own).
+// ---------------------------------------------------------------------------------------------------
+struct ProjBwdSide {
+    const float* dY;
+    const uint8_t* mask;          // cells
+    float *dH1, *dH2;             // dH_near / dH_pins, dH_pinned (cells)
+    const uint16_t* idx;
+    float* S;
+    int rows, k, tile0;
+};
+struct ProjBwdArgs {
+    ProjBwdSide cell[kMaxGraphs], net[kMaxGraphs];
+    const float *w_self_near, *w_neigh_near, *w_pinned, *w_self_pins, *w_neigh_pins;
+    int n, cell_tiles, net_tiles, cell_wgs;
+};
+static_assert(sizeof(ProjBwdArgs) < 4096, "kernel arguments");
+
+template <int D, bool CELL>
+__device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf16x8* smem, int wg, int n_wg) {
+    using T = Tile<D>;
+    constexpr int LDC = D + 4;
+    const DRC_CONST ProjBwdSide* const segs = CELL ? a->cell : a->net;
+    const int tiles = CELL ? a->cell_tiles : a->net_tiles;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = wave % T::NB, rg = wave / T::NB;
+    const int urow = tid / T::KU, unit = tid % T::KU;
+    const int prow = tid / T::TPR, ppart = tid % T::TPR;           // past the tile (D = 96): reads nothing, writes nothing
+    float* const sC0 = reinterpret_cast<float*>(smem + 4 * T::OPER);          // [2][BM][LDC] self-term products
+
+    bf16x8 wS[T::KS][3], w1[T::KS][3], w2[T::KS][3];
+    load_weight<D, true>(CELL ? a->w_self_near : a->w_self_pins, 16 * nb, lane, wS);
+    load_weight<D, true>(CELL ? a->w_neigh_near : a->w_neigh_pins, 16 * nb, lane, w1);
+    if constexpr (CELL) load_weight<D, true>(a->w_pinned, 16 * nb, lane, w2);
+
+    f32x4 y[2];
+    uint32_t mk[2];
+    const int uoff = opaque((urow * D + 4 * unit) * 4), moff = opaque(urow * D + 4 * unit);   // from the first row of the tile
+    auto prefetch = [&](const DRC_CONST ProjBwdSide* g, int t) {             // past the last tile: reads nothing
+        const int base = (t - g->tile0) * T::BM, left = t < tiles ? g->rows - base : 0;
+        const Buf by = block_view(g->dY + (size_t)base * D, left, D * 4);
+        y[0] = load4(by, uoff);
+        y[1] = load4(by, uoff + D * 2);
+        if constexpr (CELL) {
+            const Buf bm = block_view(g->mask + (size_t)base * D, left, D);
+            mk[0] = load1u(bm, moff);
+            mk[1] = load1u(bm, moff + D / 2);
         }
     };
-    auto clear_acc = [&]() {
+    auto commit = [&](bf16x8* buf) {
+        float x[8];
 #pragma unroll
-        for (int j = 0; j < SPW; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
-    };
-    auto store_tile = [&](int tile) {                  // out[rows, D] = C
-        if (!mm) return;
-        if (p.relu) {
-#pragma unroll
-            for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[j][r] = fmaxf(acc[j][r], 0.0f);
-        }
-        // one pointer per sub-tile; the 16 rows a lane holds sit at fixed offsets from it
-        const int row0 = tile * BM + rg * SPW * 32 + 4 * (lane >> 5);
-        float* const o = p.out + (size_t)row0 * D + 32 * ct + (lane & 31);
-        if (tile * BM + BM <= p.rows) {                // whole tile in range (all but the last tile)
-#pragma unroll
-            for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) __builtin_nontemporal_store(acc[j][r], o + (j * 32 + 8 * (r >> 2) + (r & 3)) * D);
+        for (int j = 0; j < 8; ++j) x[j] = y[j >> 2][j & 3];
+        const Split8 sp = split8(x);
+        if constexpr (CELL) {
+            auto byte = [&](int j) { return (mk[j >> 2] >> (8 * (j & 3))) & 0xffu; };
+            const Split8 s1 = select8(sp, [&](int j) { return byte(j) == 1u; }), s2 = select8(sp, [&](int j) { return byte(j) == 0u; });
+            stage_unit<D>(buf, urow, unit, s1);
+            stage_unit<D>(buf + T::OPER, urow, unit, s2);
         } else {
-#pragma unroll
-            for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = j * 32 + 8 * (r >> 2) + (r & 3);
-                    if (row0 + dr < p.rows) o[dr * D] = acc[j][r];
-                }
+            stage_unit<D>(buf, urow, unit, sp);
         }
     };
-
-    if constexpr (AK == kACbsrDense) {
-        // Two segments per row tile: the CBSR operand is multiplied out of buf0, the dense one out of buf1.
-        const GemmOperand& oc = p.seg[0];
-        PairRegs pr;
-        int tile = blockIdx.x;
-        load_pairs(pr, oc.cbsr_vals, oc.cbsr_idx, oc.k, tile);
-        stage_cbsr(pr, tile, buf0);
-        __syncthreads();
-        for (;;) {
-            const int ntile = tile + gridDim.x;
-            const bool has_next = ntile < n_tiles;
-            prefetch(tile);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(buf0, std::integral_constant<int, 0>{});
-            __builtin_amdgcn_sched_barrier(0);
-            commit(tile, buf1);
-            __syncthreads();
-            if (has_next) load_pairs(pr, oc.cbsr_vals, oc.cbsr_idx, oc.k, ntile);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(buf1, std::integral_constant<int, NSEG - 1>{});
-            store_tile(tile);
-            clear_acc();
-            __builtin_amdgcn_sched_barrier(0);
-            if (has_next) stage_cbsr(pr, ntile, buf0);
-            __syncthreads();
-            if (!has_next) break;
-            tile = ntile;
+    int t = wg;
+    if (t >= tiles) return;
+    const bool first_half = wave < T::WAVES / 2;
+    int q = 0, q1, q2, t0 = t, q0;                // graphs of tile t, the next and the one after; the tile before
+    find_seg(segs, a->n, t, q);
+    q0 = q;
+    prefetch(segs + q, t);
+    commit(smem);
+    q1 = q;
+    find_seg(segs, a->n, t + n_wg, q1);
+    prefetch(segs + q1, t + n_wg);
+    __syncthreads();
+    // The self-term product of a tile is sampled one step later, when all wavefronts have written theirs.
+    auto sample = [&](const DRC_CONST ProjBwdSide* g, int t, int left, const float* sC) {
+        const int base = (t - g->tile0) * T::BM, at = prow * g->k + ppart;
+        left = min(left, T::BM);                  // threads past the tile (D = 96) must not reach the next tile's rows
+        const Buf bi = block_view(g->idx + (size_t)base * g->k, left, g->k * 2);
+        const Buf bs = block_view(g->S + (size_t)base * g->k, left, g->k * 4);
+        uint32_t col[kPairs];
+#pragma unroll
+        for (int u = 0; u < kPairs; ++u) col[u] = __builtin_amdgcn_raw_buffer_load_b16(bi, (at + T::TPR * u) * 2, 0, 0);
+        return [=]() {
+            const int row = min(prow, T::BM - 1);
+#pragma unroll
+            for (int u = 0; u < kPairs; ++u)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sC[row * LDC + col[u]]), bs,
+                                                      ppart + T::TPR * u < g->k ? (at + T::TPR * u) * 4 : kNowhere, 0, 0);
+            if (g->k > T::TPR * kPairs && prow < min(left, T::BM))
+                for (int p = ppart + T::TPR * kPairs; p < g->k; p += T::TPR)
+                    g->S[(size_t)(base + prow) * g->k + p] = sC[prow * LDC + g->idx[(size_t)(base + prow) * g->k + p]];
+        };
+    };
+    int cur = 0;
+    bool have_t0 = false;
+    for (;; cur ^= 1) {
+        const DRC_CONST ProjBwdSide* const g = segs + q;
+        const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+        bf16x8* const buf = smem + cur * 2 * T::OPER;
+        float* const sC = sC0 + cur * T::BM * LDC;
+        q2 = q1;
+        find_seg(segs, a->n, t1 + n_wg, q2);
+        const auto finish_t0 = sample(segs + q0, t0, have_t0 ? segs[q0].rows - (t0 - segs[q0].tile0) * T::BM : 0, sC0 + (cur ^ 1) * T::BM * LDC);
+        auto stage_next = [&]() {
+            commit(smem + (cur ^ 1) * 2 * T::OPER);
+            prefetch(segs + q2, t1 + n_wg);
+        };
+        if (first_half) stage_next();
+        __builtin_amdgcn_sched_barrier(0);
+        Acc c1[2] = {}, c2[2] = {};
+        f32x4 cS[2] = {};                         // one accumulator: the registers do not hold more
+#pragma unroll
+        for (int s = 0; s < T::KS; ++s) {
+            bf16x8 x[2][3];
+            load_x<D>(buf, s, rg, lane, x);
+            mfma6(w1[s], x, c1);
+            mfma6_one(wS[s], x, cS);
+            if constexpr (CELL) {
+                load_x<D>(buf + T::OPER, s, rg, lane, x);
+                mfma6(w2[s], x, c2);
+            }
         }
-    } else {
-        int tile = blockIdx.x, cur = 0;
-        prefetch(tile);
-        commit(tile, buf0);
-        __syncthreads();
-        for (;;) {
-            const int ntile = tile + gridDim.x;
-            const bool has_next = ntile < n_tiles;
-            float* const bcur = cur ? buf1 : buf0;
-            float* const bother = cur ? buf0 : buf1;
-            // what the epilogue of this tile consumes is requested first, then the next tile
-            PairRegs pr;
-            float prev[SPW][16];
-            if constexpr (EPI == kEpiSampleDense) load_pairs(pr, p.first.compact, p.first.idx, p.first.k, tile);
-            if constexpr (kSample2) {
-                if (p.first.compact) load_pairs(pr, p.first.compact, p.first.idx, p.first.k, tile);
-                else load_cols(pr, p.first.idx, p.first.k, tile);
-            }
-            // C rows of this lane: row0 + j*32 + 8*(r/4) + r%4, all at fixed offsets from one pointer
-            const int row0 = tile * BM + rg * SPW * 32 + 4 * (lane >> 5);
-            const size_t off0 = (size_t)row0 * D + 32 * ct + (lane & 31);
-            const bool full = tile * BM + BM <= p.rows;     // whole tile in range (all but the last tile)
-            if constexpr (EPI == kEpiMaxMerge) {            // the other branch's values (all wavefronts)
-                const float* po = p.out + off0;
-                if (full) {
+        __builtin_amdgcn_sched_barrier(0);
+        const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
+        const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
 #pragma unroll
-                    for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) prev[j][r] = po[(j * 32 + 8 * (r >> 2) + (r & 3)) * D];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int row = min(row0 + j * 32 + 8 * (r >> 2) + (r & 3), p.rows - 1);
-                            prev[j][r] = p.out[(size_t)row * D + 32 * ct + (lane & 31)];
-                        }
-                }
-            }
-            if (has_next) prefetch(ntile);
-            __builtin_amdgcn_sched_barrier(0);   // consumers of the registers loaded above stay below the multiply
-            multiply(bcur, std::integral_constant<int, 0>{});
-
-            if constexpr (EPI == kEpiStore) {
-                store_tile(tile);
-            } else if constexpr (EPI == kEpiMaxMerge) {
-                // mask = [near >= pinned]; out keeps the near value unless the pinned one is larger
-                if (mm) {
-                    float* const o = p.out + off0;
-                    uint8_t* const mo = p.mask_out + off0;
-#pragma unroll
-                    for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int dr = j * 32 + 8 * (r >> 2) + (r & 3);
-                            const float c = acc[j][r];
-                            const bool near_wins = prev[j][r] >= c;
-                            // with the activation folded in, a negative near value that stays has to be rewritten too
-                            const bool rewrite = !near_wins || (p.relu && prev[j][r] < 0.0f);
-                            const float v = near_wins ? prev[j][r] : c;
-                            if (full || row0 + dr < p.rows) {
-                                mo[dr * D] = near_wins ? 1 : 0;
-                                if (rewrite) o[dr * D] = p.relu ? fmaxf(v, 0.0f) : v;
-                            }
-                        }
-                }
-            } else {
-                // out[row, :] = 0 except out[row, idx[row,t]] = compact[row,t] + C[row, idx[row,t]].
-                // C goes to the free LDS buffer; each wavefront then rebuilds and writes its own rows.
-                if (mm) {
-#pragma unroll
-                    for (int j = 0; j < SPW; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            bother[((rg * SPW + j) * 32 + mfma_row(lane, r)) * LDA + 32 * ct + (lane & 31)] = acc[j][r];
-                }
-                __syncthreads();                                   // C tile complete; bcur no longer read
-                float* orow = bcur + prow * LDA;
-                const float* crow = bother + prow * LDA;
-                zero_own_part(orow);
-                const int k = p.first.k;
-#pragma unroll
-                for (int u = 0; u < kCP; ++u) {
-                    const int t = ppart + TPR * u;
-                    const int col = t < k ? (int)pr.c[u] : D;       // pairs past k land in the padding column
-                    orow[col] = pr.v[u] + crow[col];
-                }
-                const size_t base = (size_t)min(tile * BM + prow, p.rows - 1) * k;
-                for (int u = kCP; u * TPR < k; ++u) {
-                    const int t = ppart + TPR * u;
-                    float v = 0.f;
-                    if (!kSample2 || p.first.compact) v = p.first.compact[base + min(t, k - 1)];
-                    const int c = p.first.idx[base + min(t, k - 1)];
-                    const int col = t < k ? c : D;
-                    orow[col] = v + crow[col];
-                }
-                if constexpr (kSample2) {
-                    // second selection: its compact gradient is added at its own columns (the columns of one row
-                    // are distinct, and a row's threads share a wavefront, so the updates do not collide)
-                    if (p.second.idx) {
-                        __builtin_amdgcn_wave_barrier();
-                        const int k2 = p.second.k;
-                        const size_t base2 = (size_t)min(tile * BM + prow, p.rows - 1) * k2;
-                        // fetched here, four pairs per thread at a time: no registers held across the multiply
-                        for (int u0 = 0; u0 * TPR < k2; u0 += 4) {
-                            float v[4];
-                            int cc[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const int t = ppart + TPR * (u0 + u);
-                                v[u] = p.second.compact[base2 + min(t, k2 - 1)];
-                                const int c = p.second.idx[base2 + min(t, k2 - 1)];
-                                cc[u] = t < k2 ? c : D;
-                            }
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) orow[cc[u]] += v[u];
-                        }
-                    }
-                }
-                if constexpr (kSample2) {
-                    // ReLU in front of the layer: the gradient of a selected input that was not positive is zero
-                    // (outside the selections the row is zero anyway); the values are fetched here, late
-                    for (int pass = 0; pass < 2; ++pass) {
-                        const SampleSet& ss = pass ? p.second : p.first;
-                        if (!ss.gate || !ss.idx) continue;
-                        __builtin_amdgcn_wave_barrier();
-                        const int kg = ss.k;
-                        const size_t baseg = (size_t)min(tile * BM + prow, p.rows - 1) * kg;
-                        for (int u0 = 0; u0 * TPR < kg; u0 += 4) {
-                            float gv[4];
-                            int gc[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const int t = ppart + TPR * (u0 + u);
-                                gv[u] = ss.gate[baseg + min(t, kg - 1)];
-                                gc[u] = t < kg ? (int)ss.idx[baseg + min(t, kg - 1)] : D;
-                            }
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (!(gv[u] > 0.0f)) orow[gc[u]] = 0.0f;
-                        }
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < F4; ++it) {
-                    const int q = it * kWave + lane;
-                    const int row = wave * RPW + q / (D / 4), c4 = (q % (D / 4)) * 4;
-                    const int grow = tile * BM + row;
-                    const float4 v = *reinterpret_cast<const float4*>(bcur + row * LDA + c4);
-                    if (grow < p.rows) { float* oo = p.out + (size_t)grow * D + c4; __builtin_nontemporal_store(v.x, oo); __builtin_nontemporal_store(v.y, oo + 1); __builtin_nontemporal_store(v.z, oo + 2); __builtin_nontemporal_store(v.w, oo + 3); }
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-            clear_acc();
-            __builtin_amdgcn_sched_barrier(0);
-            if (has_next) commit(ntile, bother);    // a wavefront overwrites only the C rows it has just consumed
-            __syncthreads();
-            if (!has_next) break;
-            tile = ntile; cur ^= 1;
+        for (int rb = 0; rb < 2; ++rb) {
+            const int r = rg * 32 + rb * 16 + (lane & 15), c = 16 * nb + 4 * (lane >> 4);
+            *reinterpret_cast<f32x4*>(sC + r * LDC + c) = cS[rb];
+            // gathered next: these stay in the caches
+            store4<0>(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
+            if constexpr (CELL) store4<0>(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
         }
+        finish_t0();
+        if (!first_half) stage_next();
+        __syncthreads();                          // this self-term tile and the next operand tiles are complete
+        t0 = t;
+        q0 = q;
+        have_t0 = true;
+        if (t1 >= tiles) break;
+        t = t1;
+        q = q1;
+        q1 = q2;
     }
+    sample(segs + q0, t0, segs[q0].rows - (t0 - segs[q0].tile0) * T::BM, sC0 + cur * T::BM * LDC)();
 }
 
-template <int NT, int AK, int EPI>
-static int launch_proj(const GemmParams& p, hipStream_t s) {
-    using C = ProjCfg<NT>;
-    static std::atomic<int> resident_cache{0};         // persistent workgroups = what fits the chip at once
-    int resident = resident_cache.load(std::memory_order_acquire);
-    if (!resident) {                                   // concurrent first calls repeat the query: same answer
-        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&proj_kernel<NT, AK, EPI>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::kLds));
-        int per_cu = 0, dev = 0;
-        hipDeviceProp_t prop;
-        DRC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, proj_kernel<NT, AK, EPI>, kPT, C::kLds));
-        DRC_HIP(hipGetDevice(&dev));
-        DRC_HIP(hipGetDeviceProperties(&prop, dev));
-        resident = (per_cu < 1 ? 1 : per_cu) * prop.multiProcessorCount;
-        resident_cache.store(resident, std::memory_order_release);
-    }
-    const int n_tiles = (p.rows + C::BM - 1) / C::BM;
-    int grid = resident;
-    if (grid > n_tiles) grid = n_tiles;
-    hipLaunchKernelGGL((proj_kernel<NT, AK, EPI>), dim3((unsigned)grid), dim3(kPT), C::kLds, s, p);
-    DRC_HIP(hipGetLastError());
-    return DR_OK;
-}
-
-template <int NT>
-static int launch_proj_nt(const GemmParams& p, int ak, hipStream_t s) {
-    const int key = ak * 10 + p.epi;
-    switch (key) {
-        case kADense * 10 + kEpiStore: return launch_proj<NT, kADense, kEpiStore>(p, s);
-        case kADense * 10 + kEpiMaxMerge: return launch_proj<NT, kADense, kEpiMaxMerge>(p, s);
-        case kADense * 10 + kEpiSampleDense: return launch_proj<NT, kADense, kEpiSampleDense>(p, s);
-        case kADenseMasked * 10 + kEpiStore: return launch_proj<NT, kADenseMasked, kEpiStore>(p, s);
-        case kADenseMasked * 10 + kEpiSampleDense: return launch_proj<NT, kADenseMasked, kEpiSampleDense>(p, s);
-        case kADense * 10 + kEpiSampleDense2: return launch_proj<NT, kADense, kEpiSampleDense2>(p, s);
-        case kADenseMasked * 10 + kEpiSampleDense2: return launch_proj<NT, kADenseMasked, kEpiSampleDense2>(p, s);
-        case kACbsrDense * 10 + kEpiStore: return launch_proj<NT, kACbsrDense, kEpiStore>(p, s);
-        default: return fail(DR_ERR_UNSUPPORTED, "projection operand kind %d with epilogue %d is not built", ak, p.epi);
-    }
-}
-
-int launch_gemm(const GemmOperand* segs, int nseg, int64_t rows, int D, GemmEpilogue epi, float* out,
-                uint8_t* mask_out, SampleSet first, SampleSet second, hipStream_t s, int relu_out) {
-    if (rows == 0) return DR_OK;
-    GemmParams p{};
-    for (int i = 0; i < nseg; ++i) p.seg[i] = segs[i];
-    p.nseg = nseg;
-    p.rows = (int)rows;
-    p.epi = (int)epi;
-    p.out = out;
-    p.mask_out = mask_out;
-    p.first = first;
-    p.second = second;
-    p.relu = relu_out;
-    if (epi == kEpiSampleDense) {
-        if (first.k < 1 || !first.idx) return fail(DR_ERR_INVALID_ARG, "sampling epilogue without indices");
-        if (second.idx && (second.k < 1 || !second.compact))
-            return fail(DR_ERR_INVALID_ARG, "sampling epilogue: second selection without its compact gradient");
-        if (second.idx || !first.compact || first.gate || second.gate) p.epi = kEpiSampleDense2;
-    }
-    int ak;
-    if (nseg == 2) {
-        if (!segs[0].cbsr_vals || !segs[0].cbsr_idx || segs[0].k < 1 || !segs[1].dense || segs[1].mask)
-            return fail(DR_ERR_UNSUPPORTED, "two-segment projection expects (CBSR, unmasked dense) operands");
-        ak = kACbsrDense;
-    } else if (nseg == 1 && segs[0].dense) {
-        ak = segs[0].mask ? kADenseMasked : kADense;
-    } else {
-        return fail(DR_ERR_UNSUPPORTED, "projection with %d segments / a lone CBSR operand is not built", nseg);
-    }
-    switch (D / 32) {
-        case 1: return launch_proj_nt<1>(p, ak, s);
-        case 2: return launch_proj_nt<2>(p, ak, s);
-        case 3: return launch_proj_nt<3>(p, ak, s);
-        case 4: return launch_proj_nt<4>(p, ak, s);
-        default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
-    }
+template <int D>
+__global__ __launch_bounds__(Tile<D>::THREADS, waves_per_simd<D>()) void dproj_kernel(ProjBwdArgs a) {
+    extern __shared__ bf16x8 smem8[];
+    const DRC_CONST ProjBwdArgs* const k = kernel_args<ProjBwdArgs>();
+    if ((int)blockIdx.x < k->cell_wgs) proj_bwd_side<D, true>(k, smem8, blockIdx.x, k->cell_wgs);
+    else proj_bwd_side<D, false>(k, smem8, blockIdx.x - k->cell_wgs, gridDim.x - k->cell_wgs);
 }
 
 // ---------------------------------------------------------------------------------------------------
-// weight gradients  dW[D,D] = A^T B  (reduction over the graph's rows).  Persistent workgroups reduce a
-// contiguous slab of rows each: 16- or 32-row chunks of A and B are double-buffered through LDS (loads of the
-// next chunk in flight during the multiply of the current one), the full D x D accumulator lives in MFMA
-// registers (wavefront w owns row-tile w of dW), and the per-workgroup partials are summed by a second
-// kernel in a fixed order (deterministic, no atomics).
+// weight gradients  dW[D,D] = A^T B, reduced over the graph's rows
+//   cells  dW_neigh_near = H_near^T dZ_near,  dW_self_near = Xs^T dZ_near,  dW_pinned = H_pinned^T dZ_pinned
+//   nets   dW_neigh_pins = H_pins^T dY,       dW_self_pins = Xs^T dY
+// A workgroup takes every n-th chunk of rows of one side of one graph; all products of the side are accumulated in
+// registers (wavefront w: 16 rows of every dW, 96 registers for three products at D = 128) from one read of every
+// operand.  The contraction runs over rows, so a unit is eight rows of one column: a thread loads eight dwords down its
+// column.  A wavefront is alone in needing its 16 columns of H, so those go from memory to registers; what all wavefronts
+// need (dZ, and the scattered CBSR) goes through LDS.  Partial sums go to scratch and are added by a second kernel in a fixed order.
 // ---------------------------------------------------------------------------------------------------
-// rows staged per step: 16 at D = 128 (smaller staging registers: three wavefronts per SIMD), 32 below
-__host__ __device__ constexpr int wg_rows(int nt) { return nt == 4 ? 16 : 32; }
-constexpr int kWgRC = 32;                  // row slabs of the workgroups are multiples of this
-constexpr int kWgCP = 4;                   // CBSR pairs per thread prefetched into registers
-
-struct WgradParams {
-    WgradOperand op;
-    int rows;
-    int rows_per_block;
-    float* scratch;
+template <int D> struct WTile {
+    using T = Tile<D>;
+    static constexpr int RGN = T::THREADS / D;         // row groups of 8 rows in a chunk
+    static constexpr int CR = 8 * RGN;                 // rows per chunk: 32, or 64 / 128 for narrow D
+    static constexpr int KG = RGN / 4;                 // wavefronts that share output columns: each takes 32 rows of the chunk
+    static constexpr int PLANE = RGN * D;              // units per part
+    static constexpr int OPER = 3 * PLANE;
+    static constexpr int TPR = D == 32 ? 4 : 8;        // threads per CBSR row: a wavefront owns whole row groups
+    static_assert(KG == T::RG && CR * TPR <= T::THREADS, "chunk shape");
 };
 
-// AK: 0 = A dense, 1 = A as CBSR, 2 = both at once against the same B (two products, two partials: the dense
-// operand's first, the CBSR operand's nb partials after it)
-template <int NT, int AK, bool MASKED>
-__global__ __launch_bounds__(kPT, (NT == 4 && AK != 2 ? 3 : 2)) void wgrad_partial_kernel(WgradParams p) {
-    constexpr bool ADENSE = AK != 1, ACBSR = AK != 0;
-    constexpr int NA = AK == 2 ? 2 : 1;          // products accumulated
-    constexpr int kWgRC = wg_rows(NT);           // shadows the slab granule: rows per staged chunk here
-    constexpr int kWgTPR = kPT / kWgRC;          // threads sharing one chunk row when A arrives as CBSR
-    constexpr int D = NT * 32;
-    constexpr int LD = D + 4;
-    constexpr int F4 = kWgRC * D / 4 / kPT;      // float4 per thread per operand chunk
-    constexpr int kBuf = (NA + 1) * kWgRC * LD;  // one staging buffer: dense A | B | CBSR A (when both)
-    extern __shared__ __align__(16) float smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rb = blockIdx.x * p.rows_per_block;
-    const int re = min(rb + p.rows_per_block, p.rows);
-    const bool mm = wave < NT;                   // wavefront w owns dW rows [32w, 32w+32)
-    const int prow = tid / kWgTPR, ppart = tid % kWgTPR;
+struct WgradSeg {                 // one side of one graph
+    const float *dY, *H1, *H2, *vals;     // H2, mask: cells only
+    const uint8_t* mask;
+    const uint16_t* idx;
+    float* scratch;               // [products][wgs * KG][D * D]
+    float* dW[3];                 // H1's, CBSR's, H2's
+    int rows, k, wg0, wgs;
+};
+struct WgradArgs { WgradSeg s[2 * kMaxGraphs]; int n; };
+static_assert(sizeof(WgradArgs) < 4096, "kernel arguments");
 
-    floatx16 acc[NA][NT];
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][j][r] = 0.0f;
+template <int D, bool CELL>
+__device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* smem, int wg) {
+    using T = Tile<D>;
+    using W = WTile<D>;
+    constexpr int NP = CELL ? 3 : 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mb = wave % T::NB, kg = wave / T::NB;
+    const int col = tid % D, rgi = tid / D;                        // this thread's unit of a dense operand
+    const int prow = tid / W::TPR, ppart = tid % W::TPR;
+    const bool pairs = wave * 64 < W::CR * W::TPR;                 // whole wavefronts
+    const int hrow = (4 * kg + (lane >> 4)) * 8, hcol = 16 * mb + (lane & 15);   // this lane's unit of the H operands
 
-    // loads only (mask bytes raw); masking and range checks happen when the chunk is written to LDS.  Two register
-    // sets: a chunk's loads are issued two chunks ahead of its multiply (a whole multiply phase lies between a load
-    // and the LDS write that consumes it, which covers the memory latency under load); rows past the slab's end
-    // are clamped, so every load and every LDS write is unconditional.
-    struct Pre {
-        float4 a[F4], b[F4];
-        uint32_t m[F4];
-        float pv[kWgCP];
-        uint32_t pc[kWgCP];
-    };
-    Pre P0, P1;
-    auto prefetch = [&](int rr, Pre& P) {
+    f32x4 acc[NP][T::NB];
 #pragma unroll
-        for (int it = 0; it < F4; ++it) {
-            const int q = it * kPT + tid;
-            const int row = q / (D / 4), c4 = (q % (D / 4)) * 4;
-            const size_t off = (size_t)min(rr + row, re - 1) * D + c4;
-            P.b[it] = *reinterpret_cast<const float4*>(p.op.b + off);
-            if (MASKED) P.m[it] = *reinterpret_cast<const uint32_t*>(p.op.b_mask + off);
-            if (ADENSE) P.a[it] = *reinterpret_cast<const float4*>(p.op.a_dense + off);
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) acc[p][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    float y[8], h1[8], h2[8];
+    uint32_t mk[8];
+    PairRegs pr;
+    const int yoff = opaque((rgi * 8 * D + col) * 4), moff = opaque(rgi * 8 * D + col), hoff = opaque((hrow * D + hcol) * 4);
+    auto load_y = [&](int chunk) {                // past the last chunk: reads nothing
+        const int base = chunk * W::CR, left = g->rows - base;
+        const Buf by = block_view(g->dY + (size_t)base * D, left, D * 4);
+        const Buf bm = block_view(g->mask + (size_t)base * D, left, D);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            y[j] = load1(by, yoff + j * D * 4);
+            if constexpr (CELL) mk[j] = __builtin_amdgcn_raw_buffer_load_b8(bm, moff + j * D, 0, kNt);
         }
-        if (ACBSR) {
-            const int k = p.op.k;
-            const size_t base = (size_t)min(rr + prow, re - 1) * k;
+        load_pairs<W::TPR>(pr, block_view(g->vals + (size_t)base * g->k, left, g->k * 4), block_view(g->idx + (size_t)base * g->k, left, g->k * 2),
+                           g->k, prow, ppart);
+    };
+    auto load_h = [&](int chunk) {
+        const int base = chunk * W::CR, left = g->rows - base;
+        const Buf b1 = block_view(g->H1 + (size_t)base * D, left, D * 4);
+        const Buf b2 = block_view(g->H2 + (size_t)base * D, left, D * 4);
 #pragma unroll
-            for (int u = 0; u < kWgCP; ++u) {
-                const int t = min(ppart + kWgTPR * u, k - 1);
-                P.pv[u] = p.op.a_cbsr_vals[base + t];
-                P.pc[u] = p.op.a_cbsr_idx[base + t];
-            }
+        for (int j = 0; j < 8; ++j) {
+            h1[j] = load1(b1, hoff + j * D * 4);
+            if constexpr (CELL) h2[j] = load1(b2, hoff + j * D * 4);
         }
     };
-    auto commit = [&](int rr, float* buf, const Pre& P) {
-        float* const sA = buf;
-        float* const sB = buf + kWgRC * LD;
-        float* const sC = buf + (NA == 2 ? 2 * kWgRC * LD : 0);
-        const uint32_t keep = (uint32_t)p.op.b_mask_keep;
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto put = [&](bf16x8* oper, const Split8& s) {
 #pragma unroll
-        for (int it = 0; it < F4; ++it) {
-            const int q = it * kPT + tid;
-            const int row = q / (D / 4), c4 = (q % (D / 4)) * 4;
-            const bool in = rr + row < re;
-            float4 vb = P.b[it];
-            if (MASKED) {
-                const uint32_t m = P.m[it];
-                vb.x = (((m >> 0) & 0xffu) == keep) ? vb.x : 0.f;
-                vb.y = (((m >> 8) & 0xffu) == keep) ? vb.y : 0.f;
-                vb.z = (((m >> 16) & 0xffu) == keep) ? vb.z : 0.f;
-                vb.w = (((m >> 24) & 0xffu) == keep) ? vb.w : 0.f;
-            }
-            if (!in) vb = make_float4(0.f, 0.f, 0.f, 0.f);
-            *reinterpret_cast<float4*>(sB + row * LD + c4) = vb;
-            if (ADENSE) {
-                float4 va = P.a[it];
-                if (!in) va = make_float4(0.f, 0.f, 0.f, 0.f);
-                *reinterpret_cast<float4*>(sA + row * LD + c4) = va;
-            }
+        for (int p = 0; p < 3; ++p) oper[p * W::PLANE + tid] = s.p[p];          // unit (rgi, col) sits at rgi * D + col = tid
+    };
+    auto commit = [&](int chunk, bf16x8* buf) {
+        const Split8 sp = split8(y);
+        if constexpr (CELL) {
+            const Split8 s1 = select8(sp, [&](int j) { return mk[j] == 1u; }), s2 = select8(sp, [&](int j) { return mk[j] == 0u; });
+            put(buf, s1);
+            put(buf + 2 * W::OPER, s2);
+        } else {
+            put(buf, sp);
         }
-        if (ACBSR) {
-            // row-owned: the kWgTPR threads of a row share a wavefront, which zeroes the row and then
-            // scatters the pairs into it (LDS keeps a wavefront's accesses in order); every write is
-            // unconditional, pairs past k go to the padding column
-            float* rowp = sC + prow * LD;
+        if (pairs) {
+            // a wavefront owns whole row groups: it clears their units, then places the pairs (LDS keeps its order)
+            constexpr int RGW = 64 / W::TPR / 8;                               // row groups per wavefront
+            bf16x8* const opS = buf + W::OPER;
+            const bf16x8 z = {};
+            bf16x8* const mine = opS + wave * RGW * D + lane;
 #pragma unroll
-            for (int i = 0; i < D / kWgTPR / 4; ++i)
-                *reinterpret_cast<float4*>(rowp + ppart * (D / kWgTPR) + 4 * i) = z;
+            for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                for (int u = 0; u < RGW * D; u += 64)
+                    if (RGW * D % 64 == 0 || u + lane < RGW * D) mine[p * W::PLANE + u] = z;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            const int k = p.op.k;
-            const bool rin = rr + prow < re;
+            auto put_one = [&](int c, float v) {
+                put_parts(reinterpret_cast<__bf16*>(opS + (prow >> 3) * D + c) + (prow & 7), 8 * W::PLANE, v);
+            };
 #pragma unroll
-            for (int u = 0; u < kWgCP; ++u) {
-                const int t = ppart + kWgTPR * u;
-                rowp[t < k ? (int)P.pc[u] : D] = rin ? P.pv[u] : 0.f;
-            }
-            const size_t base = (size_t)min(rr + prow, re - 1) * k;
-            for (int u = kWgCP; u * kWgTPR < k; ++u) {
-                const int t = ppart + kWgTPR * u;
-                const float v = p.op.a_cbsr_vals[base + min(t, k - 1)];
-                const int c = p.op.a_cbsr_idx[base + min(t, k - 1)];
-                rowp[t < k ? c : D] = rin ? v : 0.f;
-            }
+            for (int u = 0; u < kPairs; ++u)
+                if (ppart + W::TPR * u < g->k) put_one((int)pr.c[u], pr.v[u]);      // rows past the end: a zero at column 0
+            const int row = chunk * W::CR + prow;
+            if (g->k > W::TPR * kPairs && row < g->rows)
+                for (int p = ppart + W::TPR * kPairs; p < g->k; p += W::TPR)
+                    put_one(g->idx[(size_t)row * g->k + p], g->vals[(size_t)row * g->k + p]);
         }
     };
-    auto multiply = [&](const float* buf) {
-        if (mm) {
-            // operands of k-step i+1 are read from LDS before the MFMAs of k-step i are issued
-            const float* pa = buf + (lane >> 5) * LD + wave * 32 + (lane & 31);
-            const float* pb = buf + kWgRC * LD + (lane >> 5) * LD + (lane & 31);
-            float av[2][NA], b[2][NT];
-#pragma unroll
-            for (int a = 0; a < NA; ++a) av[0][a] = pa[a * 2 * kWgRC * LD];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) b[0][j] = pb[j * 32];
-#pragma unroll
-            for (int i = 0; i < kWgRC / 2; ++i) {
-                if (i + 1 < kWgRC / 2) {
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) av[(i + 1) & 1][a] = pa[a * 2 * kWgRC * LD + (2 * i + 2) * LD];
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) b[(i + 1) & 1][j] = pb[(2 * i + 2) * LD + j * 32];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int a = 0; a < NA; ++a)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[a][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i & 1][a], b[i & 1][j], acc[a][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-
-    if (rb < re) {
-        float* const buf0 = smem;
-        float* const buf1 = smem + kBuf;
-        prefetch(rb, P0);
-        prefetch(rb + kWgRC, P1);
-        commit(rb, buf0, P0);
-        __syncthreads();
-        // buf0 holds chunk rr, P1 the loads of chunk rr + kWgRC; sched_barriers keep the consumers of the
-        // prefetched registers below the multiply
-        // (two chunks per trip, one exit at the bottom: the register sets stay where they are across the back edge;
-        // a slab with an odd number of chunks stages one chunk of zeros and skips its multiply)
-        int rr = rb;
-        do {
-            prefetch(rr + 2 * kWgRC, P0);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(buf0);
-            __builtin_amdgcn_sched_barrier(0);
-            commit(rr + kWgRC, buf1, P1);
-            __syncthreads();
-            prefetch(rr + 3 * kWgRC, P1);
-            __builtin_amdgcn_sched_barrier(0);
-            if (rr + kWgRC < re) multiply(buf1);
-            __builtin_amdgcn_sched_barrier(0);
-            commit(rr + 2 * kWgRC, buf0, P0);
-            __syncthreads();
-            rr += 2 * kWgRC;
-        } while (rr < re);
+    const int chunks = (g->rows + W::CR - 1) / W::CR;
+    const bool first_half = wave < T::WAVES / 2;
+    int chunk = wg, cur = 0;
+    if (chunk < chunks) {
+        load_y(chunk);
+        load_h(chunk);
+        commit(chunk, smem);
+        load_y(chunk + g->wgs);
     }
-
-    if (mm) {
+    for (; chunk < chunks; chunk += g->wgs, cur ^= 1) {
+        __syncthreads();                          // this chunk is in LDS; the other buffer may be overwritten
+        const int next = chunk + g->wgs;
+        bf16x8* const buf = smem + cur * 3 * W::OPER;
+        auto stage_next = [&]() {
+            commit(next, smem + (cur ^ 1) * 3 * W::OPER);
+            load_y(next + g->wgs);
+        };
+        if (first_half) stage_next();
+        __builtin_amdgcn_sched_barrier(0);
+        const Split8 a1 = split8(h1);
+        Split8 a2;
+        if constexpr (CELL) a2 = split8(h2);
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 aS[3];
 #pragma unroll
-        for (int a = 0; a < NA; ++a) {
-            float* out = p.scratch + ((size_t)a * gridDim.x + blockIdx.x) * D * D;
+        for (int p = 0; p < 3; ++p) aS[p] = buf[W::OPER + p * W::PLANE + (hrow >> 3) * D + hcol];
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
+        for (int j = 0; j < T::NB; ++j) {
+            // The five small products of this chunk are summed from zero and added with one rounding: inside the matrix
+            // unit they would be cut off below the running sum, always downwards, which over a million rows adds up (a
+            // 3e-6 error on random gradients, against 1e-6 for the fp32 instruction).
+            constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
+            const int ub = (hrow >> 3) * D + 16 * j + (lane & 15);
+            f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};
+            bf16x8 b[3];
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    out[(size_t)(wave * 32 + mfma_row(lane, r)) * D + j * 32 + (lane & 31)] = acc[a][j][r];
+            for (int p = 0; p < 3; ++p) b[p] = buf[p * W::PLANE + ub];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                lo0 = mfma(b[BW[i]], a1.p[AW[i]], lo0);
+                lo1 = mfma(b[BW[i]], aS[AW[i]], lo1);
+            }
+            acc[0][j] = mfma(b[0], a1.p[0], acc[0][j]);
+            acc[1][j] = mfma(b[0], aS[0], acc[1][j]);
+            acc[0][j] += lo0;
+            acc[1][j] += lo1;
+            asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]));       // added here: the compiler would keep all sums to the end of the loop
+            __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
+            if constexpr (CELL) {
+#pragma unroll
+                for (int p = 0; p < 3; ++p) b[p] = buf[2 * W::OPER + p * W::PLANE + ub];
+                lo0 = lo1 = f32x4{0.f, 0.f, 0.f, 0.f};
+                lo0 = mfma(b[2], a2.p[0], lo0);
+                lo1 = mfma(b[1], a2.p[0], lo1);
+                lo0 = mfma(b[0], a2.p[2], lo0);
+                lo1 = mfma(b[0], a2.p[1], lo1);
+                lo0 = mfma(b[1], a2.p[1], lo0);
+                acc[2][j] = mfma(b[0], a2.p[0], acc[2][j]);
+                acc[2][j] += lo0 + lo1;
+                asm volatile("" : "+v"(acc[2][j]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
+        load_h(next);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!first_half) stage_next();
+    }
+    // lane: row 16 mb + (lane & 15) of dW, columns 16 j + 4 (lane >> 4) ..
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        float* out = g->scratch + ((size_t)p * g->wgs * W::KG + (size_t)wg * W::KG + kg) * D * D;
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j)
+            *reinterpret_cast<f32x4*>(out + (size_t)(16 * mb + (lane & 15)) * D + 16 * j + 4 * (lane >> 4)) = acc[p][j];
     }
 }
 
-// dW[q] = sum over partials, fixed order: wavefront j of a workgroup sums every 8th partial starting at j
-// for 64 consecutive outputs, then the 8 wavefront sums are added in order.
-__global__ __launch_bounds__(512) void wgrad_reduce_kernel(const float* __restrict__ scratch, int nb, int dd,
-                                                           float* __restrict__ dW) {
-    __shared__ float part[8][64];
+template <int D>
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void wgrad_partial_kernel(WgradArgs a) {
+    extern __shared__ bf16x8 smem8[];
+    int q = 0;
+    const DRC_CONST WgradArgs* const k = kernel_args<WgradArgs>();
+    while (q + 1 < k->n && (int)blockIdx.x >= k->s[q + 1].wg0) ++q;
+    const DRC_CONST WgradSeg* const g = k->s + q;
+    if (g->mask) wgrad_side<D, true>(g, smem8, blockIdx.x - g->wg0);
+    else wgrad_side<D, false>(g, smem8, blockIdx.x - g->wg0);
+}
+
+// dW[i] = sum over a side's partials in a fixed order: wavefront w of the workgroup sums partials w, w + 16, ... of 64 x 4
+// consecutive entries, then the 16 sums are added in order.  One launch for all products of all sides and graphs.
+constexpr int kRedWaves = 16;
+template <int D>
+__global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs a) {
+    __shared__ f32x4 part[kRedWaves][64];
+    constexpr int kBlocks = D * D / 256;                 // workgroups per product
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int q = blockIdx.x * 64 + lane;
-    float s = 0.0f;
-    if (q < dd) {
-        // eight loads in flight at a time (the adds keep their order): the kernel is bound by load latency otherwise
-        int b = wave;
-        for (; b + 56 < nb; b += 64) {
-            float v[8];
+    const int job = blockIdx.x / kBlocks, q = job / 3, prod = job % 3;
+    const WgradSeg& g = a.s[q];
+    if (g.dW[prod] == nullptr) return;
+    const int n = g.wgs * WTile<D>::KG;
+    const int at = (blockIdx.x % kBlocks) * 256 + 4 * lane;
+    const float* src = g.scratch + (size_t)prod * n * D * D + at;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int b = wave;
+    for (; b + 3 * kRedWaves < n; b += 4 * kRedWaves) {  // four loads in flight
+        f32x4 v[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = scratch[(size_t)(b + 8 * u) * dd + q];
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(src + (size_t)(b + u * kRedWaves) * D * D);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
-        }
-        for (; b < nb; b += 8) s += scratch[(size_t)b * dd + q];
+        for (int u = 0; u < 4; ++u) s += v[u];
     }
+    for (; b < n; b += kRedWaves) s += *reinterpret_cast<const f32x4*>(src + (size_t)b * D * D);
     part[wave][lane] = s;
     __syncthreads();
-    if (wave == 0 && q < dd) {
-        float t = 0.0f;
+    if (wave == 0) {
+        f32x4 t = part[0][lane];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) t += part[w][lane];
-        dW[q] = t;
+        for (int w = 1; w < kRedWaves; ++w) t += part[w][lane];
+        float* o = g.dW[prod] + at;                      // weight gradients need not be 16-byte aligned
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = t[r];
     }
 }
 
-static int wgrad_blocks(int64_t rows) {
-    int64_t nb = (rows + kWgRC - 1) / kWgRC;
-    if (nb > 512) nb = 512;
-    if (nb < 1) nb = 1;
-    return (int)nb;
+// ---------------------------------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------------------------------
+static int cu_count(int* out) {
+    static std::atomic<int> cached{0};
+    int n = cached.load(std::memory_order_acquire);
+    if (!n) {
+        int dev = 0;
+        DRC_HIP(hipGetDevice(&dev));
+        DRC_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        cached.store(n, std::memory_order_release);
+    }
+    *out = n;
+    return DR_OK;
 }
 
-// room for the two partial sets of a paired launch
-size_t wgrad_scratch_bytes(int64_t rows, int D) { return sizeof(float) * 2 * (size_t)wgrad_blocks(rows) * D * D; }
-
-template <int NT, int AK, bool MASKED>
-static int launch_wgrad_kernel(const WgradParams& p, int nb, hipStream_t s) {
-    constexpr size_t lds = sizeof(float) * 2 * (AK == 2 ? 3 : 2) * wg_rows(NT) * (NT * 32 + 4);
-    static std::atomic<bool> configured{false};
-    if (!configured.load(std::memory_order_acquire)) {
-        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_partial_kernel<NT, AK, MASKED>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        configured.store(true, std::memory_order_release);
+// raises a kernel's LDS limit once and returns how many of its workgroups fit the chip
+template <typename K> static int resident(K kernel, int threads, size_t lds, std::atomic<int>& cache, int* out) {
+    int n = cache.load(std::memory_order_acquire);
+    if (!n) {                                          // concurrent first calls repeat the query: same answer
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        int per_cu = 0, cus = 0;
+        DRC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
+        DRC_TRY(cu_count(&cus));
+        n = (per_cu < 1 ? 1 : per_cu) * cus;
+        cache.store(n, std::memory_order_release);
     }
-    hipLaunchKernelGGL((wgrad_partial_kernel<NT, AK, MASKED>), dim3((unsigned)nb), dim3(kPT), lds, s, p);
+    *out = n;
+    return DR_OK;
+}
+
+// Workgroups of the two sides: in proportion to their work (three and two products per row), all of them resident.
+static void share(int64_t cell_work, int64_t net_work, int cell_tiles, int net_tiles, int res, int* cells, int* nets) {
+    if (cell_tiles + net_tiles <= res) { *cells = cell_tiles; *nets = net_tiles; return; }
+    int64_t c = (cell_work * res + (cell_work + net_work) / 2) / (cell_work + net_work);
+    if (c < 1 && cell_tiles) c = 1;
+    if (c > res - 1 && net_tiles) c = res - 1;
+    if (!cell_tiles) c = 0;
+    if (c > cell_tiles) c = cell_tiles;
+    *cells = (int)c;
+    int64_t n = res - c;
+    if (n > net_tiles) n = net_tiles;
+    *nets = (int)n;
+}
+
+template <int D> static int launch_proj_fwd_d(ProjFwdArgs& a, hipStream_t s) {
+    using T = Tile<D>;
+    static std::atomic<int> cache{0};
+    constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * T::OPER;
+    int res = 0;
+    DRC_TRY(resident(&proj_kernel<D>, T::THREADS, lds, cache, &res));
+    a.cell_tiles = a.net_tiles = 0;
+    for (int i = 0; i < a.n; ++i) {
+        a.cell[i].tile0 = a.cell_tiles; a.net[i].tile0 = a.net_tiles;
+        a.cell_tiles += (a.cell[i].rows + T::BM - 1) / T::BM;
+        a.net_tiles += (a.net[i].rows + T::BM - 1) / T::BM;
+    }
+    int nets = 0;
+    share(3ll * a.cell_tiles, 2ll * a.net_tiles, a.cell_tiles, a.net_tiles, res, &a.cell_wgs, &nets);
+    if (a.cell_wgs + nets == 0) return DR_OK;
+    hipLaunchKernelGGL((proj_kernel<D>), dim3((unsigned)(a.cell_wgs + nets)), dim3(T::THREADS), lds, s, a);
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
 
-template <int NT>
-static int launch_wgrad_nt(const WgradParams& p, int nb, hipStream_t s) {
-    const bool dense = p.op.a_dense != nullptr, cbsr = p.op.a_cbsr_vals != nullptr, masked = p.op.b_mask != nullptr;
-    if (dense && cbsr) return masked ? launch_wgrad_kernel<NT, 2, true>(p, nb, s) : launch_wgrad_kernel<NT, 2, false>(p, nb, s);
-    if (cbsr) return masked ? launch_wgrad_kernel<NT, 1, true>(p, nb, s) : launch_wgrad_kernel<NT, 1, false>(p, nb, s);
-    return masked ? launch_wgrad_kernel<NT, 0, true>(p, nb, s) : launch_wgrad_kernel<NT, 0, false>(p, nb, s);
-}
-
-// dW = A^T B.  With both a dense and a CBSR A operand in `op` the two products are formed in one pass over B:
-// the dense operand's goes to dW, the CBSR operand's to dW_cbsr (unused otherwise).
-int launch_wgrad(const WgradOperand& op, int64_t rows, int D, float* dW, float* dW_cbsr, void* scratch, hipStream_t s) {
-    const bool cbsr = op.a_cbsr_vals != nullptr;
-    if (cbsr && (!op.a_cbsr_idx || op.k < 1)) return fail(DR_ERR_INVALID_ARG, "weight gradient: incomplete CBSR operand");
-    if (!op.a_dense && !cbsr) return fail(DR_ERR_INVALID_ARG, "weight gradient without an A operand");
-    const bool pair = op.a_dense && cbsr;
-    if (pair && !dW_cbsr) return fail(DR_ERR_INVALID_ARG, "paired weight gradient without its second output");
-    int nb = wgrad_blocks(rows);
-    int rpb = (int)((rows + nb - 1) / nb);
-    rpb = (rpb + kWgRC - 1) / kWgRC * kWgRC;
-    if (rpb < kWgRC) rpb = kWgRC;
-    nb = (int)((rows + rpb - 1) / rpb);
-    if (nb < 1) nb = 1;
-    WgradParams p{op, (int)rows, rpb, static_cast<float*>(scratch)};
-    int rc;
-    switch (D / 32) {
-        case 1: rc = launch_wgrad_nt<1>(p, nb, s); break;
-        case 2: rc = launch_wgrad_nt<2>(p, nb, s); break;
-        case 3: rc = launch_wgrad_nt<3>(p, nb, s); break;
-        case 4: rc = launch_wgrad_nt<4>(p, nb, s); break;
+int launch_proj_fwd(const ProjFwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, bool relu, hipStream_t s) {
+    if (n > kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "projection of %d graphs in one launch", n);
+    ProjFwdArgs a{};
+    a.n = n;
+    a.relu = relu ? 1 : 0;
+    a.w_self_near = W.self_near; a.w_neigh_near = W.neigh_near; a.w_pinned = W.pinned;
+    a.w_self_pins = W.self_pins; a.w_neigh_pins = W.neigh_pins;
+    for (int i = 0; i < n; ++i) {
+        const ProjFwdJob& j = jobs[i];
+        a.cell[i] = ProjFwdSide{j.vals_near, j.H_near, j.H_pinned, j.idx_near, j.Y_cell, j.mask, (int)j.Nc, j.k_near, 0};
+        a.net[i] = ProjFwdSide{j.vals_self, j.H_pins, nullptr, j.idx_self, j.Y_net, nullptr, (int)j.Nn, j.k_self, 0};
+    }
+    switch (D) {
+        case 32: return launch_proj_fwd_d<32>(a, s);
+        case 64: return launch_proj_fwd_d<64>(a, s);
+        case 96: return launch_proj_fwd_d<96>(a, s);
+        case 128: return launch_proj_fwd_d<128>(a, s);
         default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
     }
-    if (rc) return rc;
-    const int dd = D * D;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((dd + 63) / 64)), dim3(512), 0, s,
-                       static_cast<float*>(scratch), nb, dd, dW);
-    if (pair)
-        hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((dd + 63) / 64)), dim3(512), 0, s,
-                           static_cast<float*>(scratch) + (size_t)nb * dd, nb, dd, dW_cbsr);
+}
+
+template <int D> static int launch_proj_bwd_d(ProjBwdArgs& a, hipStream_t s) {
+    using T = Tile<D>;
+    static std::atomic<int> cache{0};
+    constexpr size_t lds = sizeof(bf16x8) * 4 * T::OPER + sizeof(float) * 2 * T::BM * (D + 4);
+    int res = 0;
+    DRC_TRY(resident(&dproj_kernel<D>, T::THREADS, lds, cache, &res));
+    a.cell_tiles = a.net_tiles = 0;
+    for (int i = 0; i < a.n; ++i) {
+        a.cell[i].tile0 = a.cell_tiles; a.net[i].tile0 = a.net_tiles;
+        a.cell_tiles += (a.cell[i].rows + T::BM - 1) / T::BM;
+        a.net_tiles += (a.net[i].rows + T::BM - 1) / T::BM;
+    }
+    int nets = 0;
+    share(3ll * a.cell_tiles, 2ll * a.net_tiles, a.cell_tiles, a.net_tiles, res, &a.cell_wgs, &nets);
+    if (a.cell_wgs + nets == 0) return DR_OK;
+    hipLaunchKernelGGL((dproj_kernel<D>), dim3((unsigned)(a.cell_wgs + nets)), dim3(T::THREADS), lds, s, a);
     DRC_HIP(hipGetLastError());
     return DR_OK;
+}
+
+int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, hipStream_t s) {
+    if (n > kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "projection of %d graphs in one launch", n);
+    ProjBwdArgs a{};
+    a.n = n;
+    a.w_self_near = W.self_near; a.w_neigh_near = W.neigh_near; a.w_pinned = W.pinned;
+    a.w_self_pins = W.self_pins; a.w_neigh_pins = W.neigh_pins;
+    for (int i = 0; i < n; ++i) {
+        const ProjBwdJob& j = jobs[i];
+        a.cell[i] = ProjBwdSide{j.dY_cell, j.mask, j.dH_near, j.dH_pinned, j.idx_near, j.S_cell, (int)j.Nc, j.k_near, 0};
+        a.net[i] = ProjBwdSide{j.dY_net, nullptr, j.dH_pins, nullptr, j.idx_self, j.S_net, (int)j.Nn, j.k_self, 0};
+    }
+    switch (D) {
+        case 32: return launch_proj_bwd_d<32>(a, s);
+        case 64: return launch_proj_bwd_d<64>(a, s);
+        case 96: return launch_proj_bwd_d<96>(a, s);
+        case 128: return launch_proj_bwd_d<128>(a, s);
+        default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
+    }
+}
+
+constexpr int kWgradMaxWgs = 256;                       // one workgroup per compute unit (its tiles take 147 KB of LDS)
+
+template <int D> static int64_t wgrad_chunks(int64_t rows) { return (rows + WTile<D>::CR - 1) / WTile<D>::CR; }
+// at least two chunks per workgroup: the partial sums a workgroup writes weigh as much as the rows of four chunks
+template <int D> static int64_t wgrad_most(int64_t rows) {
+    const int64_t n = (wgrad_chunks<D>(rows) + 1) / 2;
+    return n > kWgradMaxWgs ? kWgradMaxWgs : (n < 1 ? 1 : n);
+}
+template <int D> static size_t wgrad_bytes_d(int64_t rows, int products) {
+    return sizeof(float) * products * (size_t)wgrad_most<D>(rows) * WTile<D>::KG * D * D;
+}
+size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
+    switch (D) {
+        case 32: return wgrad_bytes_d<32>(rows, products);
+        case 64: return wgrad_bytes_d<64>(rows, products);
+        case 96: return wgrad_bytes_d<96>(rows, products);
+        default: return wgrad_bytes_d<128>(rows, products);
+    }
+}
+
+template <int D> static int launch_wgrad_d(WgradArgs& a, hipStream_t s) {
+    using T = Tile<D>;
+    static std::atomic<int> cache{0};
+    constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * WTile<D>::OPER;
+    int res = 0;
+    DRC_TRY(resident(&wgrad_partial_kernel<D>, T::THREADS, lds, cache, &res));
+    if (res > kWgradMaxWgs) res = kWgradMaxWgs;
+    int64_t work = 0;
+    for (int i = 0; i < a.n; ++i) work += (int64_t)a.s[i].rows * (a.s[i].mask ? 3 : 2);
+    int wgs = 0;
+    for (int i = 0; i < a.n; ++i) {
+        WgradSeg& g = a.s[i];
+        int64_t n = work ? (int64_t)g.rows * (g.mask ? 3 : 2) * res / work : 1;
+        const int64_t most = wgrad_most<D>(g.rows);
+        g.wgs = (int)(n < 1 ? 1 : (n > most ? most : n));
+        g.wg0 = wgs;
+        wgs += g.wgs;
+    }
+    hipLaunchKernelGGL((wgrad_partial_kernel<D>), dim3((unsigned)wgs), dim3(T::THREADS), lds, s, a);
+    hipLaunchKernelGGL((wgrad_reduce_kernel<D>), dim3((unsigned)(a.n * 3 * (D * D / 256))), dim3(64 * kRedWaves), 0, s, a);
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+int launch_wgrads(const WgradJob* jobs, int n, int D, hipStream_t s) {
+    if (n > 2 * kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "weight gradients of %d operands in one launch", n);
+    WgradArgs a{};
+    a.n = n;
+    for (int i = 0; i < n; ++i) {
+        const WgradJob& j = jobs[i];
+        a.s[i] = WgradSeg{j.dY, j.H1, j.H2, j.vals, j.mask, j.idx, static_cast<float*>(j.scratch), {j.dW_H1, j.dW_cbsr, j.dW_H2},
+                          (int)j.rows, j.k, 0, 0};
+    }
+    if (n == 0) return DR_OK;
+    switch (D) {
+        case 32: return launch_wgrad_d<32>(a, s);
+        case 64: return launch_wgrad_d<64>(a, s);
+        case 96: return launch_wgrad_d<96>(a, s);
+        case 128: return launch_wgrad_d<128>(a, s);
+        default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
+    }
 }
 
 }  // namespace drc

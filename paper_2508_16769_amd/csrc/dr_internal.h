@@ -50,11 +50,20 @@ __device__ __forceinline__ int xcd_contiguous_tile(int wg, int per_xcd) {
 
 // launchers (host side, argument checks already done by the ABI layer) ------------------------------
 int launch_topk(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, hipStream_t s);
-// the same rows selected at two widths in one pass over X (vals2 == nullptr: only the first)
-int launch_topk2(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, int k2, float* vals2, uint16_t* idx2,
-                 hipStream_t s);
+// Several embedding matrices in one launch; vals2 != nullptr: the same rows are selected at a second width in the same pass.
+struct TopkJob {
+    const float* X;
+    int64_t n;
+    int k;
+    float* vals;
+    uint16_t* idx;
+    int k2;
+    float* vals2;
+    uint16_t* idx2;
+};
+int launch_topks(const TopkJob* jobs, int n, int D, hipStream_t s);
 // DR-SpMM.  A job is one relation; jobs of one call may share launches and run side by side.
-constexpr int kMaxSegs = 24;     // relations per launch (their descriptors travel as kernel arguments)
+constexpr int kMaxSegs = 18;     // relations per launch (their descriptors travel as kernel arguments)
 struct SpmmFwdJob {
     const dr_csr* A;
     const float* xs_vals;
@@ -70,6 +79,28 @@ struct SpmmBwdJob {
     float* dXs;
     int accumulate;
 };
+struct CompactPiece {            // gradient on a selection [rows, k]; entries whose gate value is not positive are dropped
+    const uint16_t* idx;
+    int k;
+    const float *vals, *gate;     // gate may be null
+};
+// Input gradient of one kind of source rows, written dense: dX[row, :] = 0 except at the columns of the row's selection
+// idx[row, :], where it is  init[row, t] + sum over the row's edges of At (gathering dH rows) and of At2 (gathering dH rows
+// col2_off further on); entries whose gate value is not positive are zero.  Up to two further compact pieces are added at
+// their own columns.  At, At2, init, gate and the pieces may be absent (k = 0: no selection of its own).
+struct SpmmDenseJob {
+    int64_t n_rows;
+    const dr_csr *At, *At2;
+    int col2_off;
+    const float* dH;              // at least one row is readable
+    const uint16_t* idx;
+    int k;
+    float* dX;
+    const float *init, *gate;
+    CompactPiece more[2];
+};
+constexpr int kDenseMaxK = 64;   // one window of compact slots
+int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s);    // n <= 64
 int launch_spmm_fwds(const SpmmFwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
 int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
 int launch_spmm_fwd(const dr_csr* A, const float* xs_vals, const uint16_t* xs_idx, int D, int k, float* H,
@@ -102,6 +133,8 @@ void spmm_plan_destroy(dr_spmm_plan* p);
 int launch_spmm_bwd_planned(const dr_spmm_plan* p, const float* dH, const uint16_t* xs_idx, int k, float* dXs, int accumulate,
                             hipStream_t s);
 
+constexpr int kMaxGraphs = 16;    // graphs per launch (their descriptors travel as kernel arguments)
+
 // shape of a layer context (heteroconv.hip owns the struct)
 struct HeteroDims {
     int64_t Nc, Nn;
@@ -121,56 +154,75 @@ struct ForwardOptions {
     bool relu_out = false;          // clamp Y_cell and Y_net at zero as they are written (the mask compares raw values)
     bool skip_net_output = false;   // Y_net (and H_pins) are not wanted: the pins module is not evaluated
 };
-int heteroconv_forward(dr_heteroconv* c, const float* X_cell, const float* X_net, const dr_heteroconv_weights* W, float* Y_cell,
-                       float* Y_net, const dr_heteroconv_saved* S, void* stream, ForwardOptions opt);
+// A layer pass over up to kMaxGraphs graphs that share the weights: every step is one launch for all of them.
+struct LayerFwd {
+    dr_heteroconv* c;
+    const float *X_cell, *X_net;
+    float *Y_cell, *Y_net;
+    const dr_heteroconv_saved* S;
+};
+int heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, ForwardOptions opt);
 struct BackwardOptions {
     bool gate_inputs = false;     // zero dX where the layer's input was not positive (ReLU in front of the layer)
     bool skip_dx = false;         // weight gradients only: dX_cell / dX_net are not written (and may be null)
     bool dy_net_zero = false;     // dY_net is all zeros: what it would feed is not computed (fills instead)
 };
-int heteroconv_backward(dr_heteroconv* c, const float* dY_cell, const float* dY_net, const dr_heteroconv_weights* W,
-                        const dr_heteroconv_saved* S, float* dX_cell, float* dX_net, const dr_heteroconv_wgrads* dW, void* stream,
-                        BackwardOptions opt);
+struct LayerBwd {
+    dr_heteroconv* c;
+    const float *dY_cell, *dY_net;
+    const dr_heteroconv_saved* S;
+    float *dX_cell, *dX_net;
+    dr_heteroconv_wgrads dW;
+};
+int heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt);
 int heteroconv_create_widths(dr_heteroconv** ctx, const dr_csr* near, const dr_csr* pins, const dr_csr* pinned, int32_t D,
                              int32_t k_near, int32_t k_pins, int32_t k_self, int32_t k_pinned);
 
 // dense part of the layer ------------------------------------------------------------------------------
-struct GemmOperand {              // one K-segment of C = sum_seg A_seg * B_seg
-    const float* dense;           // [rows, D] or nullptr
-    const float* cbsr_vals;       // [rows, k] (with cbsr_idx) when the operand is a D-ReLU output
-    const uint16_t* cbsr_idx;
-    int k;
-    const uint8_t* mask;          // optional [rows, D] gate applied to `dense`
-    int mask_keep;                // keep elements whose mask byte equals this value
-    const float* W;               // [D, D]
-    int transpose_w;              // 0: B = W, 1: B = W^T
+struct ProjFwdJob {               // one graph: Y_cell, mask, and (Nn > 0) Y_net from the saved selections and messages
+    int64_t Nc, Nn;               // Nn = 0: the net output is not wanted
+    const float* vals_near;
+    const uint16_t* idx_near;
+    int k_near;
+    const float *H_near, *H_pinned;
+    float* Y_cell;
+    uint8_t* mask;
+    const float* vals_self;
+    const uint16_t* idx_self;
+    int k_self;
+    const float* H_pins;
+    float* Y_net;
 };
-enum GemmEpilogue { kEpiStore = 0, kEpiMaxMerge = 1, kEpiSampleDense = 2 };
-struct SampleSet {                // a top-k selection [rows, k] and a compact gradient that lives on it
+int launch_proj_fwd(const ProjFwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, bool relu, hipStream_t s);
+
+struct ProjBwdJob {               // one graph: dH of the three relations and the sampled self-term gradients S [rows, k]
+    int64_t Nc, Nn;               // Nn = 0: dY_net is zero
+    const float* dY_cell;
+    const uint8_t* mask;
+    float *dH_near, *dH_pinned;
+    const uint16_t* idx_near;
+    int k_near;
+    float* S_cell;
+    const float* dY_net;
+    float* dH_pins;
+    const uint16_t* idx_self;
+    int k_self;
+    float* S_net;
+};
+int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, hipStream_t s);
+
+struct WgradJob {                 // one node type of one graph; with a mask: cells (three products), without: nets (two)
+    int64_t rows;
+    const float* dY;
+    const uint8_t* mask;
+    const float *H1, *H2;
+    const float* vals;
     const uint16_t* idx;
     int k;
-    const float* compact;         // [rows, k]; may be null in `first` (nothing to add to the sampled C)
-    const float* gate;            // optional [rows, k]: the selected input values; out is zeroed where they are <= 0
-};                                //   (the ReLU in front of the layer, applied to the layer's input gradient)
-// C[rows, D] = sum over segments; epilogue:
-//   kEpiStore       : out[rows,D] = C
-//   kEpiMaxMerge    : mask_out = (out >= C); out = max(out, C)        (out holds the near branch on entry)
-//   relu_out (kEpiStore, kEpiMaxMerge): what is written is clamped at zero (the mask still compares the raw values)
-//   kEpiSampleDense : out[row,:] = 0, then out[row, first.idx[row,t]] = C[row, first.idx[row,t]] + first.compact[row,t],
-//                     then (if second.idx) out[row, second.idx[row,t]] += second.compact[row,t]
-int launch_gemm(const GemmOperand* segs, int nseg, int64_t rows, int D, GemmEpilogue epi, float* out,
-                uint8_t* mask_out, SampleSet first, SampleSet second, hipStream_t s, int relu_out = 0);
-
-struct WgradOperand {             // dW[D,D] = A^T B over `rows` rows
-    const float* a_dense;         // [rows, D] or nullptr
-    const float* a_cbsr_vals;     // CBSR alternative for A
-    const uint16_t* a_cbsr_idx;
-    int k;
-    const float* b;               // [rows, D]
-    const uint8_t* b_mask;        // optional gate on b
-    int b_mask_keep;
+    float *dW_H1, *dW_cbsr, *dW_H2;
+    void* scratch;                // wgrad_scratch_bytes(rows, D, products)
 };
-size_t wgrad_scratch_bytes(int64_t rows, int D);
-int launch_wgrad(const WgradOperand& op, int64_t rows, int D, float* dW, float* dW_cbsr, void* scratch, hipStream_t s);
+size_t wgrad_scratch_bytes(int64_t rows, int D, int products);
+int launch_wgrads(const WgradJob* jobs, int n, int D, hipStream_t s);      // n <= 2 * kMaxGraphs
 
 }  // namespace drc

@@ -1,7 +1,11 @@
-// HeteroConv layer: per-graph context and the forward / backward schedules.  The three relation
-// pipelines (near, pins, pinned) run on three HIP streams of the one GPU and are joined by events only
-// where the data flow demands it (paper Section 3.4: independent sub-graph updates launched together,
-// merged at the cell node type).  The host never waits inside fwd / bwd.
+// HeteroConv layer: per-graph context and the forward / backward schedules.  The three relation modules (near, pins,
+// pinned) are independent of one another up to the merge at the cells (paper Section 3.4: independent sub-graph updates
+// launched together).  A step of the layer is ONE launch in which the workgroups of all relations -- and, in a model, of
+// all sub-graphs -- run side by side: a forward is three launches (D-ReLU, DR-SpMM, projections), a backward five (weight
+// gradients and their reduction, projection gradients, transposed DR-SpMM of a placed `near`, the other transposed DR-SpMMs
+// with the dense input gradients).  Three streams joined by events did the same with 24 launches and some 30 event
+// operations; a 2048-cell layer pass then took 0.21 ms, nearly all of it launch and event overhead.
+// Everything runs on the caller's stream, in order; the host never waits inside fwd / bwd.
 #include "dr_internal.h"
 
 #include <new>
@@ -10,16 +14,13 @@
 namespace {
 // kernel ids for the optional per-kernel timing (heteroconv_profile / heteroconv_kernel_times)
 enum KernelId {
-    kTopkCell, kTopkNet, kFwdNear, kFwdPins, kFwdPinned, kProjNear, kProjPins, kProjPinnedMerge,
-    kDhNear, kBwdNear, kWgNear, kDhPins, kBwdPins, kSelfNearSample,
-    kWgPins, kDhPinned, kBwdPinned, kSelfPinsSample, kWgPinned, kNumKernels
+    kTopkCell, kTopkNet, kFwdNear, kFwdPins, kFwdPinned, kProjCell, kProjPins,
+    kWgCell, kWgPins, kDhCell, kDhPins, kBwdNear, kBwdNearPins, kBwdPins, kBwdPinned, kNumKernels
 };
 const char* const kKernelNames[kNumKernels] = {
     "dr_topk.cell", "dr_topk.net", "dr_spmm_fwd.near", "dr_spmm_fwd.pins", "dr_spmm_fwd.pinned",
-    "proj.near", "proj.pins", "proj.pinned+merge",
-    "dproj.near", "dr_spmm_bwd.near", "wgrad.near", "dproj.pins", "dr_spmm_bwd.pins",
-    "dself.near+dX", "wgrad.pins", "dproj.pinned",
-    "dr_spmm_bwd.pinned", "dself.pins+dX", "wgrad.pinned"};
+    "proj.cell+merge", "proj.pins", "wgrad.cell", "wgrad.pins", "dproj.cell", "dproj.pins",
+    "dr_spmm_bwd.near", "dr_spmm_bwd.near+pins+dX", "dr_spmm_bwd.pins+dX", "dr_spmm_bwd.pinned+dX"};
 struct TimedLaunch { int id; hipEvent_t start, stop; bool start_shared; };   // start_shared: start is the previous launch's stop
 }  // namespace
 
@@ -40,24 +41,22 @@ struct dr_heteroconv {
     size_t t_wsb[3];
     void* owned[32];
     int n_owned;
-    hipStream_t st[3];  // near, pins, pinned
-    hipEvent_t ev_fork, ev_topk_cell, ev_topk_net, ev_near, ev_pins, ev_pinned, ev_gnear, ev_gpins;
     // backward scratch
-    float* dH[3];       // [Nc,D], [Nn,D], [Nc,D]
-    float* dXs_cell;    // [Nc,k_near]  compact gradient at the near selection (both cell pieces when k_pins == k_near)
-    float* dXs_cell_b;  // [Nc,k_pins]  pins piece at its own selection (only when k_pins != k_near)
-    float* dXs_net;     // [Nn,k_pinned]
-    float* wg_scratch[3];
+    float* dH;          // [Nc,D] near | [Nn,D] pins, behind one another so that one kernel can gather both
+    float* dH_pinned;   // [Nc,D]
+    float* S_cell;      // [Nc,k_near]  near self-term gradient at the near selection (plus near's own piece, where that is summed apart)
+    float* S_net;       // [Nn,k_self]  pins self-term gradient at its selection
+    float* G_pins;      // [Nc,k_pins]   pins piece, only where it needs a buffer of its own
+    float* G_pinned;    // [Nn,k_pinned] pinned piece, likewise
+    void* wg_scratch[2];   // cells, nets
     int device;
-    int overlap;        // DR_OVERLAP_*: whether the relation pipelines run on separate streams
+    int overlap;        // DR_OVERLAP_*: whether the relations of a step share a launch
     dr_spmm_plan* near_plan;   // transposed `near` with its dH rows staged in LDS tile by tile (heteroconv_set_cell_order), or null
     // optional per-kernel timing
     bool profile;
     std::vector<TimedLaunch>* timed;      // launches recorded since the last heteroconv_kernel_times
     std::vector<hipEvent_t>* event_pool;  // idle timing events
-    hipEvent_t chain_stop;                // stop event of the previous timed launch of this call, when it can serve
-    hipStream_t chain_stream;             //   as the start of the next one (same stream, nothing but launches between)
-    bool chain_ok;                        // all relations on one stream: consecutive launches run back to back
+    hipEvent_t chain_stop;                // stop event of the previous timed launch of this call: the start of the next one
 };
 
 using namespace drc;
@@ -74,7 +73,7 @@ namespace {
 
 int dev_alloc(dr_heteroconv* c, void** p, size_t bytes) {
     *p = nullptr;
-    if (bytes == 0) bytes = 256;
+    bytes += 1024;                        // a gather may read row 0 of an empty array
     DRC_HIP(hipMalloc(p, bytes));
     c->owned[c->n_owned++] = *p;
     return DR_OK;
@@ -84,12 +83,6 @@ void release(dr_heteroconv* c) {
     if (!c) return;
     spmm_plan_destroy(c->near_plan);
     for (int i = 0; i < c->n_owned; ++i) (void)hipFree(c->owned[i]);
-    for (int i = 0; i < 3; ++i)
-        if (c->st[i]) (void)hipStreamDestroy(c->st[i]);
-    hipEvent_t* evs[] = {&c->ev_fork, &c->ev_topk_cell, &c->ev_topk_net, &c->ev_near,
-                         &c->ev_pins, &c->ev_pinned, &c->ev_gnear, &c->ev_gpins};
-    for (hipEvent_t* e : evs)
-        if (*e) (void)hipEventDestroy(*e);
     if (c->timed) {
         for (TimedLaunch& t : *c->timed) { if (!t.start_shared) (void)hipEventDestroy(t.start); (void)hipEventDestroy(t.stop); }
         delete c->timed;
@@ -101,9 +94,9 @@ void release(dr_heteroconv* c) {
     delete c;
 }
 
-// Brackets one launch with timing events on its own stream when profiling is on.  With all relations on one
-// stream the launches of a call run back to back, so the stop event of one launch also serves as the start of
-// the next: one event record per launch instead of two (each record is a packet the GPU has to process).
+// Brackets one launch with timing events when profiling is on.  The launches of a call run back to back on one stream, so
+// the stop event of one launch also serves as the start of the next: one event record per launch instead of two (each
+// record is a packet the GPU has to process).
 struct ScopedTiming {
     dr_heteroconv* c; hipStream_t s; TimedLaunch t; bool on;
     hipEvent_t take() {
@@ -114,7 +107,7 @@ struct ScopedTiming {
     }
     ScopedTiming(dr_heteroconv* c_, int id, hipStream_t s_) : c(c_), s(s_), t{id, nullptr, nullptr, false}, on(false) {
         if (!c->profile) return;
-        if (c->chain_ok && c->chain_stop && c->chain_stream == s) {
+        if (c->chain_stop) {
             t.start = c->chain_stop;
             t.start_shared = true;
             t.stop = take();
@@ -130,7 +123,6 @@ struct ScopedTiming {
         (void)hipEventRecord(t.stop, s);
         c->timed->push_back(t);
         c->chain_stop = t.stop;
-        c->chain_stream = s;
     }
 };
 
@@ -170,14 +162,6 @@ int drc::heteroconv_create_capacity(dr_heteroconv** ctx, int64_t Nc, int64_t Nn,
     int rc = DR_OK;
     auto bail = [&](int code) { release(c); return code; };
     if (hipGetDevice(&c->device) != hipSuccess) return bail(hip_fail(hipGetLastError(), "hipGetDevice"));
-    for (int i = 0; i < 3; ++i)
-        if (hipStreamCreateWithFlags(&c->st[i], hipStreamNonBlocking) != hipSuccess)
-            return bail(hip_fail(hipGetLastError(), "hipStreamCreateWithFlags"));
-    hipEvent_t* evs[] = {&c->ev_fork, &c->ev_topk_cell, &c->ev_topk_net, &c->ev_near,
-                         &c->ev_pins, &c->ev_pinned, &c->ev_gnear, &c->ev_gpins};
-    for (hipEvent_t* e : evs)
-        if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess)
-            return bail(hip_fail(hipGetLastError(), "hipEventCreateWithFlags"));
 
     // buffers of the transposed adjacencies: A^T of relation i has as many rows as A has columns
     const int64_t t_rows[3] = {Nc, Nc, Nn}, a_rows[3] = {Nc, Nn, Nc};
@@ -188,14 +172,14 @@ int drc::heteroconv_create_capacity(dr_heteroconv** ctx, int64_t Nc, int64_t Nn,
         c->t_wsb[i] = dr_csr_transpose_workspace_bytes(a_rows[i], t_rows[i], E[i]);
         if (keep_workspace && (rc = dev_alloc(c, &c->t_ws[i], c->t_wsb[i]))) return bail(rc);
     }
-    const int64_t drows[3] = {Nc, Nn, Nc};
-    for (int i = 0; i < 3; ++i) {
-        if ((rc = dev_alloc(c, (void**)&c->dH[i], 4 * (size_t)drows[i] * D))) return bail(rc);
-        if ((rc = dev_alloc(c, (void**)&c->wg_scratch[i], wgrad_scratch_bytes(Nc > Nn ? Nc : Nn, D)))) return bail(rc);
-    }
-    if ((rc = dev_alloc(c, (void**)&c->dXs_cell, 4 * (size_t)Nc * k_near))) return bail(rc);
-    if (k_pins != k_near && (rc = dev_alloc(c, (void**)&c->dXs_cell_b, 4 * (size_t)Nc * k_pins))) return bail(rc);
-    if ((rc = dev_alloc(c, (void**)&c->dXs_net, 4 * (size_t)Nn * k_pinned))) return bail(rc);
+    if ((rc = dev_alloc(c, (void**)&c->dH, 4 * (size_t)(Nc + Nn) * D))) return bail(rc);
+    if ((rc = dev_alloc(c, (void**)&c->dH_pinned, 4 * (size_t)Nc * D))) return bail(rc);
+    if ((rc = dev_alloc(c, &c->wg_scratch[0], wgrad_scratch_bytes(Nc, D, 3)))) return bail(rc);
+    if ((rc = dev_alloc(c, &c->wg_scratch[1], wgrad_scratch_bytes(Nn, D, 2)))) return bail(rc);
+    if ((rc = dev_alloc(c, (void**)&c->S_cell, 4 * (size_t)Nc * k_near))) return bail(rc);
+    if ((rc = dev_alloc(c, (void**)&c->S_net, 4 * (size_t)Nn * k_self))) return bail(rc);
+    if (k_pins != k_near && k_pins > kDenseMaxK && (rc = dev_alloc(c, (void**)&c->G_pins, 4 * (size_t)Nc * k_pins))) return bail(rc);
+    if (k_self != k_pinned && k_pinned > kDenseMaxK && (rc = dev_alloc(c, (void**)&c->G_pinned, 4 * (size_t)Nn * k_pinned))) return bail(rc);
     *ctx = c;
     return DR_OK;
 }
@@ -253,7 +237,7 @@ int drc::heteroconv_create_widths(dr_heteroconv** ctx, const dr_csr* near, const
     int rc = DR_OK;
     for (int i = 0; i < 3 && rc == DR_OK; ++i)
         if (hipMalloc(&c->t_ws[i], c->t_wsb[i] ? c->t_wsb[i] : 256) != hipSuccess) rc = hip_fail(hipGetLastError(), "hipMalloc(transpose workspace)");
-    if (rc == DR_OK) rc = heteroconv_bind(c, near, pins, pinned, c->st[0]);
+    if (rc == DR_OK) rc = heteroconv_bind(c, near, pins, pinned, nullptr);
     const hipError_t e = hipDeviceSynchronize();
     for (int i = 0; i < 3; ++i) {
         if (c->t_ws[i]) (void)hipFree(c->t_ws[i]);
@@ -332,15 +316,14 @@ int heteroconv_set_overlap(dr_heteroconv* ctx, int mode) {
     return DR_OK;
 }
 
-// Separate streams pay off while one relation's kernels leave CUs idle at their tails (measured on MI355X:
-// 1.6x on 60k-cell graphs, 1.15x at 250k cells).  At 1.2M cells every launch has tens of thousands of
-// workgroups and the three pipelines only time-slice the CUs (1.5% difference), so they are issued back to
-// back on one stream instead, which keeps per-kernel timings attributable.
-static bool relations_overlap(const dr_heteroconv* c) {
-    if (c->overlap == DR_OVERLAP_ON) return true;
-    if (c->overlap == DR_OVERLAP_OFF) return false;
+// Whether each relation gets launches of its own.  Shared launches pay off while one relation's workgroups leave compute
+// units idle; at 1.2 M cells every launch has tens of thousands of workgroups, and a relation that is gathered right after
+// its D-ReLU was written still finds part of it in the memory-side cache.  Per-kernel timing needs separate launches.
+static bool relations_apart(const dr_heteroconv* c) {
+    if (c->profile || c->overlap == DR_OVERLAP_OFF) return true;
+    if (c->overlap == DR_OVERLAP_ON) return false;
     const int64_t rows = c->Nc > c->Nn ? c->Nc : c->Nn;
-    return rows * c->D < (int64_t(1) << 26);
+    return rows * c->D >= (int64_t(1) << 26);
 }
 
 int heteroconv_profile(dr_heteroconv* ctx, int enable) {
@@ -369,7 +352,7 @@ int heteroconv_profile_k(dr_heteroconv* c, const float* X_cell, const float* X_n
     float *vals = nullptr, *H = nullptr, *G = nullptr;
     uint16_t* idx = nullptr;
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
-    hipStream_t s = c->st[0];
+    hipStream_t s = nullptr;
     auto body = [&]() -> int {
         DRC_HIP(hipDeviceSynchronize());
         DRC_HIP(hipMalloc((void**)&vals, 4 * rows * kmax + 256));
@@ -485,198 +468,189 @@ static CbsrSets cbsr_sets(const dr_heteroconv* c, const dr_heteroconv_saved* S) 
 
 int heteroconv_fwd(dr_heteroconv* c, const float* X_cell, const float* X_net, const dr_heteroconv_weights* W,
                    float* Y_cell, float* Y_net, const dr_heteroconv_saved* S, void* stream) {
-    return heteroconv_forward(c, X_cell, X_net, W, Y_cell, Y_net, S, stream, ForwardOptions{});
+    const LayerFwd g{c, X_cell, X_net, Y_cell, Y_net, S};
+    return heteroconv_forward(&g, 1, W, as_stream(stream), ForwardOptions{});
 }
 
 int heteroconv_bwd(dr_heteroconv* c, const float* dY_cell, const float* dY_net, const dr_heteroconv_weights* W,
                    const dr_heteroconv_saved* S, float* dX_cell, float* dX_net, const dr_heteroconv_wgrads* dW,
                    void* stream) {
-    return heteroconv_backward(c, dY_cell, dY_net, W, S, dX_cell, dX_net, dW, stream, BackwardOptions{});
+    DRC_REQUIRE(dW && dW->self_near && dW->neigh_near && dW->self_pins && dW->neigh_pins && dW->pinned,
+                "heteroconv_bwd: null weight gradient");
+    const LayerBwd g{c, dY_cell, dY_net, S, dX_cell, dX_net, *dW};
+    return heteroconv_backward(&g, 1, W, as_stream(stream), BackwardOptions{});
 }
 
 }  // extern "C"
 
-int drc::heteroconv_forward(dr_heteroconv* c, const float* X_cell, const float* X_net, const dr_heteroconv_weights* W,
-                            float* Y_cell, float* Y_net, const dr_heteroconv_saved* S, void* stream, ForwardOptions opt) {
+int drc::heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, ForwardOptions opt) {
     // opt.skip_net_output: Y_net is not wanted (last layer of a model whose read-out uses the cells only): the pins
     // module -- its DR-SpMM and its projection -- is not launched, and H_pins / Y_net are left untouched.
-    const bool relu_out = opt.relu_out, pins_module = !opt.skip_net_output;
-    DRC_REQUIRE(c != nullptr, "heteroconv_fwd: null context");
-    DRC_REQUIRE(X_cell && X_net && Y_cell && Y_net, "heteroconv_fwd: null tensor");
-    DRC_REQUIRE(aligned(X_cell, 16) && aligned(X_net, 16) && aligned(Y_cell, 16) && aligned(Y_net, 16),
-                "heteroconv_fwd: tensors must be 16-byte aligned");
+    const bool pins_module = !opt.skip_net_output;
+    DRC_REQUIRE(n >= 1 && n <= kMaxGraphs, "heteroconv_fwd: %d graphs in one pass", n);
     DRC_TRY(check_weights(W, "heteroconv_fwd"));
-    DRC_TRY(check_saved(c, S, "heteroconv_fwd"));
-    hipStream_t user = as_stream(stream);
-    const bool ov = relations_overlap(c);
-    hipStream_t s_near = c->st[0], s_pins = ov ? c->st[1] : c->st[0], s_pinned = ov ? c->st[2] : c->st[0];
-    c->chain_stop = nullptr; c->chain_ok = !ov;
-    const int D = c->D;
-
-    DRC_HIP(hipEventRecord(c->ev_fork, user));
-    for (int i = 0; i < (ov ? 3 : 1); ++i) DRC_HIP(hipStreamWaitEvent(c->st[i], c->ev_fork, 0));   // only the streams that get work
-
-    // Enqueue order (it is the execution order when all relations share one stream): every D-ReLU output is
-    // gathered right after it is written, while it is still resident in the memory-side cache; the random
-    // relations (pinned, pins) come before the grid-local one, and the streaming projections last.
-    const CbsrSets q = cbsr_sets(c, S);
-
-    // D-ReLU(net), then pinned: net -> cell.  A node type that is read at two widths is selected at both in one
-    // pass over its embeddings.
-    {
-        ScopedTiming tm(c, kTopkNet, s_pinned);
-        DRC_TRY(launch_topk2(X_net, c->Nn, D, c->k_pinned, S->vals_net, S->idx_net, c->k_self,
-                             q.net_split ? S->vals_net_self : nullptr, q.net_split ? S->idx_net_self : nullptr, s_pinned));
+    TopkJob tk[2 * kMaxGraphs];
+    SpmmFwdJob sp[3 * kMaxGraphs];
+    ProjFwdJob pj[kMaxGraphs];
+    int n_sp = 0;
+    bool apart = false;
+    const int D = g[0].c ? g[0].c->D : 0;
+    for (int i = 0; i < n; ++i) {
+        const LayerFwd& L = g[i];
+        dr_heteroconv* c = L.c;
+        DRC_REQUIRE(c != nullptr, "heteroconv_fwd: null context");
+        DRC_REQUIRE(L.X_cell && L.X_net && L.Y_cell && L.Y_net, "heteroconv_fwd: null tensor");
+        DRC_REQUIRE(aligned(L.X_cell, 16) && aligned(L.X_net, 16) && aligned(L.Y_cell, 16) && aligned(L.Y_net, 16),
+                    "heteroconv_fwd: tensors must be 16-byte aligned");
+        const dr_heteroconv_saved* S = L.S;
+        DRC_TRY(check_saved(c, S, "heteroconv_fwd"));
+        c->chain_stop = nullptr;
+        apart = apart || relations_apart(c);
+        const CbsrSets q = cbsr_sets(c, S);
+        // A node type that is read at two widths is selected at both in one pass over its embeddings.
+        tk[2 * i] = TopkJob{L.X_net, c->Nn, c->k_pinned, S->vals_net, S->idx_net, c->k_self,
+                            q.net_split ? S->vals_net_self : nullptr, q.net_split ? S->idx_net_self : nullptr};
+        tk[2 * i + 1] = TopkJob{L.X_cell, c->Nc, c->k_near, S->vals_cell, S->idx_cell, c->k_pins,
+                                q.cell_split ? S->vals_cell_pins : nullptr, q.cell_split ? S->idx_cell_pins : nullptr};
+        if (pins_module) sp[n_sp++] = SpmmFwdJob{&c->A[1], q.v_pins, q.i_pins, c->k_pins, S->H_pins};     // the high-fanout nets start first
+        sp[n_sp++] = SpmmFwdJob{&c->A[2], q.v_pinned, q.i_pinned, c->k_pinned, S->H_pinned};
+        sp[n_sp++] = SpmmFwdJob{&c->A[0], q.v_near, q.i_near, c->k_near, S->H_near};
+        pj[i] = ProjFwdJob{c->Nc, pins_module ? c->Nn : 0, q.v_near, q.i_near, c->k_near, S->H_near, S->H_pinned, L.Y_cell, S->mask,
+                           q.v_self, q.i_self, c->k_self, S->H_pins, L.Y_net};
     }
-    DRC_HIP(hipEventRecord(c->ev_topk_net, s_pinned));
-    { ScopedTiming tm(c, kFwdPinned, s_pinned); DRC_TRY(launch_spmm_fwd(&c->A[2], q.v_pinned, q.i_pinned, D, c->k_pinned, S->H_pinned, s_pinned)); }
-
-    // D-ReLU(cell), then pins: cell -> net and near: cell -> cell
-    {
-        ScopedTiming tm(c, kTopkCell, s_near);
-        DRC_TRY(launch_topk2(X_cell, c->Nc, D, c->k_near, S->vals_cell, S->idx_cell, c->k_pins,
-                             q.cell_split ? S->vals_cell_pins : nullptr, q.cell_split ? S->idx_cell_pins : nullptr, s_near));
+    if (!(apart && n == 1)) {
+        DRC_TRY(launch_topks(tk, 2 * n, D, s));
+        DRC_TRY(launch_spmm_fwds(sp, n_sp, D, s));
+        return launch_proj_fwd(pj, n, *W, D, opt.relu_out, s);
     }
-    DRC_HIP(hipEventRecord(c->ev_topk_cell, s_near));
-    DRC_HIP(hipStreamWaitEvent(s_pins, c->ev_topk_cell, 0));
-    if (pins_module) { ScopedTiming tm(c, kFwdPins, s_pins); DRC_TRY(launch_spmm_fwd(&c->A[1], q.v_pins, q.i_pins, D, c->k_pins, S->H_pins, s_pins)); }
-    { ScopedTiming tm(c, kFwdNear, s_near); DRC_TRY(launch_spmm_fwd(&c->A[0], q.v_near, q.i_near, D, c->k_near, S->H_near, s_near)); }
-
-    // projections: near (self + neighbour), pins (self + neighbour), pinned merged into Y_cell by max
-    {
-        GemmOperand seg[2] = {};
-        seg[0].cbsr_vals = q.v_near; seg[0].cbsr_idx = q.i_near; seg[0].k = c->k_near; seg[0].W = W->self_near;
-        seg[1].dense = S->H_near; seg[1].W = W->neigh_near;
-        { ScopedTiming tm(c, kProjNear, s_near); DRC_TRY(launch_gemm(seg, 2, c->Nc, D, kEpiStore, Y_cell, nullptr, SampleSet{}, SampleSet{}, s_near)); }
-    }
-    DRC_HIP(hipEventRecord(c->ev_near, s_near));
-    DRC_HIP(hipStreamWaitEvent(s_pins, c->ev_topk_net, 0));
-    if (pins_module) {
-        GemmOperand seg[2] = {};
-        seg[0].cbsr_vals = q.v_self; seg[0].cbsr_idx = q.i_self; seg[0].k = c->k_self; seg[0].W = W->self_pins;
-        seg[1].dense = S->H_pins; seg[1].W = W->neigh_pins;
-        { ScopedTiming tm(c, kProjPins, s_pins); DRC_TRY(launch_gemm(seg, 2, c->Nn, D, kEpiStore, Y_net, nullptr, SampleSet{}, SampleSet{}, s_pins, relu_out ? 1 : 0)); }
-    }
-    DRC_HIP(hipEventRecord(c->ev_pins, s_pins));
-    DRC_HIP(hipStreamWaitEvent(s_pinned, c->ev_near, 0));
-    {
-        GemmOperand seg[1] = {};
-        seg[0].dense = S->H_pinned; seg[0].W = W->pinned;
-        { ScopedTiming tm(c, kProjPinnedMerge, s_pinned); DRC_TRY(launch_gemm(seg, 1, c->Nc, D, kEpiMaxMerge, Y_cell, S->mask, SampleSet{}, SampleSet{}, s_pinned, relu_out ? 1 : 0)); }
-    }
-    DRC_HIP(hipEventRecord(c->ev_pinned, s_pinned));
-
-    DRC_HIP(hipStreamWaitEvent(user, c->ev_pins, 0));
-    DRC_HIP(hipStreamWaitEvent(user, c->ev_pinned, 0));
+    // One launch per relation: every D-ReLU output is gathered right after it is written, the random relations (pinned,
+    // pins) before the grid-local one, the streaming projections last.
+    dr_heteroconv* c = g[0].c;
+    { ScopedTiming tm(c, kTopkNet, s); DRC_TRY(launch_topks(&tk[0], 1, D, s)); }
+    { ScopedTiming tm(c, kFwdPinned, s); DRC_TRY(launch_spmm_fwds(&sp[n_sp - 2], 1, D, s)); }
+    { ScopedTiming tm(c, kTopkCell, s); DRC_TRY(launch_topks(&tk[1], 1, D, s)); }
+    if (pins_module) { ScopedTiming tm(c, kFwdPins, s); DRC_TRY(launch_spmm_fwds(&sp[0], 1, D, s)); }
+    { ScopedTiming tm(c, kFwdNear, s); DRC_TRY(launch_spmm_fwds(&sp[n_sp - 1], 1, D, s)); }
+    ProjFwdJob part = pj[0];
+    part.Nn = 0;
+    { ScopedTiming tm(c, kProjCell, s); DRC_TRY(launch_proj_fwd(&part, 1, *W, D, opt.relu_out, s)); }
+    part = pj[0];
+    part.Nc = 0;
+    if (pins_module) { ScopedTiming tm(c, kProjPins, s); DRC_TRY(launch_proj_fwd(&part, 1, *W, D, opt.relu_out, s)); }
     return DR_OK;
 }
 
-int drc::heteroconv_backward(dr_heteroconv* c, const float* dY_cell, const float* dY_net, const dr_heteroconv_weights* W,
-                             const dr_heteroconv_saved* S, float* dX_cell, float* dX_net, const dr_heteroconv_wgrads* dW,
-                             void* stream, BackwardOptions opt) {
+int drc::heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt) {
     // opt.skip_dx: only the weight gradients are wanted (first layer of a model: nobody reads the gradient of the
     // input features), so the projections to dH, the transposed SpMMs and the dX write-outs are not launched.
     // opt.dy_net_zero: dY_net holds zeros (last layer of a model whose loss reads the cells only): everything it
-    // would feed is zero, so the pins module's dH, transposed SpMM and weight-gradient kernels are replaced by fills.
-    const bool gate_inputs = opt.gate_inputs, need_dx = !opt.skip_dx, net_zero = opt.dy_net_zero;
-    DRC_REQUIRE(c != nullptr, "heteroconv_bwd: null context");
-    DRC_REQUIRE(dY_cell && dY_net && (!need_dx || (dX_cell && dX_net)), "heteroconv_bwd: null tensor");
-    DRC_REQUIRE(aligned(dY_cell, 16) && aligned(dY_net, 16) && aligned(dX_cell, 16) && aligned(dX_net, 16),
-                "heteroconv_bwd: misaligned tensor");
+    // would feed is zero, so the pins module's dH, transposed SpMM and weight gradients are not computed.
+    const bool need_dx = !opt.skip_dx, net_zero = opt.dy_net_zero;
+    DRC_REQUIRE(n >= 1 && n <= kMaxGraphs, "heteroconv_bwd: %d graphs in one pass", n);
     DRC_TRY(check_weights(W, "heteroconv_bwd"));
-    DRC_TRY(check_saved(c, S, "heteroconv_bwd"));
-    DRC_REQUIRE(dW && dW->self_near && dW->neigh_near && dW->self_pins && dW->neigh_pins && dW->pinned,
-                "heteroconv_bwd: null weight gradient");
-    hipStream_t user = as_stream(stream);
-    const bool ov = relations_overlap(c);
-    hipStream_t s_near = c->st[0], s_pins = ov ? c->st[1] : c->st[0], s_pinned = ov ? c->st[2] : c->st[0];
-    c->chain_stop = nullptr; c->chain_ok = !ov;
-    const int D = c->D;
-
-    DRC_HIP(hipEventRecord(c->ev_fork, user));
-    for (int i = 0; i < (ov ? 3 : 1); ++i) DRC_HIP(hipStreamWaitEvent(c->st[i], c->ev_fork, 0));   // only the streams that get work
-
-    const CbsrSets q = cbsr_sets(c, S);
-
-    // ---- near stream: dH_near, its transposed SpMM (first piece of dXs_cell), near weight gradients ----
-    if (need_dx) {
-        GemmOperand seg[1] = {};
-        seg[0].dense = dY_cell; seg[0].mask = S->mask; seg[0].mask_keep = 1;
-        seg[0].W = W->neigh_near; seg[0].transpose_w = 1;
-        { ScopedTiming tm(c, kDhNear, s_near); DRC_TRY(launch_gemm(seg, 1, c->Nc, D, kEpiStore, c->dH[0], nullptr, SampleSet{}, SampleSet{}, s_near)); }
-        {
-            ScopedTiming tm(c, kBwdNear, s_near);
-            if (c->near_plan) DRC_TRY(launch_spmm_bwd_planned(c->near_plan, c->dH[0], q.i_near, c->k_near, c->dXs_cell, 0, s_near));
-            else DRC_TRY(launch_spmm_bwd(&c->At[0], c->dH[0], q.i_near, D, c->k_near, c->dXs_cell, 0, s_near));
+    WgradJob wj[2 * kMaxGraphs];
+    ProjBwdJob pj[kMaxGraphs];
+    SpmmBwdJob first[3 * kMaxGraphs], then[kMaxGraphs];      // compact sums; `then` adds to what `first` wrote
+    SpmmDenseJob dj[2 * kMaxGraphs];
+    int n_first = 0, n_then = 0;
+    bool apart = false;
+    const int D = g[0].c ? g[0].c->D : 0;
+    for (int i = 0; i < n; ++i) {
+        const LayerBwd& L = g[i];
+        dr_heteroconv* c = L.c;
+        DRC_REQUIRE(c != nullptr, "heteroconv_bwd: null context");
+        DRC_REQUIRE(L.dY_cell && L.dY_net && (!need_dx || (L.dX_cell && L.dX_net)), "heteroconv_bwd: null tensor");
+        DRC_REQUIRE(aligned(L.dY_cell, 16) && aligned(L.dY_net, 16) && aligned(L.dX_cell, 16) && aligned(L.dX_net, 16),
+                    "heteroconv_bwd: misaligned tensor");
+        const dr_heteroconv_saved* S = L.S;
+        DRC_TRY(check_saved(c, S, "heteroconv_bwd"));
+        c->chain_stop = nullptr;
+        apart = apart || relations_apart(c);
+        const CbsrSets q = cbsr_sets(c, S);
+        wj[2 * i] = WgradJob{c->Nc, L.dY_cell, S->mask, S->H_near, S->H_pinned, q.v_near, q.i_near, c->k_near,
+                             L.dW.neigh_near, L.dW.self_near, L.dW.pinned, c->wg_scratch[0]};
+        wj[2 * i + 1] = WgradJob{net_zero ? 0 : c->Nn, L.dY_net, nullptr, S->H_pins, nullptr, q.v_self, q.i_self, c->k_self,
+                                 L.dW.neigh_pins, L.dW.self_pins, nullptr, c->wg_scratch[1]};
+        if (!need_dx) continue;
+        float* const dH_pins = c->dH + (size_t)c->Nc * D;
+        pj[i] = ProjBwdJob{c->Nc, net_zero ? 0 : c->Nn, L.dY_cell, S->mask, c->dH, c->dH_pinned, q.i_near, c->k_near, c->S_cell,
+                           L.dY_net, dH_pins, q.i_self, c->k_self, c->S_net};
+        // ---- cells: self term and near at the near selection, pins at its own (the same where the widths coincide) ----
+        const float* g_near = opt.gate_inputs ? q.v_near : nullptr;
+        const float* g_pins = opt.gate_inputs ? q.v_pins : nullptr;
+        const bool split = q.cell_split && !net_zero;
+        const dr_csr* pins_t = net_zero ? nullptr : &c->At[1];
+        SpmmDenseJob& jc = dj[2 * i];
+        jc = SpmmDenseJob{};
+        jc.n_rows = c->Nc; jc.dX = L.dX_cell; jc.dH = c->dH;
+        const CompactPiece near_piece{q.i_near, c->k_near, c->S_cell, g_near};
+        const bool near_apart = c->near_plan || split || c->k_near > kDenseMaxK;   // near's sum joins the self term in S_cell first
+        if (near_apart && !c->near_plan) first[n_first++] = SpmmBwdJob{&c->At[0], c->dH, q.i_near, c->k_near, c->S_cell, 1};
+        if (!split) {
+            if (c->k_near <= kDenseMaxK) {
+                jc.idx = q.i_near; jc.k = c->k_near; jc.init = c->S_cell; jc.gate = g_near;
+                if (near_apart) { jc.At2 = pins_t; jc.dH = dH_pins; }
+                else { jc.At = &c->At[0]; jc.At2 = pins_t; jc.col2_off = (int)c->Nc; }
+            } else {
+                if (pins_t) then[n_then++] = SpmmBwdJob{pins_t, dH_pins, q.i_near, c->k_near, c->S_cell, 1};
+                jc.more[0] = near_piece;
+            }
+        } else {
+            jc.more[0] = near_piece;
+            if (c->k_pins <= kDenseMaxK) {
+                jc.idx = q.i_pins; jc.k = c->k_pins; jc.gate = g_pins;
+                jc.At2 = pins_t; jc.dH = dH_pins;
+            } else {
+                first[n_first++] = SpmmBwdJob{pins_t, dH_pins, q.i_pins, c->k_pins, c->G_pins, 0};
+                jc.more[1] = CompactPiece{q.i_pins, c->k_pins, c->G_pins, g_pins};
+            }
         }
-        DRC_HIP(hipEventRecord(c->ev_gnear, s_near));
+        // ---- nets: pinned at its selection, the pins self term at its own ----
+        const float* g_self = opt.gate_inputs ? q.v_self : nullptr;
+        const float* g_pinned = opt.gate_inputs ? q.v_pinned : nullptr;
+        SpmmDenseJob& jn = dj[2 * i + 1];
+        jn = SpmmDenseJob{};
+        jn.n_rows = c->Nn; jn.dX = L.dX_net; jn.dH = c->dH_pinned;
+        if (c->k_pinned <= kDenseMaxK) {
+            jn.At = &c->At[2]; jn.idx = q.i_pinned; jn.k = c->k_pinned; jn.gate = g_pinned;
+            if (!net_zero && !q.net_split) jn.init = c->S_net;
+        } else {
+            float* const to = q.net_split ? c->G_pinned : c->S_net;
+            first[n_first++] = SpmmBwdJob{&c->At[2], c->dH_pinned, q.i_pinned, c->k_pinned, to, (!q.net_split && !net_zero) ? 1 : 0};
+            jn.more[1] = CompactPiece{q.i_pinned, c->k_pinned, to, g_pinned};
+        }
+        if (q.net_split && !net_zero) jn.more[0] = CompactPiece{q.i_self, c->k_self, c->S_net, g_self};
     }
-    {
-        // both near weight gradients share dZ_near: one pass forms H_near^T dZ and Xs_cell^T dZ together
-        WgradOperand op = {};
-        op.a_dense = S->H_near; op.a_cbsr_vals = q.v_near; op.a_cbsr_idx = q.i_near; op.k = c->k_near;
-        op.b = dY_cell; op.b_mask = S->mask; op.b_mask_keep = 1;
-        { ScopedTiming tm(c, kWgNear, s_near); DRC_TRY(launch_wgrad(op, c->Nc, D, dW->neigh_near, dW->self_near, c->wg_scratch[0], s_near)); }
+    const bool alone = apart && n == 1;
+    // The weight gradients come first: what the projections write is then gathered right away.
+    if (!alone) {
+        DRC_TRY(launch_wgrads(wj, 2 * n, D, s));
+        if (!need_dx) return DR_OK;
+        DRC_TRY(launch_proj_bwd(pj, n, *W, D, s));
+        for (int i = 0; i < n; ++i)
+            if (g[i].c->near_plan)
+                DRC_TRY(launch_spmm_bwd_planned(g[i].c->near_plan, g[i].c->dH, cbsr_sets(g[i].c, g[i].S).i_near, g[i].c->k_near, g[i].c->S_cell, 1, s));
+        if (n_first) DRC_TRY(launch_spmm_bwds(first, n_first, D, s));
+        if (n_then) DRC_TRY(launch_spmm_bwds(then, n_then, D, s));
+        return launch_spmm_dense(dj, 2 * n, D, s);
     }
-    DRC_HIP(hipEventRecord(c->ev_near, s_near));
-
-    // ---- pins stream: dH_pins, second piece of the cell gradient, near self term, dense dX_cell, pins weight gradients.
-    // With one width for the cells the pins piece is added into dXs_cell; with two it keeps its own buffer and
-    // the write-out kernel adds it at its own positions. ----
-    const bool pins_piece = need_dx && !net_zero;           // the pins module's contribution to the cell gradient
-    if (pins_piece) {
-        GemmOperand seg[1] = {};
-        seg[0].dense = dY_net; seg[0].W = W->neigh_pins; seg[0].transpose_w = 1;
-        { ScopedTiming tm(c, kDhPins, s_pins); DRC_TRY(launch_gemm(seg, 1, c->Nn, D, kEpiStore, c->dH[1], nullptr, SampleSet{}, SampleSet{}, s_pins)); }
-        if (!q.cell_split) DRC_HIP(hipStreamWaitEvent(s_pins, c->ev_gnear, 0));
-        { ScopedTiming tm(c, kBwdPins, s_pins); DRC_TRY(launch_spmm_bwd(&c->At[1], c->dH[1], q.i_pins, D, c->k_pins, q.cell_split ? c->dXs_cell_b : c->dXs_cell,
-                                                                        q.cell_split ? 0 : 1, s_pins)); }
+    dr_heteroconv* c = g[0].c;
+    { ScopedTiming tm(c, kWgCell, s); DRC_TRY(launch_wgrads(&wj[0], 1, D, s)); }
+    { ScopedTiming tm(c, kWgPins, s); DRC_TRY(launch_wgrads(&wj[1], 1, D, s)); }
+    if (!need_dx) return DR_OK;
+    ProjBwdJob part = pj[0];
+    part.Nc = 0;
+    if (part.Nn) { ScopedTiming tm(c, kDhPins, s); DRC_TRY(launch_proj_bwd(&part, 1, *W, D, s)); }
+    part = pj[0];
+    part.Nn = 0;
+    { ScopedTiming tm(c, kDhCell, s); DRC_TRY(launch_proj_bwd(&part, 1, *W, D, s)); }
+    { ScopedTiming tm(c, kBwdPinned, s); DRC_TRY(launch_spmm_dense(&dj[1], dj[1].At ? 1 : 0, D, s)); }
+    if (c->near_plan) {
+        ScopedTiming tm(c, kBwdNear, s);
+        DRC_TRY(launch_spmm_bwd_planned(c->near_plan, c->dH, cbsr_sets(c, g[0].S).i_near, c->k_near, c->S_cell, 1, s));
     }
-    if (need_dx) {
-        if (q.cell_split || !pins_piece) DRC_HIP(hipStreamWaitEvent(s_pins, c->ev_gnear, 0));
-        GemmOperand seg[1] = {};
-        seg[0].dense = dY_cell; seg[0].mask = S->mask; seg[0].mask_keep = 1;
-        seg[0].W = W->self_near; seg[0].transpose_w = 1;
-        const SampleSet first{q.i_near, c->k_near, c->dXs_cell, gate_inputs ? q.v_near : nullptr};
-        const SampleSet second = (q.cell_split && pins_piece) ? SampleSet{q.i_pins, c->k_pins, c->dXs_cell_b, gate_inputs ? q.v_pins : nullptr}
-                                                             : SampleSet{};
-        { ScopedTiming tm(c, kSelfNearSample, s_pins); DRC_TRY(launch_gemm(seg, 1, c->Nc, D, kEpiSampleDense, dX_cell, nullptr, first, second, s_pins)); }
-    }
-    if (net_zero) {
-        DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(dW->neigh_pins), (size_t)D * D, 0u, s_pins));
-        DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(dW->self_pins), (size_t)D * D, 0u, s_pins));
-    } else {
-        WgradOperand op = {};
-        op.a_dense = S->H_pins; op.a_cbsr_vals = q.v_self; op.a_cbsr_idx = q.i_self; op.k = c->k_self; op.b = dY_net;
-        { ScopedTiming tm(c, kWgPins, s_pins); DRC_TRY(launch_wgrad(op, c->Nn, D, dW->neigh_pins, dW->self_pins, c->wg_scratch[1], s_pins)); }
-    }
-    DRC_HIP(hipEventRecord(c->ev_pins, s_pins));
-
-    // ---- pinned stream: dH_pinned, dXs_net, pins self term, dense dX_net, pinned weight gradient.  With two widths
-    // for the nets the self term is sampled at its own selection and the pinned piece added at the other. ----
-    if (need_dx) {
-        GemmOperand seg[1] = {};
-        seg[0].dense = dY_cell; seg[0].mask = S->mask; seg[0].mask_keep = 0;
-        seg[0].W = W->pinned; seg[0].transpose_w = 1;
-        { ScopedTiming tm(c, kDhPinned, s_pinned); DRC_TRY(launch_gemm(seg, 1, c->Nc, D, kEpiStore, c->dH[2], nullptr, SampleSet{}, SampleSet{}, s_pinned)); }
-        { ScopedTiming tm(c, kBwdPinned, s_pinned); DRC_TRY(launch_spmm_bwd(&c->At[2], c->dH[2], q.i_pinned, D, c->k_pinned, c->dXs_net, 0, s_pinned)); }
-        GemmOperand sg[1] = {};
-        sg[0].dense = dY_net; sg[0].W = W->self_pins; sg[0].transpose_w = 1;
-        const float* g_self = gate_inputs ? q.v_self : nullptr;
-        const float* g_pinned = gate_inputs ? q.v_pinned : nullptr;
-        const SampleSet first = q.net_split ? SampleSet{q.i_self, c->k_self, nullptr, g_self} : SampleSet{q.i_pinned, c->k_pinned, c->dXs_net, g_pinned};
-        const SampleSet second = q.net_split ? SampleSet{q.i_pinned, c->k_pinned, c->dXs_net, g_pinned} : SampleSet{};
-        { ScopedTiming tm(c, kSelfPinsSample, s_pinned); DRC_TRY(launch_gemm(sg, 1, c->Nn, D, kEpiSampleDense, dX_net, nullptr, first, second, s_pinned)); }
-    }
-    {
-        WgradOperand op = {};
-        op.a_dense = S->H_pinned; op.b = dY_cell; op.b_mask = S->mask; op.b_mask_keep = 0;
-        { ScopedTiming tm(c, kWgPinned, s_pinned); DRC_TRY(launch_wgrad(op, c->Nc, D, dW->pinned, nullptr, c->wg_scratch[2], s_pinned)); }
-    }
-    DRC_HIP(hipEventRecord(c->ev_pinned, s_pinned));
-
-    DRC_HIP(hipStreamWaitEvent(user, c->ev_near, 0));
-    DRC_HIP(hipStreamWaitEvent(user, c->ev_pins, 0));
-    DRC_HIP(hipStreamWaitEvent(user, c->ev_pinned, 0));
+    if (n_first) { ScopedTiming tm(c, kBwdNear, s); DRC_TRY(launch_spmm_bwds(first, n_first, D, s)); }
+    if (n_then) { ScopedTiming tm(c, kBwdPins, s); DRC_TRY(launch_spmm_bwds(then, n_then, D, s)); }
+    { ScopedTiming tm(c, dj[0].At ? kBwdNearPins : kBwdPins, s); DRC_TRY(launch_spmm_dense(&dj[0], dj[1].At ? 1 : 2, D, s)); }
     return DR_OK;
 }

@@ -564,7 +564,8 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
             ForwardOptions fo;
             fo.relu_out = l < L - 1;
             fo.skip_net_output = l == L - 1 && !m->inspect;   // the read-out uses the cells only
-            DRC_TRY(heteroconv_forward(gs.ctx, xc, xn, &W, gs.act_c[l], gs.act_n[l], &gs.saved[l], s, fo));
+            const LayerFwd lf{gs.ctx, xc, xn, gs.act_c[l], gs.act_n[l], &gs.saved[l]};
+            DRC_TRY(heteroconv_forward(&lf, 1, &W, s, fo));
             xc = gs.act_c[l]; xn = gs.act_n[l];
         }
         // ---- read-out, loss, gradient of the last layer's output ----
@@ -585,7 +586,8 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
             opt.gate_inputs = l >= 1;
             opt.skip_dx = l == 0 && !m->inspect;       // nobody reads the gradient of the input features
             opt.dy_net_zero = l == L - 1;                  // the loss reads the cells only: G_n[L] is the zero fill above
-            DRC_TRY(heteroconv_backward(gs.ctx, gs.G_c[l + 1], gs.G_n[l + 1], &W, &gs.saved[l], gs.G_c[l], gs.G_n[l], &dW, s, opt));
+            const LayerBwd lb{gs.ctx, gs.G_c[l + 1], gs.G_n[l + 1], &gs.saved[l], gs.G_c[l], gs.G_n[l], dW};
+            DRC_TRY(heteroconv_backward(&lb, 1, &W, s, opt));
         }
         DRC_HIP(hipGetLastError());
         DRC_HIP(hipEventRecord(gs.done, s));

@@ -44,6 +44,10 @@
 // Backward.  Lane t of a group owns the compact outputs t, t+8, t+16, ... of its source row and keeps
 // them in registers; per edge it reads dH[destination, idx[slot]] directly (the interleaved slot
 // assignment keeps the 8 lanes of one load inside one 128-byte line of the dH row when 4k = D).
+// In the layer the backward also finishes the input gradient (DENSE): a row's edges may come from two transposed
+// relations behind one another (near and pins, both with cells as sources), the compact self-term gradient enters as one
+// more record of the row, between the two lists, read like a gathered row, and the finished row is written once, dense, zero outside its
+// selection.  Separate kernels wrote the compact sums, read them back (per relation) and wrote the dense rows.
 #include "dr_internal.h"
 
 namespace drc {
@@ -61,6 +65,7 @@ constexpr unsigned kValid = 0x80000000u, kLast = 0x40000000u, kRowMask = 0x0000f
 
 template <int RW> struct WavePlan {
     int* sRp;      // [RW + 1] row pointers of the wavefront's rows
+    int* sRp2;     // [RW + 1] the same in the second list (DENSE)
     int* sOrder;   // [RW]     slot -> local row; solo rows by degree, descending
     int* sStart;   // [RW + 1] slot -> offset of the row's records in sorted-row order
     int2* sRec;    // [kCap]   staged (column, value bits) records
@@ -69,7 +74,9 @@ template <int RW> struct WavePlan {
     unsigned long long coop_mask, zero_mask, long_mask;
 };
 
-template <int RW> __host__ __device__ constexpr int plan_ints() { return 2 * kCap + (RW + 1) + RW + (RW + 1) + 2; }   // even: 3 RW + 4 + 2 kCap
+template <int RW, bool DENSE = false> __host__ __device__ constexpr int plan_ints() {
+    return 2 * kCap + (RW + 1) + RW + (RW + 1) + 2 + (DENSE ? RW + 2 : 0);      // even
+}
 
 // Orders the LDS accesses of one wavefront for the compiler (the hardware keeps them in program order).
 __device__ __forceinline__ void lds_fence() {
@@ -77,8 +84,10 @@ __device__ __forceinline__ void lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int RW>
-__device__ __forceinline__ WavePlan<RW> make_plan(int* base, const int32_t* __restrict__ rowptr, int r0, int nr) {
+// DENSE: rowptr may be null (no first list); rowptr2: second list of every row (may be null); extra: 1 if every row has one more record behind its lists
+template <int RW, bool DENSE = false>
+__device__ __forceinline__ WavePlan<RW> make_plan(int* base, const int32_t* __restrict__ rowptr, int r0, int nr,
+                                                  const int32_t* __restrict__ rowptr2 = nullptr, int extra = 0) {
     WavePlan<RW> p;
     p.sRec = reinterpret_cast<int2*>(base);
     p.sRp = base + 2 * kCap;
@@ -87,13 +96,22 @@ __device__ __forceinline__ WavePlan<RW> make_plan(int* base, const int32_t* __re
     p.sNext = p.sStart + (RW + 1);
 
     const int lane = threadIdx.x & (kWave - 1);
-    const int rp_lo = rowptr[r0 + min(lane, nr)];
-    const int rp_hi = rowptr[r0 + min(lane + 1, nr)];
+    const bool have = !DENSE || rowptr != nullptr;
+    const int rp_lo = have ? rowptr[r0 + min(lane, nr)] : 0;
+    const int rp_hi = have ? rowptr[r0 + min(lane + 1, nr)] : 0;
     if (lane <= nr) p.sRp[lane] = rp_lo;
-    const int deg = (lane < nr) ? (rp_hi - rp_lo) : -1;
-    const bool solo = deg >= 1 && deg <= kSolo;
+    int deg = (lane < nr) ? (rp_hi - rp_lo) : -1;
+    bool solo = deg >= 1 && deg <= kSolo;
+    if constexpr (DENSE) {
+        p.sRp2 = p.sNext + 2;
+        const int lo2 = rowptr2 ? rowptr2[r0 + min(lane, nr)] : 0, hi2 = rowptr2 ? rowptr2[r0 + min(lane + 1, nr)] : 0;
+        if (lane <= nr) p.sRp2[lane] = lo2;
+        const int tail = hi2 - lo2 + extra;       // either part of the row may be solo-sized: 2 * kSolo records fit a pass
+        solo = lane < nr && deg <= kSolo && tail <= kSolo && deg + tail >= 1;
+        deg += (lane < nr) ? tail : 0;
+    }
     p.long_mask = __ballot(deg > kLong);
-    p.coop_mask = __ballot(deg > kSolo && deg <= kLong);
+    p.coop_mask = __ballot(!solo && deg >= 1 && deg <= kLong);
     p.zero_mask = __ballot(deg == 0);
     p.n_solo = __popcll(__ballot(solo));
     // rank of every solo row among the solo rows: degree descending, row ascending
@@ -139,10 +157,45 @@ __device__ __forceinline__ int tag_class(int col, const uint8_t* __restrict__ ec
     return ecls ? (col | ((int)__builtin_nontemporal_load(ecls + e) << 30)) : col;
 }
 
-template <int RW>
-__device__ __forceinline__ void stage_solo(const WavePlan<RW>& p, const int32_t* __restrict__ colidx,
-                                           const float* __restrict__ avals, int sa, int sb,
-                                           const uint8_t* __restrict__ ecls = nullptr) {
+// Where the records of a row come from.
+struct RecSrc {
+    const int32_t* colidx;
+    const float* avals;
+    const uint8_t* ecls;
+    const int32_t* colidx2;       // second list (DENSE): its columns are shifted by col2_off
+    const float* avals2;
+    int col2_off, has_self;       // has_self: the row's own compact piece comes between the lists
+};
+struct RowSpan { int b1, d1, b2, d2; };      // first entry and number of entries in either list
+constexpr uint32_t kSelfRec = 0xffffffffu;   // column of the record that stands for the row's own compact piece
+
+template <int RW, bool DENSE> __device__ __forceinline__ RowSpan span_of(const WavePlan<RW>& p, int row) {
+    RowSpan r{p.sRp[row], p.sRp[row + 1] - p.sRp[row], 0, 0};
+    if constexpr (DENSE) { r.b2 = p.sRp2[row]; r.d2 = p.sRp2[row + 1] - p.sRp2[row]; }
+    return r;
+}
+
+template <bool DENSE> __device__ __forceinline__ int2 fetch_rec(const RecSrc& s, const RowSpan& r, int off) {
+    if constexpr (!DENSE) {
+        const int e = r.b1 + off;
+        return make_int2(tag_class(__builtin_nontemporal_load(s.colidx + e), s.ecls, e),
+                         __float_as_int(__builtin_nontemporal_load(s.avals + e)));
+    } else {
+        // first list, own piece, second list: the order in which the same sums are formed when the first relation is
+        // summed onto the own piece by the staged kernel, so that both ways give the same bits
+        int2 rec = make_int2((int)kSelfRec, __float_as_int(1.0f));
+        const bool second = off >= r.d1 + s.has_self;
+        if (off < r.d1 || second) {
+            const int e = second ? r.b2 + off - r.d1 - s.has_self : r.b1 + off;
+            rec.x = __builtin_nontemporal_load((second ? s.colidx2 : s.colidx) + e) + (second ? s.col2_off : 0);
+            rec.y = __float_as_int(__builtin_nontemporal_load((second ? s.avals2 : s.avals) + e));
+        }
+        return rec;
+    }
+}
+
+template <bool DENSE, int RW>
+__device__ __forceinline__ void stage_solo(const WavePlan<RW>& p, const RecSrc& src, int sa, int sb) {
     const int lane = threadIdx.x & (kWave - 1);
     const int base = p.sStart[sa];
     const int total = p.sStart[sb] - base;
@@ -156,9 +209,7 @@ __device__ __forceinline__ void stage_solo(const WavePlan<RW>& p, const int32_t*
             const int mid = (lo + hi) >> 1;
             if (p.sStart[mid] - base <= dd) lo = mid; else hi = mid;
         }
-        const int e = p.sRp[p.sOrder[lo]] + dd - (p.sStart[lo] - base);
-        r[j] = make_int2(tag_class(__builtin_nontemporal_load(colidx + e), ecls, e),
-                         __float_as_int(__builtin_nontemporal_load(avals + e)));
+        r[j] = fetch_rec<DENSE>(src, span_of<RW, DENSE>(p, p.sOrder[lo]), dd - (p.sStart[lo] - base));
     }
 #pragma unroll
     for (int j = 0; j < kStageIters; ++j) {
@@ -168,18 +219,14 @@ __device__ __forceinline__ void stage_solo(const WavePlan<RW>& p, const int32_t*
 }
 
 // Stages records [c0, c0 + n) of one long row (n <= kCap, n >= 1).
-template <int RW>
-__device__ __forceinline__ void stage_chunk(const WavePlan<RW>& p, const int32_t* __restrict__ colidx,
-                                            const float* __restrict__ avals, int c0, int n,
-                                            const uint8_t* __restrict__ ecls = nullptr) {
+template <bool DENSE, int RW>
+__device__ __forceinline__ void stage_chunk(const WavePlan<RW>& p, const RecSrc& src, const RowSpan& row, int c0, int n) {
     const int lane = threadIdx.x & (kWave - 1);
     int2 r[kStageIters];
 #pragma unroll
     for (int j = 0; j < kStageIters; ++j) {
         const int d = lane + kWave * j;
-        const int e = c0 + ((d < n) ? d : 0);
-        r[j] = make_int2(tag_class(__builtin_nontemporal_load(colidx + e), ecls, e),
-                         __float_as_int(__builtin_nontemporal_load(avals + e)));
+        r[j] = fetch_rec<DENSE>(src, row, c0 + ((d < n) ? d : 0));
     }
 #pragma unroll
     for (int j = 0; j < kStageIters; ++j) {
@@ -425,6 +472,7 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
     const float* __restrict__ xs_vals = s.xs_vals;
     const uint16_t* __restrict__ xs_idx = s.xs_idx;
     const int D = args.D, k = s.k, vec_store = s.vec_store;
+    const RecSrc src{colidx, avals, nullptr, nullptr, nullptr, 0, 0};
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = min((blk * kWPB + wave) * RW, s.M);
     const int nr = min(RW, s.M - r0);
@@ -457,7 +505,7 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
         DegreeK dkr = dk;
         if constexpr (ADAPT) dkr.k3 = dk.width(n, k);
         lds_fence();
-        stage_chunk(plan, colidx, avals, e0, n);
+        stage_chunk<false>(plan, src, RowSpan{e0, n, 0, 0}, 0, n);
         lds_fence();
         Stream st{g, n, row, g >= n ? 1 : 0};
         fwd_run<KPL, EPI, true, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dkr);
@@ -480,7 +528,7 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
         const int sb = pass_end(plan, sa);
         lds_fence();
         if (lane == 0) *plan.sNext = kNG;
-        stage_solo(plan, colidx, avals, sa, sb);
+        stage_solo<false>(plan, src, sa, sb);
         lds_fence();
         Stream st{0, 0, 0, 0};
         st.take_slot(plan, g, sa, sb - sa, plan.sStart[sa]);     // first 8 rows of the pass: one per group
@@ -502,7 +550,7 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
             for (int c0 = w0; c0 < w1; c0 += kCap) {
                 const int n = min(kCap, w1 - c0);
                 lds_fence();
-                stage_chunk(plan, colidx, avals, c0, n);
+                stage_chunk<false>(plan, src, RowSpan{c0, n, 0, 0}, 0, n);
                 lds_fence();
                 Stream st{g, n, 0, g >= n ? 1 : 0};
                 fwd_run<KPL, EPI, true, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dkr);
@@ -647,26 +695,33 @@ template <int KPL, int EPI> struct BwdBatch {
     unsigned meta[EPI];
 };
 
+// A staged saved column carries a flag in its top bit (columns are below 2^15): the slot's gradient is gated off.
+constexpr unsigned kIdxMask = 0x7fffu, kGateOff = 0x8000u;
+
 // saved columns of the slots lane t owns; ci[KPL] (one extra word) = column of the row's slot 0, which the
 // adaptive-K kernel reads in place of the slots a destination does not take
-template <int KPL>
+template <int KPL, bool DENSE>
 __device__ __forceinline__ void load_ci(int (&ci)[KPL + 1], const uint16_t* sIdx, int row, int t) {
 #pragma unroll
-    for (int u = 0; u < KPL; ++u) ci[u] = sIdx[row * (kLPE * KPL) + t + kLPE * u];
-    ci[KPL] = sIdx[row * (kLPE * KPL)];
+    for (int u = 0; u < KPL; ++u) ci[u] = sIdx[row * (kLPE * KPL) + t + kLPE * u] & (DENSE ? kIdxMask : 0xffffu);
+    ci[KPL] = sIdx[row * (kLPE * KPL)] & (DENSE ? kIdxMask : 0xffffu);
 }
 
 constexpr unsigned kClassShift = 16;   // adaptive-K backward: degree class of the record's destination in meta bits 16-17
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+// What DENSE adds: the rows' own compact pieces (rowbase: row number of local row 0).
+struct SelfPiece { const float* init; int rowbase; };
+
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, bool DENSE, int RW>
 __device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int (&ci)[KPL + 1], const WavePlan<RW>& plan,
                                           const uint16_t* sIdx, const float* __restrict__ dH, int D, int k, int t, int g,
-                                          int sa, int npass, int base, const DegreeK& dk) {
+                                          int sa, int npass, int base, const DegreeK& dk, const SelfPiece& self) {
 #pragma unroll
     for (int q = 0; q < EPI; ++q) {
         const bool valid = !st.done;
         const int2 rec = plan.sRec[valid ? st.cur : 0];
         uint32_t col = valid ? (uint32_t)rec.x : 0u;
+        const bool own = DENSE && col == kSelfRec;
         unsigned cls = 0;
         if constexpr (ADAPT) { cls = col >> 30; col &= kColMask; }
         b.a[q] = __int_as_float(rec.y);
@@ -677,6 +732,10 @@ __device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int
             const int kq = dk.width_of_class((int)cls, k);
 #pragma unroll
             for (int u = 0; u < KPL; ++u) b.v[q][u] = rowp[(t + kLPE * u < kq) ? ci[u] : ci[KPL]];
+        } else if constexpr (DENSE) {
+            const float* p = own ? self.init + (size_t)(self.rowbase + st.row) * (uint32_t)k : rowp;
+#pragma unroll
+            for (int u = 0; u < KPL; ++u) b.v[q][u] = p[own ? min(t + kLPE * u, k - 1) : ci[u]];
         } else {
 #pragma unroll
             for (int u = 0; u < KPL; ++u) b.v[q][u] = rowp[ci[u]];
@@ -684,15 +743,47 @@ __device__ __forceinline__ void bwd_issue(BwdBatch<KPL, EPI>& b, Stream& st, int
         unsigned m = 0;
         if (valid) {
             m = st.template advance<STRIDED, RW>(plan, sa, npass, base) | (cls << kClassShift);
-            if (!STRIDED && (m & kLast) && !st.done) load_ci<KPL>(ci, sIdx, st.row, t);
+            if (!STRIDED && (m & kLast) && !st.done) load_ci<KPL, DENSE>(ci, sIdx, st.row, t);
         }
         b.meta[q] = m;
     }
 }
 
-template <int KPL, int EPI, bool ADAPT>
+// Further pieces and output of a dense row: out[row, :] = rowbuf, plus a second compact piece at its own columns.
+struct DenseOut {
+    float* out;              // [N, D]
+    const CompactPiece* more;    // [2] further pieces at selections of their own (idx null: none)
+    int D;
+    float* rowbuf;           // [D] LDS, zero between rows
+    const uint16_t* sIdx;
+};
+
+// rowbuf holds the row's own values; called by a whole wavefront
+__device__ __forceinline__ void emit_row(const DenseOut& o, size_t row, int lane) {
+    lds_fence();
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const CompactPiece& c = o.more[m];
+        if (!c.idx) continue;
+        for (int q = lane; q < c.k; q += kWave) {           // the columns of one selection are distinct
+            const size_t at = row * c.k + q;
+            o.rowbuf[c.idx[at]] += (c.gate && !(c.gate[at] > 0.0f)) ? 0.0f : c.vals[at];
+        }
+        lds_fence();
+    }
+    float* p = o.out + row * o.D;
+    for (int c = 2 * lane; c < o.D; c += 2 * kWave) {       // D is a multiple of 32
+        const float2 v = *reinterpret_cast<const float2*>(o.rowbuf + c);
+        __builtin_nontemporal_store(v.x, p + c);
+        __builtin_nontemporal_store(v.y, p + c + 1);
+        *reinterpret_cast<float2*>(o.rowbuf + c) = make_float2(0.f, 0.f);
+    }
+    lds_fence();
+}
+
+template <int KPL, int EPI, bool ADAPT, bool DENSE>
 __device__ __forceinline__ void bwd_consume(const BwdBatch<KPL, EPI>& b, float (&acc)[KPL], float* __restrict__ Gblk,
-                                            int k, int s0, int t, int accumulate, const DegreeK& dk) {
+                                            int k, int s0, int t, int accumulate, const DegreeK& dk, const DenseOut& dense, int r0) {
 #pragma unroll
     for (int q = 0; q < EPI; ++q) {
         if (b.meta[q] & kValid) {
@@ -704,7 +795,7 @@ __device__ __forceinline__ void bwd_consume(const BwdBatch<KPL, EPI>& b, float (
 #pragma unroll
                 for (int u = 0; u < KPL; ++u) acc[u] = fmaf(b.a[q], b.v[q][u], acc[u]);
             }
-            if (b.meta[q] & kLast) {
+            if (!DENSE && (b.meta[q] & kLast)) {
                 float* o = Gblk + (size_t)(b.meta[q] & kRowMask) * k;
 #pragma unroll
                 for (int u = 0; u < KPL; ++u) {
@@ -714,47 +805,72 @@ __device__ __forceinline__ void bwd_consume(const BwdBatch<KPL, EPI>& b, float (
                 }
             }
         }
+        if constexpr (DENSE) {
+            // finished rows of this record, one after the other: the group scatters its slots, the wavefront writes the row
+            const int lane = threadIdx.x & (kWave - 1);
+            unsigned long long last = __ballot((b.meta[q] & (kValid | kLast)) == (kValid | kLast));
+            while (last) {
+                const int src = __ffsll((long long)last) - 1;
+                const int row = (int)((unsigned)__builtin_amdgcn_readlane((int)b.meta[q], src) & kRowMask);
+                if ((lane / kLPE) == (src / kLPE)) {
+#pragma unroll
+                    for (int u = 0; u < KPL; ++u) {
+                        const unsigned c = dense.sIdx[row * (kLPE * KPL) + t + kLPE * u];
+                        if (t + kLPE * u < k) dense.rowbuf[c & kIdxMask] = (c & kGateOff) ? 0.0f : acc[u];
+                        acc[u] = 0.f;
+                    }
+                }
+                emit_row(dense, (size_t)(r0 + row), lane);
+                last &= ~(0xffull << (src & ~(kLPE - 1)));
+            }
+        }
     }
 }
 
-template <int KPL, int EPI, bool STRIDED, bool ADAPT, int RW>
+template <int KPL, int EPI, bool STRIDED, bool ADAPT, bool DENSE, int RW>
 __device__ __forceinline__ void bwd_run(Stream& st, int (&ci)[KPL + 1], float (&acc)[KPL], const WavePlan<RW>& plan,
                                         const uint16_t* sIdx, const float* __restrict__ dH, float* __restrict__ Gblk,
                                         int D, int k, int s0, int t, int g, int sa, int npass, int base,
-                                        int accumulate, const DegreeK& dk) {
+                                        int accumulate, const DegreeK& dk, const SelfPiece& self, const DenseOut& dense) {
+    constexpr bool kFlush = DENSE && !STRIDED;       // a strided row is put together from the groups' parts afterwards
     BwdBatch<KPL, EPI> A, B;
-    bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
+    bwd_issue<KPL, EPI, STRIDED, ADAPT, DENSE, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk, self);
     for (;;) {
-        bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(B, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
-        bwd_consume<KPL, EPI, ADAPT>(A, acc, Gblk, k, s0, t, accumulate, dk);
+        bwd_issue<KPL, EPI, STRIDED, ADAPT, DENSE, RW>(B, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk, self);
+        bwd_consume<KPL, EPI, ADAPT, kFlush>(A, acc, Gblk, k, s0, t, accumulate, dk, dense, self.rowbase);
         if (!__any(B.meta[0] & kValid)) break;
-        bwd_issue<KPL, EPI, STRIDED, ADAPT, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk);
-        bwd_consume<KPL, EPI, ADAPT>(B, acc, Gblk, k, s0, t, accumulate, dk);
+        bwd_issue<KPL, EPI, STRIDED, ADAPT, DENSE, RW>(A, st, ci, plan, sIdx, dH, D, k, t, g, sa, npass, base, dk, self);
+        bwd_consume<KPL, EPI, ADAPT, kFlush>(B, acc, Gblk, k, s0, t, accumulate, dk, dense, self.rowbase);
         if (!__any(A.meta[0] & kValid)) break;
     }
 }
 
-struct SpmmBwdSeg {              // one transposed relation of a launch
+struct SpmmBwdSeg {              // the transposed relation (or pair of relations) of one kind of source rows
     const int32_t *rowptr, *colidx;
     const float *avals, *dH;
     const uint16_t* xs_idx;
-    float* dXs;
+    float* dXs;                  // compact [N, k], or (DENSE) dense [N, D]
     const uint8_t* ecls;
     int N, k, accumulate;
     int n_blocks, per_xcd, first;
+    // DENSE
+    const int32_t *rowptr2, *colidx2;
+    const float *avals2, *init, *gate;
+    CompactPiece more[2];
+    int col2_off;
 };
 struct SpmmBwdArgs { SpmmBwdSeg s[kMaxSegs]; int n, D; };
+static_assert(sizeof(SpmmBwdArgs) < 4096, "kernel arguments");
 
-template <int KPL, int RW> constexpr int bwd_wave_words() {     // LDS words of one wavefront
-    return kNG * kLPE * KPL + RW * kLPE * KPL / 2 + plan_ints<RW>();
+template <int KPL, int RW, bool DENSE> constexpr int bwd_wave_words(int D) {     // LDS words of one wavefront
+    return kNG * kLPE * KPL + RW * kLPE * KPL / 2 + plan_ints<RW, DENSE>() + (DENSE ? D : 0);
 }
 
-template <int KPL, int EPI, int RW, bool ADAPT>
-__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk) {
+template <int KPL, int EPI, int RW, bool ADAPT, bool DENSE>
+__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL == 4 ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk) {
     extern __shared__ float4 smem4[];
     __shared__ unsigned long long sLong[kWPB];
     constexpr int kWin = kLPE * KPL;                                       // compact slots per pass over the block
-    constexpr int kWords = bwd_wave_words<KPL, RW>();
     const int local = blockIdx.x / kNumXcd, xcd = blockIdx.x % kNumXcd;
     int sg = 0;
     while (sg + 1 < args.n && local >= args.s[sg + 1].first) ++sg;
@@ -762,60 +878,75 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
     const int blk = xcd * s.per_xcd + local - s.first;
     if (blk >= s.n_blocks) return;
     const int32_t* __restrict__ t_rowptr = s.rowptr;
-    const int32_t* __restrict__ t_colidx = s.colidx;
-    const float* __restrict__ t_vals = s.avals;
     const float* __restrict__ dH = s.dH;
     const uint16_t* __restrict__ xs_idx = s.xs_idx;
-    const uint8_t* __restrict__ ecls = ADAPT ? s.ecls : nullptr;
     const int D = args.D, k = s.k, accumulate = s.accumulate;
+    const RecSrc src{s.colidx, s.avals, ADAPT ? s.ecls : nullptr, s.colidx2, s.avals2, s.col2_off, DENSE && s.init ? 1 : 0};
+    const int kWords = bwd_wave_words<KPL, RW, DENSE>(D);
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float* const base0 = reinterpret_cast<float*>(smem4);
     float* part = base0 + wave * kWords;                                   // [kNG][kWin] long-row partials
     uint16_t* sIdx = reinterpret_cast<uint16_t*>(part + kNG * kWin);       // [RW][kWin] saved columns of the window
+    float* rowbuf = part + kNG * kWin + RW * kWin / 2 + plan_ints<RW, DENSE>();    // DENSE: [D]
     const int r0 = min((blk * kWPB + wave) * RW, s.N);
     const int nr = min(RW, s.N - r0);
     const int g = lane / kLPE, t = lane % kLPE;
     float* Gblk = s.dXs + (size_t)r0 * k;
+    const SelfPiece self{s.init, r0};
+    const DenseOut dense{s.dXs, s.more, D, rowbuf, sIdx};
 
-    WavePlan<RW> plan = make_plan<RW>(reinterpret_cast<int*>(part + kNG * kWin + RW * kWin / 2), t_rowptr, r0, nr);
+    WavePlan<RW> plan = make_plan<RW, DENSE>(reinterpret_cast<int*>(part + kNG * kWin + RW * kWin / 2), t_rowptr, r0, nr,
+                                             DENSE ? s.rowptr2 : nullptr, DENSE && s.init ? 1 : 0);
+    if constexpr (DENSE)
+        for (int c = lane; c < D; c += kWave) rowbuf[c] = 0.0f;
     if (lane == 0) sLong[wave] = plan.long_mask;
     __syncthreads();
     unsigned long long any_long = 0;
 #pragma unroll
     for (int w = 0; w < kWPB; ++w) any_long |= sLong[w];
 
-    for (int s0 = 0; s0 < k; s0 += kWin) {
+    for (int s0 = 0; s0 < (DENSE ? 1 : k); s0 += kWin) {         // DENSE: k <= kWin, one window
         // saved columns of this window for every row of the block (0 beyond k)
         lds_fence();
         for (int i = lane; i < nr * kWin; i += kWave) {
             const int row = i / kWin, w = i % kWin;
-            sIdx[i] = (s0 + w < k) ? __builtin_nontemporal_load(xs_idx + (size_t)(r0 + row) * k + s0 + w) : (uint16_t)0;
+            const size_t at = (size_t)(r0 + row) * k + s0 + w;
+            uint16_t c = (s0 + w < k) ? __builtin_nontemporal_load(xs_idx + at) : (uint16_t)0;
+            if constexpr (DENSE)
+                if (s.gate && w < k && !(__builtin_nontemporal_load(s.gate + at) > 0.0f)) c |= kGateOff;
+            sIdx[i] = c;
         }
         lds_fence();
 
-        // ---- rows without edges ----
-        if (!accumulate) {
+        // ---- rows without records ----
+        if (DENSE || !accumulate) {
             for (unsigned long long m = plan.zero_mask; m; m &= m - 1) {
-                float* o = Gblk + (size_t)(__ffsll((long long)m) - 1) * k;
-                for (int w = lane; w < kWin; w += kWave)
-                    if (s0 + w < k) o[s0 + w] = 0.0f;
+                const int row = __ffsll((long long)m) - 1;
+                if constexpr (DENSE) {
+                    emit_row(dense, (size_t)(r0 + row), lane);
+                } else {
+                    float* o = Gblk + (size_t)row * k;
+                    for (int w = lane; w < kWin; w += kWave)
+                        if (s0 + w < k) o[s0 + w] = 0.0f;
+                }
             }
         }
 
         // ---- long rows ----
         for (unsigned long long m = plan.coop_mask; m; m &= m - 1) {
             const int row = __ffsll((long long)m) - 1;
-            const int e0 = plan.sRp[row], n = plan.sRp[row + 1] - e0;      // n <= kLong = kCap: one staged chunk
+            const RowSpan span = span_of<RW, DENSE>(plan, row);
+            const int n = span.d1 + span.d2 + (DENSE && s.init ? 1 : 0);   // n <= kLong = kCap: one staged chunk
             int ci[KPL + 1];
             float acc[KPL];
-            load_ci<KPL>(ci, sIdx, row, t);
+            load_ci<KPL, DENSE>(ci, sIdx, row, t);
 #pragma unroll
             for (int u = 0; u < KPL; ++u) acc[u] = 0.f;
             lds_fence();
-            stage_chunk(plan, t_colidx, t_vals, e0, n, ecls);
+            stage_chunk<DENSE>(plan, src, span, 0, n);
             lds_fence();
             Stream st{g, n, row, g >= n ? 1 : 0};
-            bwd_run<KPL, EPI, true, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk);
+            bwd_run<KPL, EPI, true, ADAPT, DENSE, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk, self, dense);
 #pragma unroll
             for (int u = 0; u < KPL; ++u) part[g * kWin + t + kLPE * u] = acc[u];
             lds_fence();
@@ -824,10 +955,16 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
                     float sum = 0.f;
 #pragma unroll
                     for (int q = 0; q < kNG; ++q) sum += part[q * kWin + w];
-                    float* o = Gblk + (size_t)row * k + s0 + w;
-                    *o = accumulate ? (*o + sum) : sum;
+                    if constexpr (DENSE) {
+                        const unsigned c = sIdx[row * kWin + w];
+                        rowbuf[c & kIdxMask] = (c & kGateOff) ? 0.0f : sum;
+                    } else {
+                        float* o = Gblk + (size_t)row * k + s0 + w;
+                        *o = accumulate ? (*o + sum) : sum;
+                    }
                 }
             }
+            if constexpr (DENSE) emit_row(dense, (size_t)(r0 + row), lane);
             lds_fence();
         }
 
@@ -836,7 +973,7 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
             const int sb = pass_end(plan, sa);
             lds_fence();
             if (lane == 0) *plan.sNext = kNG;
-            stage_solo(plan, t_colidx, t_vals, sa, sb, ecls);
+            stage_solo<DENSE>(plan, src, sa, sb);
             lds_fence();
             Stream st{0, 0, 0, 0};
             st.take_slot(plan, g, sa, sb - sa, plan.sStart[sa]);
@@ -845,9 +982,9 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
             ci[KPL] = 0;
 #pragma unroll
             for (int u = 0; u < KPL; ++u) { ci[u] = 0; acc[u] = 0.f; }
-            if (!st.done) load_ci<KPL>(ci, sIdx, st.row, t);
-            bwd_run<KPL, EPI, false, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, sa, sb - sa, plan.sStart[sa],
-                                                accumulate, dk);
+            if (!st.done) load_ci<KPL, DENSE>(ci, sIdx, st.row, t);
+            bwd_run<KPL, EPI, false, ADAPT, DENSE, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, sa, sb - sa, plan.sStart[sa],
+                                                       accumulate, dk, self, dense);
             sa = sb;
         }
 
@@ -856,9 +993,12 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
         for (int w = 0; w < kWPB; ++w) {
             for (unsigned long long m = sLong[w]; m; m &= m - 1) {
                 const int row = (blk * kWPB + w) * RW + __ffsll((long long)m) - 1;
-                const int e0 = t_rowptr[row], e1 = t_rowptr[row + 1];
-                const int per = (e1 - e0 + kWPB - 1) / kWPB;
-                const int w0 = min(e0 + wave * per, e1), w1 = min(w0 + per, e1);
+                RowSpan span{0, 0, 0, 0};
+                if (!DENSE || t_rowptr) { span.b1 = t_rowptr[row]; span.d1 = t_rowptr[row + 1] - span.b1; }
+                if (DENSE && s.rowptr2) { span.b2 = s.rowptr2[row]; span.d2 = s.rowptr2[row + 1] - span.b2; }
+                const int n_all = span.d1 + span.d2 + (DENSE && s.init ? 1 : 0);
+                const int per = (n_all + kWPB - 1) / kWPB;
+                const int w0 = min(wave * per, n_all), w1 = min(w0 + per, n_all);
                 int ci[KPL + 1];
                 float acc[KPL];
 #pragma unroll
@@ -871,23 +1011,31 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
                 for (int c0 = w0; c0 < w1; c0 += kCap) {
                     const int n = min(kCap, w1 - c0);
                     lds_fence();
-                    stage_chunk(plan, t_colidx, t_vals, c0, n, ecls);
+                    stage_chunk<DENSE>(plan, src, span, c0, n);
                     lds_fence();
                     Stream st{g, n, 0, g >= n ? 1 : 0};
-                    bwd_run<KPL, EPI, true, ADAPT, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk);
+                    bwd_run<KPL, EPI, true, ADAPT, DENSE, RW>(st, ci, acc, plan, sIdx, dH, Gblk, D, k, s0, t, g, 0, 0, 0, accumulate, dk,
+                                                              SelfPiece{s.init, row}, dense);
                 }
 #pragma unroll
                 for (int u = 0; u < KPL; ++u) part[g * kWin + t + kLPE * u] = acc[u];
                 __syncthreads();
-                for (int i = threadIdx.x; i < kWin; i += kWPB * kWave) {
-                    if (s0 + i < k) {
-                        float sum = 0.f;
-                        for (int q = 0; q < kWPB; ++q)
+                if (wave == 0) {
+                    for (int i = lane; i < kWin; i += kWave) {
+                        if (s0 + i < k) {
+                            float sum = 0.f;
+                            for (int q = 0; q < kWPB; ++q)
 #pragma unroll
-                            for (int p = 0; p < kNG; ++p) sum += base0[q * kWords + p * kWin + i];
-                        float* o = s.dXs + (size_t)row * k + s0 + i;
-                        *o = accumulate ? (*o + sum) : sum;
+                                for (int p = 0; p < kNG; ++p) sum += base0[q * kWords + p * kWin + i];
+                            const size_t at = (size_t)row * k + s0 + i;
+                            if constexpr (DENSE) {
+                                rowbuf[xs_idx[at]] = (s.gate && !(s.gate[at] > 0.0f)) ? 0.0f : sum;
+                            } else {
+                                s.dXs[at] = accumulate ? (s.dXs[at] + sum) : sum;
+                            }
+                        }
                     }
+                    if constexpr (DENSE) emit_row(dense, (size_t)row, lane);
                 }
                 __syncthreads();
             }
@@ -895,7 +1043,7 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT ? 5 : 6)) void 
     }
 }
 
-template <int KPL, int EPI, bool ADAPT>
+template <int KPL, int EPI, bool ADAPT, bool DENSE>
 static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s) {
     int64_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.s[i].N;
@@ -909,10 +1057,10 @@ static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s) {
         g.first = first;
         first += g.per_xcd;
     }
-    const size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8>() : bwd_wave_words<KPL, 32>());
+    const size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8, DENSE>(a.D) : bwd_wave_words<KPL, 32, DENSE>(a.D));
     const dim3 grid((unsigned)(first * kNumXcd)), block(kWPB * kWave);
-    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT>), grid, block, lds, s, a, dk);
-    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT>), grid, block, lds, s, a, dk);
+    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds, s, a, dk);
+    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, DENSE>), grid, block, lds, s, a, dk);
 }
 
 static int bwd_kind(int k) { return k <= 8 ? 1 : (k <= 16 ? 2 : (k <= 32 ? 4 : 8)); }
@@ -935,14 +1083,47 @@ int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s) {
             const SpmmBwdJob& q = jobs[r];
             if ((done >> r & 1) || q.At->nnz == 0 || bwd_kind(q.k) != kind) continue;
             done |= 1ull << r;
-            a.s[a.n++] = SpmmBwdSeg{q.At->rowptr, q.At->colidx, q.At->vals, q.dH, q.xs_idx, q.dXs, nullptr, (int)q.At->n_rows, q.k,
-                                    q.accumulate ? 1 : 0, 0, 0, 0};
+            SpmmBwdSeg& g = a.s[a.n++];
+            g.rowptr = q.At->rowptr; g.colidx = q.At->colidx; g.avals = q.At->vals;
+            g.dH = q.dH; g.xs_idx = q.xs_idx; g.dXs = q.dXs;
+            g.N = (int)q.At->n_rows; g.k = q.k; g.accumulate = q.accumulate ? 1 : 0;
         }
         switch (kind) {
-            case 1: launch_bwd_kernel<1, 4, false>(a, DegreeK{}, s); break;
-            case 2: launch_bwd_kernel<2, 4, false>(a, DegreeK{}, s); break;
-            case 4: launch_bwd_kernel<4, 2, false>(a, DegreeK{}, s); break;
-            default: launch_bwd_kernel<8, 1, false>(a, DegreeK{}, s); break;
+            case 1: launch_bwd_kernel<1, 4, false, false>(a, DegreeK{}, s); break;
+            case 2: launch_bwd_kernel<2, 4, false, false>(a, DegreeK{}, s); break;
+            case 4: launch_bwd_kernel<4, 2, false, false>(a, DegreeK{}, s); break;
+            default: launch_bwd_kernel<8, 1, false, false>(a, DegreeK{}, s); break;
+        }
+    }
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+// The dense input gradient of several kinds of source rows (k <= kDenseMaxK).
+int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s) {
+    unsigned long long done = 0;
+    for (int i = 0; i < n; ++i) {
+        if ((done >> i & 1) || jobs[i].n_rows == 0) continue;
+        const int kind = bwd_kind(jobs[i].k);
+        SpmmBwdArgs a{};
+        a.D = D;
+        for (int r = i; r < n && a.n < kMaxSegs; ++r) {
+            const SpmmDenseJob& q = jobs[r];
+            if ((done >> r & 1) || q.n_rows == 0 || bwd_kind(q.k) != kind) continue;
+            done |= 1ull << r;
+            SpmmBwdSeg& g = a.s[a.n++];
+            if (q.At) { g.rowptr = q.At->rowptr; g.colidx = q.At->colidx; g.avals = q.At->vals; }
+            if (q.At2) { g.rowptr2 = q.At2->rowptr; g.colidx2 = q.At2->colidx; g.avals2 = q.At2->vals; g.col2_off = q.col2_off; }
+            g.dH = q.dH; g.xs_idx = q.idx; g.dXs = q.dX;
+            g.N = (int)q.n_rows; g.k = q.k;
+            g.init = q.init; g.gate = q.gate;
+            g.more[0] = q.more[0]; g.more[1] = q.more[1];
+        }
+        switch (kind) {
+            case 1: launch_bwd_kernel<1, 4, false, true>(a, DegreeK{}, s); break;
+            case 2: launch_bwd_kernel<2, 4, false, true>(a, DegreeK{}, s); break;
+            case 4: launch_bwd_kernel<4, 2, false, true>(a, DegreeK{}, s); break;
+            default: launch_bwd_kernel<8, 1, false, true>(a, DegreeK{}, s); break;
         }
     }
     DRC_HIP(hipGetLastError());
@@ -965,12 +1146,15 @@ int launch_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const 
     SpmmBwdArgs a{};
     a.D = D;
     a.n = 1;
-    a.s[0] = SpmmBwdSeg{At->rowptr, At->colidx, At->vals, dH, xr_idx, dXr, edge_class, (int)At->n_rows, c->k1, accumulate ? 1 : 0, 0, 0, 0};
+    SpmmBwdSeg& g = a.s[0];
+    g.rowptr = At->rowptr; g.colidx = At->colidx; g.avals = At->vals; g.ecls = edge_class;
+    g.dH = dH; g.xs_idx = xr_idx; g.dXs = dXr;
+    g.N = (int)At->n_rows; g.k = c->k1; g.accumulate = accumulate ? 1 : 0;
     switch (bwd_kind(c->k1)) {
-        case 1: launch_bwd_kernel<1, 4, true>(a, dk, s); break;
-        case 2: launch_bwd_kernel<2, 4, true>(a, dk, s); break;
-        case 4: launch_bwd_kernel<4, 2, true>(a, dk, s); break;
-        default: launch_bwd_kernel<8, 1, true>(a, dk, s); break;   // k <= 64: one window of slots (checked by the caller)
+        case 1: launch_bwd_kernel<1, 4, true, false>(a, dk, s); break;
+        case 2: launch_bwd_kernel<2, 4, true, false>(a, dk, s); break;
+        case 4: launch_bwd_kernel<4, 2, true, false>(a, dk, s); break;
+        default: launch_bwd_kernel<8, 1, true, false>(a, dk, s); break;   // k <= 64: one window of slots (checked by the caller)
     }
     DRC_HIP(hipGetLastError());
     return DR_OK;

@@ -29,17 +29,31 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
 
 constexpr int kRowsInFlight = 4;   // rows whose loads are outstanding per wavefront
 
+struct TopkSeg {                   // one embedding matrix of a launch
+    const float* X;
+    float *vals, *vals2;           // vals2 / idx2: a second selection of the same rows, or null
+    uint16_t *idx, *idx2;
+    int n, k, k2, blk0, n_blocks;  // workgroups [blk0, blk0 + n_blocks)
+};
+constexpr int kTopkSegs = 32;
+struct TopkArgs { TopkSeg s[kTopkSegs]; int n, D; };
+
 template <int EPL, bool DUAL, bool RANKED>
-__global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict__ X, int n, int D, int k,
-                                                        float* __restrict__ vals, uint16_t* __restrict__ idx, int k2,
-                                                        float* __restrict__ vals2, uint16_t* __restrict__ idx2) {
+__global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
     extern __shared__ uint4 kept_keys4[];                     // RANKED: [4 wavefronts][k rounded up to 4] keys of the current row
+    int sg = 0;
+    while (sg + 1 < args.n && (int)blockIdx.x >= args.s[sg + 1].blk0) ++sg;
+    const TopkSeg& seg = args.s[sg];
+    const float* __restrict__ X = seg.X;
+    float* __restrict__ vals = seg.vals;
+    uint16_t* __restrict__ idx = seg.idx;
+    const int n = seg.n, D = args.D, k = seg.k;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const int k4 = (k + 3) >> 2;
     uint32_t* const my_keys = reinterpret_cast<uint32_t*>(kept_keys4 + wave * k4);
-    const int stride = gridDim.x * (blockDim.x >> 6);        // rows between consecutive rows of one wavefront
-    const int row0 = blockIdx.x * (blockDim.x >> 6) + wave;
+    const int stride = seg.n_blocks * (blockDim.x >> 6);     // rows between consecutive rows of one wavefront
+    const int row0 = (blockIdx.x - seg.blk0) * (blockDim.x >> 6) + wave;
 
     // loads are unconditional (row and column clamped to valid addresses): the next rows stay in flight
     // while the current one is selected
@@ -157,7 +171,9 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict_
             const int row = base + i * stride;
             if (row < n) {
                 select_row(v[i], row, k, vals, idx, hint);
-                if constexpr (DUAL) select_row(v[i], row, k2, vals2, idx2, hint2);
+                if constexpr (DUAL) {
+                    if (seg.vals2) select_row(v[i], row, seg.k2, seg.vals2, seg.idx2, hint2);
+                }
             }
             load_row(v[i], row + kRowsInFlight * stride);
         }
@@ -165,48 +181,56 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict_
 }
 
 template <int EPL>
-static void launch_epl(const float* X, int n, int D, int k, float* vals, uint16_t* idx, int k2, float* vals2,
-                       uint16_t* idx2, bool ranked, hipStream_t s) {
-    // Each wavefront strides over rows with four of them in flight, so it wants at least four rows (a wavefront with
-    // one row pays the whole load latency for it: 20 000 rows took 15 us on 4096 workgroups, 9 us on 1250); beyond
-    // 8192 workgroups (four rounds of 8 waves per SIMD) nothing is gained.  Measured on 20 k ... 1.2 M rows.
-    const int waves_per_block = 4;
-    long blocks = ((long)n + 4 * waves_per_block - 1) / (4 * waves_per_block);
-    if (blocks > 8192) blocks = 8192;
-    if (ranked)
+static void launch_epl(const TopkArgs& a, int blocks, bool dual, int ranked_k, hipStream_t s) {
+    if (ranked_k)
         hipLaunchKernelGGL((topk_rows_kernel<EPL, false, true>), dim3((unsigned)blocks), dim3(256),
-                           sizeof(uint4) * 4 * (size_t)((k + 3) / 4), s, X, n, D, k, vals, idx, 0, nullptr, nullptr);
-    else if (vals2)
-        hipLaunchKernelGGL((topk_rows_kernel<EPL, true, false>), dim3((unsigned)blocks), dim3(256), 0, s, X, n, D, k, vals, idx,
-                           k2, vals2, idx2);
+                           sizeof(uint4) * 4 * (size_t)((ranked_k + 3) / 4), s, a);
+    else if (dual)
+        hipLaunchKernelGGL((topk_rows_kernel<EPL, true, false>), dim3((unsigned)blocks), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL((topk_rows_kernel<EPL, false, false>), dim3((unsigned)blocks), dim3(256), 0, s, X, n, D, k, vals,
-                           idx, 0, nullptr, nullptr);
+        hipLaunchKernelGGL((topk_rows_kernel<EPL, false, false>), dim3((unsigned)blocks), dim3(256), 0, s, a);
 }
 
-static int launch_any(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, int k2, float* vals2, uint16_t* idx2,
-                      bool ranked, hipStream_t s) {
-    if (n == 0) return DR_OK;
-    if (D <= 64) launch_epl<1>(X, (int)n, D, k, vals, idx, k2, vals2, idx2, ranked, s);
-    else if (D <= 128) launch_epl<2>(X, (int)n, D, k, vals, idx, k2, vals2, idx2, ranked, s);
-    else if (D <= 256) launch_epl<4>(X, (int)n, D, k, vals, idx, k2, vals2, idx2, ranked, s);
-    else if (D <= 512) launch_epl<8>(X, (int)n, D, k, vals, idx, k2, vals2, idx2, ranked, s);
-    else launch_epl<16>(X, (int)n, D, k, vals, idx, k2, vals2, idx2, ranked, s);
+static int launch_any(const TopkJob* jobs, int n, int D, bool ranked, hipStream_t s) {
+    for (int i = 0; i < n;) {
+        TopkArgs a{};
+        a.D = D;
+        int blocks = 0;
+        bool dual = false;
+        for (; i < n && a.n < kTopkSegs; ++i) {
+            const TopkJob& j = jobs[i];
+            if (j.n == 0) continue;
+            // Each wavefront strides over rows with four of them in flight, so it wants at least four rows (a wavefront
+            // with one row pays the whole load latency for it: 20 000 rows took 15 us on 4096 workgroups, 9 us on 1250);
+            // beyond 8192 workgroups (four rounds of 8 waves per SIMD) nothing is gained.  Measured on 20 k ... 1.2 M rows.
+            int64_t b = (j.n + 15) / 16;
+            if (b > 8192) b = 8192;
+            a.s[a.n++] = TopkSeg{j.X, j.vals, j.vals2, j.idx, j.idx2, (int)j.n, j.k, j.k2, blocks, (int)b};
+            blocks += (int)b;
+            dual = dual || j.vals2;
+        }
+        if (a.n == 0) break;
+        const int rk = ranked ? a.s[0].k : 0;
+        if (D <= 64) launch_epl<1>(a, blocks, dual, rk, s);
+        else if (D <= 128) launch_epl<2>(a, blocks, dual, rk, s);
+        else if (D <= 256) launch_epl<4>(a, blocks, dual, rk, s);
+        else if (D <= 512) launch_epl<8>(a, blocks, dual, rk, s);
+        else launch_epl<16>(a, blocks, dual, rk, s);
+    }
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
 
-int launch_topk2(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, int k2, float* vals2, uint16_t* idx2,
-                 hipStream_t s) {
-    return launch_any(X, n, D, k, vals, idx, k2, vals2, idx2, false, s);
-}
+int launch_topks(const TopkJob* jobs, int n, int D, hipStream_t s) { return launch_any(jobs, n, D, false, s); }
 
 int launch_topk(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, hipStream_t s) {
-    return launch_any(X, n, D, k, vals, idx, 0, nullptr, nullptr, false, s);
+    const TopkJob j{X, n, k, vals, idx, 0, nullptr, nullptr};
+    return launch_any(&j, 1, D, false, s);
 }
 
 int launch_topk_ranked(const float* X, int64_t n, int D, int k, float* vals, uint16_t* idx, hipStream_t s) {
-    return launch_any(X, n, D, k, vals, idx, 0, nullptr, nullptr, true, s);
+    const TopkJob j{X, n, k, vals, idx, 0, nullptr, nullptr};
+    return launch_any(&j, 1, D, true, s);
 }
 
 }  // namespace drc
