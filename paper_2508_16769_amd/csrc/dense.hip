@@ -52,8 +52,11 @@ template <int D> struct Tile {
 // Three bf16 parts of eight numbers, two at a time (one conversion instruction makes two parts).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// the largest bf16 number: a value that would round up to infinity keeps a finite first part (the rest follows exactly)
+// The largest bf16 number.  The first two parts stay within it: a value that would round up to infinity keeps a finite
+// first part (the rest follows exactly), and an infinite value becomes max + max + infinity -- with an infinite first part
+// the remainder, and with it every product, would be not-a-number where the fp32 product is infinite.
 constexpr float kMaxBf16 = 3.3895313892515355e38f;
+__device__ __forceinline__ float finite_bf16(float v) { return __builtin_amdgcn_fmed3f(v, -kMaxBf16, kMaxBf16); }
 struct Split8 { bf16x8 p[3]; };
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
@@ -65,9 +68,9 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float a = x[2 * j], b = x[2 * j + 1];
-        w[0][j] = pack2(__builtin_amdgcn_fmed3f(a, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(b, -kMaxBf16, kMaxBf16));
+        w[0][j] = pack2(finite_bf16(a), finite_bf16(b));
         const float ra = a - low_part(w[0][j]), rb = b - high_part(w[0][j]);
-        w[1][j] = pack2(ra, rb);
+        w[1][j] = pack2(finite_bf16(ra), finite_bf16(rb));
         w[2][j] = pack2(ra - low_part(w[1][j]), rb - high_part(w[1][j]));
     }
     Split8 s;
@@ -92,9 +95,9 @@ template <typename K> __device__ __forceinline__ Split8 select8(const Split8& s,
 }
 // the three parts of one number, `stride` bf16 numbers apart
 __device__ __forceinline__ void put_parts(__bf16* at, int stride, float v) {
-    const __bf16 a = (__bf16)__builtin_amdgcn_fmed3f(v, -kMaxBf16, kMaxBf16);
+    const __bf16 a = (__bf16)finite_bf16(v);
     const float r = v - (float)a;
-    const __bf16 b = (__bf16)r;
+    const __bf16 b = (__bf16)finite_bf16(r);
     at[0] = a;
     at[stride] = b;
     at[2 * stride] = (__bf16)(r - (float)b);

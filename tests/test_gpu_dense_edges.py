@@ -1,0 +1,129 @@
+"""The layer's dense products (three bf16 parts per fp32 operand) where their tiles and dispatch change: row counts around
+the row tile of every width (128 rows at D = 32, 64 at D = 64, 32 at D = 96 and 128), selections wider than the pairs a
+thread holds in registers, widths of their own per relation, and values at the ends of the fp32 range."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2508_16769_amd as P
+from gpu_util import dev, random_csr, say
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = [(32, 4, 20, 32), (64, 16, 16, 16), (64, 40, 8, 64), (96, 33, 12, 33), (128, 32, 32, 32), (128, 70, 128, 16)]
+
+
+def _run(Nc, Nn, D, ks, rng, X_cell, X_net, W, dY_cell, dY_net, edges=True):
+    """A layer pass; returns everything as fp64 numpy, with H and the selections the dense products read.  Without edges the
+    products see the inputs alone."""
+    deg = 3 if edges else 0
+    near, pins, pinned = random_csr(rng, Nc, Nc, deg), random_csr(rng, Nn, Nc, deg), random_csr(rng, Nc, Nn, deg)
+    rel = [P.Csr(m, n, *(dev(a) for a in r)) for m, n, r in ((Nc, Nc, near), (Nn, Nc, pins), (Nc, Nn, pinned))]
+    layer = P.HeteroConv(*rel, D, per_relation=ks)
+    saved = layer.alloc_saved()
+    Wd = {n: dev(W[n]) for n in P.WEIGHT_NAMES}
+    nan = lambda *s: torch.full(s, float("nan"), device="cuda")          # noqa: E731
+    out = dict(Y_cell=nan(Nc, D), Y_net=nan(Nn, D), dX_cell=nan(Nc, D), dX_net=nan(Nn, D))
+    dW = {n: nan(D, D) for n in P.WEIGHT_NAMES}
+    layer.heteroconv_fwd(dev(X_cell), dev(X_net), Wd, out["Y_cell"], out["Y_net"], saved)
+    layer.heteroconv_bwd(dev(dY_cell), dev(dY_net), Wd, saved, out["dX_cell"], out["dX_net"], dW)
+    torch.cuda.synchronize()
+    got = {n: t.cpu().numpy().astype(np.float64) for n, t in {**out, **dW, **{n: saved[n] for n in ("H_near", "H_pins", "H_pinned")}}.items()}
+    got["mask"] = saved["mask"].cpu().numpy()
+    k_near, k_pins, k_pinned = ks
+    if not edges:
+        layer.heteroconv_destroy()
+        return got
+    got["Xs_cell"] = oracle.densify(*oracle.topk(X_cell, k_near), D)
+    got["Xs_self"] = oracle.densify(*oracle.topk(X_net, k_pins), D)
+    got["sel"] = dict(near=oracle.topk(X_cell, k_near)[1], pins=oracle.topk(X_cell, k_pins)[1],
+                      self=oracle.topk(X_net, k_pins)[1], pinned=oracle.topk(X_net, k_pinned)[1])
+    layer.heteroconv_destroy()
+    return got, near, pins, pinned
+
+
+def _within(got, terms, what, n):
+    """got against sum of A @ B over `terms`: n summed products, each off by at most 2^-24 of the running sum, plus the
+    products a split leaves out (2^-24 of each): n * 2^-23 of the L1 norm of the terms bounds both, with 4 as the floor."""
+    want = sum(a @ b for a, b in terms)
+    l1 = sum(np.abs(a) @ np.abs(b) for a, b in terms)
+    assert np.all(np.abs(got - want) <= max(n, 4) * 2.0 ** -23 * l1), (what, float((np.abs(got - want) / np.maximum(l1, 1e-300)).max()))
+
+
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 63, 65, 128, 129, 257])
+@pytest.mark.parametrize("D,k_near,k_pins,k_pinned", WIDTHS)
+def test_products_at_tile_edges(D, k_near, k_pins, k_pinned, rows):
+    Nc, Nn = rows, max(1, rows - 1)
+    say(f"dense rows={rows} D={D} k=({k_near},{k_pins},{k_pinned})")
+    rng = np.random.default_rng(1000 * D + rows)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)             # noqa: E731
+    W = {n: (f(D, D) / np.sqrt(D)).astype(np.float32) for n in P.WEIGHT_NAMES}
+    dYc, dYn = f(Nc, D), f(Nn, D)
+    got, near, pins, pinned = _run(Nc, Nn, D, (k_near, k_pins, k_pinned), rng, f(Nc, D), f(Nn, D), W, dYc, dYn)
+    W = {n: w.astype(np.float64) for n, w in W.items()}
+    dYc, dYn = dYc.astype(np.float64), dYn.astype(np.float64)
+    # forward: the merge takes the larger branch, and the mask says which
+    zn = [(got["Xs_cell"], W["self_near"]), (got["H_near"], W["neigh_near"])]
+    zq = [(got["H_pinned"], W["pinned"])]
+    want = np.where(got["mask"] == 1, sum(a @ b for a, b in zn), sum(a @ b for a, b in zq))
+    l1 = sum(np.abs(a) @ np.abs(b) for a, b in zn + zq)
+    bound = 2 * D * 2.0 ** -23 * l1
+    assert np.all(np.abs(got["Y_cell"] - want) <= bound)
+    assert np.all(got["Y_cell"] >= np.maximum(sum(a @ b for a, b in zn), zq[0][0] @ zq[0][1]) - bound)
+    _within(got["Y_net"], [(got["Xs_self"], W["self_pins"]), (got["H_pins"], W["neigh_pins"])], "Y_net", 2 * D)
+    # weight gradients
+    dZn, dZq = np.where(got["mask"] == 1, dYc, 0.0), np.where(got["mask"] == 0, dYc, 0.0)
+    for n, A, B in (("self_near", "Xs_cell", dZn), ("neigh_near", "H_near", dZn), ("pinned", "H_pinned", dZq),
+                    ("self_pins", "Xs_self", dYn), ("neigh_pins", "H_pins", dYn)):
+        _within(got[n], [(got[A].T, B)], "dW." + n, len(B))
+    # input gradients: dZ W^T sampled at the selections, and the transposed relations over dZ W^T
+
+    def dense(r, m, n):
+        a = np.zeros((m, n))
+        np.add.at(a, (np.repeat(np.arange(m), np.diff(r[0])), r[1]), r[2].astype(np.float64))
+        return a
+    keep = {u: np.zeros((len(i), D)) for u, i in got["sel"].items()}
+    for u, i in got["sel"].items():
+        np.put_along_axis(keep[u], i.astype(np.int64), 1.0, axis=1)
+    an, ap, aq = dense(near, Nc, Nc), dense(pins, Nn, Nc), dense(pinned, Nc, Nn)
+
+    def grads(absolute):
+        g = (lambda x: np.abs(x)) if absolute else (lambda x: x)
+        w = {n: g(x) for n, x in W.items()}
+        c = keep["near"] * (g(dZn) @ w["self_near"].T + an.T @ (g(dZn) @ w["neigh_near"].T)) + keep["pins"] * (ap.T @ (g(dYn) @ w["neigh_pins"].T))
+        n = keep["self"] * (g(dYn) @ w["self_pins"].T) + keep["pinned"] * (aq.T @ (g(dZq) @ w["pinned"].T))
+        return c, n
+    for name, want, l1 in zip(("dX_cell", "dX_net"), grads(False), grads(True)):
+        assert np.all(np.abs(got[name] - want) <= 2 * D * 2.0 ** -23 * l1), name
+
+
+@pytest.mark.parametrize("D", [32, 96, 128])
+def test_ends_of_the_range(D):
+    """Infinite operands give the infinities and not-a-numbers of the fp32 products, the largest finite numbers stay finite."""
+    say(f"dense range D={D}")
+    Nc, Nn = 40, 70
+    rng = np.random.default_rng(D)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)             # noqa: E731
+    W = {n: rng.uniform(0.01, 0.02, (D, D)).astype(np.float32) * np.where(np.arange(D) % 2, 1, -1).astype(np.float32) for n in P.WEIGHT_NAMES}
+    X_cell, X_net, dYc, dYn = f(Nc, D), f(Nn, D), f(Nc, D), f(Nn, D)
+    big = np.finfo(np.float32).max
+    X_net[3, 5], X_net[4, 6], X_net[5, 7], X_net[6, 8] = np.inf, -np.inf, big, -big
+    X_cell[0, 1] = np.inf
+    dYn[10, 2], dYn[11, 3], dYn[12, 4] = np.inf, big, np.nan
+    got = _run(Nc, Nn, D, (D, D, D), rng, X_cell, X_net, W, dYc, dYn, edges=False)
+    with np.errstate(invalid="ignore", over="ignore"):
+        y = X_net.astype(np.float64) @ W["self_pins"].astype(np.float64)
+        dw = X_net.astype(np.float64).T @ dYn.astype(np.float64)
+        dx = dYn.astype(np.float64) @ W["self_pins"].astype(np.float64).T
+    rows = [3, 4, 5, 6]
+    assert np.array_equal(got["Y_net"][3:5], y[3:5]) and np.isinf(y[3:5]).all()
+    assert np.allclose(got["Y_net"][5:7], y[5:7], rtol=1e-6, atol=0)
+    others = [r for r in range(Nn) if r not in rows]
+    assert np.isfinite(got["Y_net"][others]).all()
+    assert np.array_equal(got["dX_net"][10], dx[10]) and np.isinf(dx[10]).all()
+    assert np.allclose(got["dX_net"][11], dx[11], rtol=1e-6, atol=0) and np.isnan(got["dX_net"][12]).all()
+    assert np.isnan(got["self_pins"][:, 4]).all()
+    plain = [c for c in range(D) if c not in (2, 3, 4)]
+    assert np.array_equal(got["self_pins"][5, plain], dw[5, plain]) and np.isinf(dw[5, plain]).all()
+    assert np.isinf(got["Y_cell"][0]).any() and np.isfinite(got["Y_cell"][1:]).all()
