@@ -1,14 +1,12 @@
 // Multi-layer training step (paper Section 4.1): L stacked HeteroConv layers with ReLU between them, a
 // per-cell read-out pred = X_cell^(L) . w_head, mean-squared error over all cells of the batch, Adam with
 // the L2 form of weight decay.  The sub-graphs of a batch are independent (Section 3.4): each runs its
-// whole forward and backward on its own stream (the relation streams of its layer context fork below
-// that), and the streams are joined only before the parameter update.
+// whole forward and backward on its own stream, and the streams are joined only before the parameter update.
 //
 // What is new here next to the layer is element-wise or a small reduction:
 //   (the ReLU between layers and its gate are folded into the layer kernels that write Y and dX)
-//   head_fwd_kernel                    one wavefront per cell: dot product, residual, loss partials
-//   head_bwd_kernel                    dY = dpred (x) w_head, per-workgroup partials of dw_head = Y^T dpred
-//   loss_reduce_kernel, adam_kernel    fixed-order sums over sub-graphs and partials, then the update
+//   head_kernel      read-out: dot product, residual, loss and read-out weight partials, dY = dpred (x) w_head
+//   update_kernel    fixed-order sums over sub-graphs and partials, loss, Adam
 // Every sum has a fixed order, so a step is reproducible bit for bit.
 //
 // Batched mode (hgnn_create_batched): the sub-graphs are stacked into ONE block-diagonal graph on the device
@@ -36,111 +34,134 @@ inline int head_blocks(int64_t n) {
 }
 constexpr int kMaxWorkers = 8;    // host threads that enqueue sub-graphs side by side
 
-__device__ __forceinline__ float wave_sum(float v) {
+// Read-out, forward and backward in one pass over Y:  pred[i] = Y[i,:] . w;  dpred[i] = scale * (pred[i] - target[i]);
+// dY[i,c] = dpred[i] * w[c];  per workgroup the sum of squared residuals (loss_part) and of dpred[i] * Y[i,:] (dw_part).
+// LPR lanes share a row, four columns each, so that the row that was read for the dot product is still in registers when
+// its gradient is formed; four rows per lane group are in flight.  Bound by HBM: one read of Y and one write of dY.
+// As two kernels with one dword per lane and one row in flight the 160 000 x 128 read-out took 95 + 71 us, now 45 us
+// (164 MB, 3.6 TB/s).
+template <int LPR>
+__global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ Y, const float* __restrict__ w,
+                                                   const float* __restrict__ target, int n, int D, float scale,
+                                                   float* __restrict__ pred, float* __restrict__ dpred, float* __restrict__ dY,
+                                                   float* __restrict__ loss_part, float* __restrict__ dw_part) {
+    constexpr int G = 256 / LPR, U = 4;                         // lane groups per workgroup, rows in flight
+    __shared__ float4 part[G][LPR];
+    __shared__ float sq[G];
+    const int t = threadIdx.x % LPR, g = threadIdx.x / LPR;
+    const bool on = 4 * t < D;                                  // D = 96: 24 of 32 lanes
+    const int c = on ? 4 * t : 0;
+    const float w0 = on ? w[c] : 0.f, w1 = on ? w[c + 1] : 0.f, w2 = on ? w[c + 2] : 0.f, w3 = on ? w[c + 3] : 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float loss = 0.f;                                           // (lane 0 of the group)
+    const int step = gridDim.x * G;
+    for (int r0 = blockIdx.x * G + g; r0 < n; r0 += U * step) {
+        float4 y[U];
+        float tg[U];
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-    return v;
-}
-
-// pred[i] = Y[i,:] . w;  dpred[i] = scale * (pred[i] - target[i]);  loss_part[block] = sum of squared residuals
-__global__ __launch_bounds__(256) void head_fwd_kernel(const float* __restrict__ Y, const float* __restrict__ w,
-                                                       const float* __restrict__ target, int n, int D, float scale,
-                                                       float* __restrict__ pred, float* __restrict__ dpred,
-                                                       float* __restrict__ loss_part) {
-    __shared__ float sq[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float acc = 0.f;                                            // squared residuals seen by this wavefront (lane 0)
-    for (int row = blockIdx.x * 4 + wave; row < n; row += gridDim.x * 4) {
-        float s = 0.f;
-        for (int c = lane; c < D; c += kWave) s += Y[(size_t)row * D + c] * w[c];
-        s = wave_sum(s);
-        const float r = s - target[row];
-        if (lane == 0) {
-            pred[row] = s;
-            dpred[row] = scale * r;
-            acc += r * r;
+        for (int u = 0; u < U; ++u) {                           // rows past the end: the last row, whose values are not used
+            const int row = min(r0 + u * step, n - 1);
+            y[u] = *reinterpret_cast<const float4*>(Y + (size_t)row * D + c);
+            tg[u] = target[row];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = r0 + u * step;
+            float s = fmaf(y[u].x, w0, y[u].y * w1) + fmaf(y[u].z, w2, y[u].w * w3);
+            s = on ? s : 0.f;
+#pragma unroll
+            for (int d = LPR / 2; d >= 1; d >>= 1) s += __shfl_xor(s, d, kWave);
+            if (row < n) {
+                const float r = s - tg[u], gr = scale * r;
+                if (t == 0) {
+                    pred[row] = s;
+                    dpred[row] = gr;
+                    loss += r * r;
+                }
+                if (on) *reinterpret_cast<float4*>(dY + (size_t)row * D + c) = make_float4(gr * w0, gr * w1, gr * w2, gr * w3);
+                acc.x = fmaf(gr, y[u].x, acc.x);
+                acc.y = fmaf(gr, y[u].y, acc.y);
+                acc.z = fmaf(gr, y[u].z, acc.z);
+                acc.w = fmaf(gr, y[u].w, acc.w);
+            }
         }
     }
-    if (lane == 0) sq[wave] = acc;
+    part[g][t] = acc;
+    if (t == 0) sq[g] = loss;
     __syncthreads();
-    if (threadIdx.x == 0) loss_part[blockIdx.x] = (sq[0] + sq[1]) + (sq[2] + sq[3]);
-}
-
-// dY[i,c] = dpred[i] * w[c];  dw_part[block][c] = sum over the block's rows of dpred[i] * Y[i,c]
-__global__ __launch_bounds__(256) void head_bwd_kernel(const float* __restrict__ Y, const float* __restrict__ w,
-                                                       const float* __restrict__ dpred, int n, int D,
-                                                       float* __restrict__ dY, float* __restrict__ dw_part) {
-    extern __shared__ float part[];                             // [256]
-    const int rows_per_pass = 256 / D;                          // D in {32,64,96,128}: 8, 4, 2, 2 row lanes
-    const int c = threadIdx.x % D, rl = threadIdx.x / D;
-    const bool active = rl < rows_per_pass;
-    const int per_block = (n + gridDim.x - 1) / gridDim.x;
-    const int r0 = blockIdx.x * per_block, r1 = min(n, r0 + per_block);
-    float acc = 0.f;
-    if (active) {
-        const float wc = w[c];
-        for (int row = r0 + rl; row < r1; row += rows_per_pass) {
-            const float g = dpred[row];
-            acc = fmaf(g, Y[(size_t)row * D + c], acc);
-            dY[(size_t)row * D + c] = g * wc;
-        }
-    }
-    part[threadIdx.x] = active ? acc : 0.f;
-    __syncthreads();
-    if (threadIdx.x < D) {
+    if ((int)threadIdx.x < D) {
         float s = 0.f;
-        for (int q = 0; q < rows_per_pass; ++q) s += part[q * D + threadIdx.x];
+#pragma unroll
+        for (int q = 0; q < G; ++q) s += reinterpret_cast<const float*>(part[q])[threadIdx.x];
         dw_part[(size_t)blockIdx.x * D + threadIdx.x] = s;
     }
+    if (threadIdx.x == 0) {
+        float s = 0.f;
+        for (int q = 0; q < G; ++q) s += sq[q];
+        loss_part[blockIdx.x] = s;
+    }
 }
 
-__global__ __launch_bounds__(64) void loss_reduce_kernel(const float* __restrict__ loss_part, int n_parts, float inv_n,
-                                                         float* __restrict__ loss_out) {
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n_parts; i += kWave) s += loss_part[i];
-    s = wave_sum(s);
-    if (threadIdx.x == 0) *loss_out = s * inv_n;
+static void launch_head(const float* Y, const float* w, const float* target, int n, int D, float scale, float* pred, float* dpred,
+                        float* dY, float* loss_part, float* dw_part, int blocks, hipStream_t s) {
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Y, w, target, n, D, scale, pred, dpred, dY, loss_part, dw_part);
+    };
+    if (D <= 32) go(head_kernel<8>);
+    else if (D <= 64) go(head_kernel<16>);
+    else go(head_kernel<32>);
 }
 
-// dwh[c] = sum over all read-out partials (fixed order: thread t takes partials t, t + 256, ..., then a tree over
-// the 256 thread sums); one workgroup per column
-__global__ __launch_bounds__(256) void head_reduce_kernel(const float* __restrict__ dwh_part, int n_parts, int D,
-                                                          float* __restrict__ dwh) {
+// sum of x[0], x[stride], ..., x[(n - 1) * stride] by a workgroup of 256, in a fixed order (thread t takes elements t,
+// t + 256, ..., then a tree over the 256 thread sums); the result is in thread 0
+__device__ __forceinline__ float block_sum(const float* __restrict__ x, int n, int stride) {
     __shared__ float sh[256];
-    const int c = blockIdx.x;
     float s = 0.f;
-    for (int q = threadIdx.x; q < n_parts; q += 256) s += dwh_part[(size_t)q * D + c];
+    for (int q = threadIdx.x; q < n; q += 256) s += x[(size_t)q * stride];
     sh[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) dwh[c] = sh[0];
+    return sh[0];
 }
 
-// g = sum over sub-graphs (fixed order) of the gradient pieces; Adam with L2 weight decay, bias-corrected
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                                                   float* __restrict__ grad_out, const float* __restrict__ gall,
-                                                   const float* __restrict__ dwh, int n_graphs, int64_t PL, int D,
-                                                   float lr, float beta1, float beta2, float omb1, float omb2,
-                                                   float eps, float wd, float inv_bc1, float inv_bc2) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= PL + D) return;
+// The end of a step, one launch: g = sum over sub-graphs (fixed order) of the gradient pieces, Adam with L2 weight decay,
+// bias-corrected.  Workgroups: ceil(PL / 256) on the layers' parameters, then one per column of the read-out weight (sums
+// its partials first), then one that sums the loss.
+struct AdamArgs {
+    float *theta, *m, *v, *grad_out, *loss_out;
+    const float *gall, *dwh_part, *loss_part;
+    int n_graphs, n_parts, D;
+    int64_t PL;
+    float inv_n, lr, beta1, beta2, omb1, omb2, eps, wd, inv_bc1, inv_bc2;
+};
+__global__ __launch_bounds__(256) void update_kernel(AdamArgs a) {
+    const int layer_blocks = (int)((a.PL + 255) / 256);
+    const int b = (int)blockIdx.x - layer_blocks;
+    int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     float g = 0.f;
-    if (e < PL) {
-        for (int q = 0; q < n_graphs; ++q) g += gall[(size_t)q * PL + e];
+    if (b < 0) {
+        if (e >= a.PL) return;
+        for (int q = 0; q < a.n_graphs; ++q) g += a.gall[(size_t)q * a.PL + e];
+    } else if (b < a.D) {
+        g = block_sum(a.dwh_part + b, a.n_parts, a.D);
+        if (threadIdx.x != 0) return;
+        e = a.PL + b;
     } else {
-        g = dwh[e - PL];
+        const float s = block_sum(a.loss_part, a.n_parts, 1);
+        if (threadIdx.x == 0) *a.loss_out = s * a.inv_n;
+        return;
     }
-    grad_out[e] = g;
-    const float th = theta[e];
-    g = fmaf(wd, th, g);
-    const float m2 = beta1 * m[e] + omb1 * g;        // omb = 1 - beta, formed in double on the host
-    const float v2 = beta2 * v[e] + omb2 * g * g;
-    m[e] = m2;
-    v[e] = v2;
-    theta[e] = th - lr * (m2 * inv_bc1) / (sqrtf(v2 * inv_bc2) + eps);
+    a.grad_out[e] = g;
+    const float th = a.theta[e];
+    g = fmaf(a.wd, th, g);
+    const float m2 = a.beta1 * a.m[e] + a.omb1 * g;        // omb = 1 - beta, formed in double on the host
+    const float v2 = a.beta2 * a.v[e] + a.omb2 * g * g;
+    a.m[e] = m2;
+    a.v[e] = v2;
+    a.theta[e] = th - a.lr * (m2 * a.inv_bc1) / (sqrtf(v2 * a.inv_bc2) + a.eps);
 }
 
 // block-diagonal stacking of CSR parts: part q's rows go to [row_off, row_off + n_rows), its columns are
@@ -273,7 +294,7 @@ struct dr_hgnn {
     int64_t n_cells_total;
     std::vector<drc::GraphState> g;
     std::vector<void*> owned;
-    float *gall, *loss_part, *dwh_part, *dwh;  // dwh[D]: the read-out weight gradient, summed over all partials
+    float *gall, *loss_part, *dwh_part;
     int n_head_parts;                          // read-out partials of all states together
     hipEvent_t fork;
     int device;
@@ -352,7 +373,7 @@ static int create_model(dr_hgnn** model, int32_t n_graphs, dr_heteroconv* const*
     m->n_graphs = batched ? 1 : n_graphs; m->L = n_layers; m->D = d0.D;
     m->PL = (int64_t)n_layers * 5 * d0.D * d0.D;
     m->n_cells_total = 0;
-    m->gall = m->loss_part = m->dwh_part = m->dwh = nullptr;
+    m->gall = m->loss_part = m->dwh_part = nullptr;
     m->Xc_all = m->Xn_all = m->tg_all = nullptr;
     m->big = nullptr;
     m->fork = nullptr;
@@ -417,7 +438,6 @@ static int create_model(dr_hgnn** model, int32_t n_graphs, dr_heteroconv* const*
         for (int q = 0; q < ns; ++q) m->n_head_parts += head_blocks(cap_cells(q));
         DRC_TRY(alloc_t(m, &m->loss_part, (size_t)m->n_head_parts));
         DRC_TRY(alloc_t(m, &m->dwh_part, (size_t)m->n_head_parts * m->D));
-        DRC_TRY(alloc_t(m, &m->dwh, (size_t)m->D));
         int part0 = 0;
         for (int q = 0; q < ns; ++q) {
             GraphState& gs = m->g[q];
@@ -462,6 +482,8 @@ static int create_model(dr_hgnn** model, int32_t n_graphs, dr_heteroconv* const*
                 DRC_TRY(alloc_t(m, &gs.G_c[l], nc * D));
                 DRC_TRY(alloc_t(m, &gs.G_n[l], nn * D));
             }
+            // nets feed no loss: the gradient of the last layer's net output is this buffer of zeros, which no kernel writes
+            DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(gs.G_n[L]), nn * D, 0u, nullptr));
             DRC_TRY(alloc_t(m, &gs.pred, nc));
             DRC_TRY(alloc_t(m, &gs.dpred, nc));
         }
@@ -570,11 +592,7 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
         }
         // ---- read-out, loss, gradient of the last layer's output ----
         const float* w_head = theta + m->PL;
-        hipLaunchKernelGGL(head_fwd_kernel, dim3(gs.hb), dim3(256), 0, s, gs.act_c[L - 1], w_head, target[q], n, D,
-                           scale, gs.pred, gs.dpred, gs.loss_part);
-        hipLaunchKernelGGL(head_bwd_kernel, dim3(gs.hb), dim3(256), 256 * sizeof(float), s, gs.act_c[L - 1], w_head,
-                           gs.dpred, n, D, gs.G_c[L], gs.dwh_part);
-        DRC_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(gs.G_n[L]), (size_t)gs.Nn * D, 0u, s));   // nets feed no loss
+        launch_head(gs.act_c[L - 1], w_head, target[q], n, D, scale, gs.pred, gs.dpred, gs.G_c[L], gs.loss_part, gs.dwh_part, gs.hb, s);
         DRC_HIP(hipGetLastError());
         // ---- backward ----
         for (int l = L - 1; l >= 0; --l) {
@@ -585,7 +603,7 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
             BackwardOptions opt;
             opt.gate_inputs = l >= 1;
             opt.skip_dx = l == 0 && !m->inspect;       // nobody reads the gradient of the input features
-            opt.dy_net_zero = l == L - 1;                  // the loss reads the cells only: G_n[L] is the zero fill above
+            opt.dy_net_zero = l == L - 1;                  // the loss reads the cells only: G_n[L] holds zeros
             const LayerBwd lb{gs.ctx, gs.G_c[l + 1], gs.G_n[l + 1], &gs.saved[l], gs.G_c[l], gs.G_n[l], dW};
             DRC_TRY(heteroconv_backward(&lb, 1, &W, s, opt));
         }
@@ -616,15 +634,11 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
     for (int q = 0; q < m->n_graphs; ++q) DRC_HIP(hipStreamWaitEvent(user, m->g[q].done, 0));
 
     // ---- loss and parameter update, after every sub-graph has delivered its gradient ----
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(kWave), 0, user, m->loss_part, m->n_head_parts,
-                       (float)(1.0 / (double)m->n_cells_total), loss_out);
-    hipLaunchKernelGGL(head_reduce_kernel, dim3((unsigned)D), dim3(256), 0, user, m->dwh_part, m->n_head_parts, D, m->dwh);
-    const int64_t P = m->PL + D;
-    const float inv_bc1 = (float)(1.0 / (1.0 - std::pow(beta1, (double)step)));
-    const float inv_bc2 = (float)(1.0 / (1.0 - std::pow(beta2, (double)step)));
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, user, theta, adam_m, adam_v, grad_out,
-                       m->gall, m->dwh, m->n_graphs, m->PL, D, (float)lr, (float)beta1, (float)beta2, (float)(1.0 - beta1),
-                       (float)(1.0 - beta2), (float)eps, (float)weight_decay, inv_bc1, inv_bc2);
+    const AdamArgs a{theta, adam_m, adam_v, grad_out, loss_out, m->gall, m->dwh_part, m->loss_part, m->n_graphs, m->n_head_parts, D,
+                     m->PL, (float)(1.0 / (double)m->n_cells_total), (float)lr, (float)beta1, (float)beta2, (float)(1.0 - beta1),
+                     (float)(1.0 - beta2), (float)eps, (float)weight_decay, (float)(1.0 / (1.0 - std::pow(beta1, (double)step))),
+                     (float)(1.0 / (1.0 - std::pow(beta2, (double)step)))};
+    hipLaunchKernelGGL(update_kernel, dim3((unsigned)((m->PL + 255) / 256 + D + 1)), dim3(256), 0, user, a);
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }
