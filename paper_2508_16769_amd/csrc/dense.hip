@@ -155,6 +155,20 @@ template <int CP> __device__ __forceinline__ void store4(Buf b, int off, const f
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, CP);
 }
 
+// The two halves of a workgroup's wavefronts run loops of their own (yes: stage, then multiply).  With one loop and the
+// staging under `if (half)` the compiler has to assume that a wavefront may change sides from one trip to the next: the
+// waits in front of the staging and of the multiply then covered loads and stores that had only just been issued, and every
+// trip stood for a whole memory latency.
+struct yes { static constexpr bool value = true; };
+struct no { static constexpr bool value = false; };
+// Stores that write nothing, behind the first prefetch of a loop in which stores come behind the prefetch: the number of
+// operations that may be outstanding at the loop's first wait is the smaller one of the way in and of the way round.
+template <int N> __device__ __forceinline__ void pad_stores(float* p) {
+    const Buf b = block_view(p, 0, 0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, b, kNowhere - 4 * i, 0, 0);
+}
+
 // Weight fragments of one 16-column block: output column n = first + (lane & 15), unit 4 s + (lane >> 4) per step.
 // TRANS: B[k][n] = W[n][k].
 template <int D, bool TRANS>
@@ -309,73 +323,76 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
         }
         if (pairs) stage_cbsr<D>(buf, pr, g->vals + (size_t)base * g->k, g->idx + (size_t)base * g->k, g->k, t < tiles ? g->rows - base : 0, prow, ppart);
     };
-    int t = wg;
-    if (t >= tiles) return;
-    const bool first_half = wave < T::WAVES / 2;
-    int q = 0, q1, q2;                            // graphs of tile t, of the next one and of the one after
-    find_seg(segs, a->n, t, q);
-    prefetch(segs + q, t);
-    commit(segs + q, t, smem);
-    q1 = q;
-    find_seg(segs, a->n, t + n_wg, q1);
-    prefetch(segs + q1, t + n_wg);
-    __syncthreads();
-    for (int cur = 0;; cur ^= 1) {
-        const DRC_CONST ProjFwdSide* const g = segs + q;
-        const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
-        bf16x8* const buf = smem + cur * 3 * T::OPER;
-        q2 = q1;
-        find_seg(segs, a->n, t1 + n_wg, q2);
-        auto stage_next = [&]() {
-            commit(segs + q1, t1, smem + (cur ^ 1) * 3 * T::OPER);
-            prefetch(segs + q2, t1 + n_wg);
-        };
-        if (first_half) stage_next();
-        __builtin_amdgcn_sched_barrier(0);
-        Acc c1[2] = {}, c2[2] = {};
-#pragma unroll
-        for (int s = 0; s < T::KS; ++s) {
-            bf16x8 x[2][3];
-            load_x<D>(buf, s, rg, lane, x);
-            mfma6(wS[s], x, c1);
-            load_x<D>(buf + T::OPER, s, rg, lane, x);
-            mfma6(w1[s], x, c1);
-            if constexpr (CELL) {
-                load_x<D>(buf + 2 * T::OPER, s, rg, lane, x);
-                mfma6(w2[s], x, c2);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const Buf by = block_view(g->Y + (size_t)base * D, g->rows - base, D * 4);
-        const Buf bm = block_view(g->mask + (size_t)base * D, g->rows - base, D);
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-            const int at = (rg * 32 + rb * 16 + (lane & 15)) * D + 16 * nb + 4 * (lane >> 4);
-            f32x4 v = c1[rb].hi + c1[rb].lo;
-            if constexpr (CELL) {                 // mask = [near >= pinned]
-                const f32x4 p = c2[rb].hi + c2[rb].lo;
-                uint32_t m = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool near_wins = v[r] >= p[r];
-                    m |= near_wins ? 1u << (8 * r) : 0u;
-                    v[r] = near_wins ? v[r] : p[r];
-                }
-                __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, kNt);
-            }
-            if (a->relu) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
-            }
-            store4<kNt>(by, at * 4, v);
-        }
-        if (!first_half) stage_next();
-        if (t1 >= tiles) break;
+    if (wg >= tiles) return;
+    const auto walk = [&](auto first) {
+        constexpr bool kFirst = decltype(first)::value;
+        int t = wg, q = 0, q1, q2;                // graphs of tile t, of the next one and of the one after
+        find_seg(segs, a->n, t, q);
+        prefetch(segs + q, t);
+        commit(segs + q, t, smem);
+        q1 = q;
+        find_seg(segs, a->n, t + n_wg, q1);
+        prefetch(segs + q1, t + n_wg);
+        if constexpr (kFirst) pad_stores<CELL ? 4 : 2>(segs->Y);          // a tile's stores come behind its prefetch
         __syncthreads();
-        t = t1;
-        q = q1;
-        q1 = q2;
-    }
+        for (int cur = 0;; cur ^= 1) {
+            const DRC_CONST ProjFwdSide* const g = segs + q;
+            const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+            bf16x8* const buf = smem + cur * 3 * T::OPER;
+            q2 = q1;
+            find_seg(segs, a->n, t1 + n_wg, q2);
+            auto stage_next = [&]() {
+                commit(segs + q1, t1, smem + (cur ^ 1) * 3 * T::OPER);
+                prefetch(segs + q2, t1 + n_wg);
+            };
+            if constexpr (kFirst) stage_next();
+            __builtin_amdgcn_sched_barrier(0);
+            Acc c1[2] = {}, c2[2] = {};
+#pragma unroll
+            for (int s = 0; s < T::KS; ++s) {
+                bf16x8 x[2][3];
+                load_x<D>(buf, s, rg, lane, x);
+                mfma6(wS[s], x, c1);
+                load_x<D>(buf + T::OPER, s, rg, lane, x);
+                mfma6(w1[s], x, c1);
+                if constexpr (CELL) {
+                    load_x<D>(buf + 2 * T::OPER, s, rg, lane, x);
+                    mfma6(w2[s], x, c2);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const Buf by = block_view(g->Y + (size_t)base * D, g->rows - base, D * 4);
+            const Buf bm = block_view(g->mask + (size_t)base * D, g->rows - base, D);
+            const bool relu = a->relu != 0;
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+                const int at = (rg * 32 + rb * 16 + (lane & 15)) * D + 16 * nb + 4 * (lane >> 4);
+                f32x4 v = c1[rb].hi + c1[rb].lo;
+                if constexpr (CELL) {             // mask = [near >= pinned]
+                    const f32x4 p = c2[rb].hi + c2[rb].lo;
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool near_wins = v[r] >= p[r];
+                        m |= near_wins ? 1u << (8 * r) : 0u;
+                        v[r] = near_wins ? v[r] : p[r];
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, kNt);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = relu ? fmaxf(v[r], 0.0f) : v[r];
+                store4<kNt>(by, at * 4, v);
+            }
+            if constexpr (!kFirst) stage_next();
+            if (t1 >= tiles) break;
+            __syncthreads();
+            t = t1;
+            q = q1;
+            q1 = q2;
+        }
+    };
+    if (wave < T::WAVES / 2) walk(yes{});
+    else walk(no{});
 }
 
 template <int D> constexpr int waves_per_simd() { return 2; }
@@ -457,90 +474,98 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
             stage_unit<D>(buf, urow, unit, sp);
         }
     };
-    int t = wg;
-    if (t >= tiles) return;
-    const bool first_half = wave < T::WAVES / 2;
-    int q = 0, q1, q2, t0 = t, q0;                // graphs of tile t, the next and the one after; the tile before
-    find_seg(segs, a->n, t, q);
-    q0 = q;
-    prefetch(segs + q, t);
-    commit(smem);
-    q1 = q;
-    find_seg(segs, a->n, t + n_wg, q1);
-    prefetch(segs + q1, t + n_wg);
-    __syncthreads();
+    if (wg >= tiles) return;
     // The self-term product of a tile is sampled one step later, when all wavefronts have written theirs.
     auto sample = [&](const DRC_CONST ProjBwdSide* g, int t, int left, const float* sC) {
         const int base = (t - g->tile0) * T::BM, at = prow * g->k + ppart;
         left = min(left, T::BM);                  // threads past the tile (D = 96) must not reach the next tile's rows
         const Buf bi = block_view(g->idx + (size_t)base * g->k, left, g->k * 2);
         const Buf bs = block_view(g->S + (size_t)base * g->k, left, g->k * 4);
-        uint32_t col[kPairs];
+        // as loaded: a conversion here would wait for the loads before the multiply
+        struct { uint16_t v[kPairs]; } col;
 #pragma unroll
-        for (int u = 0; u < kPairs; ++u) col[u] = __builtin_amdgcn_raw_buffer_load_b16(bi, (at + T::TPR * u) * 2, 0, 0);
+        for (int u = 0; u < kPairs; ++u) col.v[u] = __builtin_amdgcn_raw_buffer_load_b16(bi, (at + T::TPR * u) * 2, 0, 0);
         return [=]() {
             const int row = min(prow, T::BM - 1);
 #pragma unroll
-            for (int u = 0; u < kPairs; ++u)
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sC[row * LDC + col[u]]), bs,
+            for (int u = 0; u < kPairs; ++u) {
+                uint16_t c = col.v[u];
+                asm volatile("" : "+v"(c));
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sC[row * LDC + c]), bs,
                                                       ppart + T::TPR * u < g->k ? (at + T::TPR * u) * 4 : kNowhere, 0, 0);
+            }
             if (g->k > T::TPR * kPairs && prow < min(left, T::BM))
                 for (int p = ppart + T::TPR * kPairs; p < g->k; p += T::TPR)
                     g->S[(size_t)(base + prow) * g->k + p] = sC[prow * LDC + g->idx[(size_t)(base + prow) * g->k + p]];
         };
     };
-    int cur = 0;
-    bool have_t0 = false;
-    for (;; cur ^= 1) {
-        const DRC_CONST ProjBwdSide* const g = segs + q;
-        const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
-        bf16x8* const buf = smem + cur * 2 * T::OPER;
-        float* const sC = sC0 + cur * T::BM * LDC;
-        q2 = q1;
-        find_seg(segs, a->n, t1 + n_wg, q2);
-        const auto finish_t0 = sample(segs + q0, t0, have_t0 ? segs[q0].rows - (t0 - segs[q0].tile0) * T::BM : 0, sC0 + (cur ^ 1) * T::BM * LDC);
-        auto stage_next = [&]() {
-            commit(smem + (cur ^ 1) * 2 * T::OPER);
-            prefetch(segs + q2, t1 + n_wg);
-        };
-        if (first_half) stage_next();
-        __builtin_amdgcn_sched_barrier(0);
-        Acc c1[2] = {}, c2[2] = {};
-        f32x4 cS[2] = {};                         // one accumulator: the registers do not hold more
-#pragma unroll
-        for (int s = 0; s < T::KS; ++s) {
-            bf16x8 x[2][3];
-            load_x<D>(buf, s, rg, lane, x);
-            mfma6(w1[s], x, c1);
-            mfma6_one(wS[s], x, cS);
-            if constexpr (CELL) {
-                load_x<D>(buf + T::OPER, s, rg, lane, x);
-                mfma6(w2[s], x, c2);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
-        const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-            const int r = rg * 32 + rb * 16 + (lane & 15), c = 16 * nb + 4 * (lane >> 4);
-            *reinterpret_cast<f32x4*>(sC + r * LDC + c) = cS[rb];
-            // gathered next: these stay in the caches
-            store4<0>(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
-            if constexpr (CELL) store4<0>(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
-        }
-        finish_t0();
-        if (!first_half) stage_next();
-        __syncthreads();                          // this self-term tile and the next operand tiles are complete
-        t0 = t;
+    const auto walk = [&](auto first) {
+        constexpr bool kFirst = decltype(first)::value;
+        int t = wg, q = 0, q1, q2, t0 = t, q0;    // graphs of tile t, the next and the one after; the tile before
+        find_seg(segs, a->n, t, q);
         q0 = q;
-        have_t0 = true;
-        if (t1 >= tiles) break;
-        t = t1;
-        q = q1;
-        q1 = q2;
-    }
-    sample(segs + q0, t0, segs[q0].rows - (t0 - segs[q0].tile0) * T::BM, sC0 + cur * T::BM * LDC)();
+        prefetch(segs + q, t);
+        commit(smem);
+        q1 = q;
+        find_seg(segs, a->n, t + n_wg, q1);
+        prefetch(segs + q1, t + n_wg);
+        if constexpr (kFirst) pad_stores<(CELL ? 4 : 2) + kPairs>(segs->dH1);       // a tile's stores come behind its prefetch
+        __syncthreads();
+        int cur = 0;
+        bool have_t0 = false;
+        for (;; cur ^= 1) {
+            const DRC_CONST ProjBwdSide* const g = segs + q;
+            const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+            bf16x8* const buf = smem + cur * 2 * T::OPER;
+            float* const sC = sC0 + cur * T::BM * LDC;
+            q2 = q1;
+            find_seg(segs, a->n, t1 + n_wg, q2);
+            const auto finish_t0 = sample(segs + q0, t0, have_t0 ? segs[q0].rows - (t0 - segs[q0].tile0) * T::BM : 0, sC0 + (cur ^ 1) * T::BM * LDC);
+            auto stage_next = [&]() {
+                commit(smem + (cur ^ 1) * 2 * T::OPER);
+                prefetch(segs + q2, t1 + n_wg);
+            };
+            if constexpr (kFirst) stage_next();
+            __builtin_amdgcn_sched_barrier(0);
+            Acc c1[2] = {}, c2[2] = {};
+            f32x4 cS[2] = {};                     // one accumulator: the registers do not hold more
+#pragma unroll
+            for (int s = 0; s < T::KS; ++s) {
+                bf16x8 x[2][3];
+                load_x<D>(buf, s, rg, lane, x);
+                mfma6(w1[s], x, c1);
+                mfma6_one(wS[s], x, cS);
+                if constexpr (CELL) {
+                    load_x<D>(buf + T::OPER, s, rg, lane, x);
+                    mfma6(w2[s], x, c2);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
+            const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+                const int r = rg * 32 + rb * 16 + (lane & 15), c = 16 * nb + 4 * (lane >> 4);
+                *reinterpret_cast<f32x4*>(sC + r * LDC + c) = cS[rb];
+                // gathered next: these stay in the caches
+                store4<0>(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
+                if constexpr (CELL) store4<0>(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
+            }
+            finish_t0();
+            if constexpr (!kFirst) stage_next();
+            __syncthreads();                      // this self-term tile and the next operand tiles are complete
+            t0 = t;
+            q0 = q;
+            have_t0 = true;
+            if (t1 >= tiles) break;
+            t = t1;
+            q = q1;
+            q1 = q2;
+        }
+        sample(segs + q0, t0, segs[q0].rows - (t0 - segs[q0].tile0) * T::BM, sC0 + cur * T::BM * LDC)();
+    };
+    if (wave < T::WAVES / 2) walk(yes{});
+    else walk(no{});
 }
 
 template <int D>
@@ -667,72 +692,77 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
         }
     };
     const int chunks = (g->rows + W::CR - 1) / W::CR;
-    const bool first_half = wave < T::WAVES / 2;
-    int chunk = wg, cur = 0;
-    if (chunk < chunks) {
-        load_y(chunk);
-        load_h(chunk);
-        commit(chunk, smem);
-        load_y(chunk + g->wgs);
-    }
-    for (; chunk < chunks; chunk += g->wgs, cur ^= 1) {
-        __syncthreads();                          // this chunk is in LDS; the other buffer may be overwritten
-        const int next = chunk + g->wgs;
-        bf16x8* const buf = smem + cur * 3 * W::OPER;
-        auto stage_next = [&]() {
-            commit(next, smem + (cur ^ 1) * 3 * W::OPER);
-            load_y(next + g->wgs);
-        };
-        if (first_half) stage_next();
-        __builtin_amdgcn_sched_barrier(0);
-        const Split8 a1 = split8(h1);
-        Split8 a2;
-        if constexpr (CELL) a2 = split8(h2);
-        __builtin_amdgcn_sched_barrier(0);
-        bf16x8 aS[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) aS[p] = buf[W::OPER + p * W::PLANE + (hrow >> 3) * D + hcol];
-#pragma unroll
-        for (int j = 0; j < T::NB; ++j) {
-            // The five small products of this chunk are summed from zero and added with one rounding: inside the matrix
-            // unit they would be cut off below the running sum, always downwards, which over a million rows adds up (a
-            // 3e-6 error on random gradients, against 1e-6 for the fp32 instruction).
-            constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
-            const int ub = (hrow >> 3) * D + 16 * j + (lane & 15);
-            f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};
-            bf16x8 b[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p) b[p] = buf[p * W::PLANE + ub];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                lo0 = mfma(b[BW[i]], a1.p[AW[i]], lo0);
-                lo1 = mfma(b[BW[i]], aS[AW[i]], lo1);
-            }
-            acc[0][j] = mfma(b[0], a1.p[0], acc[0][j]);
-            acc[1][j] = mfma(b[0], aS[0], acc[1][j]);
-            acc[0][j] += lo0;
-            acc[1][j] += lo1;
-            asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]));       // added here: the compiler would keep all sums to the end of the loop
-            __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
-            if constexpr (CELL) {
-#pragma unroll
-                for (int p = 0; p < 3; ++p) b[p] = buf[2 * W::OPER + p * W::PLANE + ub];
-                lo0 = lo1 = f32x4{0.f, 0.f, 0.f, 0.f};
-                lo0 = mfma(b[2], a2.p[0], lo0);
-                lo1 = mfma(b[1], a2.p[0], lo1);
-                lo0 = mfma(b[0], a2.p[2], lo0);
-                lo1 = mfma(b[0], a2.p[1], lo1);
-                lo0 = mfma(b[1], a2.p[1], lo0);
-                acc[2][j] = mfma(b[0], a2.p[0], acc[2][j]);
-                acc[2][j] += lo0 + lo1;
-                asm volatile("" : "+v"(acc[2][j]));
-                __builtin_amdgcn_sched_barrier(0);
-            }
+    const auto walk = [&](auto first) {
+        constexpr bool kFirst = decltype(first)::value;
+        int chunk = wg, cur = 0;
+        if (chunk < chunks) {
+            load_y(chunk);
+            if constexpr (!kFirst) load_h(chunk);
+            commit(chunk, smem);
+            load_y(chunk + g->wgs);
+            if constexpr (kFirst) load_h(chunk);          // the order in which the loop issues them
         }
-        load_h(next);
-        __builtin_amdgcn_sched_barrier(0);
-        if (!first_half) stage_next();
-    }
+        for (; chunk < chunks; chunk += g->wgs, cur ^= 1) {
+            __syncthreads();                          // this chunk is in LDS; the other buffer may be overwritten
+            const int next = chunk + g->wgs;
+            bf16x8* const buf = smem + cur * 3 * W::OPER;
+            auto stage_next = [&]() {
+                commit(next, smem + (cur ^ 1) * 3 * W::OPER);
+                load_y(next + g->wgs);
+            };
+            if constexpr (kFirst) stage_next();
+            __builtin_amdgcn_sched_barrier(0);
+            const Split8 a1 = split8(h1);
+            Split8 a2;
+            if constexpr (CELL) a2 = split8(h2);
+            __builtin_amdgcn_sched_barrier(0);
+            bf16x8 aS[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) aS[p] = buf[W::OPER + p * W::PLANE + (hrow >> 3) * D + hcol];
+#pragma unroll
+            for (int j = 0; j < T::NB; ++j) {
+                // The five small products of this chunk are summed from zero and added with one rounding: inside the matrix
+                // unit they would be cut off below the running sum, always downwards, which over a million rows adds up (a
+                // 3e-6 error on random gradients, against 1e-6 for the fp32 instruction).
+                constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
+                const int ub = (hrow >> 3) * D + 16 * j + (lane & 15);
+                f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};
+                bf16x8 b[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) b[p] = buf[p * W::PLANE + ub];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) {
+                    lo0 = mfma(b[BW[i]], a1.p[AW[i]], lo0);
+                    lo1 = mfma(b[BW[i]], aS[AW[i]], lo1);
+                }
+                acc[0][j] = mfma(b[0], a1.p[0], acc[0][j]);
+                acc[1][j] = mfma(b[0], aS[0], acc[1][j]);
+                acc[0][j] += lo0;
+                acc[1][j] += lo1;
+                asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]));       // added here: the compiler would keep all sums to the end of the loop
+                __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
+                if constexpr (CELL) {
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) b[p] = buf[2 * W::OPER + p * W::PLANE + ub];
+                    lo0 = lo1 = f32x4{0.f, 0.f, 0.f, 0.f};
+                    lo0 = mfma(b[2], a2.p[0], lo0);
+                    lo1 = mfma(b[1], a2.p[0], lo1);
+                    lo0 = mfma(b[0], a2.p[2], lo0);
+                    lo1 = mfma(b[0], a2.p[1], lo1);
+                    lo0 = mfma(b[1], a2.p[1], lo0);
+                    acc[2][j] = mfma(b[0], a2.p[0], acc[2][j]);
+                    acc[2][j] += lo0 + lo1;
+                    asm volatile("" : "+v"(acc[2][j]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            load_h(next);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!kFirst) stage_next();
+        }
+    };
+    if (wave < T::WAVES / 2) walk(yes{});
+    else walk(no{});
     // lane: row 16 mb + (lane & 15) of dW, columns 16 j + 4 (lane >> 4) ..
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
