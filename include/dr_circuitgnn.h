@@ -189,7 +189,7 @@ int dr_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64_t n
                              const int32_t* rowptr, const int32_t* colidx, float* vals_out, void* stream);
 
 /* ------------------------------------------------------------------------------------------------
- * The HeteroConv layer (paper Fig. 3, Sections 3.2-3.4): three relation modules on three HIP streams,
+ * The HeteroConv layer (paper Fig. 3, Sections 3.2-3.4): three relation modules whose kernels share launches,
  *     near   (cell->cell, SageConv mean):  Z_near   = f(X_cell) Wself_near + (A_near   f(X_cell)) Wneigh_near
  *     pins   (cell->net,  SageConv mean):  Y_net    = f(X_net)  Wself_pins + (A_pins   f(X_cell)) Wneigh_pins
  *     pinned (net->cell,  GraphConv sym):  Z_pinned =                        (A_pinned f(X_net))  W_pinned
@@ -198,7 +198,7 @@ int dr_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64_t n
  * Every weight is [D,D] row-major with the Y = X W convention; there are no biases.
  * ---------------------------------------------------------------------------------------------- */
 
-typedef struct dr_heteroconv dr_heteroconv;   /* opaque: transposed adjacencies, streams, events, scratch */
+typedef struct dr_heteroconv dr_heteroconv;   /* opaque: transposed adjacencies, scratch */
 
 typedef struct dr_heteroconv_weights {        /* device pointers, each [D,D]; read-only in fwd and bwd */
     const float* self_near;
@@ -234,8 +234,7 @@ typedef struct dr_heteroconv_saved {          /* caller-owned device buffers wri
 
 /*
  * Build the per-graph context: validates the three relations (near Nc x Nc, pins Nn x Nc,
- * pinned Nc x Nn, all with vals), transposes them on the device, creates three streams and the events
- * that join them, and allocates the scratch the backward pass needs.  Device memory is allocated only by the
+ * pinned Nc x Nn, all with vals), transposes them on the device and allocates the scratch the backward pass needs.  Device memory is allocated only by the
  * *_create calls (released by the matching *_destroy) and, temporarily, by heteroconv_profile_k.  The CSR arrays passed in stay
  * owned by the caller and must outlive the context.  The call synchronises the device before returning.
  * Requires D in {32, 64, 96, 128}, 1 <= k_cell, k_net <= D.
@@ -277,8 +276,7 @@ int heteroconv_profile_k(dr_heteroconv* ctx, const float* X_cell, const float* X
 
 /*
  * Forward of one layer.  Inputs X_cell[Nc,D], X_net[Nn,D]; outputs Y_cell[Nc,D], Y_net[Nn,D] and every
- * buffer of `saved`.  Work is forked from `stream` onto the context's three relation streams and joined
- * back into `stream` before the call returns (device-side joins; the host does not wait).
+ * buffer of `saved`.  All work is enqueued on `stream`, in order; the host does not wait.
  */
 int heteroconv_fwd(dr_heteroconv* ctx, const float* X_cell, const float* X_net,
                    const dr_heteroconv_weights* W, float* Y_cell, float* Y_net,
@@ -312,11 +310,11 @@ int heteroconv_destroy(dr_heteroconv* ctx);
 int heteroconv_set_cell_order(dr_heteroconv* ctx, const int32_t* cell_order, int* staged, void* stream);
 
 /*
- * Relation concurrency (paper Section 3.4).  DR_OVERLAP_ON: the near, pins and pinned pipelines are enqueued on
- * three HIP streams and joined by events only where the data flow demands it.  DR_OVERLAP_OFF: the same kernels,
- * in the same dependency order, back to back on one stream.  DR_OVERLAP_AUTO (default): separate streams while one
- * relation's launches leave CUs idle at their tails (max(Nc, Nn) * D < 2^26), one stream beyond that, where
- * overlapping launches only time-slice the CUs.  Takes effect from the next heteroconv_fwd / heteroconv_bwd.
+ * Relation concurrency (paper Section 3.4).  DR_OVERLAP_ON: a step of the layer is one launch in which the workgroups
+ * of near, pins and pinned run side by side.  DR_OVERLAP_OFF: a launch per relation, back to back, in the same dependency
+ * order.  DR_OVERLAP_AUTO (default): shared launches while one relation's workgroups leave CUs idle at their tails
+ * (max(Nc, Nn) * D < 2^26), a launch per relation beyond that, where every launch fills the chip and a relation finds
+ * part of what was just written in the caches.  Takes effect from the next heteroconv_fwd / heteroconv_bwd.
  */
 #define DR_OVERLAP_AUTO 0
 #define DR_OVERLAP_ON   1
@@ -325,8 +323,8 @@ int heteroconv_set_overlap(dr_heteroconv* ctx, int mode);
 
 /*
  * Measurement aid (not part of the method): per-kernel device time of the layer's launches.
- * heteroconv_profile(ctx, 1) makes every later heteroconv_fwd / heteroconv_bwd bracket each of its kernel
- * launches with a pair of HIP events recorded on the stream that launch runs on; heteroconv_profile(ctx, 0)
+ * heteroconv_profile(ctx, 1) makes every later heteroconv_fwd / heteroconv_bwd give every relation
+ * launches of its own (as DR_OVERLAP_OFF) and bracket each with HIP events on the caller's stream; heteroconv_profile(ctx, 0)
  * stops that.  heteroconv_kernel_times synchronises the device, adds up the elapsed time per kernel id since
  * the previous call into ms_sum[n] / launches[n] (host arrays, n >= heteroconv_num_kernels()) and forgets the
  * recorded launches.  heteroconv_kernel_name(id) names a kernel id ("dr_spmm_fwd.near", ...).
@@ -340,7 +338,7 @@ int heteroconv_kernel_times(dr_heteroconv* ctx, double* ms_sum, int64_t* launche
 /* ------------------------------------------------------------------------------------------------
  * Multi-layer training step (paper Section 4.1: stacked HeteroConv layers with ReLU between them, a
  * per-cell congestion read-out, mean-squared error, Adam with weight decay), over a batch of independent
- * sub-graphs that share the parameters and are processed concurrently on HIP streams (Section 3.4).
+ * sub-graphs that share the parameters and are processed side by side (Section 3.4).
  *
  *   X^(0) = input;  (Y_cell, Y_net) = HeteroConv_l(X^(l-1));  X^(l) = ReLU(Y) for l < L,  X^(L) = Y;
  *   pred_i = X_cell^(L)[i,:] . w_head;   loss = mean over all cells of the batch of (pred_i - target_i)^2.
@@ -396,8 +394,9 @@ int hgnn_create_batched(dr_hgnn** model, int32_t n_graphs, dr_heteroconv* const*
  * place (step = 1 for the first update; moments start at zero); the hyper-parameters are doubles so that
  * 1 - beta and the bias corrections are formed exactly before they are rounded to the fp32 the kernel uses.  grad_out: device vector of the same
  * length that receives the batch gradient (before weight decay).  loss_out: one device float.
- * Work is forked from `stream` onto one stream per sub-graph (and the relation streams below them) and
- * joined back before the parameter update; the host never waits.
+ * Sub-graphs that do not fill the chip share their launches; a batch that is one such group is enqueued on `stream`
+ * itself, several groups are forked from `stream` onto a stream each and joined back before the parameter update; the
+ * host never waits.
  */
 int hgnn_train_step(dr_hgnn* model, const float* const* X_cell, const float* const* X_net,
                     const float* const* target, float* theta, float* adam_m, float* adam_v,

@@ -134,6 +134,7 @@ int launch_spmm_bwd_planned(const dr_spmm_plan* p, const float* dH, const uint16
                             hipStream_t s);
 
 constexpr int kMaxGraphs = 16;    // graphs per launch (their descriptors travel as kernel arguments)
+constexpr int64_t kFullLaunch = int64_t(1) << 26;   // elements of a node type's rows from which on one relation's launch fills the chip
 
 // shape of a layer context (heteroconv.hip owns the struct)
 struct HeteroDims {
@@ -161,6 +162,7 @@ struct LayerFwd {
     float *Y_cell, *Y_net;
     const dr_heteroconv_saved* S;
 };
+bool heteroconv_relations_apart(const dr_heteroconv* c);     // whether a pass over this graph alone has a launch per relation
 int heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, ForwardOptions opt);
 struct BackwardOptions {
     bool gate_inputs = false;     // zero dX where the layer's input was not positive (ReLU in front of the layer)

@@ -316,16 +316,6 @@ int heteroconv_set_overlap(dr_heteroconv* ctx, int mode) {
     return DR_OK;
 }
 
-// Whether each relation gets launches of its own.  Shared launches pay off while one relation's workgroups leave compute
-// units idle; at 1.2 M cells every launch has tens of thousands of workgroups, and a relation that is gathered right after
-// its D-ReLU was written still finds part of it in the memory-side cache.  Per-kernel timing needs separate launches.
-static bool relations_apart(const dr_heteroconv* c) {
-    if (c->profile || c->overlap == DR_OVERLAP_OFF) return true;
-    if (c->overlap == DR_OVERLAP_ON) return false;
-    const int64_t rows = c->Nc > c->Nn ? c->Nc : c->Nn;
-    return rows * c->D >= (int64_t(1) << 26);
-}
-
 int heteroconv_profile(dr_heteroconv* ctx, int enable) {
     DRC_REQUIRE(ctx != nullptr, "heteroconv_profile: null context");
     DRC_REQUIRE(ctx->timed && ctx->event_pool, "heteroconv_profile: out of host memory");
@@ -483,6 +473,16 @@ int heteroconv_bwd(dr_heteroconv* c, const float* dY_cell, const float* dY_net, 
 
 }  // extern "C"
 
+// Whether each relation gets launches of its own.  Shared launches pay off while one relation's workgroups leave compute
+// units idle; at 1.2 M cells every launch has tens of thousands of workgroups, and a relation that is gathered right after
+// its D-ReLU was written still finds part of it in the memory-side cache.  Per-kernel timing needs separate launches.
+bool drc::heteroconv_relations_apart(const dr_heteroconv* c) {
+    if (c->profile || c->overlap == DR_OVERLAP_OFF) return true;
+    if (c->overlap == DR_OVERLAP_ON) return false;
+    const int64_t rows = c->Nc > c->Nn ? c->Nc : c->Nn;
+    return rows * c->D >= kFullLaunch;
+}
+
 int drc::heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, ForwardOptions opt) {
     // opt.skip_net_output: Y_net is not wanted (last layer of a model whose read-out uses the cells only): the pins
     // module -- its DR-SpMM and its projection -- is not launched, and H_pins / Y_net are left untouched.
@@ -505,7 +505,7 @@ int drc::heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weight
         const dr_heteroconv_saved* S = L.S;
         DRC_TRY(check_saved(c, S, "heteroconv_fwd"));
         c->chain_stop = nullptr;
-        apart = apart || relations_apart(c);
+        apart = apart || heteroconv_relations_apart(c);
         const CbsrSets q = cbsr_sets(c, S);
         // A node type that is read at two widths is selected at both in one pass over its embeddings.
         tk[2 * i] = TopkJob{L.X_net, c->Nn, c->k_pinned, S->vals_net, S->idx_net, c->k_self,
@@ -565,7 +565,7 @@ int drc::heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weigh
         const dr_heteroconv_saved* S = L.S;
         DRC_TRY(check_saved(c, S, "heteroconv_bwd"));
         c->chain_stop = nullptr;
-        apart = apart || relations_apart(c);
+        apart = apart || heteroconv_relations_apart(c);
         const CbsrSets q = cbsr_sets(c, S);
         wj[2 * i] = WgradJob{c->Nc, L.dY_cell, S->mask, S->H_near, S->H_pinned, q.v_near, q.i_near, c->k_near,
                              L.dW.neigh_near, L.dW.self_near, L.dW.pinned, c->wg_scratch[0]};

@@ -1,7 +1,8 @@
 // Multi-layer training step (paper Section 4.1): L stacked HeteroConv layers with ReLU between them, a
 // per-cell read-out pred = X_cell^(L) . w_head, mean-squared error over all cells of the batch, Adam with
-// the L2 form of weight decay.  The sub-graphs of a batch are independent (Section 3.4): each runs its
-// whole forward and backward on its own stream, and the streams are joined only before the parameter update.
+// the L2 form of weight decay.  The sub-graphs of a batch are independent (Section 3.4): sub-graphs that do
+// not fill the chip by themselves share every launch of the step, larger ones run on a stream each, joined before the
+// parameter update.
 //
 // What is new here next to the layer is element-wise or a small reduction:
 //   (the ReLU between layers and its gate are folded into the layer kernels that write Y and dX)
@@ -11,9 +12,7 @@
 //
 // Batched mode (hgnn_create_batched): the sub-graphs are stacked into ONE block-diagonal graph on the device
 // (rows and columns of sub-graph q shifted by the node counts of the sub-graphs before it) and the step runs
-// as a single-graph step: one launch per kernel for the whole batch instead of one per sub-graph.  A
-// 20 000-cell launch fills a fraction of the chip and a streamed step of 8 x 3 layers issues some 800 of
-// them, so for small sub-graphs stacking is the faster mapping of "independent sub-graphs" (Section 3.4).
+// as a single-graph step.  Sub-graphs that are not stacked keep their own sizes and widths and may be bound anew.
 #include "dr_internal.h"
 
 #include <cmath>
@@ -32,7 +31,7 @@ inline int head_blocks(int64_t n) {
     int64_t b = (n + 255) / 256;
     return (int)(b < 64 ? 64 : (b > 2048 ? 2048 : b));
 }
-constexpr int kMaxWorkers = 8;    // host threads that enqueue sub-graphs side by side
+constexpr int kMaxWorkers = 8;    // host threads that enqueue groups of sub-graphs side by side
 
 // Read-out, forward and backward in one pass over Y:  pred[i] = Y[i,:] . w;  dpred[i] = scale * (pred[i] - target[i]);
 // dY[i,c] = dpred[i] * w[c];  per workgroup the sum of squared residuals (loss_part) and of dpred[i] * Y[i,:] (dw_part).
@@ -40,11 +39,29 @@ constexpr int kMaxWorkers = 8;    // host threads that enqueue sub-graphs side b
 // its gradient is formed; four rows per lane group are in flight.  Bound by HBM: one read of Y and one write of dY.
 // As two kernels with one dword per lane and one row in flight the 160 000 x 128 read-out took 95 + 71 us, now 32 us
 // (164 MB, 5.1 TB/s).
+struct HeadSeg {                  // one sub-graph: workgroups block0 .. block0 + blocks - 1
+    const float *Y, *target;
+    float *pred, *dpred, *dY, *loss_part, *dw_part;
+    int n, block0, blocks;
+};
+struct HeadArgs {
+    HeadSeg s[kMaxGraphs];
+    const float* w;
+    int n, D;
+    float scale;
+};
 template <int LPR>
-__global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ Y, const float* __restrict__ w,
-                                                   const float* __restrict__ target, int n, int D, float scale,
-                                                   float* __restrict__ pred, float* __restrict__ dpred, float* __restrict__ dY,
-                                                   float* __restrict__ loss_part, float* __restrict__ dw_part) {
+__global__ __launch_bounds__(256) void head_kernel(HeadArgs a) {
+    int q = 0;
+    while (q + 1 < a.n && (int)blockIdx.x >= a.s[q + 1].block0) ++q;
+    const float* __restrict__ const Y = a.s[q].Y;
+    const float* __restrict__ const target = a.s[q].target;
+    const float* __restrict__ const w = a.w;
+    float* __restrict__ const pred = a.s[q].pred;
+    float* __restrict__ const dpred = a.s[q].dpred;
+    float* __restrict__ const dY = a.s[q].dY;
+    const int n = a.s[q].n, D = a.D, block = (int)blockIdx.x - a.s[q].block0;
+    const float scale = a.scale;
     constexpr int G = 256 / LPR, U = 4;                         // lane groups per workgroup, rows in flight
     __shared__ float4 part[G][LPR];
     __shared__ float sq[G];
@@ -54,8 +71,8 @@ __global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ Y, 
     const float w0 = on ? w[c] : 0.f, w1 = on ? w[c + 1] : 0.f, w2 = on ? w[c + 2] : 0.f, w3 = on ? w[c + 3] : 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float loss = 0.f;                                           // (lane 0 of the group)
-    const int step = gridDim.x * G;
-    for (int r0 = blockIdx.x * G + g; r0 < n; r0 += U * step) {
+    const int step = a.s[q].blocks * G;
+    for (int r0 = block * G + g; r0 < n; r0 += U * step) {
         float4 y[U];
         float tg[U];
 #pragma unroll
@@ -92,23 +109,21 @@ __global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ Y, 
     if ((int)threadIdx.x < D) {
         float s = 0.f;
 #pragma unroll
-        for (int q = 0; q < G; ++q) s += reinterpret_cast<const float*>(part[q])[threadIdx.x];
-        dw_part[(size_t)blockIdx.x * D + threadIdx.x] = s;
+        for (int i = 0; i < G; ++i) s += reinterpret_cast<const float*>(part[i])[threadIdx.x];
+        a.s[q].dw_part[(size_t)block * D + threadIdx.x] = s;
     }
     if (threadIdx.x == 0) {
         float s = 0.f;
-        for (int q = 0; q < G; ++q) s += sq[q];
-        loss_part[blockIdx.x] = s;
+        for (int i = 0; i < G; ++i) s += sq[i];
+        a.s[q].loss_part[block] = s;
     }
 }
 
-static void launch_head(const float* Y, const float* w, const float* target, int n, int D, float scale, float* pred, float* dpred,
-                        float* dY, float* loss_part, float* dw_part, int blocks, hipStream_t s) {
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, Y, w, target, n, D, scale, pred, dpred, dY, loss_part, dw_part);
-    };
-    if (D <= 32) go(head_kernel<8>);
-    else if (D <= 64) go(head_kernel<16>);
+static void launch_head(const HeadArgs& a, hipStream_t s) {
+    const unsigned blocks = (unsigned)(a.s[a.n - 1].block0 + a.s[a.n - 1].blocks);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a); };
+    if (a.D <= 32) go(head_kernel<8>);
+    else if (a.D <= 64) go(head_kernel<16>);
     else go(head_kernel<32>);
 }
 
@@ -213,8 +228,8 @@ struct GraphState {
 }  // namespace drc
 
 namespace drc {
-// Host threads that enqueue the sub-graphs of a step side by side.  They are started once, with the model, and sleep
-// between steps: starting and joining threads on every step costs more than enqueueing a small sub-graph.
+// Host threads that enqueue the groups of sub-graphs of a step side by side.  They are started once, with the model, and sleep
+// between steps: starting and joining threads on every step costs more than enqueueing a small group.
 class EnqueuePool {
   public:
     EnqueuePool(int n_threads, int device) : rcs_(n_threads, DR_OK), errs_(n_threads) {
@@ -293,6 +308,7 @@ struct dr_hgnn {
     int64_t PL;                                // layer parameters: L*5*D*D
     int64_t n_cells_total;
     std::vector<drc::GraphState> g;
+    std::vector<int> group_first;              // first sub-graph of each group of the current step, and one past the last
     std::vector<void*> owned;
     float *gall, *loss_part, *dwh_part;
     int n_head_parts;                          // read-out partials of all states together
@@ -429,6 +445,7 @@ static int create_model(dr_hgnn** model, int32_t n_graphs, dr_heteroconv* const*
             DRC_TRY(alloc_t(m, &m->tg_all, (size_t)Nc));
         }
         const int ns = m->n_graphs;
+        m->group_first.assign(ns + 1, 0);
         DRC_TRY(alloc_t(m, &m->gall, (size_t)ns * m->PL));
         m->n_head_parts = 0;
         // Buffers are sized for the contexts' capacities: a context that a pipeline re-binds to the next sub-graph keeps
@@ -569,69 +586,102 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
     const int L = m->L, D = m->D;
     const float scale = (float)(2.0 / (double)m->n_cells_total);
 
-    DRC_HIP(hipEventRecord(m->fork, user));
-    // One sub-graph = one stream = one host thread (of the model's pool): a step of small sub-graphs issues several
-    // hundred launches and event operations, and a single host thread cannot enqueue them as fast as the GPU drains them.
-    auto enqueue_graph = [&](int q) -> int {
-        GraphState& gs = m->g[q];
-        hipStream_t s = gs.stream;
-        DRC_HIP(hipStreamWaitEvent(s, m->fork, 0));
-        gs.X_cell = X_cell[q]; gs.X_net = X_net[q];
-        const int n = (int)gs.Nc;
+    // Which sub-graphs share their launches: consecutive ones, until together they fill the chip.  A sub-graph whose
+    // context wants a launch per relation (its size, or timing or DR_OVERLAP_OFF asked of it) stays by itself.
+    std::vector<int>& first = m->group_first;
+    int n_groups = 0;
+    {
+        int64_t elements = 0;
+        bool alone = false;
+        for (int q = 0; q < m->n_graphs; ++q) {
+            const GraphState& gs = m->g[q];
+            const int64_t mine = (gs.Nc > gs.Nn ? gs.Nc : gs.Nn) * D;
+            const bool apart = heteroconv_relations_apart(gs.ctx);
+            if (q == 0 || alone || apart || q - first[n_groups - 1] == kMaxGraphs || elements + mine > kFullLaunch) {
+                first[n_groups++] = q;
+                elements = 0;
+            }
+            alone = apart;
+            elements += mine;
+        }
+        first[n_groups] = m->n_graphs;
+    }
+
+    // One group: everything goes to the caller's stream.  Several: one group = one stream = one host thread (of the model's
+    // pool), because a single host thread cannot enqueue the launches of many groups as fast as the GPU drains them.
+    const bool forked = n_groups > 1;
+    auto enqueue_group = [&](int grp) -> int {
+        GraphState* const g = &m->g[first[grp]];
+        const int n = first[grp + 1] - first[grp];
+        const hipStream_t s = forked ? g->stream : user;
+        if (forked) DRC_HIP(hipStreamWaitEvent(s, m->fork, 0));
+        LayerFwd lf[kMaxGraphs];
+        LayerBwd lb[kMaxGraphs];
+        for (int i = 0; i < n; ++i) {
+            g[i].X_cell = X_cell[first[grp] + i];
+            g[i].X_net = X_net[first[grp] + i];
+        }
         // ---- forward ----
-        const float *xc = X_cell[q], *xn = X_net[q];
         for (int l = 0; l < L; ++l) {
             const dr_heteroconv_weights W = layer_weights(theta, l, D);
             // the ReLU between layers is folded into the kernels that write the layer's outputs
             ForwardOptions fo;
             fo.relu_out = l < L - 1;
             fo.skip_net_output = l == L - 1 && !m->inspect;   // the read-out uses the cells only
-            const LayerFwd lf{gs.ctx, xc, xn, gs.act_c[l], gs.act_n[l], &gs.saved[l]};
-            DRC_TRY(heteroconv_forward(&lf, 1, &W, s, fo));
-            xc = gs.act_c[l]; xn = gs.act_n[l];
+            for (int i = 0; i < n; ++i)
+                lf[i] = LayerFwd{g[i].ctx, l ? g[i].act_c[l - 1] : g[i].X_cell, l ? g[i].act_n[l - 1] : g[i].X_net,
+                                 g[i].act_c[l], g[i].act_n[l], &g[i].saved[l]};
+            DRC_TRY(heteroconv_forward(lf, n, &W, s, fo));
         }
         // ---- read-out, loss, gradient of the last layer's output ----
-        const float* w_head = theta + m->PL;
-        launch_head(gs.act_c[L - 1], w_head, target[q], n, D, scale, gs.pred, gs.dpred, gs.G_c[L], gs.loss_part, gs.dwh_part, gs.hb, s);
+        HeadArgs h{};
+        h.w = theta + m->PL; h.n = n; h.D = D; h.scale = scale;
+        int blocks = 0;
+        for (int i = 0; i < n; ++i) {
+            h.s[i] = HeadSeg{g[i].act_c[L - 1], target[first[grp] + i], g[i].pred, g[i].dpred, g[i].G_c[L], g[i].loss_part,
+                             g[i].dwh_part, (int)g[i].Nc, blocks, g[i].hb};
+            blocks += g[i].hb;
+        }
+        launch_head(h, s);
         DRC_HIP(hipGetLastError());
         // ---- backward ----
         for (int l = L - 1; l >= 0; --l) {
             const dr_heteroconv_weights W = layer_weights(theta, l, D);
-            const dr_heteroconv_wgrads dW = layer_wgrads(gs.gvec, l, D);
             // layers above the first sit behind a ReLU: its gate on the input gradient is folded into the kernels
             // that write dX (the saved D-ReLU values are the layer's inputs at every position dX can be non-zero)
             BackwardOptions opt;
             opt.gate_inputs = l >= 1;
             opt.skip_dx = l == 0 && !m->inspect;       // nobody reads the gradient of the input features
             opt.dy_net_zero = l == L - 1;                  // the loss reads the cells only: G_n[L] holds zeros
-            const LayerBwd lb{gs.ctx, gs.G_c[l + 1], gs.G_n[l + 1], &gs.saved[l], gs.G_c[l], gs.G_n[l], dW};
-            DRC_TRY(heteroconv_backward(&lb, 1, &W, s, opt));
+            for (int i = 0; i < n; ++i)
+                lb[i] = LayerBwd{g[i].ctx, g[i].G_c[l + 1], g[i].G_n[l + 1], &g[i].saved[l], g[i].G_c[l], g[i].G_n[l],
+                                 layer_wgrads(g[i].gvec, l, D)};
+            DRC_TRY(heteroconv_backward(lb, n, &W, s, opt));
         }
         DRC_HIP(hipGetLastError());
-        DRC_HIP(hipEventRecord(gs.done, s));
+        if (forked) DRC_HIP(hipEventRecord(g->done, s));
         return DR_OK;
     };
-    // Whatever a sub-graph's enqueueing ends with, its `done` event is recorded behind what did get enqueued, and the
-    // caller's stream waits for every sub-graph before this call returns -- also when one of them failed, so that no
-    // work of this step is still reading theta or the gradient buffers once the caller sees the error.
-    const std::function<int(int)> enqueue_and_mark = [&](int q) -> int {
-        const int rc = enqueue_graph(q);
-        if (rc != DR_OK) (void)hipEventRecord(m->g[q].done, m->g[q].stream);
-        return rc;
-    };
-    int step_rc = DR_OK;
-    std::string step_err;
-    if (m->n_graphs == 1) {
-        step_rc = enqueue_and_mark(0);
-        if (step_rc != DR_OK) step_err = dr_last_error();
+    if (!forked) {
+        DRC_TRY(enqueue_group(0));
     } else {
-        step_rc = m->pool->run(m->n_graphs, enqueue_and_mark, &step_err);
+        DRC_HIP(hipEventRecord(m->fork, user));
+        // Whatever a group's enqueueing ends with, its `done` event is recorded behind what did get enqueued, and the
+        // caller's stream waits for every group before this call returns -- also when one of them failed, so that no
+        // work of this step is still reading theta or the gradient buffers once the caller sees the error.
+        const std::function<int(int)> enqueue_and_mark = [&](int grp) -> int {
+            const int rc = enqueue_group(grp);
+            if (rc != DR_OK) (void)hipEventRecord(m->g[first[grp]].done, m->g[first[grp]].stream);
+            return rc;
+        };
+        std::string step_err;
+        const int step_rc = m->pool->run(n_groups, enqueue_and_mark, &step_err);
+        if (step_rc != DR_OK) {
+            for (int i = 0; i < n_groups; ++i) (void)hipStreamWaitEvent(user, m->g[first[i]].done, 0);
+            return fail(step_rc, "%s", step_err.c_str());
+        }
+        for (int i = 0; i < n_groups; ++i) DRC_HIP(hipStreamWaitEvent(user, m->g[first[i]].done, 0));
     }
-    if (step_rc != DR_OK) {
-        for (int q = 0; q < m->n_graphs; ++q) (void)hipStreamWaitEvent(user, m->g[q].done, 0);
-        return fail(step_rc, "%s", step_err.c_str());
-    }
-    for (int q = 0; q < m->n_graphs; ++q) DRC_HIP(hipStreamWaitEvent(user, m->g[q].done, 0));
 
     // ---- loss and parameter update, after every sub-graph has delivered its gradient ----
     const AdamArgs a{theta, adam_m, adam_v, grad_out, loss_out, m->gall, m->dwh_part, m->loss_part, m->n_graphs, m->n_head_parts, D,

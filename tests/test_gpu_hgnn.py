@@ -579,3 +579,38 @@ def test_batched_model_with_one_k_per_edge_type():
     assert np.allclose(ga, gb, rtol=1e-4, atol=1e-6 * np.abs(ga).max())
     for c in ctxs:
         c.heteroconv_destroy()
+
+
+@pytest.mark.parametrize("n_graphs,by_itself", [(18, ()), (16, ()), (4, (1,)), (3, (0, 2))],
+                         ids=["more_than_one_launch_takes", "one_full_launch", "one_by_itself", "first_and_last_by_themselves"])
+def test_shared_launches_equal_a_launch_per_subgraph(n_graphs, by_itself):
+    """Sub-graphs whose launches are shared against the same sub-graphs with launches of their own: the last layer's
+    selections, predictions and gradients per cell are the same numbers, sums over rows agree up to their order."""
+    D, L = 64, 2
+    graphs, rels, ctxs, keep, Xc, Xn, tg, theta0 = _setup(n_graphs, 320, 200, (60, 40), D, 16, L, seed0=300)
+    x = [dev(a) for a in Xc], [dev(a) for a in Xn], [dev(a) for a in tg]
+    n_par = P.hgnn_num_params(L, D)
+
+    def step(alone):
+        for q, c in enumerate(ctxs):
+            c.heteroconv_set_overlap(P.DR_OVERLAP_OFF if q in alone else P.DR_OVERLAP_AUTO)
+        model = P.Hgnn(ctxs, L)
+        th, m, v = dev(theta0), torch.zeros(n_par, device="cuda"), torch.zeros(n_par, device="cuda")
+        grad, loss = torch.full((n_par,), float("nan"), device="cuda"), torch.full((1,), float("nan"), device="cuda")
+        model.hgnn_train_step(*x, th, m, v, LR, B1, B2, EPS, WD, 1, grad, loss)
+        torch.cuda.synchronize()
+        rows = [{n: b[n].cpu().numpy() for n in ("idx_cell", "mask", "Y_cell", "pred", "dpred", "dY_cell")}
+                for b in (model.hgnn_get_layer_buffers(q, L - 1) for q in range(n_graphs))]
+        model.hgnn_destroy()
+        return float(loss.cpu()[0]), grad.cpu().numpy().astype(np.float64), rows
+
+    loss_a, grad_a, rows_a = step(by_itself)
+    loss_b, grad_b, rows_b = step(range(n_graphs))
+    for a, b in zip(rows_a, rows_b):
+        for n in a:
+            assert np.array_equal(a[n], b[n]), n
+    # sums of up to 18 x 1400 fp32 terms in two orders
+    assert abs(loss_a - loss_b) <= 1e-5 * abs(loss_b)
+    assert np.linalg.norm(grad_a - grad_b) <= 1e-5 * np.linalg.norm(grad_b)
+    for c in ctxs:
+        c.heteroconv_destroy()
