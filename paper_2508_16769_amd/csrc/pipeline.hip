@@ -4,9 +4,10 @@
 // largest graph it will see, a re-bindable layer context and a stream.  dr_pipeline_submit hands a host graph to
 // a worker thread, which
 //   1. waits (on the host, in the worker) until the GPU is done with the slot's previous graph,
-//   2. copies the caller's arrays into the slot's pinned staging memory (so the upload is a true async copy),
-//   3. enqueues on the slot's stream: the uploads, the pinned pattern (= transpose of pins), the edge values of
+//   2. copies the caller's patterns into the slot's pinned staging memory (so the upload is a true async copy) and
+//      enqueues on the slot's stream: their uploads, the pinned pattern (= transpose of pins), the edge values of
 //      the three modules, and the three transposed adjacencies of the layer context,
+//   3. stages and uploads the embeddings in pieces,
 //   4. records the slot's `ready` event.
 // dr_pipeline_acquire waits for step 4 to have been ENQUEUED and makes the caller's stream wait for the event:
 // the host never waits for the GPU on the consumer side, and nothing here allocates after dr_pipeline_create.
@@ -66,6 +67,19 @@ namespace {
 
 size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
+// A host array to the device through its place in the staging memory, piece by piece: a piece is uploaded while the next
+// one is staged.  (Whole arrays one behind the other left the copy engine idle for the time of the host's copy, which
+// is the longer one of the two.)
+constexpr size_t kPiece = size_t(2) << 20;
+int upload(void* dst, char* stage, const void* src, size_t bytes, hipStream_t st) {
+    for (size_t at = 0; at < bytes; at += kPiece) {
+        const size_t n = bytes - at < kPiece ? bytes - at : kPiece;
+        std::memcpy(stage + at, static_cast<const char*>(src) + at, n);
+        DRC_HIP(hipMemcpyAsync(static_cast<char*>(dst) + at, stage + at, n, hipMemcpyHostToDevice, st));
+    }
+    return DR_OK;
+}
+
 int process(dr_pipeline* p, Slot& s) {
     const dr_host_graph& g = s.job;
     const int D = p->D;
@@ -76,19 +90,12 @@ int process(dr_pipeline* p, Slot& s) {
     const size_t n_rp = 4 * (size_t)(g.n_cells + 1), n_ci = 4 * (size_t)g.nnz_near;
     const size_t p_rp = 4 * (size_t)(g.n_nets + 1), p_ci = 4 * (size_t)g.nnz_pins;
     const size_t xc = g.X_cell ? 4 * (size_t)g.n_cells * D : 0, xn = g.X_net ? 4 * (size_t)g.n_nets * D : 0;
-    std::memcpy(s.stage, g.near_rowptr, n_rp);
-    if (n_ci) std::memcpy(s.stage + s.off_near_ci, g.near_colidx, n_ci);
-    std::memcpy(s.stage + s.off_pins_rp, g.pins_rowptr, p_rp);
-    if (p_ci) std::memcpy(s.stage + s.off_pins_ci, g.pins_colidx, p_ci);
-    if (xc) std::memcpy(s.stage + s.off_xc, g.X_cell, xc);
-    if (xn) std::memcpy(s.stage + s.off_xn, g.X_net, xn);
     hipStream_t st = s.stream;
-    DRC_HIP(hipMemcpyAsync(s.near_rp, s.stage, n_rp, hipMemcpyHostToDevice, st));
-    if (n_ci) DRC_HIP(hipMemcpyAsync(s.near_ci, s.stage + s.off_near_ci, n_ci, hipMemcpyHostToDevice, st));
-    DRC_HIP(hipMemcpyAsync(s.pins_rp, s.stage + s.off_pins_rp, p_rp, hipMemcpyHostToDevice, st));
-    if (p_ci) DRC_HIP(hipMemcpyAsync(s.pins_ci, s.stage + s.off_pins_ci, p_ci, hipMemcpyHostToDevice, st));
-    if (xc) DRC_HIP(hipMemcpyAsync(s.X_cell, s.stage + s.off_xc, xc, hipMemcpyHostToDevice, st));
-    if (xn) DRC_HIP(hipMemcpyAsync(s.X_net, s.stage + s.off_xn, xn, hipMemcpyHostToDevice, st));
+    // The patterns first and the setup right behind them, so that it runs under the staging of the embeddings.
+    DRC_TRY(upload(s.near_rp, s.stage, g.near_rowptr, n_rp, st));
+    DRC_TRY(upload(s.near_ci, s.stage + s.off_near_ci, g.near_colidx, n_ci, st));
+    DRC_TRY(upload(s.pins_rp, s.stage + s.off_pins_rp, g.pins_rowptr, p_rp, st));
+    DRC_TRY(upload(s.pins_ci, s.stage + s.off_pins_ci, g.pins_colidx, p_ci, st));
     // pinned pattern = transpose of the pins pattern
     dr_csr pins_pat{g.n_nets, g.n_cells, g.nnz_pins, s.pins_rp, s.pins_ci, nullptr};
     DRC_TRY(dr_csr_transpose(&pins_pat, s.pinned_rp, s.pinned_ci, nullptr, s.ws_t, s.ws_t_bytes, st));
@@ -100,6 +107,8 @@ int process(dr_pipeline* p, Slot& s) {
     s.rel[1] = dr_csr{g.n_nets, g.n_cells, g.nnz_pins, s.pins_rp, s.pins_ci, s.pins_v};
     s.rel[2] = dr_csr{g.n_cells, g.n_nets, g.nnz_pins, s.pinned_rp, s.pinned_ci, s.pinned_v};
     DRC_TRY(heteroconv_bind(s.ctx, &s.rel[0], &s.rel[1], &s.rel[2], st));
+    DRC_TRY(upload(s.X_cell, s.stage + s.off_xc, g.X_cell, xc, st));
+    DRC_TRY(upload(s.X_net, s.stage + s.off_xn, g.X_net, xn, st));
     DRC_HIP(hipEventRecord(s.ready, st));
     return DR_OK;
 }
