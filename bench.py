@@ -310,7 +310,7 @@ def main() -> int:
     ap.add_argument("--cpu-scale", type=int, default=None, help="oracle layer sample = 1/scale of the workload")
     ap.add_argument("--no-profile-events", action="store_true", help="layer steps without per-kernel HIP events")
     ap.add_argument("--overlap", choices=("auto", "on", "off"), default="auto",
-                    help="layer step: three streams (on), one stream (off), or the library's size rule")
+                    help="layer step: launches shared by the relations (on), a launch per relation (off), or the library's size rule")
     ap.add_argument("--permute-cells", action="store_true",
                     help="sensitivity run: relabel the cells at random (removes the grid locality of `near`)")
     ap.add_argument("--copy-calibration", action="store_true",

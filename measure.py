@@ -5,7 +5,7 @@
     python3 measure.py adaptive  ...   degree-adaptive K next to uniform K, per relation
     python3 measure.py train     ...   the multi-layer training step: one stream per sub-graph against the stacked batch
     python3 measure.py pipeline  ...   host-side pipeline against the per-graph path
-    python3 measure.py overlap   ...   three relation streams against one: whole layer and the D-ReLU / DR-SpMM region
+    python3 measure.py overlap   ...   relations side by side against one after the other: whole layer and the D-ReLU / DR-SpMM region
     python3 measure.py traffic   ...   rocprofv3 FETCH_SIZE / WRITE_SIZE runs of bench.py -> HBM bytes per kernel
 
 `python3 measure.py <mode> --help` describes each.  The headline benchmark is `bench.py`.
@@ -310,20 +310,16 @@ own streams while the GPU computes; the consumer never waits for the GPU until t
     return 0
 
 
-# (label, substring the dispatched kernel's name must contain) in single-stream dispatch order of one
-# forward + backward step
+# (label, substring the dispatched kernel's name must contain) in dispatch order of one forward + backward
+# step with a launch per relation and near^T on staged tiles
 SCHEDULE = (
     ("dr_topk.net", "topk_rows"), ("dr_spmm_fwd.pinned", "spmm_fwd"),
     ("dr_topk.cell", "topk_rows"), ("dr_spmm_fwd.pins", "spmm_fwd"), ("dr_spmm_fwd.near", "spmm_fwd"),
-    ("proj.near", "proj_kernel"), ("proj.pins", "proj_kernel"), ("proj.pinned+merge", "proj_kernel"),
-    ("dproj.near", "proj_kernel"), ("dr_spmm_bwd.near", "spmm_bwd"),
-    ("wgrad.near", "wgrad_partial"), ("wgrad.near.reduce_neigh", "wgrad_reduce"), ("wgrad.near.reduce_self", "wgrad_reduce"),
-    ("dproj.pins", "proj_kernel"), ("dr_spmm_bwd.pins", "spmm_bwd"),
-    ("dself.near+dX", "proj_kernel"),
-    ("wgrad.pins", "wgrad_partial"), ("wgrad.pins.reduce_neigh", "wgrad_reduce"), ("wgrad.pins.reduce_self", "wgrad_reduce"),
-    ("dproj.pinned", "proj_kernel"), ("dr_spmm_bwd.pinned", "spmm_bwd"),
-    ("dself.pins+dX", "proj_kernel"),
-    ("wgrad.pinned", "wgrad_partial"), ("wgrad.pinned.reduce", "wgrad_reduce"),
+    ("proj.cell+merge", "proj_kernel"), ("proj.pins", "proj_kernel"),
+    ("wgrad.cell", "wgrad_partial"), ("wgrad.cell.reduce", "wgrad_reduce"),
+    ("wgrad.pins", "wgrad_partial"), ("wgrad.pins.reduce", "wgrad_reduce"),
+    ("dproj.pins", "proj_kernel"), ("dproj.cell", "proj_kernel"),
+    ("dr_spmm_bwd.pinned+dX", "spmm_bwd"), ("dr_spmm_bwd.near", "spmm_bwd"), ("dr_spmm_bwd.pins+dX", "spmm_bwd"),
 )
 # single-stream dispatch order of `bench.py --only dr --serial` (the timed D-ReLU / DR-SpMM region alone)
 SCHEDULE_DR = (
@@ -402,8 +398,9 @@ bytes actually fetched (factor 2.0) and WRITE_SIZE reads them all (factor 1.0)."
     return 0
 
 def mode_overlap(argv) -> int:
-    """Relation concurrency (paper Section 3.4): the three relations on three HIP streams against one stream, for the whole
-    layer (heteroconv_fwd + heteroconv_bwd) and for the D-ReLU / DR-SpMM region of bench.py alone.
+    """Relation concurrency (paper Section 3.4): the whole layer (heteroconv_fwd + heteroconv_bwd) with launches shared by
+    the relations against a launch per relation, and the D-ReLU / DR-SpMM region of bench.py alone on three HIP streams
+    against one.
 
         python3 measure.py overlap [--workloads small,medium,large] [--steps 30] [--out table.md]
 
@@ -417,9 +414,9 @@ def mode_overlap(argv) -> int:
     ap.add_argument("--out", default=None)
     args = ap.parse_args(argv)
     from circuit_synth import make_tensors
-    lines = ["# Relation concurrency: three streams against one", "",
+    lines = ["# Relation concurrency: side by side against one after the other", "",
              f"Command: `python3 measure.py overlap --workloads {args.workloads} --steps {args.steps}`.", "",
-             "| workload | layer step, one stream ms | layer step, three streams ms | ratio | DR region, one stream ms | DR region, three streams ms | ratio |",
+             "| workload | layer step, launch per relation ms | layer step, shared launches ms | ratio | DR region, one stream ms | DR region, three streams ms | ratio |",
              "|---|---|---|---|---|---|---|"]
     for name in args.workloads.split(","):
         w = workload(name)
