@@ -151,7 +151,7 @@ __device__ __forceinline__ int opaque(int v) {
 __device__ __forceinline__ f32x4 load4(Buf b, int off) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, kNt)); }
 __device__ __forceinline__ float load1(Buf b, int off) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt)); }
 __device__ __forceinline__ uint32_t load1u(Buf b, int off) { return __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt); }
-template <int CP> __device__ __forceinline__ void store4(Buf b, int off, const f32x4& v) {
+template <int CP = 0> __device__ __forceinline__ void store4(Buf b, int off, const f32x4& v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, CP);
 }
 
@@ -278,7 +278,13 @@ struct ProjFwdArgs {
 };
 static_assert(sizeof(ProjFwdArgs) < 4096, "kernel arguments");
 
-template <int D, bool CELL>
+// CP: cache policy of the stores.  A wavefront writes 64 bytes of a row of Y and 16 of the mask, others the rest of a line.
+// Through the L2 the pieces leave as one line; streamed, they leave one by one (1.2 M x 128 cells: 1.53 GB counted as written
+// for 0.77 GB).  What the L2 still holds at the end is written back before the next launch may start, so the stores are
+// streamed while all of Y would stay there (kL2Bytes, eight of 4 MB).  Through the L2 / streamed: layer of 1.2 M cells, D = 128
+// 6.14 / 6.22 ms, 250 000 cells 1.234 / 1.245, 60 000 cells, D = 64 0.206 / 0.203, 33 331 cells, D = 96 0.239 / 0.235.
+constexpr int64_t kL2Bytes = 32ll << 20;
+template <int D, bool CELL, int CP>
 __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf16x8* smem, int wg, int n_wg) {
     using T = Tile<D>;
     const DRC_CONST ProjFwdSide* const segs = CELL ? a->cell : a->net;
@@ -377,11 +383,11 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
                         m |= near_wins ? 1u << (8 * r) : 0u;
                         v[r] = near_wins ? v[r] : p[r];
                     }
-                    __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, kNt);
+                    __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, CP);
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = relu ? fmaxf(v[r], 0.0f) : v[r];
-                store4<kNt>(by, at * 4, v);
+                store4<CP>(by, at * 4, v);
             }
             if constexpr (!kFirst) stage_next();
             if (t1 >= tiles) break;
@@ -397,12 +403,12 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
 
 template <int D> constexpr int waves_per_simd() { return 2; }
 
-template <int D>
+template <int D, int CP>
 __global__ __launch_bounds__(Tile<D>::THREADS, waves_per_simd<D>()) void proj_kernel(ProjFwdArgs a) {
     extern __shared__ bf16x8 smem8[];
     const DRC_CONST ProjFwdArgs* const k = kernel_args<ProjFwdArgs>();
-    if ((int)blockIdx.x < k->cell_wgs) proj_fwd_side<D, true>(k, smem8, blockIdx.x, k->cell_wgs);
-    else proj_fwd_side<D, false>(k, smem8, blockIdx.x - k->cell_wgs, gridDim.x - k->cell_wgs);
+    if ((int)blockIdx.x < k->cell_wgs) proj_fwd_side<D, true, CP>(k, smem8, blockIdx.x, k->cell_wgs);
+    else proj_fwd_side<D, false, CP>(k, smem8, blockIdx.x - k->cell_wgs, gridDim.x - k->cell_wgs);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -548,8 +554,8 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
                 const int r = rg * 32 + rb * 16 + (lane & 15), c = 16 * nb + 4 * (lane >> 4);
                 *reinterpret_cast<f32x4*>(sC + r * LDC + c) = cS[rb];
                 // gathered next: these stay in the caches
-                store4<0>(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
-                if constexpr (CELL) store4<0>(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
+                store4(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
+                if constexpr (CELL) store4(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
             }
             finish_t0();
             if constexpr (!kFirst) stage_next();
@@ -865,12 +871,12 @@ static void share(int64_t cell_work, int64_t net_work, int cell_tiles, int net_t
     *nets = (int)n;
 }
 
-template <int D> static int launch_proj_fwd_d(ProjFwdArgs& a, hipStream_t s) {
+template <int D, int CP> static int launch_proj_fwd_cp(ProjFwdArgs& a, hipStream_t s) {
     using T = Tile<D>;
     static std::atomic<int> cache{0};
     constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * T::OPER;
     int res = 0;
-    DRC_TRY(resident(&proj_kernel<D>, T::THREADS, lds, cache, &res));
+    DRC_TRY(resident(&proj_kernel<D, CP>, T::THREADS, lds, cache, &res));
     a.cell_tiles = a.net_tiles = 0;
     for (int i = 0; i < a.n; ++i) {
         a.cell[i].tile0 = a.cell_tiles; a.net[i].tile0 = a.net_tiles;
@@ -880,9 +886,15 @@ template <int D> static int launch_proj_fwd_d(ProjFwdArgs& a, hipStream_t s) {
     int nets = 0;
     share(3ll * a.cell_tiles, 2ll * a.net_tiles, a.cell_tiles, a.net_tiles, res, &a.cell_wgs, &nets);
     if (a.cell_wgs + nets == 0) return DR_OK;
-    hipLaunchKernelGGL((proj_kernel<D>), dim3((unsigned)(a.cell_wgs + nets)), dim3(T::THREADS), lds, s, a);
+    hipLaunchKernelGGL((proj_kernel<D, CP>), dim3((unsigned)(a.cell_wgs + nets)), dim3(T::THREADS), lds, s, a);
     DRC_HIP(hipGetLastError());
     return DR_OK;
+}
+
+template <int D> static int launch_proj_fwd_d(ProjFwdArgs& a, hipStream_t s) {
+    int64_t rows = 0;
+    for (int i = 0; i < a.n; ++i) rows += (int64_t)a.cell[i].rows + a.net[i].rows;
+    return rows * D * 4 > kL2Bytes ? launch_proj_fwd_cp<D, 0>(a, s) : launch_proj_fwd_cp<D, kNt>(a, s);
 }
 
 int launch_proj_fwd(const ProjFwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, bool relu, hipStream_t s) {
