@@ -1,6 +1,7 @@
 // Per-graph setup kernels: module edge values (mean / symmetric normalisation) and the stable CSR
 // transpose used by the backward pass (paper Alg. 2, stage 1).
 #include "dr_internal.h"
+#include "partition_shape.h"
 
 #include <atomic>
 #include <mutex>
@@ -51,8 +52,8 @@ __device__ __forceinline__ int wave_rows_from(const int32_t* __restrict__ rowptr
     int row = base;
     bool open = true;
     do {
-        const int i = base + 1 + lane;
-        const int end = i <= n_rows ? rowptr[i] : 0x7fffffff;
+        const uint32_t i = (uint32_t)base + 1u + (uint32_t)lane;             // may lie past 2^31
+        const int end = i <= (uint32_t)n_rows ? rowptr[i] : 0x7fffffff;
         int c = 0;                                             // row ends at or before e among these 64 (sorted)
 #pragma unroll
         for (int w = 32; w >= 1; w >>= 1) c += (__shfl(end, c + w - 1, 64) <= e) ? w : 0;
@@ -65,8 +66,8 @@ __device__ __forceinline__ int wave_rows_from(const int32_t* __restrict__ rowptr
 }
 
 __global__ void count_columns_kernel(const int32_t* __restrict__ colidx, int nnz, int32_t* __restrict__ count) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < nnz) atomicAdd(&count[colidx[e]], 1);
+    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < (uint32_t)nnz) atomicAdd(&count[colidx[e]], 1);
 }
 
 // Edge values.  A wavefront takes kNormSteps * 64 consecutive edges.
@@ -75,11 +76,12 @@ __global__ __launch_bounds__(256) void normalize_kernel(int mode, const int32_t*
                                                         int n_rows, int nnz, const int32_t* __restrict__ deg_out,
                                                         float* __restrict__ vals) {
     const int lane = threadIdx.x & 63;
-    const int first = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)) * (kNormSteps * 64);
-    if (first >= nnz) return;
+    const uint32_t at = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (uint32_t)(kNormSteps * 64);
+    if (at >= (uint32_t)nnz) return;
+    const int first = (int)at, left = min(nnz - first, kNormSteps * 64);
     int row = wave_row_of(rowptr, n_rows, first);
-    for (int s = 0; s < kNormSteps && first + s * 64 < nnz; ++s) {
-        const int e = min(first + s * 64 + lane, nnz - 1);
+    for (int s = 0; s < left; s += 64) {
+        const int e = first + min(s + lane, left - 1);
         const int i = wave_rows_from(rowptr, n_rows, row, e);
         const int di = rowptr[i + 1] - rowptr[i];
         float v;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(256) void normalize_kernel(int mode, const int32_t*
             const double a = (double)(di > 1 ? di : 1) * (double)(dj > 1 ? dj : 1);
             v = (float)(1.0 / sqrt(a));
         }
-        if (first + s * 64 + lane < nnz) vals[e] = v;
+        if (s + lane < left) vals[e] = v;
         row = __builtin_amdgcn_readlane(i, 63);
     }
 }
@@ -160,38 +162,6 @@ int launch_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64
 // All three relations of a context go through one set of launches.
 // ---------------------------------------------------------------------------------------------------
 
-constexpr int kPartThreads = 512, kPartWaves = kPartThreads / 64;
-constexpr int kMaxBuckets = 1024;      // level-1 digits: their counters, one set per wavefront, take 32 KB of LDS
-constexpr int kMaxSub = 2048;          // columns a workgroup of step 4 owns: 64 KB of LDS counters
-constexpr int kMinTile = 4096;         // entries a workgroup of steps 1 and 3 takes at least (512 per wavefront)
-constexpr int kMaxTiles = 512;         // two workgroups per compute unit; more would only lengthen the scan of step 2
-
-struct PartShape {
-    int shift;          // bucket = column >> shift
-    int nb, nb_pad;     // buckets; rounded up to 64
-    int sub_shift;      // columns a step-4 workgroup owns = 1 << sub_shift (a bucket wider than kMaxSub is read by several)
-    int tile, n_tiles;  // entries per workgroup of steps 1 and 3
-};
-
-static PartShape part_shape(int64_t n_cols, int64_t nnz) {
-    PartShape p;
-    // Buckets of about 2048 entries (a step-4 workgroup has four 64-entry steps per wavefront), at least 64 columns wide
-    // and at most kMaxBuckets of them.
-    p.shift = 6;
-    while (((n_cols + (int64_t(1) << p.shift) - 1) >> p.shift) > kMaxBuckets) ++p.shift;
-    while (p.shift < 11 && (nnz << p.shift) < 2048 * n_cols) ++p.shift;
-    p.nb = (int)((n_cols + (int64_t(1) << p.shift) - 1) >> p.shift);
-    if (p.nb < 1) p.nb = 1;
-    p.nb_pad = (p.nb + 63) / 64 * 64;
-    p.sub_shift = p.shift < 11 ? p.shift : 11;
-    int64_t tile = (nnz + kMaxTiles - 1) / kMaxTiles;
-    if (tile < kMinTile) tile = kMinTile;
-    tile = (tile + kPartThreads - 1) / kPartThreads * kPartThreads;
-    p.tile = (int)tile;
-    p.n_tiles = (int)((nnz + tile - 1) / tile);
-    return p;
-}
-
 struct PartSeg {
     PartShape p;
     const int32_t *rowptr, *colidx;
@@ -234,14 +204,15 @@ __global__ __launch_bounds__(kPartThreads) void part_count_kernel(PartBatch b) {
     const int tile = blockIdx.x - g.tile0;
     for (int i = threadIdx.x; i < g.p.nb_pad; i += kPartThreads) cnt[i] = 0u;
     __syncthreads();
-    const int e0 = tile * g.p.tile, e1 = min(e0 + g.p.tile, g.nnz);
-    for (int e = e0 + threadIdx.x; e < e1; e += 4 * kPartThreads) {        // four loads in flight
+    const PartRange r = part_tile(g.p, g.nnz, tile);
+    const int32_t* const col = g.colidx + r.begin;
+    for (int i = threadIdx.x; i < r.len; i += 4 * kPartThreads) {          // four loads in flight
         int c[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = g.colidx[min(e + u * kPartThreads, e1 - 1)];
+        for (int u = 0; u < 4; ++u) c[u] = col[min(i + u * kPartThreads, r.len - 1)];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (e + u * kPartThreads < e1) atomicAdd(&cnt[c[u] >> g.p.shift], 1u);
+            if (i + u * kPartThreads < r.len) atomicAdd(&cnt[c[u] >> g.p.shift], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < g.p.nb_pad; i += kPartThreads) g.hist[(size_t)tile * g.p.nb_pad + i] = cnt[i];
@@ -301,16 +272,16 @@ __global__ __launch_bounds__(kPartThreads) void part_scatter_kernel(PartBatch b)
     const int nbp = g.p.nb_pad, shift = g.p.shift;
     for (int i = threadIdx.x; i < kPartWaves * nbp; i += kPartThreads) cnt[i] = 0u;
     __syncthreads();
-    const int per = g.p.tile / kPartWaves;
-    const int w0 = tile * g.p.tile + wave * per, w1 = min(w0 + per, g.nnz);
+    const PartRange r = part_tile_wave(g.p, g.nnz, tile, wave);
+    const int32_t* const col = g.colidx + r.begin;
     uint32_t* const mine = cnt + wave * nbp;
-    for (int e = w0 + lane; e < w1; e += 4 * 64) {
+    for (int i = lane; i < r.len; i += 4 * 64) {
         int c[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = g.colidx[min(e + u * 64, w1 - 1)];
+        for (int u = 0; u < 4; ++u) c[u] = col[min(i + u * 64, r.len - 1)];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (e + u * 64 < w1) atomicAdd(&mine[c[u] >> shift], 1u);
+            if (i + u * 64 < r.len) atomicAdd(&mine[c[u] >> shift], 1u);
     }
     __syncthreads();
     // first place of (bucket, wavefront): bucket start + what earlier workgroups and earlier wavefronts put there
@@ -339,15 +310,15 @@ __global__ __launch_bounds__(kPartThreads) void part_scatter_kernel(PartBatch b)
         }
     }
     __syncthreads();
-    if (w0 >= w1) return;
+    if (r.len <= 0) return;
     const int nbits = 32 - __builtin_clz(max(g.p.nb - 1, 1));
     const bool records = !g.count_only;
-    int row = records ? wave_row_of(g.rowptr, g.n_rows, w0) : 0;
-    int c = g.colidx[min(w0 + lane, w1 - 1)];
-    for (int s = w0; s < w1; s += 64) {
-        const int e = min(s + lane, w1 - 1);
-        const bool on = s + lane < w1;
-        const int c_next = g.colidx[min(e + 64, w1 - 1)];
+    int row = records ? wave_row_of(g.rowptr, g.n_rows, r.begin) : 0;
+    int c = col[min(lane, r.len - 1)];
+    for (int s = 0; s < r.len; s += 64) {
+        const int i_e = min(s + lane, r.len - 1), e = r.begin + i_e;
+        const bool on = s + lane < r.len;
+        const int c_next = col[min(i_e + 64, r.len - 1)];
         const uint32_t d = (uint32_t)c >> shift;
         const unsigned long long m = same_digit(d, nbits, on);
         const uint32_t at = mine[d];
@@ -388,18 +359,17 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
     if (threadIdx.x == 0) s_before = 0u;
     __syncthreads();
     const int begin = (int)s_begin, n = (int)g.totals[bucket];
-    const int per = ((n + kPartWaves - 1) / kPartWaves + 63) / 64 * 64;
-    const int w0 = min(wave * per, n), w1 = min(w0 + per, n);
+    const PartRange w = part_bucket_wave(n, wave);
     uint32_t* const mine = cnt + wave * sub;
-    const int32_t* key = g.key + begin;
+    const int32_t* key = g.key + begin + w.begin;
     uint32_t earlier = 0;                                   // records of the bucket in columns before this workgroup's
-    for (int i = w0 + lane; i < w1; i += 4 * 64) {
+    for (int i = lane; i < w.len; i += 4 * 64) {
         int c[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = key[min(i + u * 64, w1 - 1)] - first;
+        for (int u = 0; u < 4; ++u) c[u] = key[min(i + u * 64, w.len - 1)] - first;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (i + u * 64 < w1) {
+            if (i + u * 64 < w.len) {
                 if (c[u] >= 0 && c[u] < ncol) atomicAdd(&mine[c[u]], 1u);
                 earlier += c[u] < 0 ? 1u : 0u;
             }
@@ -444,11 +414,11 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
     }
     if (first + ncol == g.n_cols && threadIdx.x == 0) g.t_rowptr[g.n_cols] = g.nnz;
     __syncthreads();
-    const int2* rec = g.rec + begin;
-    for (int s = w0; s < w1; s += 64) {
-        const int i = min(s + lane, w1 - 1);
+    const int2* rec = g.rec + begin + w.begin;
+    for (int s = 0; s < w.len; s += 64) {
+        const int i = min(s + lane, w.len - 1);
         const int c = key[i] - first;
-        const bool on = s + lane < w1 && c >= 0 && c < ncol;
+        const bool on = s + lane < w.len && c >= 0 && c < ncol;
         const int2 r = rec[i];
         const uint32_t d = on ? (uint32_t)c : 0u;
         const unsigned long long m = same_digit(d, g.p.sub_shift, on);

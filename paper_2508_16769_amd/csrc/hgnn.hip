@@ -185,10 +185,10 @@ __global__ __launch_bounds__(256) void concat_csr_kernel(const int32_t* __restri
                                                          const float* __restrict__ vals, int n_rows, int nnz, int row_off,
                                                          int col_off, int nnz_off, int write_end, int32_t* __restrict__ o_rowptr,
                                                          int32_t* __restrict__ o_colidx, float* __restrict__ o_vals) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n_rows) o_rowptr[row_off + i] = rowptr[i] + nnz_off;
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < (uint32_t)n_rows) o_rowptr[row_off + i] = rowptr[i] + nnz_off;
     if (i == 0 && write_end) o_rowptr[row_off + n_rows] = nnz_off + nnz;
-    for (int e = i; e < nnz; e += gridDim.x * 256) {
+    for (uint32_t e = i; e < (uint32_t)nnz; e += gridDim.x * 256) {
         o_colidx[nnz_off + e] = colidx[e] + col_off;
         o_vals[nnz_off + e] = vals[e];
     }

@@ -546,11 +546,11 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
             DegreeK dkr = dk;
             if constexpr (ADAPT) dkr.k3 = dk.width(e1 - e0, k);
             const int per = (e1 - e0 + kWPB - 1) / kWPB;
-            const int w0 = min(e0 + wave * per, e1), w1 = min(w0 + per, e1);
-            for (int c0 = w0; c0 < w1; c0 += kCap) {
-                const int n = min(kCap, w1 - c0);
+            const int w0 = min(wave * per, e1 - e0), len = min(per, e1 - e0 - w0);      // lengths: sums may pass 2^31
+            for (int c0 = 0; c0 < len; c0 += kCap) {
+                const int n = min(kCap, len - c0);
                 lds_fence();
-                stage_chunk<false>(plan, src, RowSpan{c0, n, 0, 0}, 0, n);
+                stage_chunk<false>(plan, src, RowSpan{e0 + w0 + c0, n, 0, 0}, 0, n);
                 lds_fence();
                 Stream st{g, n, 0, g >= n ? 1 : 0};
                 fwd_run<KPL, EPI, true, ADAPT, RW>(st, plan, xs_vals, xs_idx, buf, Hblk, D, k, t, g, 0, 0, 0, vec_store, dkr);
@@ -1164,7 +1164,7 @@ int launch_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const 
 __global__ __launch_bounds__(256) void edge_class_kernel(const int32_t* __restrict__ t_colidx, int nnz,
                                                          const int32_t* __restrict__ a_rowptr, int t1, int t2,
                                                          uint8_t* __restrict__ out) {
-    for (int e = blockIdx.x * 256 + threadIdx.x; e < nnz; e += gridDim.x * 256) {
+    for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < (uint32_t)nnz; e += gridDim.x * 256) {
         const int i = t_colidx[e];
         const int deg = a_rowptr[i + 1] - a_rowptr[i];
         out[e] = (uint8_t)(deg <= t1 ? 0 : (deg <= t2 ? 1 : 2));

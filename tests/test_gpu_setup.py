@@ -54,3 +54,56 @@ def test_transpose_and_values_exact(M, N, E, law):
     assert np.array_equal(At.rowptr.cpu().numpy(), t_rp)
     assert np.array_equal(At.colidx.cpu().numpy(), t_ci)
     assert np.array_equal(At.vals.view(torch.int32).cpu().numpy(), np.argsort(ci, kind="stable"))
+
+
+def test_as_many_entries_as_accepted():
+    """2^31 - 1 entries, the most a relation may have: entry e sits in row e // d and column e % N, so every result is known
+    in closed form and compared in full, piece by piece."""
+    import torch
+    import paper_2508_16769_amd as P
+    E, N, d = 2 ** 31 - 1, 1_000_003, 21_475
+    M = -(-E // d)
+    say(f"setup M={M} N={N} E={E}")
+    dev, step = "cuda", 1 << 26
+    rp = torch.clamp(torch.arange(M + 1, dtype=torch.int64, device=dev) * d, max=E).to(torch.int32)
+    ci = torch.empty(E, dtype=torch.int32, device=dev)
+    ids = torch.empty(E, dtype=torch.int32, device=dev)
+    for s in range(0, E, step):
+        e = torch.arange(s, min(s + step, E), dtype=torch.int64, device=dev)
+        ci[s:s + step] = (e % N).to(torch.int32)
+        ids[s:s + step] = e.to(torch.int32)
+    vals = torch.empty(E, device=dev)
+
+    def check_values(mode, what):
+        say(what)
+        for s in range(0, E, step):
+            e = torch.arange(s, min(s + step, E), dtype=torch.int64, device=dev)
+            deg = torch.where(e // d == M - 1, E - d * (M - 1), d).to(torch.float64)
+            if mode == P.DR_NORM_MEAN:
+                want = 1.0 / deg
+            else:
+                want = 1.0 / torch.sqrt(deg * (E // N + (e % N < E % N).to(torch.int64)).to(torch.float64))
+            assert torch.equal(vals[s:s + step], want.to(torch.float32)), (what, s)
+
+    for mode in (P.DR_NORM_MEAN, P.DR_NORM_SYM):
+        ws = torch.empty(max(256, P.dr_csr_normalize_workspace_bytes(mode, M, N, E)), dtype=torch.uint8, device=dev)
+        vals.zero_()
+        P.dr_csr_normalize(mode, M, N, rp, ci, vals, ws)
+        check_values(mode, f"normalize {mode}")
+        del ws
+        vals.zero_()
+        P.dr_csr_normalize_noalloc(mode, M, N, rp, ci, vals)
+        check_values(mode, f"normalize_noalloc {mode}")
+    del vals
+    say("transpose")
+    At = P.device_transpose(P.Csr(M, N, rp, ci, ids.view(torch.float32)))
+    c = torch.arange(N + 1, dtype=torch.int64, device=dev)
+    start = c * (E // N) + torch.clamp(c, max=E % N)                      # the first E % N columns hold one entry more
+    assert torch.equal(At.rowptr.to(torch.int64), start)
+    got = At.vals.view(torch.int32)
+    for s in range(0, E, step):
+        at = torch.arange(s, min(s + step, E), dtype=torch.int64, device=dev)
+        col = torch.searchsorted(start, at, right=True) - 1
+        e = col + (at - start[col]) * N
+        assert torch.equal(got[s:s + step].to(torch.int64), e), s
+        assert torch.equal(At.colidx[s:s + step].to(torch.int64), e // d), s
