@@ -56,6 +56,41 @@ def test_transpose_and_values_exact(M, N, E, law):
     assert np.array_equal(At.vals.view(torch.int32).cpu().numpy(), np.argsort(ci, kind="stable"))
 
 
+def test_gaps_of_empty_rows_cost_little():
+    """Entries on either side of 2^26 empty rows, and entries a few hundred or some thousand empty rows apart: exact results,
+    and no wavefront walks a gap row by row (64 rows per 0.4 us would take this call 0.4 s; it takes well below 1 ms)."""
+    import torch
+    import paper_2508_16769_amd as P
+    M, N = (1 << 26) + 5000, 97
+    deg = torch.zeros(M, dtype=torch.int64)
+    deg[0], deg[1], deg[M - 1] = 40, 1, 700
+    deg[2:600:7] = 3
+    deg[1000:3000:260], deg[M - 5000:M - 100:331] = 2, 1              # just past the windows that are walked before a search
+    rp = torch.zeros(M + 1, dtype=torch.int64)
+    rp[1:] = torch.cumsum(deg, 0)
+    E = int(rp[-1])
+    say(f"setup gaps M={M} E={E}")
+    rows = torch.repeat_interleave(torch.arange(M), deg).numpy()
+    rng = np.random.default_rng(5)
+    ci = rng.integers(0, N, E).astype(np.int32)
+    d_rp, d_ci = rp.to(torch.int32).cuda(), torch.from_numpy(ci).cuda()
+    vals = torch.empty(E, device="cuda")
+    P.dr_csr_normalize(P.DR_NORM_MEAN, M, N, d_rp, d_ci, vals, None)
+    assert np.array_equal(vals.cpu().numpy(), (1.0 / deg.numpy()[rows]).astype(np.float32))
+    ids = torch.arange(E, dtype=torch.int32, device="cuda").view(torch.float32)
+    A = P.Csr(M, N, d_rp, d_ci, ids)
+    At = P.device_transpose(A)
+    order = np.argsort(ci, kind="stable")
+    assert np.array_equal(At.vals.view(torch.int32).cpu().numpy(), order)
+    assert np.array_equal(At.colidx.cpu().numpy(), rows[order])
+    start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
+    P.dr_csr_normalize(P.DR_NORM_MEAN, M, N, d_rp, d_ci, vals, None)
+    stop.record()
+    torch.cuda.synchronize()
+    assert start.elapsed_time(stop) < 50.0
+
+
 def test_as_many_entries_as_accepted():
     """2^31 - 1 entries, the most a relation may have: entry e sits in row e // d and column e % N, so every result is known
     in closed form and compared in full, piece by piece."""
