@@ -32,6 +32,8 @@ def _pattern(rng, M, N, E, law):
     (700, 4097, 4097, "skewed_cols"), (5000, 1, 3000, "uniform"), (5000, 333, 9000, "tail_rows"), (1, 90_000, 8193, "one_row"),
     (40_000, 65_537, 300_001, "skewed_cols"), (9_000, 2_000, 70_000, "one_col"), (100_000, 1_300_000, 2_100_000, "uniform"),
     (60_000, 2_200_001, 400_000, "skewed_cols"),
+    # the line between counting columns with atomics and by the partition
+    (90_000, 70_000, 1 << 19, "skewed_cols"), (90_000, 70_000, (1 << 19) + 1, "skewed_cols"), (60_000, 2_200_001, 600_000, "skewed_cols"),
 ])
 def test_transpose_and_values_exact(M, N, E, law):
     import torch
