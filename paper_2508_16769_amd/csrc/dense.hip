@@ -8,13 +8,14 @@
 //
 // Arithmetic.  Operands are fp32, the matrix cores' fp32 rate is 155 TFLOP/s (measured from registers) and was what bound
 // these kernels.  Each fp32 number is therefore written as the sum of three bf16 numbers, x = x1 + x2 + x3 (round to
-// nearest each time: 3 x 8 significant bits hold all 24, so the sum is exact), and a product is formed from six bf16
-// products, x1 y1 + x1 y2 + x2 y1 + x1 y3 + x2 y2 + x3 y1, each exact, all accumulated in fp32.  What is left out,
-// x2 y3 + x3 y2 + x3 y3, is below 2^-25 |x y|: half an ulp of one fp32 rounding, which an fp32 multiply-add commits for
-// every term anyway.  Measured against fp64 on N(0,1) data (2-norm): K = 128: 6.5e-8 with the small products in an
-// accumulator of their own, 1.6e-7 in one accumulator, 1.9e-7 for the fp32 instruction; K = 4096: 4.0e-7 / 1.0e-6 /
-// 1.1e-6.  Six bf16 products run at 250 .. 300 TFLOP/s of fp32 work, above what memory feeds these kernels, so they are
-// bound by HBM now: every operand is read once for all the products it takes part in.
+// nearest each time: 3 x 8 significant bits hold all 24, so from about 2^-108 upwards the sum is exact; smaller numbers lose
+// what lies below bf16's smallest, 2^-133), and a product is formed from six bf16 products, x1 y1 + x1 y2 + x2 y1 +
+// x1 y3 + x2 y2 + x3 y1, each exact.  What is left out, x2 y3 + x3 y2 + x3 y3, is below 2^-25 |x y|: half an ulp of one fp32
+// rounding, which an fp32 multiply-add commits for every term anyway.  The leading products x1 y1 and the five small ones
+// have accumulators of their own: the small sum is added once, with one rounding, and it can be left out where the leading
+// one is not finite, so that infinite and overflowing products are what they are in fp32 (with_small).
+// Six bf16 products run at 250 .. 300 TFLOP/s of fp32 work, above what memory feeds these kernels, so they are bound by HBM
+// now: every operand is read once for all the products it takes part in.
 //
 // Layouts.  The 16x16x32 instruction takes eight consecutive contraction indices per lane, as one 16-byte register
 // group.  LDS holds the operand tile in exactly those units, one plane per part.  The contraction index is permuted
@@ -49,14 +50,11 @@ template <int D> struct Tile {
     static_assert(BM * KU == THREADS && BM * TPR <= THREADS && 64 % TPR == 0, "one unit per thread");
 };
 
-// Three bf16 parts of eight numbers, two at a time (one conversion instruction makes two parts).
+// Three bf16 parts of half of each of eight numbers, two at a time (one conversion instruction makes two parts).
+// Half, so that no finite number rounds up to an infinite first part; kUnscale takes a sum of products back.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// The largest bf16 number.  The first two parts stay within it: a value that would round up to infinity keeps a finite
-// first part (the rest follows exactly), and an infinite value becomes max + max + infinity -- with an infinite first part
-// the remainder, and with it every product, would be not-a-number where the fp32 product is infinite.
-constexpr float kMaxBf16 = 3.3895313892515355e38f;
-__device__ __forceinline__ float finite_bf16(float v) { return __builtin_amdgcn_fmed3f(v, -kMaxBf16, kMaxBf16); }
+constexpr float kScale = 0.5f, kUnscale = 4.0f;
 struct Split8 { bf16x8 p[3]; };
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
@@ -67,10 +65,10 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
     uint32_t w[3][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float a = x[2 * j], b = x[2 * j + 1];
-        w[0][j] = pack2(finite_bf16(a), finite_bf16(b));
+        const float a = kScale * x[2 * j], b = kScale * x[2 * j + 1];
+        w[0][j] = pack2(a, b);
         const float ra = a - low_part(w[0][j]), rb = b - high_part(w[0][j]);
-        w[1][j] = pack2(finite_bf16(ra), finite_bf16(rb));
+        w[1][j] = pack2(ra, rb);
         w[2][j] = pack2(ra - low_part(w[1][j]), rb - high_part(w[1][j]));
     }
     Split8 s;
@@ -93,11 +91,12 @@ template <typename K> __device__ __forceinline__ Split8 select8(const Split8& s,
     }
     return r;
 }
-// the three parts of one number, `stride` bf16 numbers apart
+// the three parts of (half of) one number, `stride` bf16 numbers apart
 __device__ __forceinline__ void put_parts(__bf16* at, int stride, float v) {
-    const __bf16 a = (__bf16)finite_bf16(v);
+    v *= kScale;
+    const __bf16 a = (__bf16)v;
     const float r = v - (float)a;
-    const __bf16 b = (__bf16)finite_bf16(r);
+    const __bf16 b = (__bf16)r;
     at[0] = a;
     at[stride] = b;
     at[2 * stride] = (__bf16)(r - (float)b);
@@ -109,6 +108,17 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f3
 // hi += leading products, lo += the five small ones (smallest first), for two tiles of rows at a time: consecutive
 // instructions go to different accumulators
 struct Acc { f32x4 hi, lo; };
+// The sum of leading products and small ones.  An infinite or overflowing operand makes the leading sum infinite or
+// not-a-number as in fp32, but its remainder is not-a-number and its small products may be infinities of either sign: the
+// small sum must not decide then, and it is finite whenever the leading one is.
+__device__ __forceinline__ f32x4 with_small(const f32x4& hi, const f32x4& lo) {
+    constexpr float m = 3.4028234663852886e38f;
+    f32x4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = hi[r] + __builtin_amdgcn_fmed3f(lo[r], -m, m);     // (not-a-number: -m)
+    return v;
+}
+__device__ __forceinline__ f32x4 total(const Acc& c) { return kUnscale * with_small(c.hi, c.lo); }
 __device__ __forceinline__ void mfma6(const bf16x8 (&w)[3], const bf16x8 (&x)[2][3], Acc (&c)[2]) {
     constexpr int W[5] = {2, 0, 1, 1, 0}, X[5] = {0, 2, 1, 0, 1};
 #pragma unroll
@@ -118,15 +128,6 @@ __device__ __forceinline__ void mfma6(const bf16x8 (&w)[3], const bf16x8 (&x)[2]
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) c[rb].hi = mfma(w[0], x[rb][0], c[rb].hi);
 }
-// the same into one accumulator
-__device__ __forceinline__ void mfma6_one(const bf16x8 (&w)[3], const bf16x8 (&x)[2][3], f32x4 (&c)[2]) {
-    constexpr int W[6] = {2, 0, 1, 1, 0, 0}, X[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) c[rb] = mfma(w[W[i]], x[rb][X[i]], c[rb]);
-}
-
 // Row blocks are read and written through buffer descriptors: the base is the block's first row and the size ends with
 // the array, so rows past the end read as zero and are not written.  No access in the pipelines is conditional, which
 // lets the compiler count exactly how many may still be outstanding (a store under a branch makes every later wait for a
@@ -373,9 +374,9 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
                 const int at = (rg * 32 + rb * 16 + (lane & 15)) * D + 16 * nb + 4 * (lane >> 4);
-                f32x4 v = c1[rb].hi + c1[rb].lo;
+                f32x4 v = total(c1[rb]);
                 if constexpr (CELL) {             // mask = [near >= pinned]
-                    const f32x4 p = c2[rb].hi + c2[rb].lo;
+                    const f32x4 p = total(c2[rb]);
                     uint32_t m = 0;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
@@ -533,29 +534,37 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
-            Acc c1[2] = {}, c2[2] = {};
-            f32x4 cS[2] = {};                     // one accumulator: the registers do not hold more
+            // near (or the net's only branch) first, then pinned: the accumulators of both would not fit the registers
+            const int r0 = rg * 32 + (lane & 15), c0 = 16 * nb + 4 * (lane >> 4);
+            {
+                Acc c1[2] = {}, cS[2] = {};
 #pragma unroll
-            for (int s = 0; s < T::KS; ++s) {
-                bf16x8 x[2][3];
-                load_x<D>(buf, s, rg, lane, x);
-                mfma6(w1[s], x, c1);
-                mfma6_one(wS[s], x, cS);
-                if constexpr (CELL) {
+                for (int s = 0; s < T::KS; ++s) {
+                    bf16x8 x[2][3];
+                    load_x<D>(buf, s, rg, lane, x);
+                    mfma6(w1[s], x, c1);
+                    mfma6(wS[s], x, cS);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) {
+                    *reinterpret_cast<f32x4*>(sC + (r0 + rb * 16) * LDC + c0) = total(cS[rb]);
+                    store4(b1, ((r0 + rb * 16) * D + c0) * 4, total(c1[rb]));      // gathered next: these stay in the caches
+                }
+            }
+            if constexpr (CELL) {
+                Acc c2[2] = {};
+#pragma unroll
+                for (int s = 0; s < T::KS; ++s) {
+                    bf16x8 x[2][3];
                     load_x<D>(buf + T::OPER, s, rg, lane, x);
                     mfma6(w2[s], x, c2);
                 }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
-            const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
+                __builtin_amdgcn_sched_barrier(0);
+                const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
-                const int r = rg * 32 + rb * 16 + (lane & 15), c = 16 * nb + 4 * (lane >> 4);
-                *reinterpret_cast<f32x4*>(sC + r * LDC + c) = cS[rb];
-                // gathered next: these stay in the caches
-                store4(b1, (r * D + c) * 4, c1[rb].hi + c1[rb].lo);
-                if constexpr (CELL) store4(b2, (r * D + c) * 4, c2[rb].hi + c2[rb].lo);
+                for (int rb = 0; rb < 2; ++rb) store4(b2, ((r0 + rb * 16) * D + c0) * 4, total(c2[rb]));
             }
             finish_t0();
             if constexpr (!kFirst) stage_next();
@@ -727,9 +736,9 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             for (int p = 0; p < 3; ++p) aS[p] = buf[W::OPER + p * W::PLANE + (hrow >> 3) * D + hcol];
 #pragma unroll
             for (int j = 0; j < T::NB; ++j) {
-                // The five small products of this chunk are summed from zero and added with one rounding: inside the matrix
-                // unit they would be cut off below the running sum, always downwards, which over a million rows adds up (a
-                // 3e-6 error on random gradients, against 1e-6 for the fp32 instruction).
+                // The products of this chunk are summed from zero, leading and small ones apart, and added to the running sum
+                // with one rounding: inside the matrix unit they would be cut off below it, always downwards, which over
+                // many chunks adds up.
                 constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
                 const int ub = (hrow >> 3) * D + 16 * j + (lane & 15);
                 f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};
@@ -741,10 +750,9 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
                     lo0 = mfma(b[BW[i]], a1.p[AW[i]], lo0);
                     lo1 = mfma(b[BW[i]], aS[AW[i]], lo1);
                 }
-                acc[0][j] = mfma(b[0], a1.p[0], acc[0][j]);
-                acc[1][j] = mfma(b[0], aS[0], acc[1][j]);
-                acc[0][j] += lo0;
-                acc[1][j] += lo1;
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                acc[0][j] += with_small(mfma(b[0], a1.p[0], zero), lo0);
+                acc[1][j] += with_small(mfma(b[0], aS[0], zero), lo1);
                 asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]));       // added here: the compiler would keep all sums to the end of the loop
                 __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
                 if constexpr (CELL) {
@@ -756,8 +764,7 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
                     lo0 = mfma(b[0], a2.p[2], lo0);
                     lo1 = mfma(b[0], a2.p[1], lo1);
                     lo0 = mfma(b[1], a2.p[1], lo0);
-                    acc[2][j] = mfma(b[0], a2.p[0], acc[2][j]);
-                    acc[2][j] += lo0 + lo1;
+                    acc[2][j] += with_small(mfma(b[0], a2.p[0], zero), lo0 + lo1);
                     asm volatile("" : "+v"(acc[2][j]));
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -822,7 +829,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs 
         for (int w = 1; w < kRedWaves; ++w) t += part[w][lane];
         float* o = g.dW[prod] + at;                      // weight gradients need not be 16-byte aligned
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = t[r];
+        for (int r = 0; r < 4; ++r) o[r] = kUnscale * t[r];
     }
 }
 

@@ -127,3 +127,49 @@ def test_ends_of_the_range(D):
     plain = [c for c in range(D) if c not in (2, 3, 4)]
     assert np.array_equal(got["self_pins"][5, plain], dw[5, plain]) and np.isinf(dw[5, plain]).all()
     assert np.isinf(got["Y_cell"][0]).any() and np.isfinite(got["Y_cell"][1:]).all()
+
+
+def _as_fp32(got, want, what):
+    """Single products: infinite where the fp32 product is, with its sign, and close to it elsewhere (a product off the exact
+    one by 2^-24, in sums that add zeros only)."""
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf].astype(np.float64)), (what, got[inf][:8], want[inf][:8])
+    w = want[~inf].astype(np.float64)
+    assert np.all(np.abs(got[~inf] - w) <= 2.0 ** -22 * np.abs(w)), what
+    assert inf.any() and (~inf).any()
+
+
+@pytest.mark.parametrize("D", [32, 64, 96, 128])
+def test_overflow_as_in_fp32(D):
+    """Products with large factors on either side: an infinite or overflowing product is an infinity of the right sign whatever
+    the other factor's lower parts are (their products with the large factor overflow too, to either side), and a product
+    just below the largest number is finite."""
+    say(f"dense overflow D={D}")
+    rng = np.random.default_rng(100 + D)
+
+    def factors(*s):
+        x = np.exp2(rng.uniform(-3, 12, s)) * rng.choice([-1.0, 1.0], s)
+        x[..., 0], x[..., 1], x[..., 2], x[..., 3] = 1.999, 998.5, -514.9, 1002.5
+        return x.astype(np.float32)
+    W = {n: factors(D, D) for n in P.WEIGHT_NAMES}
+    big = np.array([np.inf, -np.inf, 3e38, -np.finfo(np.float32).max, 1.7e38, -1.7e38, 3.39e38, 1e36, -1e30, 1.0, -1e-30], np.float32)
+    # one large entry per row: every output is one product
+    n = 4 * len(big) + 1
+    vals, at = np.resize(big, n), (np.arange(n) * 7) % D
+    X = np.zeros((n, D), np.float32)
+    X[np.arange(n), at] = vals
+    zero = np.zeros((n, D), np.float32)
+    got = _run(n, n, D, (D, D, D), rng, X, X, W, zero, X, edges=False)
+    with np.errstate(over="ignore"):
+        _as_fp32(got["Y_net"], vals[:, None] * W["self_pins"][at], "Y_net")
+        near = vals[:, None] * W["self_near"][at]
+        _as_fp32(got["Y_cell"], np.maximum(near, np.float32(0)), "Y_cell")               # the pinned branch is zero
+        _as_fp32(got["dX_net"], vals[:, None] * W["self_pins"].T[at], "dX_net")
+        # one row of large entries: every entry of the weight gradient is one product
+        for row in (0, n // 2, n - 1):
+            Xr, dY = np.zeros((n, D), np.float32), np.zeros((n, D), np.float32)
+            Xr[row], dY[row] = np.resize(big, D), factors(D)
+            got = _run(n, n, D, (D, D, D), rng, zero, Xr, W, zero, dY, edges=False)
+            _as_fp32(got["self_pins"], Xr[row][:, None] * dY[row][None, :], "dW large entries")
+            got = _run(n, n, D, (D, D, D), rng, zero, dY, W, zero, Xr, edges=False)
+            _as_fp32(got["self_pins"], dY[row][:, None] * Xr[row][None, :], "dW large gradients")
