@@ -798,11 +798,13 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void wgrad_partial_kernel(Wgra
 }
 
 // dW[i] = sum over a side's partials in a fixed order: wavefront w of the workgroup sums partials w, w + 16, ... of 64 x 4
-// consecutive entries, then the 16 sums are added in order.  One launch for all products of all sides and graphs.
+// consecutive entries, then the 16 sums are added in order.  In 64 bits: up to 256 partials of nearly equal size lose as much
+// in 32-bit sums as everything before.  One launch for all products of all sides and graphs.
 constexpr int kRedWaves = 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int D>
 __global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs a) {
-    __shared__ f32x4 part[kRedWaves][64];
+    __shared__ f64x4 part[kRedWaves][64];
     constexpr int kBlocks = D * D / 256;                 // workgroups per product
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int job = blockIdx.x / kBlocks, q = job / 3, prod = job % 3;
@@ -811,25 +813,25 @@ __global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs 
     const int n = g.wgs * WTile<D>::KG;
     const int at = (blockIdx.x % kBlocks) * 256 + 4 * lane;
     const float* src = g.scratch + (size_t)prod * n * D * D + at;
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    f64x4 s = {0., 0., 0., 0.};
     int b = wave;
     for (; b + 3 * kRedWaves < n; b += 4 * kRedWaves) {  // four loads in flight
         f32x4 v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(src + (size_t)(b + u * kRedWaves) * D * D);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s += v[u];
+        for (int u = 0; u < 4; ++u) s += __builtin_convertvector(v[u], f64x4);
     }
-    for (; b < n; b += kRedWaves) s += *reinterpret_cast<const f32x4*>(src + (size_t)b * D * D);
+    for (; b < n; b += kRedWaves) s += __builtin_convertvector(*reinterpret_cast<const f32x4*>(src + (size_t)b * D * D), f64x4);
     part[wave][lane] = s;
     __syncthreads();
     if (wave == 0) {
-        f32x4 t = part[0][lane];
+        f64x4 t = part[0][lane];
 #pragma unroll
         for (int w = 1; w < kRedWaves; ++w) t += part[w][lane];
         float* o = g.dW[prod] + at;                      // weight gradients need not be 16-byte aligned
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = kUnscale * t[r];
+        for (int r = 0; r < 4; ++r) o[r] = (float)((double)kUnscale * t[r]);
     }
 }
 

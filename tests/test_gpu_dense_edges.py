@@ -14,11 +14,11 @@ pytestmark = pytest.mark.gpu
 WIDTHS = [(32, 4, 20, 32), (64, 16, 16, 16), (64, 40, 8, 64), (96, 33, 12, 33), (128, 32, 32, 32), (128, 70, 128, 16)]
 
 
-def _run(Nc, Nn, D, ks, rng, X_cell, X_net, W, dY_cell, dY_net, edges=True):
+def _run(Nc, Nn, D, ks, rng, X_cell, X_net, W, dY_cell, dY_net, edges=True, dup=False):
     """A layer pass; returns everything as fp64 numpy, with H and the selections the dense products read.  Without edges the
     products see the inputs alone."""
     deg = 3 if edges else 0
-    near, pins, pinned = random_csr(rng, Nc, Nc, deg), random_csr(rng, Nn, Nc, deg), random_csr(rng, Nc, Nn, deg)
+    near, pins, pinned = (random_csr(rng, m, n, deg, dup=dup) for m, n in ((Nc, Nc), (Nn, Nc), (Nc, Nn)))
     rel = [P.Csr(m, n, *(dev(a) for a in r)) for m, n, r in ((Nc, Nc, near), (Nn, Nc, pins), (Nc, Nn, pinned))]
     layer = P.HeteroConv(*rel, D, per_relation=ks)
     saved = layer.alloc_saved()
@@ -173,3 +173,40 @@ def test_overflow_as_in_fp32(D):
             _as_fp32(got["self_pins"], Xr[row][:, None] * dY[row][None, :], "dW large entries")
             got = _run(n, n, D, (D, D, D), rng, zero, dY, W, zero, Xr, edges=False)
             _as_fp32(got["self_pins"], dY[row][:, None] * Xr[row][None, :], "dW large gradients")
+
+
+@pytest.mark.parametrize("D,k", [(32, 32), (64, 40), (96, 24), (128, 128)])
+@pytest.mark.parametrize("rows,sign", [(700, "both"), (700, "one"), (33_331, "one")])
+def test_as_accurate_as_fp32(D, k, rows, sign):
+    """2-norm errors against fp64 at which a 24-bit product stands out from one that has lost a part.  The products of a split
+    that are smallest, x1 y3, x2 y2 and x3 y1, are 2^-18 of the whole each (rms); without one of them, or with one taken from the
+    wrong place, the error is above 2e-6.  A rounding to fp32 costs 2^-25.1 = 2.8e-8 (rms); a projection adds up to 16 partial
+    sums of up to 256 terms, each rounded once: 2^-23 = 1.2e-7 leaves a factor of two over what was measured, 4e-8 .. 7e-8.
+    Weight gradients on data of one sign add some 130 partial sums per workgroup and round the total once; sums that are cut
+    off instead of rounded, or added up in 32 bits at the end, come to 6.5e-8 .. 7.4e-8 there, these to 3e-8."""
+    say(f"dense accuracy rows={rows} D={D} {sign}")
+    rng = np.random.default_rng(D + rows)
+
+    def f(*s):
+        x = rng.standard_normal(s).astype(np.float32)
+        return np.abs(x) if sign == "one" else x
+    W = {n: (f(D, D) / np.sqrt(D)).astype(np.float32) for n in P.WEIGHT_NAMES}
+    X_cell, X_net, dYc, dYn = f(rows, D), f(rows, D), f(rows, D), f(rows, D)
+    got, *_ = _run(rows, rows, D, (k, k, k), rng, X_cell, X_net, W, dYc, dYn, dup=True)
+    alone = _run(rows, rows, D, (D, D, D), rng, X_cell, X_net, W, dYc, dYn, edges=False, dup=True)      # dX: the self terms and nothing else
+    W = {n: w.astype(np.float64) for n, w in W.items()}
+    mask = got["mask"] == 1
+    dZn, dZq, dYn = np.where(mask, dYc, 0.0).astype(np.float64), np.where(mask, 0.0, dYc).astype(np.float64), dYn.astype(np.float64)
+    pairs = dict(
+        Y_cell=(got["Y_cell"], np.where(mask, got["Xs_cell"] @ W["self_near"] + got["H_near"] @ W["neigh_near"], got["H_pinned"] @ W["pinned"])),
+        Y_net=(got["Y_net"], got["Xs_self"] @ W["self_pins"] + got["H_pins"] @ W["neigh_pins"]),
+        dX_net=(alone["dX_net"], dYn @ W["self_pins"].T),
+        dX_cell=(alone["dX_cell"], np.where(alone["mask"] == 1, dYc, 0.0).astype(np.float64) @ W["self_near"].T))
+    for n, (have, want) in pairs.items():
+        err = np.linalg.norm(have - want) / np.linalg.norm(want)
+        assert err <= 2.0 ** -23, (n, err)
+    for n, A, B in (("self_near", "Xs_cell", dZn), ("neigh_near", "H_near", dZn), ("pinned", "H_pinned", dZq),
+                    ("self_pins", "Xs_self", dYn), ("neigh_pins", "H_pins", dYn)):
+        want = got[A].T @ B
+        err = np.linalg.norm(got[n] - want) / np.linalg.norm(want)
+        assert err <= (2.0 ** -24 if sign == "one" else 2.0 ** -23), (n, err)
