@@ -3,7 +3,6 @@
 #include "dr_internal.h"
 #include "partition_shape.h"
 
-#include <atomic>
 #include <mutex>
 
 namespace drc {
@@ -503,12 +502,14 @@ static int launch_partition(PartBatch& b, hipStream_t s) {
     }
     if (b.n == 0) return DR_OK;
     const size_t lds3 = 4 * (size_t)kPartWaves * nbp, lds4 = 4 * (size_t)kPartWaves * sub;
-    static std::atomic<bool> configured{false};
-    if (!configured.load(std::memory_order_acquire)) {      // counters of kMaxSub columns and the static words pass 64 KB
-        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    4 * kPartWaves * kMaxSub));
-        configured.store(true, std::memory_order_release);
-    }
+    static PerDevice raised;
+    int dev = 0, lds_max = 0;
+    DRC_HIP(hipGetDevice(&dev));
+    DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // counters of kMaxSub columns and the static words pass 64 KB
+        *n = 4 * kPartWaves * kMaxSub;
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, *n));
+        return DR_OK;
+    }));
     hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)tiles), dim3(kPartThreads), 0, s, b);
     hipLaunchKernelGGL(part_scan_kernel, dim3((unsigned)scans), dim3(1024), 0, s, b);
     hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);

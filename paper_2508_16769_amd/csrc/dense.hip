@@ -29,8 +29,6 @@
 // (With both halves in step and one LDS buffer a 1.2 M-row forward took 0.72 ms.)
 #include "dr_internal.h"
 
-#include <atomic>
-
 namespace drc {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -838,32 +836,18 @@ __global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs 
 // ---------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------
-static int cu_count(int* out) {
-    static std::atomic<int> cached{0};
-    int n = cached.load(std::memory_order_acquire);
-    if (!n) {
-        int dev = 0;
-        DRC_HIP(hipGetDevice(&dev));
-        DRC_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
-        cached.store(n, std::memory_order_release);
-    }
-    *out = n;
-    return DR_OK;
-}
-
-// raises a kernel's LDS limit once and returns how many of its workgroups fit the chip
-template <typename K> static int resident(K kernel, int threads, size_t lds, std::atomic<int>& cache, int* out) {
-    int n = cache.load(std::memory_order_acquire);
-    if (!n) {                                          // concurrent first calls repeat the query: same answer
+// raises a kernel's LDS limit, once per device, and returns how many of its workgroups fit the chip
+template <typename K> static int resident(K kernel, int threads, size_t lds, PerDevice& cache, int* out) {
+    int dev = 0;
+    DRC_HIP(hipGetDevice(&dev));
+    return cache.get(dev, out, [&](int* n) -> int {
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         int per_cu = 0, cus = 0;
         DRC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
-        DRC_TRY(cu_count(&cus));
-        n = (per_cu < 1 ? 1 : per_cu) * cus;
-        cache.store(n, std::memory_order_release);
-    }
-    *out = n;
-    return DR_OK;
+        DRC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        *n = (per_cu < 1 ? 1 : per_cu) * cus;
+        return DR_OK;
+    });
 }
 
 // Workgroups of the two sides: in proportion to their work (three and two products per row), all of them resident.
@@ -882,7 +866,7 @@ static void share(int64_t cell_work, int64_t net_work, int cell_tiles, int net_t
 
 template <int D, int CP> static int launch_proj_fwd_cp(ProjFwdArgs& a, hipStream_t s) {
     using T = Tile<D>;
-    static std::atomic<int> cache{0};
+    static PerDevice cache;
     constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * T::OPER;
     int res = 0;
     DRC_TRY(resident(&proj_kernel<D, CP>, T::THREADS, lds, cache, &res));
@@ -929,7 +913,7 @@ int launch_proj_fwd(const ProjFwdJob* jobs, int n, const dr_heteroconv_weights& 
 
 template <int D> static int launch_proj_bwd_d(ProjBwdArgs& a, hipStream_t s) {
     using T = Tile<D>;
-    static std::atomic<int> cache{0};
+    static PerDevice cache;
     constexpr size_t lds = sizeof(bf16x8) * 4 * T::OPER + sizeof(float) * 2 * T::BM * (D + 4);
     int res = 0;
     DRC_TRY(resident(&dproj_kernel<D>, T::THREADS, lds, cache, &res));
@@ -989,7 +973,7 @@ size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
 
 template <int D> static int launch_wgrad_d(WgradArgs& a, hipStream_t s) {
     using T = Tile<D>;
-    static std::atomic<int> cache{0};
+    static PerDevice cache;
     constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * WTile<D>::OPER;
     int res = 0;
     DRC_TRY(resident(&wgrad_partial_kernel<D>, T::THREADS, lds, cache, &res));

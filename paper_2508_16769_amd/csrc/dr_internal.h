@@ -9,6 +9,7 @@
 #include <cstdio>
 
 #include "dr_circuitgnn.h"
+#include "per_device.h"
 
 namespace drc {
 

@@ -278,12 +278,15 @@ template <int CW, int KS, int NS>
 static int launch_staged(const dr_spmm_plan* p, const float* dH, const uint16_t* xs_idx, int k, float* dXs, int accumulate,
                          hipStream_t s) {
     const size_t lds = staged_lds_bytes(p->cw, p->ccap, p->ecap);
-    static bool raised = false;      // per instantiation
-    if (!raised) {
+    static PerDevice raised;         // per instantiation; every plan of one instantiation needs the same LDS
+    int dev = 0, lds_max = 0;
+    DRC_HIP(hipGetDevice(&dev));
+    DRC_TRY(raised.get(dev, &lds_max, [&](int* n) -> int {
+        *n = (int)lds;
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&spmm_bwd_staged_kernel<CW, KS, NS>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        raised = true;
-    }
+        return DR_OK;
+    }));
     // one persistent workgroup per compute unit, a multiple of the XCD count
     int n_wg = std::min(p->n_cu, p->n_tiles);
     n_wg = (n_wg + kNumXcd - 1) / kNumXcd * kNumXcd;
