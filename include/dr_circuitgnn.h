@@ -285,7 +285,9 @@ int heteroconv_fwd(dr_heteroconv* ctx, const float* X_cell, const float* X_net,
 /*
  * Backward of one layer.  Inputs dY_cell[Nc,D], dY_net[Nn,D], the weights and what fwd saved.  Outputs
  * dX_cell[Nc,D] and dX_net[Nn,D] (dense; exactly zero outside the saved top-k positions) and the five
- * weight gradients.  Same stream semantics as heteroconv_fwd.
+ * weight gradients.  Same stream semantics as heteroconv_fwd.  A context has one scratch for all its backward passes: a pass
+ * on another stream than the last one's waits for that one (the first time on the host, from then on on the device; a
+ * captured pass is ordered by the graph it becomes part of).
  */
 int heteroconv_bwd(dr_heteroconv* ctx, const float* dY_cell, const float* dY_net,
                    const dr_heteroconv_weights* W, const dr_heteroconv_saved* saved,

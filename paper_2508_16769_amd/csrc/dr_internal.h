@@ -178,6 +178,9 @@ struct LayerBwd {
     dr_heteroconv_wgrads dW;
 };
 int heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt);
+// Where a context's last backward pass is: its scratch is used on one stream at a time, and a pass on another one waits.
+void heteroconv_ordered_on(dr_heteroconv* c, hipStream_t s);   // whatever it enqueued comes before what follows on s
+void heteroconv_hand_over(dr_heteroconv* c, hipStream_t from, hipStream_t to);   // `to` has just been made to wait for `from`
 int heteroconv_create_widths(dr_heteroconv** ctx, const dr_csr* near, const dr_csr* pins, const dr_csr* pinned, int32_t D,
                              int32_t k_near, int32_t k_pins, int32_t k_self, int32_t k_pinned);
 

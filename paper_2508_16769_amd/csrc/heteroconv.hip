@@ -49,6 +49,13 @@ struct dr_heteroconv {
     float* G_pins;      // [Nc,k_pins]   pins piece, only where it needs a buffer of its own
     float* G_pinned;    // [Nn,k_pinned] pinned piece, likewise
     void* wg_scratch[2];   // cells, nets
+    // The scratch above is one for all backward passes of a context: a pass on another stream than the last one's waits for it.
+    // The first change of streams waits on the host; from then on every pass records `end`, and a change waits on the device.
+    // (A context that stays on one stream does without the event: it is a packet of its own for the GPU, 3 us of a 70 us layer.
+    // Recording it later, when the stream changes, would use a stream that its owner may have destroyed since.)
+    hipStream_t last_stream;
+    bool has_last, many_streams, end_recorded;
+    hipEvent_t end;
     int device;
     int overlap;        // DR_OVERLAP_*: whether the relations of a step share a launch
     dr_spmm_plan* near_plan;   // transposed `near` with its dH rows staged in LDS tile by tile (heteroconv_set_cell_order), or null
@@ -82,6 +89,7 @@ int dev_alloc(dr_heteroconv* c, void** p, size_t bytes) {
 void release(dr_heteroconv* c) {
     if (!c) return;
     spmm_plan_destroy(c->near_plan);
+    if (c->end) (void)hipEventDestroy(c->end);
     for (int i = 0; i < c->n_owned; ++i) (void)hipFree(c->owned[i]);
     if (c->timed) {
         for (TimedLaunch& t : *c->timed) { if (!t.start_shared) (void)hipEventDestroy(t.start); (void)hipEventDestroy(t.stop); }
@@ -161,6 +169,7 @@ int drc::heteroconv_create_capacity(dr_heteroconv** ctx, int64_t Nc, int64_t Nn,
 
     int rc = DR_OK;
     auto bail = [&](int code) { release(c); return code; };
+    if (hipEventCreateWithFlags(&c->end, hipEventDisableTiming) != hipSuccess) return bail(hip_fail(hipGetLastError(), "hipEventCreate"));
     if (hipGetDevice(&c->device) != hipSuccess) return bail(hip_fail(hipGetLastError(), "hipGetDevice"));
 
     // buffers of the transposed adjacencies: A^T of relation i has as many rows as A has columns
@@ -540,7 +549,7 @@ int drc::heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weight
     return DR_OK;
 }
 
-int drc::heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt) {
+static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt) {
     // opt.skip_dx: only the weight gradients are wanted (first layer of a model: nobody reads the gradient of the
     // input features), so the projections to dH, the transposed SpMMs and the dX write-outs are not launched.
     // opt.dy_net_zero: dY_net holds zeros (last layer of a model whose loss reads the cells only): everything it
@@ -652,5 +661,42 @@ int drc::heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weigh
     if (n_first) { ScopedTiming tm(c, kBwdNear, s); DRC_TRY(launch_spmm_bwds(first, n_first, D, s)); }
     if (n_then) { ScopedTiming tm(c, kBwdPins, s); DRC_TRY(launch_spmm_bwds(then, n_then, D, s)); }
     { ScopedTiming tm(c, dj[0].At ? kBwdNearPins : kBwdPins, s); DRC_TRY(launch_spmm_dense(&dj[0], dj[1].At ? 1 : 2, D, s)); }
+    return DR_OK;
+}
+
+void drc::heteroconv_ordered_on(dr_heteroconv* c, hipStream_t s) {
+    c->last_stream = s;
+    c->has_last = true;
+}
+
+void drc::heteroconv_hand_over(dr_heteroconv* c, hipStream_t from, hipStream_t to) {
+    if (!c->has_last || c->last_stream == from) heteroconv_ordered_on(c, to);
+}
+
+int drc::heteroconv_backward(const LayerBwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, BackwardOptions opt) {
+    bool plain = true;
+    for (int i = 0; i < n; ++i) plain = plain && (!g[i].c || (g[i].c->has_last && g[i].c->last_stream == s && !g[i].c->many_streams));
+    if (plain) return backward_pass(g, n, W, s, opt);
+    // A captured pass is ordered by the graph it becomes part of: events of the world outside do not belong in it.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    DRC_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) return backward_pass(g, n, W, s, opt);
+    for (int i = 0; i < n; ++i) {
+        dr_heteroconv* const c = g[i].c;
+        if (!c) continue;
+        if (c->has_last && c->last_stream != s) {
+            if (c->end_recorded) DRC_HIP(hipStreamWaitEvent(s, c->end, 0));
+            else DRC_HIP(hipDeviceSynchronize());
+            c->many_streams = true;
+        }
+        heteroconv_ordered_on(c, s);
+        c->end_recorded = false;
+    }
+    DRC_TRY(backward_pass(g, n, W, s, opt));
+    for (int i = 0; i < n; ++i)
+        if (g[i].c->many_streams) {
+            DRC_HIP(hipEventRecord(g[i].c->end, s));
+            g[i].c->end_recorded = true;
+        }
     return DR_OK;
 }

@@ -614,7 +614,10 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
         GraphState* const g = &m->g[first[grp]];
         const int n = first[grp + 1] - first[grp];
         const hipStream_t s = forked ? g->stream : user;
-        if (forked) DRC_HIP(hipStreamWaitEvent(s, m->fork, 0));
+        if (forked) {
+            DRC_HIP(hipStreamWaitEvent(s, m->fork, 0));
+            for (int i = 0; i < n; ++i) heteroconv_hand_over(g[i].ctx, user, s);
+        }
         LayerFwd lf[kMaxGraphs];
         LayerBwd lb[kMaxGraphs];
         for (int i = 0; i < n; ++i) {
@@ -678,9 +681,11 @@ int hgnn_train_step(dr_hgnn* m, const float* const* X_cell, const float* const* 
         const int step_rc = m->pool->run(n_groups, enqueue_and_mark, &step_err);
         if (step_rc != DR_OK) {
             for (int i = 0; i < n_groups; ++i) (void)hipStreamWaitEvent(user, m->g[first[i]].done, 0);
+            for (auto& gs : m->g) heteroconv_ordered_on(gs.ctx, user);
             return fail(step_rc, "%s", step_err.c_str());
         }
         for (int i = 0; i < n_groups; ++i) DRC_HIP(hipStreamWaitEvent(user, m->g[first[i]].done, 0));
+        for (auto& gs : m->g) heteroconv_ordered_on(gs.ctx, user);      // the groups' streams go with the model
     }
 
     // ---- loss and parameter update, after every sub-graph has delivered its gradient ----
