@@ -3,7 +3,7 @@
 `profiles/` name the command that wrote them):
 
     python3 measure.py adaptive  ...   degree-adaptive K next to uniform K, per relation
-    python3 measure.py train     ...   the multi-layer training step: one stream per sub-graph against the stacked batch
+    python3 measure.py train     ...   the multi-layer training step: sub-graphs sharing launches against the stacked batch
     python3 measure.py pipeline  ...   host-side pipeline against the per-graph path
     python3 measure.py overlap   ...   relations side by side against one after the other: whole layer and the D-ReLU / DR-SpMM region
     python3 measure.py traffic   ...   rocprofv3 FETCH_SIZE / WRITE_SIZE runs of bench.py -> HBM bytes per kernel
@@ -119,8 +119,8 @@ median and the 90th percentile of the relation's in-degrees.  Prints a markdown 
 
 
 def mode_train(argv) -> int:
-    """Times the multi-layer training step on a batch of synthetic sub-graphs: one stream per sub-graph against the
-batch stacked into one block-diagonal graph.
+    """Times the multi-layer training step on a batch of synthetic sub-graphs: sub-graphs that share their launches
+against the batch stacked into one block-diagonal graph.
 
     python3 measure.py train [--workload subgraph] [--graphs 8] [--layers 3] [--steps 20] [--out table.md]
 
@@ -174,7 +174,7 @@ Prints a markdown table (wall-clock per step between device synchronisations, af
         model.hgnn_destroy()
         return dt, loss
 
-    rows = [("one stream and one enqueueing host thread per sub-graph (`hgnn_create`)", run(False, (Xc_s, Xn_s, tg_s))),
+    rows = [("sub-graphs sharing launches while they do not fill the chip (`hgnn_create`)", run(False, (Xc_s, Xn_s, tg_s))),
             ("stacked into one block-diagonal graph (`hgnn_create_batched`), inputs gathered each step", run(True, (Xc_s, Xn_s, tg_s))),
             ("stacked, inputs already behind one another in memory (read in place)", run(True, (Xc, Xn, tg)))]
     lines = [f"# Training step on {G} sub-graphs of workload `{args.workload}` ({L} layers, D = {D}, k = {k})", "",

@@ -2,7 +2,9 @@
 
 A scratch access is a vector-memory operation: the wavefront's wait for it also waits for every gather issued before
 it, which once serialized the ping-pong batches of the DR-SpMM kernels (their per-group record stream had been placed
-in scratch because one of its members was written on one side of a branch only)."""
+in scratch because one of its members was written on one side of a branch only).  The dense kernels at D = 128 fill the
+256 registers of two wavefronts per SIMD almost to the last; their pipelines count the operations that may be outstanding, which
+a spill would upset."""
 import re
 from concurrent.futures import ThreadPoolExecutor
 
@@ -10,8 +12,8 @@ from paper_2508_16769_amd import build
 
 
 def _report():
-    with ThreadPoolExecutor(max_workers=3) as pool:
-        parts = list(pool.map(build.kernel_resources, ("topk.hip", "spmm.hip", "staged.hip")))
+    with ThreadPoolExecutor(max_workers=4) as pool:
+        parts = list(pool.map(build.kernel_resources, ("topk.hip", "spmm.hip", "staged.hip", "dense.hip")))
     out = {}
     for p in parts:
         out.update(p)
@@ -33,7 +35,13 @@ def test_hot_kernels_use_no_scratch_memory():
         cw, ks = int(m.group(1)), int(m.group(2))
         if cw == 64 and ks <= 4:
             assert r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0, (name, r)
-    # the forward and backward kernels of the benchmark's width (k = 32) leave room for five wavefronts per SIMD or more
-    for name, r in spmm.items():
-        if "ILi4ELi2ELb0E" in name:
-            assert r["Occupancy"] >= 5, (name, r)
+    # the forward and backward kernels of the benchmark's width (k = 32) leave room for five wavefronts per SIMD or more:
+    # pairs per lane, batch depth, rows per wavefront (8 or 32), not adaptive; the backward compact or dense
+    k32 = {n: r for n, r in spmm.items() if re.search(r"spmm_(fwd|bwd)_kernelILi4ELi2ELi\d+ELb0E", n)}
+    assert len(k32) == 6, sorted(k32)
+    for name, r in k32.items():
+        assert r["Occupancy"] >= 5, (name, r)
+    dense = {n: r for n, r in rep.items() if re.search(r"\d(proj|dproj|wgrad_partial|wgrad_reduce)_kernelILi", n)}
+    assert len(dense) == 20, sorted(dense)           # four widths; the forward with two cache policies of its stores
+    for name, r in dense.items():
+        assert r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0 and r["Occupancy"] >= 2, (name, r)
