@@ -279,7 +279,7 @@ static_assert(sizeof(ProjFwdArgs) < 4096, "kernel arguments");
 
 // CP: cache policy of the stores.  A wavefront writes 64 bytes of a row of Y and 16 of the mask, others the rest of a line.
 // Through the L2 the pieces leave as one line; streamed, they leave one by one (1.2 M x 128 cells: 1.53 GB counted as written
-// for 0.77 GB).  What the L2 still holds at the end is written back before the next launch may start, so the stores are
+// for the 0.77 GB that leave through the L2).  What the L2 still holds at the end is written back before the next launch may start, so the stores are
 // streamed while all of Y would stay there (kL2Bytes, eight of 4 MB).  Through the L2 / streamed: layer of 1.2 M cells, D = 128
 // 6.14 / 6.22 ms, 250 000 cells 1.234 / 1.245, 60 000 cells, D = 64 0.206 / 0.203, 33 331 cells, D = 96 0.239 / 0.235.
 constexpr int64_t kL2Bytes = 32ll << 20;
@@ -400,10 +400,8 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
     else walk(no{});
 }
 
-template <int D> constexpr int waves_per_simd() { return 2; }
-
 template <int D, int CP>
-__global__ __launch_bounds__(Tile<D>::THREADS, waves_per_simd<D>()) void proj_kernel(ProjFwdArgs a) {
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void proj_kernel(ProjFwdArgs a) {
     extern __shared__ bf16x8 smem8[];
     const DRC_CONST ProjFwdArgs* const k = kernel_args<ProjFwdArgs>();
     if ((int)blockIdx.x < k->cell_wgs) proj_fwd_side<D, true, CP>(k, smem8, blockIdx.x, k->cell_wgs);
@@ -582,7 +580,7 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
 }
 
 template <int D>
-__global__ __launch_bounds__(Tile<D>::THREADS, waves_per_simd<D>()) void dproj_kernel(ProjBwdArgs a) {
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs a) {
     extern __shared__ bf16x8 smem8[];
     const DRC_CONST ProjBwdArgs* const k = kernel_args<ProjBwdArgs>();
     if ((int)blockIdx.x < k->cell_wgs) proj_bwd_side<D, true>(k, smem8, blockIdx.x, k->cell_wgs);

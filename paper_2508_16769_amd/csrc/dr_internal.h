@@ -156,7 +156,8 @@ struct ForwardOptions {
     bool relu_out = false;          // clamp Y_cell and Y_net at zero as they are written (the mask compares raw values)
     bool skip_net_output = false;   // Y_net (and H_pins) are not wanted: the pins module is not evaluated
 };
-// A layer pass over up to kMaxGraphs graphs that share the weights: every step is one launch for all of them.
+// A layer pass over up to kMaxGraphs graphs that share the weights: a step is one launch for all of them, or a few where their
+// relations are more than a launch takes (kMaxSegs: 16 graphs have 48 forward relations, three launches).
 struct LayerFwd {
     dr_heteroconv* c;
     const float *X_cell, *X_net;

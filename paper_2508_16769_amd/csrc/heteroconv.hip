@@ -5,7 +5,8 @@
 // gradients and their reduction, projection gradients, transposed DR-SpMM of a placed `near`, the other transposed DR-SpMMs
 // with the dense input gradients).  Three streams joined by events did the same with 24 launches and some 30 event
 // operations; a 2048-cell layer pass then took 0.21 ms, nearly all of it launch and event overhead.
-// Everything runs on the caller's stream, in order; the host never waits inside fwd / bwd.
+// Everything runs on the caller's stream, in order; the host does not wait inside fwd / bwd, except in the first backward pass
+// of a context that is called on another stream than the one before it (the scratch is the context's).
 #include "dr_internal.h"
 
 #include <new>

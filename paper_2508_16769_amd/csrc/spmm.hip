@@ -21,7 +21,7 @@
 //   * Gathers are issued in two ping-pong batches of a few edges per group: while one batch is being
 //     accumulated the other is in flight, and no load in the loop is conditional (exhausted lanes gather
 //     a valid dummy row), which lets the compiler wait on exactly the older batch.  The batch depth is
-//     chosen per k so that a wavefront stays within about 80 VGPRs and six wavefronts fit a SIMD: these
+//     chosen per k so that a wavefront stays within 80 to 96 VGPRs and five wavefronts fit a SIMD: these
 //     kernels wait on memory most of the time, and the number of wavefronts that can take turns matters
 //     more than the depth of one wavefront's own pipeline (measured: 4 -> 6 wavefronts per SIMD, -3 %
 //     of the whole layer step).
@@ -452,7 +452,7 @@ struct SpmmFwdSeg {              // one relation of a launch
 };
 struct SpmmFwdArgs { SpmmFwdSeg s[kMaxSegs]; int n, D; };
 
-// wavefronts per SIMD the registers are budgeted for (six fit the LDS as well)
+// wavefronts per SIMD the registers are budgeted for (at D = 128 five of them fit the LDS as well)
 constexpr int fwd_waves(int kpl, bool adapt) { return kpl == 16 || kpl == -8 ? 4 : (adapt || kpl < 0 || kpl > 1 ? 5 : 6); }
 
 template <int KPL, int EPI, int RW, bool ADAPT>
@@ -575,7 +575,11 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
 
 // Rows per wavefront: 32 fill the groups evenly (a group that finishes takes the next row); with few rows in all, 8 --
 // one per group -- put four times as many wavefronts on the chip and cut the serial chain of a wavefront to one row per
-// group.  The line: as long as 8 rows per wavefront still fit the chip at once (256 compute units x 24 wavefronts).
+// group.  The line is about where wavefronts of 8 rows stop fitting the chip at once (256 compute units x 20 to 24
+// wavefronts).  Measured at 40 000 rows, 8 / 32 rows per wavefront, us: D = 128, k = 32, 2 to 8 edges per row forward 15 / 17,
+// backward 21 / 26; 20 to 60 edges 51 / 101 and 105 / 114; rows of 1500 among them 39 / 100 and 55 / 98.  Where it does not
+// pay: a forward at D >= 256 or k = 128 with a few edges per row (D = 256, k = 32: 25 / 20, but 81 / 110 with 20 to 60 edges;
+// there is a row buffer per group to clear, whatever the row brings).  A line by what registers and LDS let reside was slower.
 static bool few_rows(int64_t rows) { return rows <= 8ll * 24 * 256; }
 
 static int fwd_kind(const SpmmFwdJob& j) {
