@@ -88,7 +88,8 @@ __global__ __launch_bounds__(256) void count_columns_kernel(const int32_t* __res
         if ((int)threadIdx.x + 256 * u >= left) continue;
         const int slot = c[u] & (kCountSlots - 1);
         const int32_t was = atomicCAS(&tag[slot], -1, c[u]);
-        atomicAdd(was == -1 || was == c[u] ? &cnt[slot] : &count[c[u]], 1);
+        if (was == -1 || was == c[u]) atomicAdd(&cnt[slot], 1);
+        else atomicAdd(&count[c[u]], 1);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kCountSlots; i += 256)
