@@ -27,12 +27,29 @@
 // the wavefronts of the first half split and stage the next tile and then multiply the current one, those of the second half
 // multiply first: on each SIMD the vector instructions of one wavefront run under the matrix instructions of the other.
 // (With both halves in step and one LDS buffer a 1.2 M-row forward took 0.72 ms.)
+//
+// What a tile costs (32 cells, D = 128; parts switched off one by one): staging alone and multiplying alone take about as long
+// as one another, and together little less than their sum.  A matrix instruction takes 16 clocks of the SIMD and keeps vector
+// instructions out for 8 of them; LDS reads come at 256 bytes a clock, writes at 80.  Forward projection of 250 000 cells and
+// 180 000 nets: 204 -> 191 us with fragments read ahead, conflict-free places in LDS and graph descriptors in registers;
+// global memory is no longer what it waits for (without any loads and stores 188).  Not kept: wavefronts with 32 columns and
+// all registers of a SIMD (241), and staging spread between the matrix instructions of the same wavefront (201).
 #include "dr_internal.h"
+
+#include <type_traits>
 
 namespace drc {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Keeps `base + constant` in that form: the compiler would merge the constant into known-zero bits of the base and then
+// no longer find it for the instruction's own offset field.  Inside a loop: what is computed from it is computed there and
+// does not hold a register over the multiply.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
 
 template <int D> struct Tile {
     static constexpr int NB = D / 16;                              // 16-column blocks = wavefronts side by side
@@ -43,10 +60,16 @@ template <int D> struct Tile {
     static constexpr int KU = D / 8;                               // 16-byte units per row and part
     static constexpr int KS = D / 32;                              // MFMA steps
     static constexpr int TPR = D == 128 ? 16 : (D == 32 ? 4 : 8);  // threads that share one CBSR row; a row never straddles wavefronts
-    static constexpr int PLANE = KU * (BM + 1);                    // units per part; the +1 spreads a row's units over the banks
+    static constexpr int PLANE = KU * BM + KU / 2;                 // units per part (unit_at)
     static constexpr int OPER = 3 * PLANE;                         // units per operand
     static_assert(BM * KU == THREADS && BM * TPR <= THREADS && 64 % TPR == 0, "one unit per thread");
 };
+
+// Place of a unit in its plane.  A 16-byte LDS read is served in groups of 16 lanes that mix the rows of two neighbouring
+// units: lanes 0-3, 12-15 and 20-27 of the first 32, and the rest (measured pair by pair), so those two units have to start
+// on the same bank; the units of one row, which a staging wavefront writes together, should not.  A 16-byte gap after every
+// second unit gives both.  (A gap after every unit made every read of a fragment a two-way conflict.)
+template <int D> __device__ __forceinline__ int unit_at(int unit, int row) { return unit * Tile<D>::BM + (unit >> 1) + row; }
 
 // Three bf16 parts of half of each of eight numbers, two at a time (one conversion instruction makes two parts).
 // Half, so that no finite number rounds up to an infinite first part; kUnscale takes a sum of products back.
@@ -109,22 +132,15 @@ struct Acc { f32x4 hi, lo; };
 // The sum of leading products and small ones.  An infinite or overflowing operand makes the leading sum infinite or
 // not-a-number as in fp32, but its remainder is not-a-number and its small products may be infinities of either sign: the
 // small sum must not decide then, and it is finite whenever the leading one is.
-__device__ __forceinline__ f32x4 with_small(const f32x4& hi, const f32x4& lo) {
-    constexpr float m = 3.4028234663852886e38f;
+constexpr float kFloatMax = 3.4028234663852886e38f;
+__device__ __forceinline__ f32x4 with_small(const f32x4& hi, const f32x4& lo, float m = kFloatMax) {
     f32x4 v;
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = hi[r] + __builtin_amdgcn_fmed3f(lo[r], -m, m);     // (not-a-number: -m)
     return v;
 }
-__device__ __forceinline__ f32x4 total(const Acc& c) { return kUnscale * with_small(c.hi, c.lo); }
-__device__ __forceinline__ void mfma6(const bf16x8 (&w)[3], const bf16x8 (&x)[2][3], Acc (&c)[2]) {
-    constexpr int W[5] = {2, 0, 1, 1, 0}, X[5] = {0, 2, 1, 0, 1};
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) c[rb].lo = mfma(w[W[i]], x[rb][X[i]], c[rb].lo);
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) c[rb].hi = mfma(w[0], x[rb][0], c[rb].hi);
+__device__ __forceinline__ f32x4 total(const Acc& c) {
+    return kUnscale * with_small(c.hi, c.lo, __builtin_bit_cast(float, opaque(__builtin_bit_cast(int, kFloatMax))));
 }
 // Row blocks are read and written through buffer descriptors: the base is the block's first row and the size ends with
 // the array, so rows past the end read as zero and are not written.  No access in the pipelines is conditional, which
@@ -141,12 +157,6 @@ __device__ __forceinline__ Buf block_view(const void* p, int rows_left, int row_
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), (short)0, rows * row_bytes, 0x00020000);
 }
-// Keeps `base + constant` in that form: the compiler would merge the constant into known-zero bits of the base and then
-// no longer find it for the instruction's own offset field.
-__device__ __forceinline__ int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
 __device__ __forceinline__ f32x4 load4(Buf b, int off) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, kNt)); }
 __device__ __forceinline__ float load1(Buf b, int off) { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt)); }
 __device__ __forceinline__ uint32_t load1u(Buf b, int off) { return __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, kNt); }
@@ -158,6 +168,12 @@ template <int CP = 0> __device__ __forceinline__ void store4(Buf b, int off, con
 // staging under `if (half)` the compiler has to assume that a wavefront may change sides from one trip to the next: the
 // waits in front of the staging and of the multiply then covered loads and stores that had only just been issued, and every
 // trip stood for a whole memory latency.
+template <int N, int I = 0, typename F> __device__ __forceinline__ void steps(F f) {       // f(0), ..., f(N - 1), each a constant
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        steps<N, I + 1>(f);
+    }
+}
 struct yes { static constexpr bool value = true; };
 struct no { static constexpr bool value = false; };
 // Stores that write nothing, behind the first prefetch of a loop in which stores come behind the prefetch: the number of
@@ -195,10 +211,27 @@ template <typename T> __device__ __forceinline__ const DRC_CONST T* kernel_args(
     return (const DRC_CONST T*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
-// The graph whose tiles hold tile `t` (tile0 of the graphs is increasing); q only moves forward.
-template <typename SEG> __device__ __forceinline__ void find_seg(const DRC_CONST SEG* s, int n, int t, int& q) {
-    while (q + 1 < n && t >= s[q + 1].tile0) ++q;
-}
+// The graph whose tiles hold tile `t` (tile0 of the graphs is increasing; t only grows).  Its descriptor is kept in scalar
+// registers and fetched when the graph changes: read anew for every tile, the chain of scalar loads, each waited for together
+// with all LDS traffic in flight, took longer than the arithmetic of the staging.
+template <typename SEG> struct Place {
+    SEG g;
+    int q, end;                   // graph, and the first tile past it
+    __device__ __forceinline__ void start(const DRC_CONST SEG* s, int n, int t) {
+        q = 0;
+        end = n > 1 ? s[1].tile0 : 0x7fffffff;
+        g = fetch(s);
+        seek(s, n, t);
+    }
+    __device__ __forceinline__ void seek(const DRC_CONST SEG* s, int n, int t) {
+        if (t < end) return;
+        do {
+            ++q;
+            end = q + 1 < n ? s[q + 1].tile0 : 0x7fffffff;
+        } while (t >= end);
+        g = fetch(s + q);
+    }
+};
 
 // CBSR rows -> operand tile.  Pairs ppart, ppart + TPR, ... of a row belong to thread (row, ppart); the first kPairs per
 // thread travel through registers, further ones (wide selections) are fetched when they are placed.
@@ -216,10 +249,12 @@ __device__ __forceinline__ void load_pairs(PairRegs& r, Buf vals, Buf idx, int k
     }
 }
 
-template <int D> __device__ __forceinline__ void put_pair(bf16x8* plane, int row, int col, float v) {
+// `on` false: goes to the gap behind the last unit
+template <int D> __device__ __forceinline__ void put_pair(bf16x8* plane, bool on, int row, int col, float v) {
     using T = Tile<D>;
     const int half = col >= D / 2 ? 1 : 0, c = col - half * (D / 2);
-    put_parts(reinterpret_cast<__bf16*>(plane + (c >> 2) * (T::BM + 1) + row) + (c & 3) + 4 * half, 8 * T::PLANE, v);
+    const int at = on ? unit_at<D>(c >> 2, row) : T::PLANE - 1;
+    put_parts(reinterpret_cast<__bf16*>(plane + at) + (c & 3) + 4 * half, 8 * T::PLANE, v);
 }
 
 // rows past the end hold zeros at column 0
@@ -227,32 +262,73 @@ template <int D>
 __device__ __forceinline__ void stage_cbsr(bf16x8* oper, const PairRegs& pr, const float* __restrict__ vals,
                                            const uint16_t* __restrict__ idx, int k, int rows_left, int row, int ppart) {
     using T = Tile<D>;
-    const bf16x8 z = {};
-    for (int u = ppart; u < T::KU * 3; u += T::TPR) oper[(u / T::KU) * T::PLANE + (u % T::KU) * (T::BM + 1) + row] = z;
+    ppart = opaque(ppart);
+    const int none = opaque(0);
+    struct Words { int w[4]; };
+    const bf16x8 z = __builtin_bit_cast(bf16x8, Words{none, none, none, none});
+    for (int u = ppart; u < T::KU * 3; u += T::TPR) oper[(u / T::KU) * T::PLANE + unit_at<D>(u % T::KU, row)] = z;
     // the threads of a row sit in one wavefront and LDS executes a wavefront's accesses in order
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int u = 0; u < kPairs; ++u)
-        put_pair<D>(oper, ppart + T::TPR * u < k ? row : T::BM, (int)pr.c[u], pr.v[u]);    // pairs past k go to the padding row
+        put_pair<D>(oper, ppart + T::TPR * u < k, row, (int)pr.c[u], pr.v[u]);
     if (k > T::TPR * kPairs && row < rows_left)
-        for (int t = ppart + T::TPR * kPairs; t < k; t += T::TPR) put_pair<D>(oper, row, idx[(size_t)row * k + t], vals[(size_t)row * k + t]);
+        for (int t = ppart + T::TPR * kPairs; t < k; t += T::TPR) put_pair<D>(oper, true, row, idx[(size_t)row * k + t], vals[(size_t)row * k + t]);
 }
 
 // dense unit -> operand tile
 template <int D> __device__ __forceinline__ void stage_unit(bf16x8* oper, int row, int unit, const Split8& s) {
     using T = Tile<D>;
 #pragma unroll
-    for (int p = 0; p < 3; ++p) oper[p * T::PLANE + unit * (T::BM + 1) + row] = s.p[p];
+    for (int p = 0; p < 3; ++p) oper[p * T::PLANE + unit_at<D>(unit, row)] = s.p[p];
 }
 
-template <int D> __device__ __forceinline__ void load_x(const bf16x8* oper, int s, int rg, int lane, bf16x8 (&x)[2][3]) {
-    using T = Tile<D>;
+// The activations' fragments of one step (32 rows, one contraction block): a part's registers are read again for the next step
+// as soon as its last product is issued, and the leading part, which is used last, may have two sets (SETS), so that LDS
+// latency passes under matrix instructions.  (Whole second sets would not fit the registers beside the weights.)
+template <int SETS> struct Frags { bf16x8 p0[SETS][2], p1[2], p2[2]; };
+template <int D> __device__ __forceinline__ void load_part(const bf16x8* oper, int part, int s, int rg, int lane, bf16x8 (&x)[2]) {
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
+        x[rb] = oper[part * Tile<D>::PLANE + unit_at<D>(4 * s + (lane >> 4), rg * 32 + rb * 16 + (lane & 15))];
+}
+// Step STEP's products with NW weights: w[i] the parts of a weight's fragment, c[i] its accumulators for two tiles of rows.
+// MORE: a step follows, whose fragments are at (next, s).
+template <int D, int STEP, bool MORE, int NW, int SETS>
+__device__ __forceinline__ void multiply(const bf16x8* const (&w)[NW], Acc (*const (&c)[NW])[2], Frags<SETS>& x, const bf16x8* next, int s,
+                                         int rg, int lane) {
+    constexpr int set = STEP % SETS;
+    if constexpr (MORE && SETS == 2) load_part<D>(next, 0, s, rg, lane, x.p0[set ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    const auto small = [&](int part, const bf16x8 (&f)[2]) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-            x[rb][p] = oper[p * T::PLANE + (4 * s + (lane >> 4)) * (T::BM + 1) + rg * 32 + rb * 16 + (lane & 15)];
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) (*c[i])[rb].lo = mfma(w[i][part], f[rb], (*c[i])[rb].lo);
+    };
+    small(0, x.p2);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (MORE) load_part<D>(next, 2, s, rg, lane, x.p2);
+    __builtin_amdgcn_sched_barrier(0);
+    small(1, x.p1);
+    small(0, x.p1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (MORE) load_part<D>(next, 1, s, rg, lane, x.p1);
+    __builtin_amdgcn_sched_barrier(0);
+    small(2, x.p0[set]);
+    small(1, x.p0[set]);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) (*c[i])[rb].hi = mfma(w[i][0], x.p0[set][rb], (*c[i])[rb].hi);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (MORE && SETS == 1) load_part<D>(next, 0, s, rg, lane, x.p0[0]);
+}
+template <int D, int SETS> __device__ __forceinline__ void first_frags(const bf16x8* oper, int rg, int lane, Frags<SETS>& x) {
+    load_part<D>(oper, 2, 0, rg, lane, x.p2);
+    load_part<D>(oper, 1, 0, rg, lane, x.p1);
+    load_part<D>(oper, 0, 0, rg, lane, x.p0[0]);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -270,6 +346,9 @@ struct ProjFwdSide {              // one graph's rows of one node type
     uint8_t* mask;
     int rows, k, tile0;
 };
+__device__ __forceinline__ ProjFwdSide fetch(const DRC_CONST ProjFwdSide* s) {
+    return ProjFwdSide{s->vals, s->H1, s->H2, s->idx, s->Y, s->mask, s->rows, s->k, s->tile0};
+}
 struct ProjFwdArgs {
     ProjFwdSide cell[kMaxGraphs], net[kMaxGraphs];
     const float *w_self_near, *w_neigh_near, *w_pinned, *w_self_pins, *w_neigh_pins;
@@ -287,9 +366,10 @@ template <int D, bool CELL, int CP>
 __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf16x8* smem, int wg, int n_wg) {
     using T = Tile<D>;
     const DRC_CONST ProjFwdSide* const segs = CELL ? a->cell : a->net;
-    const int tiles = CELL ? a->cell_tiles : a->net_tiles;
+    const int tiles = CELL ? a->cell_tiles : a->net_tiles, n = a->n;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = wave % T::NB, rg = wave / T::NB;
+    const bool relu = a->relu != 0;
     const int urow = tid / T::KU, unit = tid % T::KU;              // this thread's unit of a dense operand
     const int prow = tid / T::TPR, ppart = tid % T::TPR;           // past the tile (D = 96): reads nothing, writes nothing
     const bool pairs = wave * 64 < T::BM * T::TPR;                 // whole wavefronts
@@ -302,21 +382,21 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
     f32x4 h1[2], h2[2];
     PairRegs pr;
     const int uoff = opaque((urow * D + 4 * unit) * 4);                    // bytes from the first row of the tile
-    auto prefetch = [&](const DRC_CONST ProjFwdSide* g, int t) {             // past the last tile: reads nothing
-        const int base = (t - g->tile0) * T::BM, left = t < tiles ? g->rows - base : 0;
-        const Buf b1 = block_view(g->H1 + (size_t)base * D, left, D * 4);
+    auto prefetch = [&](const ProjFwdSide& g, int t) {             // past the last tile: reads nothing
+        const int base = (t - g.tile0) * T::BM, left = t < tiles ? g.rows - base : 0;
+        const Buf b1 = block_view(g.H1 + (size_t)base * D, left, D * 4);
         h1[0] = load4(b1, uoff);
         h1[1] = load4(b1, uoff + D * 2);
         if constexpr (CELL) {
-            const Buf b2 = block_view(g->H2 + (size_t)base * D, left, D * 4);
+            const Buf b2 = block_view(g.H2 + (size_t)base * D, left, D * 4);
             h2[0] = load4(b2, uoff);
             h2[1] = load4(b2, uoff + D * 2);
         }
-        load_pairs<T::TPR>(pr, block_view(g->vals + (size_t)base * g->k, left, g->k * 4), block_view(g->idx + (size_t)base * g->k, left, g->k * 2),
-                           g->k, prow, ppart);
+        load_pairs<T::TPR>(pr, block_view(g.vals + (size_t)base * g.k, left, g.k * 4), block_view(g.idx + (size_t)base * g.k, left, g.k * 2),
+                           g.k, prow, ppart);
     };
-    auto commit = [&](const DRC_CONST ProjFwdSide* g, int t, bf16x8* buf) {
-        const int base = (t - g->tile0) * T::BM;
+    auto commit = [&](const ProjFwdSide& g, int t, bf16x8* buf) {
+        const int base = (t - g.tile0) * T::BM;
         float x[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = h1[j >> 2][j & 3];
@@ -326,55 +406,63 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
             for (int j = 0; j < 8; ++j) x[j] = h2[j >> 2][j & 3];
             stage_unit<D>(buf + 2 * T::OPER, urow, unit, split8(x));
         }
-        if (pairs) stage_cbsr<D>(buf, pr, g->vals + (size_t)base * g->k, g->idx + (size_t)base * g->k, g->k, t < tiles ? g->rows - base : 0, prow, ppart);
+        if (pairs) stage_cbsr<D>(buf, pr, g.vals + (size_t)base * g.k, g.idx + (size_t)base * g.k, g.k, t < tiles ? g.rows - base : 0, prow, ppart);
     };
     if (wg >= tiles) return;
     const auto walk = [&](auto first) {
         constexpr bool kFirst = decltype(first)::value;
-        int t = wg, q = 0, q1, q2;                // graphs of tile t, of the next one and of the one after
-        find_seg(segs, a->n, t, q);
-        prefetch(segs + q, t);
-        commit(segs + q, t, smem);
-        q1 = q;
-        find_seg(segs, a->n, t + n_wg, q1);
-        prefetch(segs + q1, t + n_wg);
-        if constexpr (kFirst) pad_stores<CELL ? 4 : 2>(segs->Y);          // a tile's stores come behind its prefetch
+        int t = wg;
+        Place<ProjFwdSide> here, ahead;           // of tile t; of the next one, and in the loop of the one after
+        here.start(segs, n, t);
+        prefetch(here.g, t);
+        commit(here.g, t, smem);
+        ahead = here;
+        ahead.seek(segs, n, t + n_wg);
+        prefetch(ahead.g, t + n_wg);
+        if constexpr (kFirst) pad_stores<CELL ? 4 : 2>(here.g.Y);          // a tile's stores come behind its prefetch
         __syncthreads();
         for (int cur = 0;; cur ^= 1) {
-            const DRC_CONST ProjFwdSide* const g = segs + q;
-            const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+            const ProjFwdSide g = here.g, g1 = ahead.g;
+            const int base = (t - g.tile0) * T::BM, t1 = t + n_wg;
             bf16x8* const buf = smem + cur * 3 * T::OPER;
-            q2 = q1;
-            find_seg(segs, a->n, t1 + n_wg, q2);
+            here = ahead;
+            ahead.seek(segs, n, t1 + n_wg);
             auto stage_next = [&]() {
-                commit(segs + q1, t1, smem + (cur ^ 1) * 3 * T::OPER);
-                prefetch(segs + q2, t1 + n_wg);
+                commit(g1, t1, smem + (cur ^ 1) * 3 * T::OPER);
+                prefetch(ahead.g, t1 + n_wg);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
-            Acc c1[2] = {}, c2[2] = {};
+            // One operand after the other, so that the accumulators of near are down to its values when pinned begins: the
+            // registers then hold the fragments of the next step too, whose LDS reads run under this step's products.
+            Acc c[2] = {};
+            f32x4 near[2];
+            Frags<2> x;
+            constexpr int NS = (CELL ? 3 : 2) * T::KS;
+            first_frags<D>(buf, rg, lane, x);
+            steps<NS>([&](auto step) {
+                constexpr int i = decltype(step)::value, s = i % T::KS, o = i / T::KS;
+                const bf16x8* const next = buf + (i + 1) / T::KS * T::OPER;
+                const bf16x8* const w[1] = {o == 0 ? wS[s] : (o == 1 ? w1[s] : w2[s])};
+                Acc(*const acc[1])[2] = {&c};
+                multiply<D, i, i + 1 < NS>(w, acc, x, next, (i + 1) % T::KS, rg, lane);
+                if constexpr (CELL && i == 2 * T::KS - 1) {
 #pragma unroll
-            for (int s = 0; s < T::KS; ++s) {
-                bf16x8 x[2][3];
-                load_x<D>(buf, s, rg, lane, x);
-                mfma6(wS[s], x, c1);
-                load_x<D>(buf + T::OPER, s, rg, lane, x);
-                mfma6(w1[s], x, c1);
-                if constexpr (CELL) {
-                    load_x<D>(buf + 2 * T::OPER, s, rg, lane, x);
-                    mfma6(w2[s], x, c2);
+                    for (int rb = 0; rb < 2; ++rb) {
+                        near[rb] = total(c[rb]);
+                        c[rb] = Acc{};
+                    }
                 }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const Buf by = block_view(g->Y + (size_t)base * D, g->rows - base, D * 4);
-            const Buf bm = block_view(g->mask + (size_t)base * D, g->rows - base, D);
-            const bool relu = a->relu != 0;
+            });
+            const Buf by = block_view(g.Y + (size_t)base * D, g.rows - base, D * 4);
+            const Buf bm = block_view(g.mask + (size_t)base * D, g.rows - base, D);
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
-                const int at = (rg * 32 + rb * 16 + (lane & 15)) * D + 16 * nb + 4 * (lane >> 4);
-                f32x4 v = total(c1[rb]);
+                const int ln = opaque(lane), at = (rg * 32 + rb * 16 + (ln & 15)) * D + 16 * nb + 4 * (ln >> 4);
+                f32x4 v = total(c[rb]);
                 if constexpr (CELL) {             // mask = [near >= pinned]
-                    const f32x4 p = total(c2[rb]);
+                    const f32x4 p = v;
+                    v = near[rb];
                     uint32_t m = 0;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
@@ -392,8 +480,6 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
             if (t1 >= tiles) break;
             __syncthreads();
             t = t1;
-            q = q1;
-            q1 = q2;
         }
     };
     if (wave < T::WAVES / 2) walk(yes{});
@@ -425,6 +511,9 @@ struct ProjBwdSide {
     float* S;
     int rows, k, tile0;
 };
+__device__ __forceinline__ ProjBwdSide fetch(const DRC_CONST ProjBwdSide* s) {
+    return ProjBwdSide{s->dY, s->mask, s->dH1, s->dH2, s->idx, s->S, s->rows, s->k, s->tile0};
+}
 struct ProjBwdArgs {
     ProjBwdSide cell[kMaxGraphs], net[kMaxGraphs];
     const float *w_self_near, *w_neigh_near, *w_pinned, *w_self_pins, *w_neigh_pins;
@@ -437,7 +526,7 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
     using T = Tile<D>;
     constexpr int LDC = D + 4;
     const DRC_CONST ProjBwdSide* const segs = CELL ? a->cell : a->net;
-    const int tiles = CELL ? a->cell_tiles : a->net_tiles;
+    const int tiles = CELL ? a->cell_tiles : a->net_tiles, n = a->n;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = wave % T::NB, rg = wave / T::NB;
     const int urow = tid / T::KU, unit = tid % T::KU;
@@ -452,13 +541,13 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
     f32x4 y[2];
     uint32_t mk[2];
     const int uoff = opaque((urow * D + 4 * unit) * 4), moff = opaque(urow * D + 4 * unit);   // from the first row of the tile
-    auto prefetch = [&](const DRC_CONST ProjBwdSide* g, int t) {             // past the last tile: reads nothing
-        const int base = (t - g->tile0) * T::BM, left = t < tiles ? g->rows - base : 0;
-        const Buf by = block_view(g->dY + (size_t)base * D, left, D * 4);
+    auto prefetch = [&](const ProjBwdSide& g, int t) {             // past the last tile: reads nothing
+        const int base = (t - g.tile0) * T::BM, left = t < tiles ? g.rows - base : 0;
+        const Buf by = block_view(g.dY + (size_t)base * D, left, D * 4);
         y[0] = load4(by, uoff);
         y[1] = load4(by, uoff + D * 2);
         if constexpr (CELL) {
-            const Buf bm = block_view(g->mask + (size_t)base * D, left, D);
+            const Buf bm = block_view(g.mask + (size_t)base * D, left, D);
             mk[0] = load1u(bm, moff);
             mk[1] = load1u(bm, moff + D / 2);
         }
@@ -479,101 +568,101 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
     };
     if (wg >= tiles) return;
     // The self-term product of a tile is sampled one step later, when all wavefronts have written theirs.
-    auto sample = [&](const DRC_CONST ProjBwdSide* g, int t, int left, const float* sC) {
-        const int base = (t - g->tile0) * T::BM, at = prow * g->k + ppart;
+    auto sample = [&](const ProjBwdSide& g, int t, int left, const float* sC) {
+        const int base = (t - g.tile0) * T::BM, at = opaque(prow) * g.k + ppart;
         left = min(left, T::BM);                  // threads past the tile (D = 96) must not reach the next tile's rows
-        const Buf bi = block_view(g->idx + (size_t)base * g->k, left, g->k * 2);
-        const Buf bs = block_view(g->S + (size_t)base * g->k, left, g->k * 4);
+        const Buf bi = block_view(g.idx + (size_t)base * g.k, left, g.k * 2);
+        const Buf bs = block_view(g.S + (size_t)base * g.k, left, g.k * 4);
         // as loaded: a conversion here would wait for the loads before the multiply
         struct { uint16_t v[kPairs]; } col;
 #pragma unroll
         for (int u = 0; u < kPairs; ++u) col.v[u] = __builtin_amdgcn_raw_buffer_load_b16(bi, (at + T::TPR * u) * 2, 0, 0);
         return [=]() {
-            const int row = min(prow, T::BM - 1);
+            const int row = min(opaque(prow), T::BM - 1);
 #pragma unroll
             for (int u = 0; u < kPairs; ++u) {
                 uint16_t c = col.v[u];
                 asm volatile("" : "+v"(c));
                 __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sC[row * LDC + c]), bs,
-                                                      ppart + T::TPR * u < g->k ? (at + T::TPR * u) * 4 : kNowhere, 0, 0);
+                                                      ppart + T::TPR * u < g.k ? (at + T::TPR * u) * 4 : kNowhere, 0, 0);
             }
-            if (g->k > T::TPR * kPairs && prow < min(left, T::BM))
-                for (int p = ppart + T::TPR * kPairs; p < g->k; p += T::TPR)
-                    g->S[(size_t)(base + prow) * g->k + p] = sC[prow * LDC + g->idx[(size_t)(base + prow) * g->k + p]];
+            if (g.k > T::TPR * kPairs && prow < min(left, T::BM))
+                for (int p = ppart + T::TPR * kPairs; p < g.k; p += T::TPR)
+                    g.S[(size_t)(base + prow) * g.k + p] = sC[prow * LDC + g.idx[(size_t)(base + prow) * g.k + p]];
         };
     };
     const auto walk = [&](auto first) {
         constexpr bool kFirst = decltype(first)::value;
-        int t = wg, q = 0, q1, q2, t0 = t, q0;    // graphs of tile t, the next and the one after; the tile before
-        find_seg(segs, a->n, t, q);
-        q0 = q;
-        prefetch(segs + q, t);
+        int t = wg, t0 = t;
+        Place<ProjBwdSide> here, ahead;           // of tile t; of the next one, and in the loop of the one after
+        here.start(segs, n, t);
+        ProjBwdSide g0 = here.g;                  // of the tile before
+        prefetch(here.g, t);
         commit(smem);
-        q1 = q;
-        find_seg(segs, a->n, t + n_wg, q1);
-        prefetch(segs + q1, t + n_wg);
-        if constexpr (kFirst) pad_stores<(CELL ? 4 : 2) + kPairs>(segs->dH1);       // a tile's stores come behind its prefetch
+        ahead = here;
+        ahead.seek(segs, n, t + n_wg);
+        prefetch(ahead.g, t + n_wg);
+        if constexpr (kFirst) pad_stores<(CELL ? 4 : 2) + kPairs>(here.g.dH1);       // a tile's stores come behind its prefetch
         __syncthreads();
         int cur = 0;
         bool have_t0 = false;
         for (;; cur ^= 1) {
-            const DRC_CONST ProjBwdSide* const g = segs + q;
-            const int base = (t - g->tile0) * T::BM, t1 = t + n_wg;
+            const ProjBwdSide g = here.g;
+            const int base = (t - g.tile0) * T::BM, t1 = t + n_wg;
             bf16x8* const buf = smem + cur * 2 * T::OPER;
             float* const sC = sC0 + cur * T::BM * LDC;
-            q2 = q1;
-            find_seg(segs, a->n, t1 + n_wg, q2);
-            const auto finish_t0 = sample(segs + q0, t0, have_t0 ? segs[q0].rows - (t0 - segs[q0].tile0) * T::BM : 0, sC0 + (cur ^ 1) * T::BM * LDC);
+            here = ahead;
+            ahead.seek(segs, n, t1 + n_wg);
+            const auto finish_t0 = sample(g0, t0, have_t0 ? g0.rows - (t0 - g0.tile0) * T::BM : 0, sC0 + (cur ^ 1) * T::BM * LDC);
             auto stage_next = [&]() {
                 commit(smem + (cur ^ 1) * 2 * T::OPER);
-                prefetch(segs + q2, t1 + n_wg);
+                prefetch(ahead.g, t1 + n_wg);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
             // near (or the net's only branch) first, then pinned: the accumulators of both would not fit the registers
-            const int r0 = rg * 32 + (lane & 15), c0 = 16 * nb + 4 * (lane >> 4);
-            {
-                Acc c1[2] = {}, cS[2] = {};
-#pragma unroll
-                for (int s = 0; s < T::KS; ++s) {
-                    bf16x8 x[2][3];
-                    load_x<D>(buf, s, rg, lane, x);
-                    mfma6(w1[s], x, c1);
-                    mfma6(wS[s], x, cS);
+            const int ln = opaque(lane), r0 = rg * 32 + (ln & 15), c0 = 16 * nb + 4 * (ln >> 4);
+            Frags<1> x;
+            constexpr int NS = (CELL ? 2 : 1) * T::KS;
+            Acc c[2] = {}, cS[2] = {};
+            first_frags<D>(buf, rg, lane, x);
+            steps<NS>([&](auto step) {
+                constexpr int i = decltype(step)::value, s = i % T::KS;
+                const bf16x8* const next = buf + (i + 1) / T::KS * T::OPER;
+                if constexpr (i < T::KS) {
+                    const bf16x8* const w[2] = {w1[s], wS[s]};
+                    Acc(*const acc[2])[2] = {&c, &cS};
+                    multiply<D, i, i + 1 < NS>(w, acc, x, next, (i + 1) % T::KS, rg, lane);
+                } else {
+                    const bf16x8* const w[1] = {w2[s]};
+                    Acc(*const acc[1])[2] = {&c};
+                    multiply<D, i, i + 1 < NS>(w, acc, x, next, (i + 1) % T::KS, rg, lane);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                const Buf b1 = block_view(g->dH1 + (size_t)base * D, g->rows - base, D * 4);
+                if constexpr (i == T::KS - 1) {
+                    const Buf b1 = block_view(g.dH1 + (size_t)base * D, g.rows - base, D * 4);
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb) {
-                    *reinterpret_cast<f32x4*>(sC + (r0 + rb * 16) * LDC + c0) = total(cS[rb]);
-                    store4(b1, ((r0 + rb * 16) * D + c0) * 4, total(c1[rb]));      // gathered next: these stay in the caches
+                    for (int rb = 0; rb < 2; ++rb) {
+                        *reinterpret_cast<f32x4*>(sC + (r0 + rb * 16) * LDC + c0) = total(cS[rb]);
+                        store4(b1, ((r0 + rb * 16) * D + c0) * 4, total(c[rb]));       // gathered next: these stay in the caches
+                        c[rb] = Acc{};
+                    }
                 }
-            }
+            });
             if constexpr (CELL) {
-                Acc c2[2] = {};
+                const Buf b2 = block_view(g.dH2 + (size_t)base * D, g.rows - base, D * 4);
 #pragma unroll
-                for (int s = 0; s < T::KS; ++s) {
-                    bf16x8 x[2][3];
-                    load_x<D>(buf + T::OPER, s, rg, lane, x);
-                    mfma6(w2[s], x, c2);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                const Buf b2 = block_view(g->dH2 + (size_t)base * D, g->rows - base, D * 4);
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb) store4(b2, ((r0 + rb * 16) * D + c0) * 4, total(c2[rb]));
+                for (int rb = 0; rb < 2; ++rb) store4(b2, ((r0 + rb * 16) * D + c0) * 4, total(c[rb]));
             }
             finish_t0();
             if constexpr (!kFirst) stage_next();
             __syncthreads();                      // this self-term tile and the next operand tiles are complete
             t0 = t;
-            q0 = q;
+            g0 = g;
             have_t0 = true;
             if (t1 >= tiles) break;
             t = t1;
-            q = q1;
-            q1 = q2;
         }
-        sample(segs + q0, t0, segs[q0].rows - (t0 - segs[q0].tile0) * T::BM, sC0 + cur * T::BM * LDC)();
+        sample(g0, t0, g0.rows - (t0 - g0.tile0) * T::BM, sC0 + cur * T::BM * LDC)();
     };
     if (wave < T::WAVES / 2) walk(yes{});
     else walk(no{});
