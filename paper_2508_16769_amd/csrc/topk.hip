@@ -1,7 +1,9 @@
 // D-ReLU (paper Section 3.1): per row keep the k largest signed values, ties to the lowest column,
 // survivors written in ascending column order as CBSR (vals, idx).
 //
-// One wavefront owns one row at a time.  Lane l holds columns l, 64+l, 128+l, ... (coalesced dword
+// Two kernels: topk_groups_kernel, several rows per wavefront, for rows of up to 256 columns in whole float4s; and
+// topk_rows_kernel for everything else and for the rank order:
+// one wavefront owns one row at a time.  Lane l holds columns l, 64+l, 128+l, ... (coalesced dword
 // loads).  Values are mapped to order-preserving unsigned keys; the k-th largest key is found by a
 // most-significant-bit-first search in which every step is one v_cmp per register plus a scalar
 // popcount of the ballot, started below the previous row's sign and exponent bits when two probes confirm
@@ -12,6 +14,9 @@
 // K relies on) stages the kept keys of a row in LDS in column order and lets every kept element count the
 // keys that precede it: greater, or equal with a lower column.
 #include "dr_internal.h"
+
+#include <cmath>
+#include <type_traits>
 
 namespace drc {
 
@@ -29,14 +34,24 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
 
 constexpr int kRowsInFlight = 4;   // rows whose loads are outstanding per wavefront
 
+// Where the k-th largest of D standard normal numbers lies, and how far apart they are there.
+struct FirstGuess { float z, gap; };
+static FirstGuess first_guess(int D, int k) {
+    const double p = 1.0 - (k - 0.5) / D, z = 4.91 * (std::pow(p, 0.14) - std::pow(1.0 - p, 0.14));     // Tukey's lambda: to 0.01
+    return FirstGuess{(float)z, (float)(2.5066 * std::exp(0.5 * z * z) / D)};
+}
+
 struct TopkSeg {                   // one embedding matrix of a launch
     const float* X;
     float *vals, *vals2;           // vals2 / idx2: a second selection of the same rows, or null
     uint16_t *idx, *idx2;
     int n, k, k2, blk0, n_blocks;  // workgroups [blk0, blk0 + n_blocks)
+    int wide_out;                  // the outputs take 16-byte (values) and 8-byte (columns) stores
+    FirstGuess guess, guess2;
 };
 constexpr int kTopkSegs = 32;
-struct TopkArgs { TopkSeg s[kTopkSegs]; int n, D; };
+struct TopkArgs { TopkSeg s[kTopkSegs]; int n, D, k_max; };
+static_assert(sizeof(TopkArgs) < 4096, "kernel arguments");
 
 template <int EPL, bool DUAL, bool RANKED>
 __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
@@ -180,6 +195,299 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
     }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Rows of up to 256 columns, whole float4s: several rows per wavefront.
+//
+// L lanes share a row; lane t holds the columns 4u .. 4u+3 of its units u = t, t + L, ... (SLOTS float4 loads, each of which
+// reads whole lines).  With one row per wavefront (topk_rows_kernel) a probe of the search costs an instruction of the vector
+// and several of the scalar unit per row, and both were busy three quarters of the time; here a probe counts 64 / L rows at
+// once: two vector instructions per element and a few lane exchanges, nothing scalar.
+//   Search for T, the k-th largest key.  The first probe is where T would lie if the row's values were normally distributed
+// (from their mean and variance), the next ones follow the density of values that goes with it or the bracket's linear
+// interpolation, until every row of the wavefront is within kWalk of k keys; from there a row goes up or down key by key (the nearest key above or below is
+// one subtraction and half a three-way minimum or maximum per element, a probe two instructions).  Probing to the end would take
+// as many probes as the slowest of the rows: 8.1 on average for eight rows of 128 values with k = 32, where under 3 probes and 4
+// steps do.  (A guess from the rows before instead: 2 to 6 % slower, and no guess at all where the scale changes.)  Rows that defeat this (ties at T, infinities, scales that jump) are found by counting what would be kept, and
+// then every row of the wavefront is searched by halving its bracket in key space.
+//   Ties at T are told apart in a branch of their own (by clearing the keys that lose), so the usual row does not pay.
+//   Compaction.  The kept counts of a lane's slots travel as four bytes of one register through one scan over the lanes.  Kept
+// (value, column) pairs are placed in LDS, and the rows' pairs, which lie behind one another in memory, leave as whole
+// 16- and 8-byte stores.
+// At D = 128 bound by HBM: 1.2 M and 0.9 M rows, k = 32, together 372 -> 270 us (5.5 TB/s); 430 000 rows 91 -> 62 us.  At D = 64
+// still by its instructions: 100 000 rows, k = 16, 22 -> 12 us; 3072 rows 5.4 -> 3.9 us; two selections at D = 96, 58 000 rows,
+// 32 -> 17 us.
+// ---------------------------------------------------------------------------------------------------
+template <int CTRL> __device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+// sum over the L lanes of a group, in every lane
+template <int L> __device__ __forceinline__ uint32_t group_sum(uint32_t v) {
+    v += lane_swap<kQuadXor1>(v);
+    v += lane_swap<kQuadXor2>(v);
+    if constexpr (L >= 8) v += lane_swap<kHalfMirror>(v);
+    if constexpr (L >= 16) v += lane_swap<kMirror>(v);
+    return v;
+}
+template <int L> __device__ __forceinline__ uint32_t group_max(uint32_t v) {
+    v = max(v, lane_swap<kQuadXor1>(v));
+    v = max(v, lane_swap<kQuadXor2>(v));
+    if constexpr (L >= 8) v = max(v, lane_swap<kHalfMirror>(v));
+    if constexpr (L >= 16) v = max(v, lane_swap<kMirror>(v));
+    return v;
+}
+// sum over the lanes of the group before this one (t: lane in the group)
+template <int L> __device__ __forceinline__ uint32_t group_before(uint32_t v, int t) {
+    uint32_t x = v;
+    uint32_t y = lane_swap<0x111>(x);          // row_shr:1, 2, 4, 8
+    x += t >= 1 ? y : 0u;
+    y = lane_swap<0x112>(x);
+    x += t >= 2 ? y : 0u;
+    if constexpr (L >= 8) {
+        y = lane_swap<0x114>(x);
+        x += t >= 4 ? y : 0u;
+    }
+    if constexpr (L >= 16) {
+        y = lane_swap<0x118>(x);
+        x += t >= 8 ? y : 0u;
+    }
+    return x - v;
+}
+__device__ __forceinline__ uint32_t key_of(float v) {       // order_key in three instructions (-0 + 0 = +0)
+    const uint32_t u = __float_as_uint(v + 0.0f);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+constexpr int kGuided = 6, kWalk = 4;        // guided probes at most; distance from which keys are walked
+constexpr int kGroupBlocks = 2048;           // eight workgroups per compute unit
+constexpr int64_t kFewRows = 32768;
+struct Guide { float at, gap; };            // where T is looked for first, and the distance between neighbouring values there
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+template <int L, int SLOTS> struct GroupRow {
+    static constexpr int E = 4 * SLOTS;
+    float v[E];
+    uint32_t key[E];
+
+    __device__ __forceinline__ void make_keys(int t, int D) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) key[i] = 4 * (t + L * (i / 4)) < D ? key_of(v[i]) : 0u;      // what is no column counts below all
+    }
+    __device__ __forceinline__ uint32_t count(uint32_t cand) const {
+        uint32_t c[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < E; ++i) c[i & 3] += key[i] >= cand ? 1u : 0u;
+        return group_sum<L>((c[0] + c[1]) + (c[2] + c[3]));
+    }
+    // k-th largest key by probes and steps; wrong where k is not reached that way
+    __device__ __forceinline__ uint32_t guided_threshold(int k, const Guide& guide) const {
+        float lof = -__builtin_inff(), hif = __builtin_inff(), candf = guide.at;
+        float clo = 0.0f, chi = 0.0f;
+        uint32_t cand = key_of(candf);
+        int d;                                                // keys at or above cand, less k
+        for (int it = 0;; ++it) {
+            d = (int)count(cand) - k;
+            const bool far = abs(d) > kWalk;
+            if (it == kGuided || !__any(far)) break;
+            const float df = (float)d;
+            const bool ge = d >= 0;
+            lof = ge ? candf : lof;
+            clo = ge ? df : clo;
+            hif = ge ? hif : candf;
+            chi = ge ? chi : df;
+            const float width = hif - lof;                    // infinite until both sides have been probed
+            const float inside = lof + width * ((clo + 0.5f) * __builtin_amdgcn_rcpf(clo - chi + 1.0f));
+            const float outside = candf + guide.gap * (df + (ge ? 0.5f : -0.5f)) * (float)(it + 1);
+            const float next = fabsf(width) < __builtin_inff() ? inside : outside;
+            candf = far ? next : candf;
+            cand = key_of(candf);
+        }
+        for (int it = 0; it < kWalk && __any(d != 0); ++it) {
+            uint32_t below = 0u, above = 0xffffffffu;         // distances modulo 2^32: what lies on the other side is far away
+#pragma unroll
+            for (int i = 0; i < E; i += 2) {
+                const uint32_t x = key[i] - cand, y = key[i + 1] - cand;
+                below = max(below, max(x, y));
+                above = min(above, min(x, y));
+            }
+            below = group_max<L>(below);
+            above = ~group_max<L>(~above);
+            cand += d < 0 ? below : (d > 0 ? above + 1u : 0u);
+            d += d < 0 ? 1 : (d > 0 ? -1 : 0);
+        }
+        return cand;
+    }
+    // k-th largest key, for any keys
+    __device__ uint32_t halved_threshold(int k) const {
+        uint32_t lo = 0u, hi = 0xffffffffu;                   // at least k keys at or above lo, fewer at or above hi
+        while (__any(hi - lo > 1u)) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);       // lo itself once they meet
+            const bool ge = count(mid) >= (uint32_t)k;
+            lo = ge ? mid : lo;
+            hi = ge ? hi : (mid > lo ? mid : hi);
+        }
+        return lo;
+    }
+    // Where to begin: as if its values were normally distributed.
+    __device__ __forceinline__ Guide guide(int t, int D, const FirstGuess& f) const {
+        float s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < E; ++i)
+            if (4 * (t + L * (i / 4)) < D) {
+                s1 += v[i];
+                s2 = fmaf(v[i], v[i], s2);
+            }
+        auto more = [](float x, auto ctrl) { return x + __uint_as_float(lane_swap<decltype(ctrl)::value>(__float_as_uint(x))); };
+        auto both = [&](auto ctrl) { s1 = more(s1, ctrl); s2 = more(s2, ctrl); };
+        both(std::integral_constant<int, kQuadXor1>{});
+        both(std::integral_constant<int, kQuadXor2>{});
+        if constexpr (L >= 8) both(std::integral_constant<int, kHalfMirror>{});
+        if constexpr (L >= 16) both(std::integral_constant<int, kMirror>{});
+        const float r = __builtin_amdgcn_rcpf((float)D), mean = s1 * r;
+        const float sigma = __builtin_amdgcn_sqrtf(fmaxf(s2 * r - mean * mean, 0.0f)), gap = sigma * f.gap;
+        const bool fine = gap < __builtin_inff() && fabsf(mean) < __builtin_inff();      // also false where it is not a number
+        return Guide{fine ? fmaf(sigma, f.z, mean) : 0.0f, fine ? gap : 1.0f};
+    }
+    // Per slot, how many of the flags before this lane's (in the order of the columns) are set: byte s of the result.  *total: of
+    // the whole row.
+    template <typename F> __device__ __forceinline__ uint32_t starts(int t, F flag, uint32_t* total) const {
+        uint32_t n = 0;
+#pragma unroll
+        for (int s = SLOTS - 1; s >= 0; --s) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c += flag(4 * s + j) ? 1u : 0u;
+            n = (n << 8) + c;
+        }
+        const uint32_t all = group_sum<L>(n);
+        *total = (all & 0xffu) + (all >> 8 & 0xffu) + (all >> 16 & 0xffu) + (all >> 24);
+        return group_before<L>(n, t) + (all << 8) + (all << 16) + (all << 24);     // at most 252: no byte runs over
+    }
+    // Of the keys equal to T only the first columns are kept, k in all: the others' keys are cleared.
+    __device__ __forceinline__ void drop_ties(uint32_t T, int k, int t) {
+        uint32_t above = 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) above += key[i] > T ? 1u : 0u;
+        const uint32_t need = (uint32_t)k - group_sum<L>(above);
+        uint32_t equal;
+        const uint32_t at = starts(t, [&](int i) { return key[i] == T; }, &equal);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            uint32_t rank = (at >> (8 * s)) & 0xffu;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool eq = key[4 * s + j] == T;
+                key[4 * s + j] = eq && rank >= need ? 0u : key[4 * s + j];
+                rank += eq ? 1u : 0u;
+            }
+        }
+    }
+    // kept pairs to pairs[0 .. k) of the row; `spare`: a place of this lane's own for what is not kept
+    __device__ __forceinline__ void place(uint32_t T, uint32_t at, int t, uint2* pairs, uint2* spare) const {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            uint2* to = pairs + ((at >> (8 * s)) & 0xffu);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool keep = key[4 * s + j] >= T;
+                *(keep ? to : spare) = make_uint2(__float_as_uint(v[4 * s + j]), (uint32_t)(4 * (t + L * s) + j));
+                to += keep ? 1 : 0;
+            }
+        }
+    }
+};
+
+template <int L, int SLOTS, bool DUAL>
+__global__ __launch_bounds__(256) void topk_groups_kernel(TopkArgs args) {
+    extern __shared__ uint4 kept_keys4[];                     // per wavefront: 64 spare places, then the kept pairs of its rows
+    constexpr int R = kWave / L;                              // rows per wavefront
+    using Row = GroupRow<L, SLOTS>;
+    int sg = 0;
+    while (sg + 1 < args.n && (int)blockIdx.x >= args.s[sg + 1].blk0) ++sg;
+    const TopkSeg& seg = args.s[sg];
+    const float* __restrict__ X = seg.X;
+    const int n = seg.n, D = args.D;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = lane & (L - 1), g = lane / L;
+    uint2* const spare = reinterpret_cast<uint2*>(kept_keys4) + wave * (kWave + R * args.k_max) + lane;
+    uint2* const pairs = spare - lane + kWave;
+    const uint32_t stride = (uint32_t)seg.n_blocks * 4u * R;
+    uint32_t row0 = ((uint32_t)(blockIdx.x - seg.blk0) * 4u + (uint32_t)wave) * R;
+
+    float4v next[SLOTS];
+    auto load = [&](uint32_t first) {                         // rows and columns past the end: clamped to valid addresses
+        const float* x = X + (size_t)min(first + (uint32_t)g, (uint32_t)n - 1u) * D;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int c = 4 * (t + L * s);
+            next[s] = __builtin_nontemporal_load(reinterpret_cast<const float4v*>(x + (c < D ? c : 0)));     // read once
+        }
+    };
+    Row row;
+    auto select = [&](int k, float* __restrict__ vals, uint16_t* __restrict__ idx, const FirstGuess& guess) {
+        uint32_t T = row.guided_threshold(k, row.guide(t, D, guess)), kept;
+        const auto keep = [&](int i) { return row.key[i] >= T; };
+        uint32_t at = row.starts(t, keep, &kept);
+        const bool ties = __any(kept != (uint32_t)k);
+        if (ties) {
+            T = row.halved_threshold(k);
+            row.drop_ties(T, k, t);
+            at = row.starts(t, keep, &kept);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // one wavefront's LDS accesses run in program order
+        __builtin_amdgcn_wave_barrier();
+        row.place(T, at, t, pairs + g * k, spare);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // the pairs of the wavefront's rows are one stretch of the output, which starts at a multiple of four pairs
+        const int total = (int)min((uint32_t)R, (uint32_t)n - row0) * k;
+        const size_t base = (size_t)row0 * k;
+        for (int p = 4 * lane; p < total; p += 4 * kWave) {
+            const uint4 a = reinterpret_cast<const uint4*>(pairs)[p / 2], b = reinterpret_cast<const uint4*>(pairs)[p / 2 + 1];
+            if (seg.wide_out && p + 4 <= total) {
+                *reinterpret_cast<float4v*>(vals + base + p) =
+                    float4v{__uint_as_float(a.x), __uint_as_float(a.z), __uint_as_float(b.x), __uint_as_float(b.z)};
+                *reinterpret_cast<uint2*>(idx + base + p) = make_uint2(a.y | a.w << 16, b.y | b.w << 16);
+            } else {
+                const uint32_t vv[4] = {a.x, a.z, b.x, b.z}, cc[4] = {a.y, a.w, b.y, b.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (p + j < total) {
+                        vals[base + p + j] = __uint_as_float(vv[j]);
+                        idx[base + p + j] = (uint16_t)cc[j];
+                    }
+            }
+        }
+        return ties;
+    };
+    if (row0 >= (uint32_t)n) return;
+    load(row0);
+    for (;; row0 += stride) {
+#pragma unroll
+        for (int i = 0; i < Row::E; ++i) row.v[i] = next[i / 4][i & 3];
+        const bool more = (uint32_t)n - row0 > stride;
+        if (more) load(row0 + stride);                        // in flight while these rows are selected
+        row.make_keys(t, D);
+        const bool ties = select(seg.k, seg.vals, seg.idx, seg.guess);
+        if constexpr (DUAL) {
+            if (seg.vals2) {
+                if (ties) row.make_keys(t, D);
+                select(seg.k2, seg.vals2, seg.idx2, seg.guess2);
+            }
+        }
+        if (!more) break;
+    }
+}
+
+template <int L, int SLOTS>
+static void launch_groups(const TopkArgs& a, int blocks, bool dual, hipStream_t s) {
+    const size_t lds = sizeof(uint2) * 4 * (kWave + (size_t)(kWave / L) * a.k_max);
+    if (dual) hipLaunchKernelGGL((topk_groups_kernel<L, SLOTS, true>), dim3((unsigned)blocks), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((topk_groups_kernel<L, SLOTS, false>), dim3((unsigned)blocks), dim3(256), lds, s, a);
+}
+// Few rows (less than kFewRows in all) are spread over more lanes: fewer elements per lane shorten the one chain a wavefront
+// goes through.  Rows a wavefront takes at a time:
+static int group_rows(int D, bool few) { return few || D > 128 ? 4 : (D <= 64 ? 16 : 8); }
+
 template <int EPL>
 static void launch_epl(const TopkArgs& a, int blocks, bool dual, int ranked_k, hipStream_t s) {
     if (ranked_k)
@@ -192,6 +500,15 @@ static void launch_epl(const TopkArgs& a, int blocks, bool dual, int ranked_k, h
 }
 
 static int launch_any(const TopkJob* jobs, int n, int D, bool ranked, hipStream_t s) {
+    // Whole float4s of rows: several rows per wavefront.  Wider rows would leave a lane more columns than fit its registers, and
+    // the rank order is found per wavefront.
+    bool groups = !ranked && D <= 256 && D % 4 == 0;
+    int64_t rows = 0;
+    for (int i = 0; i < n; ++i) {
+        groups = groups && aligned(jobs[i].X, 16);
+        rows += jobs[i].n;
+    }
+    const bool few = rows < kFewRows;
     for (int i = 0; i < n;) {
         TopkArgs a{};
         a.D = D;
@@ -200,16 +517,36 @@ static int launch_any(const TopkJob* jobs, int n, int D, bool ranked, hipStream_
         for (; i < n && a.n < kTopkSegs; ++i) {
             const TopkJob& j = jobs[i];
             if (j.n == 0) continue;
-            // Each wavefront strides over rows with four of them in flight, so it wants at least four rows (a wavefront
-            // with one row pays the whole load latency for it: 20 000 rows took 15 us on 4096 workgroups, 9 us on 1250);
-            // beyond 8192 workgroups (four rounds of 8 waves per SIMD) nothing is gained.  Measured on 20 k ... 1.2 M rows.
-            int64_t b = (j.n + 15) / 16;
-            if (b > 8192) b = 8192;
-            a.s[a.n++] = TopkSeg{j.X, j.vals, j.vals2, j.idx, j.idx2, (int)j.n, j.k, j.k2, blocks, (int)b};
+            int64_t b;
+            if (groups) {
+                b = (j.n + 4 * group_rows(D, few) - 1) / (4 * group_rows(D, few));
+                if (b > kGroupBlocks) b = kGroupBlocks;
+            } else {
+                // Each wavefront strides over rows with four of them in flight, so it wants at least four rows (a wavefront
+                // with one row pays the whole load latency for it: 20 000 rows took 15 us on 4096 workgroups, 9 us on 1250);
+                // beyond 8192 workgroups (four rounds of 8 waves per SIMD) nothing is gained.  Measured on 20 k ... 1.2 M rows.
+                b = (j.n + 15) / 16;
+                if (b > 8192) b = 8192;
+            }
+            a.s[a.n++] = TopkSeg{j.X, j.vals, j.vals2, j.idx, j.idx2, (int)j.n, j.k, j.k2, blocks, (int)b,
+                                 aligned(j.vals, 16) && aligned(j.idx, 8) && aligned(j.vals2, 16) && aligned(j.idx2, 8) ? 1 : 0,
+                                 groups ? first_guess(D, j.k) : FirstGuess{}, groups && j.vals2 ? first_guess(D, j.k2) : FirstGuess{}};
+            if (j.k > a.k_max) a.k_max = j.k;
+            if (j.vals2 && j.k2 > a.k_max) a.k_max = j.k2;
             blocks += (int)b;
             dual = dual || j.vals2;
         }
         if (a.n == 0) break;
+        if (groups) {
+            if (few && D <= 64) launch_groups<16, 1>(a, blocks, dual, s);
+            else if (few && D <= 128) launch_groups<16, 2>(a, blocks, dual, s);
+            else if (D <= 32) launch_groups<4, 2>(a, blocks, dual, s);
+            else if (D <= 64) launch_groups<4, 4>(a, blocks, dual, s);
+            else if (D <= 96) launch_groups<8, 3>(a, blocks, dual, s);
+            else if (D <= 128) launch_groups<8, 4>(a, blocks, dual, s);
+            else launch_groups<16, 4>(a, blocks, dual, s);
+            continue;
+        }
         const int rk = ranked ? a.s[0].k : 0;
         if (D <= 64) launch_epl<1>(a, blocks, dual, rk, s);
         else if (D <= 128) launch_epl<2>(a, blocks, dual, rk, s);

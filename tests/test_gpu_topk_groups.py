@@ -1,0 +1,82 @@
+"""D-ReLU where several rows share a wavefront (up to 256 columns, whole float4s) and at the edges of that path: partly filled
+lane groups and wavefronts, rows of the second and later trips, and rows that its guided search has no guess for (ties,
+constant rows, infinities, scales that jump from row to row).  Exact: selections and values are compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_16769_amd as P
+from gpu_util import dev, host_idx, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _expected(X, k):
+    """k largest per row, ties to the lowest column, ascending columns (-0 ties with +0)."""
+    order = np.argsort(-(X + np.float32(0)), axis=1, kind="stable")[:, :k]
+    cols = np.sort(order, axis=1)
+    return np.take_along_axis(X, cols, axis=1), cols.astype(np.int32)
+
+
+def _rows(rng, n, D, kind):
+    X = rng.standard_normal((n, D)).astype(np.float32)
+    if kind == "ties":
+        X = np.round(X * 2).astype(np.float32) / 2
+        X[X == 0] = rng.choice(np.array([0.0, -0.0], np.float32), int((X == 0).sum()))
+    elif kind == "hard":
+        X *= np.exp2(rng.integers(-120, 120, (n, 1))).astype(np.float32)       # every row another scale, denormals among them
+        X[::7] = 3.0                                                          # constant rows
+        X[1::7] = np.where(rng.random((len(X[1::7]), D)) < 0.9, 0.0, X[1::7])
+        X[2::7, 0] = np.inf
+        X[2::7, D // 2] = -np.inf
+        X[3::7] = np.inf * np.sign(X[3::7])
+    return X
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "hard"])
+@pytest.mark.parametrize("D", [4, 32, 36, 64, 68, 96, 100, 128, 132, 192, 256, 260])
+def test_selection_at_the_edges_of_the_lane_groups(D, kind):
+    rng = np.random.default_rng(D)
+    for n in (1, 15, 16, 17, 131, 1000):
+        for k in sorted({1, 3, D // 4 + 1, D // 2, D - 1, D}):
+            if k < 1:
+                continue
+            say(f"topk groups D={D} n={n} k={k} {kind}")
+            X = _rows(rng, n, D, kind)
+            wv, wi = _expected(X, k)
+            vals = torch.full((n, k), float("nan"), device="cuda")
+            idx = torch.full((n, k), -1, dtype=torch.int16, device="cuda")
+            P.dr_topk(dev(X), k, vals, idx)
+            assert np.array_equal(host_idx(idx), wi)
+            assert np.array_equal(vals.cpu().numpy().view(np.uint32), wv.view(np.uint32))
+
+
+@pytest.mark.parametrize("n,D,k", [(300_011, 32, 8), (150_001, 64, 16), (140_003, 96, 24), (140_003, 128, 32), (70_001, 256, 64)])
+def test_later_trips_of_a_wavefront(n, D, k):
+    say(f"topk groups n={n} D={D} k={k}")
+    X = _rows(np.random.default_rng(n), n, D, "normal")
+    X[n // 2:] *= 1000.0                                    # the guess learnt on the rows before is of no use here
+    wv, wi = _expected(X, k)
+    vals, idx = torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int16, device="cuda")
+    P.dr_topk(dev(X), k, vals, idx)
+    assert np.array_equal(host_idx(idx), wi)
+    assert np.array_equal(vals.cpu().numpy(), wv)
+
+
+@pytest.mark.parametrize("D,k", [(64, 7), (128, 32)])
+def test_alignment_of_inputs_and_outputs(D, k):
+    """Inputs that take no float4 loads go the general way; outputs that take no wide stores are written one by one."""
+    say(f"topk alignment D={D} k={k}")
+    n = 1003
+    X = _rows(np.random.default_rng(k), n, D, "normal")
+    wv, wi = _expected(X, k)
+    for shift_in, shift_v, shift_i in ((1, 0, 0), (0, 1, 0), (0, 0, 1), (0, 1, 3)):
+        buf = torch.empty(n * D + 4, device="cuda")
+        x = buf[shift_in:shift_in + n * D].view(n, D)
+        x.copy_(dev(X))
+        vb, ib = torch.full((n * k + 8,), 7.0, device="cuda"), torch.full((n * k + 8,), 7, dtype=torch.int16, device="cuda")
+        vals, idx = vb[shift_v:shift_v + n * k].view(n, k), ib[shift_i:shift_i + n * k].view(n, k)
+        P.dr_topk(x, k, vals, idx)
+        assert np.array_equal(host_idx(idx), wi) and np.array_equal(vals.cpu().numpy(), wv)
+        assert bool((vb[shift_v + n * k:] == 7).all()) and bool((vb[:shift_v] == 7).all())
+        assert bool((ib[shift_i + n * k:] == 7).all()) and bool((ib[:shift_i] == 7).all())
