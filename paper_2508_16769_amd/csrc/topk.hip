@@ -1,7 +1,7 @@
 // D-ReLU (paper Section 3.1): per row keep the k largest signed values, ties to the lowest column,
 // survivors written in ascending column order as CBSR (vals, idx).
 //
-// Two kernels: topk_groups_kernel, several rows per wavefront, for rows of up to 256 columns in whole float4s; and
+// Two kernels: topk_groups_kernel, several rows per wavefront, for rows of up to 128 columns in whole float4s; and
 // topk_rows_kernel for everything else and for the rank order:
 // one wavefront owns one row at a time.  Lane l holds columns l, 64+l, 128+l, ... (coalesced dword
 // loads).  Values are mapped to order-preserving unsigned keys; the k-th largest key is found by a
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Rows of up to 256 columns, whole float4s: several rows per wavefront.
+// Rows of up to 128 columns, whole float4s: several rows per wavefront.
 //
 // L lanes share a row; lane t holds the columns 4u .. 4u+3 of its units u = t, t + L, ... (SLOTS float4 loads, each of which
 // reads whole lines).  With one row per wavefront (topk_rows_kernel) a probe of the search costs an instruction of the vector
@@ -204,18 +204,21 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
 // once: two vector instructions per element and a few lane exchanges, nothing scalar.
 //   Search for T, the k-th largest key.  The first probe is where T would lie if the row's values were normally distributed
 // (from their mean and variance), the next ones follow the density of values that goes with it or the bracket's linear
-// interpolation, until every row of the wavefront is within kWalk of k keys; from there a row goes up or down key by key (the nearest key above or below is
-// one subtraction and half a three-way minimum or maximum per element, a probe two instructions).  Probing to the end would take
-// as many probes as the slowest of the rows: 8.1 on average for eight rows of 128 values with k = 32, where under 3 probes and 4
-// steps do.  (A guess from the rows before instead: 2 to 6 % slower, and no guess at all where the scale changes.)  Rows that defeat this (ties at T, infinities, scales that jump) are found by counting what would be kept, and
-// then every row of the wavefront is searched by halving its bracket in key space.
+// interpolation, until every row of the wavefront is within kWalk of k keys; from there a row goes up or down key by key (the
+// nearest key above and below take a subtraction and half a three-way minimum and maximum per element, a probe two instructions).
+// Probing to the end would take as many probes as the slowest of the rows: 8.1 on average for eight rows of 128 normal values
+// with k = 32, where under 2 probes and 4 steps do.  (A guess from the rows before instead: 2 to 6 % slower, and no guess at all
+// where the scale changes.)  Rows that are still far after kGuided probes (skewed data) go on with a bracket in key space,
+// halved and interpolated in turn, whose ends are moved to keys of the row, so that few distinct values take few probes; and
+// when the number of keys that would be kept is not k (equal keys were walked over), that search goes on to the end.
 //   Ties at T are told apart in a branch of their own (by clearing the keys that lose), so the usual row does not pay.
 //   Compaction.  The kept counts of a lane's slots travel as four bytes of one register through one scan over the lanes.  Kept
 // (value, column) pairs are placed in LDS, and the rows' pairs, which lie behind one another in memory, leave as whole
 // 16- and 8-byte stores.
-// At D = 128 bound by HBM: 1.2 M and 0.9 M rows, k = 32, together 372 -> 270 us (5.5 TB/s); 430 000 rows 91 -> 62 us.  At D = 64
-// still by its instructions: 100 000 rows, k = 16, 22 -> 12 us; 3072 rows 5.4 -> 3.9 us; two selections at D = 96, 58 000 rows,
-// 32 -> 17 us.
+// At D = 128 bound by HBM: 1.2 M and 0.9 M rows, k = 32, together 372 -> 270 us (5.5 TB/s); 430 000 rows 91 -> 64 us.  At D = 64
+// still by its instructions: 100 000 rows, k = 16, 22 -> 13 us; 3072 rows 5.4 -> 3.9 us; two selections at D = 96, 58 000 rows,
+// 32 -> 18 us.  Other data (250 000 x 128, k = 32): normal 55 -> 41, values rounded to halves 130 -> 91, zeros and ones 115 -> 62,
+// exp(2 N) 63 -> 67, uniform with outliers of 1e6 55 -> 72.
 // ---------------------------------------------------------------------------------------------------
 template <int CTRL> __device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
@@ -257,7 +260,7 @@ __device__ __forceinline__ uint32_t key_of(float v) {       // order_key in thre
     const uint32_t u = __float_as_uint(v + 0.0f);
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
-constexpr int kGuided = 6, kWalk = 4;        // guided probes at most; distance from which keys are walked
+constexpr int kGuided = 3, kWalk = 4;        // guided probes at most; distance from which keys are walked
 constexpr int kGroupBlocks = 2048;           // eight workgroups per compute unit
 constexpr int64_t kFewRows = 32768;
 struct Guide { float at, gap; };            // where T is looked for first, and the distance between neighbouring values there
@@ -278,54 +281,99 @@ template <int L, int SLOTS> struct GroupRow {
         for (int i = 0; i < E; ++i) c[i & 3] += key[i] >= cand ? 1u : 0u;
         return group_sum<L>((c[0] + c[1]) + (c[2] + c[3]));
     }
-    // k-th largest key by probes and steps; wrong where k is not reached that way
-    __device__ __forceinline__ uint32_t guided_threshold(int k, const Guide& guide) const {
+    // nearest key below `cand` and nearest at or above it, as distances (modulo 2^32: what lies on the other side is far away)
+    __device__ __forceinline__ void neighbours(uint32_t cand, uint32_t* below, uint32_t* above) const {
+        uint32_t b = 0u, a = 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < E; i += 2) {
+            const uint32_t x = key[i] - cand, y = key[i + 1] - cand;
+            b = max(b, max(x, y));
+            a = min(a, min(x, y));
+        }
+        *below = group_max<L>(b);
+        *above = ~group_max<L>(~a);
+    }
+    // k-th largest key, and where each slot's kept keys go (starts)
+    __device__ __forceinline__ uint32_t threshold(int k, int t, int D, const Guide& guide, uint32_t* at, bool* ties) {
         float lof = -__builtin_inff(), hif = __builtin_inff(), candf = guide.at;
-        float clo = 0.0f, chi = 0.0f;
+        float clo = 0.0f, chi = 0.0f;                         // counts less k
         uint32_t cand = key_of(candf);
         int d;                                                // keys at or above cand, less k
+        const auto note = [&]() {
+            const bool ge = d >= 0;
+            lof = ge ? candf : lof;
+            clo = ge ? (float)d : clo;
+            hif = ge ? hif : candf;
+            chi = ge ? chi : (float)d;
+        };
         for (int it = 0;; ++it) {
             d = (int)count(cand) - k;
             const bool far = abs(d) > kWalk;
-            if (it == kGuided || !__any(far)) break;
+            if (it == kGuided - 1 || !__any(far)) break;
+            note();
             const float df = (float)d;
-            const bool ge = d >= 0;
-            lof = ge ? candf : lof;
-            clo = ge ? df : clo;
-            hif = ge ? hif : candf;
-            chi = ge ? chi : df;
             const float width = hif - lof;                    // infinite until both sides have been probed
             const float inside = lof + width * ((clo + 0.5f) * __builtin_amdgcn_rcpf(clo - chi + 1.0f));
-            const float outside = candf + guide.gap * (df + (ge ? 0.5f : -0.5f)) * (float)(it + 1);
+            const float outside = candf + guide.gap * (df + (d >= 0 ? 0.5f : -0.5f)) * (float)(it + 1);
             const float next = fabsf(width) < __builtin_inff() ? inside : outside;
             candf = far ? next : candf;
             cand = key_of(candf);
         }
-        for (int it = 0; it < kWalk && __any(d != 0); ++it) {
-            uint32_t below = 0u, above = 0xffffffffu;         // distances modulo 2^32: what lies on the other side is far away
+        uint32_t lo = 0u, hi = 0u, kept;                      // set where they are needed: at least k keys from lo on, fewer from hi on
+        bool open = abs(d) > kWalk;
+        for (int reach = kWalk, trip = 0;; reach = 0) {
+            if (__any(open)) {
+                if (hi == 0u) {                               // the probes so far, else the row's least and greatest key
+                    uint32_t least = 0xffffffffu, most = 0u;
 #pragma unroll
-            for (int i = 0; i < E; i += 2) {
-                const uint32_t x = key[i] - cand, y = key[i + 1] - cand;
-                below = max(below, max(x, y));
-                above = min(above, min(x, y));
+                    for (int i = 0; i < E; ++i)
+                        if (4 * (t + L * (i / 4)) < D) {
+                            least = min(least, key[i]);
+                            most = max(most, key[i]);
+                        }
+                    least = ~group_max<L>(~least);
+                    most = group_max<L>(most);
+                    if (trip == 0 && reach == kWalk) note();
+                    const bool has_lo = fabsf(lof) < __builtin_inff(), has_hi = fabsf(hif) < __builtin_inff();
+                    lo = has_lo ? key_of(lof) : least;
+                    clo = has_lo ? clo : (float)(D - k);
+                    hi = has_hi ? key_of(hif) : most + 1u;
+                    chi = has_hi ? chi : (float)-k;
+                }
+                for (; __any(open); ++trip) {
+                    uint32_t next = lo + ((hi - lo) >> 1);
+                    if (trip & 1) {
+                        const float part = (float)(hi - lo) * ((clo + 0.5f) * __builtin_amdgcn_rcpf(clo - chi + 1.0f));
+                        next = lo + min(max((uint32_t)part, 1u), hi - lo - 1u);
+                    }
+                    cand = open ? next : cand;
+                    const int c = (int)count(cand) - k;
+                    uint32_t below, above;
+                    neighbours(cand, &below, &above);         // the bracket's ends are keys of the row: few distinct ones, few trips
+                    const bool ge = open && c >= 0, lt = open && c < 0;
+                    lo = ge ? cand + above : lo;
+                    clo = ge ? (float)c : clo;
+                    hi = lt ? cand + below + 1u : hi;
+                    chi = lt ? (float)c : chi;
+                    d = open ? c : d;
+                    const bool met = hi - lo <= 1u;
+                    cand = open && met ? lo : cand;
+                    d = open && met ? 0 : d;                  // nothing to walk: what is kept is counted below
+                    open = open && !met && abs(d) > reach;
+                }
             }
-            below = group_max<L>(below);
-            above = ~group_max<L>(~above);
-            cand += d < 0 ? below : (d > 0 ? above + 1u : 0u);
-            d += d < 0 ? 1 : (d > 0 ? -1 : 0);
+            for (int it = 0; it < reach && __any(d != 0); ++it) {
+                uint32_t below, above;
+                neighbours(cand, &below, &above);
+                cand += d < 0 ? below : (d > 0 ? above + 1u : 0u);
+                d += d < 0 ? 1 : (d > 0 ? -1 : 0);
+            }
+            *at = starts(t, [&](int i) { return key[i] >= cand; }, &kept);
+            open = kept != (uint32_t)k;
+            *ties = __any(open);
+            if (reach == 0 || !*ties) break;
         }
         return cand;
-    }
-    // k-th largest key, for any keys
-    __device__ uint32_t halved_threshold(int k) const {
-        uint32_t lo = 0u, hi = 0xffffffffu;                   // at least k keys at or above lo, fewer at or above hi
-        while (__any(hi - lo > 1u)) {
-            const uint32_t mid = lo + ((hi - lo) >> 1);       // lo itself once they meet
-            const bool ge = count(mid) >= (uint32_t)k;
-            lo = ge ? mid : lo;
-            hi = ge ? hi : (mid > lo ? mid : hi);
-        }
-        return lo;
     }
     // Where to begin: as if its values were normally distributed.
     __device__ __forceinline__ Guide guide(int t, int D, const FirstGuess& f) const {
@@ -424,14 +472,12 @@ __global__ __launch_bounds__(256) void topk_groups_kernel(TopkArgs args) {
     };
     Row row;
     auto select = [&](int k, float* __restrict__ vals, uint16_t* __restrict__ idx, const FirstGuess& guess) {
-        uint32_t T = row.guided_threshold(k, row.guide(t, D, guess)), kept;
-        const auto keep = [&](int i) { return row.key[i] >= T; };
-        uint32_t at = row.starts(t, keep, &kept);
-        const bool ties = __any(kept != (uint32_t)k);
+        bool ties;
+        uint32_t at, kept;
+        const uint32_t T = row.threshold(k, t, D, row.guide(t, D, guess), &at, &ties);
         if (ties) {
-            T = row.halved_threshold(k);
             row.drop_ties(T, k, t);
-            at = row.starts(t, keep, &kept);
+            at = row.starts(t, [&](int i) { return row.key[i] >= T; }, &kept);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // one wavefront's LDS accesses run in program order
         __builtin_amdgcn_wave_barrier();
@@ -486,7 +532,7 @@ static void launch_groups(const TopkArgs& a, int blocks, bool dual, hipStream_t 
 }
 // Few rows (less than kFewRows in all) are spread over more lanes: fewer elements per lane shorten the one chain a wavefront
 // goes through.  Rows a wavefront takes at a time:
-static int group_rows(int D, bool few) { return few || D > 128 ? 4 : (D <= 64 ? 16 : 8); }
+static int group_rows(int D, bool few) { return few ? 4 : (D <= 64 ? 16 : 8); }
 
 template <int EPL>
 static void launch_epl(const TopkArgs& a, int blocks, bool dual, int ranked_k, hipStream_t s) {
@@ -500,9 +546,9 @@ static void launch_epl(const TopkArgs& a, int blocks, bool dual, int ranked_k, h
 }
 
 static int launch_any(const TopkJob* jobs, int n, int D, bool ranked, hipStream_t s) {
-    // Whole float4s of rows: several rows per wavefront.  Wider rows would leave a lane more columns than fit its registers, and
-    // the rank order is found per wavefront.
-    bool groups = !ranked && D <= 256 && D % 4 == 0;
+    // Whole float4s of rows of up to 128 columns: several rows per wavefront.  Wider rows gain less by it (250 000 x 256, k = 64:
+    // 86 -> 74 us on normal data, 100 -> 125 on skewed data), and the rank order is found per wavefront.
+    bool groups = !ranked && D <= 128 && D % 4 == 0;
     int64_t rows = 0;
     for (int i = 0; i < n; ++i) {
         groups = groups && aligned(jobs[i].X, 16);
@@ -543,8 +589,7 @@ static int launch_any(const TopkJob* jobs, int n, int D, bool ranked, hipStream_
             else if (D <= 32) launch_groups<4, 2>(a, blocks, dual, s);
             else if (D <= 64) launch_groups<4, 4>(a, blocks, dual, s);
             else if (D <= 96) launch_groups<8, 3>(a, blocks, dual, s);
-            else if (D <= 128) launch_groups<8, 4>(a, blocks, dual, s);
-            else launch_groups<16, 4>(a, blocks, dual, s);
+            else launch_groups<8, 4>(a, blocks, dual, s);
             continue;
         }
         const int rk = ranked ? a.s[0].k : 0;

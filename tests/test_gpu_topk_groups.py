@@ -1,4 +1,4 @@
-"""D-ReLU where several rows share a wavefront (up to 256 columns, whole float4s) and at the edges of that path: partly filled
+"""D-ReLU where several rows share a wavefront (up to 128 columns, whole float4s) and at the edges of that path: partly filled
 lane groups and wavefronts, rows of the second and later trips, and rows that its guided search has no guess for (ties,
 constant rows, infinities, scales that jump from row to row).  Exact: selections and values are compared bit for bit."""
 import numpy as np
@@ -23,6 +23,8 @@ def _rows(rng, n, D, kind):
     if kind == "ties":
         X = np.round(X * 2).astype(np.float32) / 2
         X[X == 0] = rng.choice(np.array([0.0, -0.0], np.float32), int((X == 0).sum()))
+    elif kind == "skewed":
+        X = np.where(X > 2, X * 1e6, np.exp(2 * X)).astype(np.float32)
     elif kind == "hard":
         X *= np.exp2(rng.integers(-120, 120, (n, 1))).astype(np.float32)       # every row another scale, denormals among them
         X[::7] = 3.0                                                          # constant rows
@@ -33,8 +35,8 @@ def _rows(rng, n, D, kind):
     return X
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "hard"])
-@pytest.mark.parametrize("D", [4, 32, 36, 64, 68, 96, 100, 128, 132, 192, 256, 260])
+@pytest.mark.parametrize("kind", ["normal", "ties", "skewed", "hard"])
+@pytest.mark.parametrize("D", [4, 32, 36, 64, 68, 96, 100, 128, 132])
 def test_selection_at_the_edges_of_the_lane_groups(D, kind):
     rng = np.random.default_rng(D)
     for n in (1, 15, 16, 17, 131, 1000):
@@ -51,7 +53,7 @@ def test_selection_at_the_edges_of_the_lane_groups(D, kind):
             assert np.array_equal(vals.cpu().numpy().view(np.uint32), wv.view(np.uint32))
 
 
-@pytest.mark.parametrize("n,D,k", [(300_011, 32, 8), (150_001, 64, 16), (140_003, 96, 24), (140_003, 128, 32), (70_001, 256, 64)])
+@pytest.mark.parametrize("n,D,k", [(300_011, 32, 8), (150_001, 64, 16), (140_003, 96, 24), (140_003, 128, 32)])
 def test_later_trips_of_a_wavefront(n, D, k):
     say(f"topk groups n={n} D={D} k={k}")
     X = _rows(np.random.default_rng(n), n, D, "normal")

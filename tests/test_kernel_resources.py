@@ -25,7 +25,7 @@ def test_hot_kernels_use_no_scratch_memory():
     topk = {k: v for k, v in rep.items() if "topk_rows_kernel" in k or "topk_groups_kernel" in k}
     spmm = {k: v for k, v in rep.items() if "spmm_fwd_kernel" in k or "spmm_bwd_kernel" in k}
     staged = {k: v for k, v in rep.items() if "spmm_bwd_staged_kernel" in k}
-    assert len(topk) >= 24 and len(spmm) >= 20 and len(staged) >= 16
+    assert len(topk) >= 22 and len(spmm) >= 20 and len(staged) >= 16
     for name, r in {**topk, **spmm}.items():
         assert r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0, (name, r)
     # staged tiles: the instantiations with 64-column slabs and up to 4 compact outputs per lane (k <= 64) hold their two
