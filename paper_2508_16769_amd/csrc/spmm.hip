@@ -285,36 +285,33 @@ struct Stream {
 
 // The pairs of one gathered CBSR row that one lane of a group handles.
 //   KPL > 0: KPL consecutive pairs [t*KPL, (t+1)*KPL), vector loads (k = 8*KPL).
-//   KPL < 0: the -KPL pairs t, t+8, t+16, ... with scalar loads, for every other k <= -8*KPL (the small K of the
-//            optimal-K candidates among them).  Pairs past k are loaded from a clamped address and accumulated
-//            into the padding words behind the row buffer, so no load or LDS access is conditional.
+//   KPL < 0: N = -KPL consecutive pairs as well, for every other k in (8*(N-1), 8*N]: lane t starts at pair N*t or, where
+//            the row ends before N*t + N, at k - N.  Pairs a lower lane has got already are accumulated into the padding
+//            words behind the row buffer, so no load or LDS access is conditional and none leaves the row.  Rows then
+//            start at any multiple of 4 (values) or 2 (columns) bytes, which global loads of any width accept here.
+//            Single pairs t, t+8, ... took 2 N loads an edge and lane in place of two to four: 45 677 x 100, k = 25, three
+//            relations, D-ReLU and backward included 162 -> 155 us; a layer with one relation at k = 24, 223 -> 220 us.
 template <int KPL> struct Pairs {
     static constexpr int N = KPL > 0 ? KPL : -KPL;
     float v[N];
     uint16_t c[N];
-    // `k`: pairs of the row that count (the row's stored width, or a prefix of it in the adaptive-K kernels).
-    // PREFIX: with consecutive pairs per lane, send the pairs at or past k to the padding words as well.
+    // `k`: stored width of the row; `kk`: pairs of it that count (all, or a prefix of them in the adaptive-K kernels).
+    // PREFIX: pairs at or past kk go to the padding words as well.
     template <bool PREFIX = false>
     __device__ __forceinline__ void load(const float* __restrict__ vals, const uint16_t* __restrict__ idx, uint32_t rowbase,
-                                         int t, int k, int D) {
-        load_raw(vals, idx, rowbase, t, k, D);
-        if constexpr (PREFIX && KPL > 0) {
+                                         int t, int k, int kk, int D) {
+        const int first = KPL > 0 ? KPL * t : min(N * t, k - N);
+        load_raw(vals, idx, rowbase, t, first);
 #pragma unroll
-            for (int u = 0; u < KPL; ++u)
-                if (KPL * t + u >= k) c[u] = (uint16_t)(D + (t & (kBufPad - 1)));
-        }
+        for (int u = 0; u < N; ++u)
+            if ((KPL < 0 && first + u < N * t) || (PREFIX && first + u >= kk)) c[u] = (uint16_t)(D + (t & (kBufPad - 1)));
     }
     __device__ __forceinline__ void load_raw(const float* __restrict__ vals, const uint16_t* __restrict__ idx, uint32_t rowbase,
-                                             int t, int k, int D) {
+                                             int t, int first) {
         if constexpr (KPL < 0) {
-#pragma unroll
-            for (int u = 0; u < N; ++u) {
-                const int q = t + kLPE * u;
-                const uint32_t off = rowbase + (uint32_t)min(q, k - 1);
-                v[u] = vals[off];
-                const uint16_t col = idx[off];
-                c[u] = q < k ? col : (uint16_t)(D + (t & (kBufPad - 1)));
-            }
+            const uint32_t off = rowbase + (uint32_t)first;
+            __builtin_memcpy(v, vals + off, sizeof v);
+            __builtin_memcpy(c, idx + off, sizeof c);
         } else if constexpr (KPL == 1) {
             v[0] = vals[rowbase + t];
             c[0] = idx[rowbase + t];
@@ -391,7 +388,7 @@ __device__ __forceinline__ void fwd_issue(FwdBatch<KPL, EPI>& b, Stream& st, con
         int kk = k;                                          // pairs of the gathered row this destination takes
         // (strided: one row, whose width the caller has put into k1 and k2 = k3 = k1)
         if constexpr (ADAPT) kk = STRIDED ? dk.k3 : dk.width(plan.sRp[st.row + 1] - plan.sRp[st.row], k);   // a prefix of the rank order
-        b.p[q].template load<ADAPT>(xs_vals, xs_idx, col * (uint32_t)k, t, kk, D);
+        b.p[q].template load<ADAPT>(xs_vals, xs_idx, col * (uint32_t)k, t, k, kk, D);
         b.meta[q] = valid ? st.template advance<STRIDED, RW>(plan, sa, npass, base) : 0u;
     }
 }
@@ -591,7 +588,7 @@ static int fwd_kind(const SpmmFwdJob& j) {
         else if (q == 2 && aligned(j.xs_vals, 8) && aligned(j.xs_idx, 4)) kpl = 2;
         else if ((q == 4 || q == 8 || q == 16) && aligned(j.xs_vals, 16) && aligned(j.xs_idx, 8)) kpl = q;
     }
-    if (kpl == 0 && k <= 4 * kLPE) kpl = -((k + kLPE - 1) / kLPE);   // strided scalar pairs, masked past k
+    if (kpl == 0 && k <= 4 * kLPE) kpl = -((k + kLPE - 1) / kLPE);   // unaligned pairs
     return kpl;
 }
 
@@ -669,7 +666,7 @@ int launch_spmm_fwd_adaptive(const dr_csr* A, const float* xr_vals, const uint16
     a.n = 1;
     a.s[0] = SpmmFwdSeg{A->rowptr, A->colidx, A->vals, xr_vals, xr_idx, H, (int)A->n_rows, k, (D % 4 == 0 && aligned(H, 16)) ? 1 : 0, 0, 0, 0};
     // widths that fill the lanes evenly keep the vector loads of the uniform kernel (pairs past the destination's
-    // width are redirected after the load); the others take the strided scalar pairs
+    // width are redirected after the load); the others take unaligned pairs
     const bool vec = (k == 8) || (k == 16 && aligned(xr_vals, 8) && aligned(xr_idx, 4)) ||
                      ((k == 32 || k == 64) && aligned(xr_vals, 16) && aligned(xr_idx, 8));
     switch (vec ? k / kLPE + 100 : (k + kLPE - 1) / kLPE) {

@@ -42,3 +42,24 @@ def test_row_lengths_at_the_dispatch_edges(M, D, k):
     P.dr_spmm_bwd(A, dev(dH), dev(oi2.astype(np.uint16).view(np.int16)), D, k, G)
     assert_row_bound(G.cpu().numpy(), want, l1row, "bwd")
     assert_elem_bound(G.cpu().numpy(), want, l1elem, "bwd")
+
+
+@pytest.mark.parametrize("k", [1, 4, 7, 9, 12, 15, 16, 17, 23, 24, 25, 31, 32])
+def test_forward_pairs_at_any_alignment(k):
+    """Widths that fill no vector, in arrays that start one element past an aligned address, with NaN on either side."""
+    M, N, D = 37, 29, 68
+    say(f"spmm pairs k={k}")
+    rng = np.random.default_rng(k)
+    rp = np.arange(M + 1, dtype=np.int32) * 6
+    ci = rng.integers(0, N, 6 * M).astype(np.int32)
+    ci[:2] = 0, N - 1                                    # the first and the last row of the arrays
+    av = rng.uniform(0.05, 1.0, 6 * M).astype(np.float32)
+    ov, oi = oracle.topk(rng.standard_normal((N, D)).astype(np.float32), k)
+    vals = torch.full((N * k + 2,), float("nan"), dtype=torch.float32, device="cuda")
+    idx = torch.zeros(N * k + 2, dtype=torch.int16, device="cuda")
+    vals[1:-1] = dev(ov, torch.float32).flatten()
+    idx[1:-1] = dev(oi.astype(np.uint16).view(np.int16)).flatten()
+    want, _, l1elem = oracle.spmm_fwd(rp, ci, av, ov, oi, D, want_l1elem=True)
+    H = torch.full((M, D), float("nan"), dtype=torch.float32, device="cuda")
+    P.dr_spmm_fwd(P.Csr(M, N, dev(rp), dev(ci), dev(av)), vals[1:-1].view(N, k), idx[1:-1].view(N, k), D, k, H)
+    assert_elem_bound(H.cpu().numpy(), want, l1elem, "fwd")
