@@ -49,25 +49,46 @@ __device__ __forceinline__ int wave_row_of(const int32_t* __restrict__ rowptr, i
     return lo;
 }
 
-// row of this lane's edge e, given a row that is at or before the row of the wavefront's first edge; e rises with the lane
-__device__ __forceinline__ int wave_rows_from(const int32_t* __restrict__ rowptr, int n_rows, int base, int e) {
-    const int lane = threadIdx.x & 63;
-    int row = base;
+// The row ends a wavefront has at hand, kept from one step to the next: lane l holds the end of row base + l, and of the row
+// 64 further on.  64 row ends serve a dozen steps where rows have a dozen edges; loaded anew for every step they were a
+// dependent load per step, which is what these kernels waited for.
+struct RowWindow { int base, start, end, next; };      // start = rowptr[base]
+
+__device__ __forceinline__ int row_end(const int32_t* __restrict__ rowptr, int n_rows, uint32_t row) {
+    return row < (uint32_t)n_rows ? rowptr[row + 1u] : 0x7fffffff;             // row may lie past 2^31
+}
+__device__ __forceinline__ RowWindow row_window(const int32_t* __restrict__ rowptr, int n_rows, int base) {
+    const uint32_t at = (uint32_t)base + (uint32_t)(threadIdx.x & 63);
+    return RowWindow{base, rowptr[base], row_end(rowptr, n_rows, at), row_end(rowptr, n_rows, at + 64u)};
+}
+
+// row of this lane's edge e and that row's number of edges, given a window whose first row is at or before the row of the
+// wavefront's first edge; e rises with the lane, and from call to call
+__device__ __forceinline__ int wave_rows(const int32_t* __restrict__ rowptr, int n_rows, RowWindow& w, int e, int* len) {
+    int row = w.base;
     bool open = true;
     for (int window = 1;; ++window) {
-        const uint32_t i = (uint32_t)base + 1u + (uint32_t)lane;             // may lie past 2^31
-        const int end = i <= (uint32_t)n_rows ? rowptr[i] : 0x7fffffff;
         int c = 0;                                             // row ends at or before e among these 64 (sorted)
 #pragma unroll
-        for (int w = 32; w >= 1; w >>= 1) c += (__shfl(end, c + w - 1, 64) <= e) ? w : 0;
-        c += (__shfl(end, c, 64) <= e) ? 1 : 0;
-        row = open ? base + c : row;
-        open = open && c == 64;
+        for (int d = 32; d >= 1; d >>= 1) c += (__shfl(w.end, c + d - 1, 64) <= e) ? d : 0;
+        const int at_c = __shfl(w.end, c, 64), below = __shfl(w.end, max(c - 1, 0), 64);
+        const bool past = at_c <= e;                           // c = 63 here: all 64
+        if (open) {
+            row = w.base + c;
+            *len = at_c - (c == 0 ? w.start : below);
+        }
+        open = open && past;
         const unsigned long long still = __ballot(open);
         if (!still) return row;
-        base += 64;                                            // rowptr[base] <= e of every open lane
-        if (window % kScanWindows == 0)
-            base = wave_row_of(rowptr, n_rows, base, __builtin_amdgcn_readlane(e, __ffsll((long long)still) - 1));
+        const int base = w.base + 64;                          // rowptr[base] <= e of every open lane
+        if (window % kScanWindows == 0) {
+            w = row_window(rowptr, n_rows, wave_row_of(rowptr, n_rows, base, __builtin_amdgcn_readlane(e, __ffsll((long long)still) - 1)));
+        } else {
+            w.start = __builtin_amdgcn_readlane(w.end, 63);
+            w.end = w.next;
+            w.base = base;
+            w.next = row_end(rowptr, n_rows, (uint32_t)base + (uint32_t)(threadIdx.x & 63) + 64u);
+        }
     }
 }
 
@@ -105,6 +126,7 @@ static int launch_count_columns(const int32_t* colidx, int64_t n_cols, int64_t n
 // Edge values.  A wavefront takes `steps` * 64 consecutive edges, one step after the other: eight steps pay for the search of
 // its first row, but while there are fewer steps in all than wavefronts that fill the chip, every step is a wavefront.
 constexpr int kNormSteps = 8;
+constexpr int kNormBatch = 4;         // steps whose column counts are requested together
 __global__ __launch_bounds__(256) void normalize_kernel(int mode, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                         int n_rows, int nnz, const int32_t* __restrict__ deg_out,
                                                         float* __restrict__ vals, int steps) {
@@ -112,21 +134,31 @@ __global__ __launch_bounds__(256) void normalize_kernel(int mode, const int32_t*
     const uint32_t at = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (uint32_t)(steps * 64);
     if (at >= (uint32_t)nnz) return;
     const int first = (int)at, left = min(nnz - first, steps * 64);
-    int row = wave_row_of(rowptr, n_rows, 0, first);
-    for (int s = 0; s < left; s += 64) {
-        const int e = first + min(s + lane, left - 1);
-        const int i = wave_rows_from(rowptr, n_rows, row, e);
-        const int di = rowptr[i + 1] - rowptr[i];
-        float v;
-        if (mode == DR_NORM_MEAN) {
-            v = (float)(1.0 / (double)di);
-        } else {
-            const int dj = deg_out[colidx[e]];
-            const double a = (double)(di > 1 ? di : 1) * (double)(dj > 1 ? dj : 1);
-            v = (float)(1.0 / sqrt(a));
+    RowWindow win = row_window(rowptr, n_rows, wave_row_of(rowptr, n_rows, 0, first));
+    for (int s0 = 0; s0 < left; s0 += 64 * kNormBatch) {
+        int dj[kNormBatch];
+        if (mode != DR_NORM_MEAN) {
+#pragma unroll
+            for (int u = 0; u < kNormBatch; ++u) dj[u] = colidx[first + min(s0 + 64 * u + lane, left - 1)];
+#pragma unroll
+            for (int u = 0; u < kNormBatch; ++u) dj[u] = deg_out[dj[u]];
         }
-        if (s + lane < left) vals[e] = v;
-        row = __builtin_amdgcn_readlane(i, 63);
+#pragma unroll
+        for (int u = 0; u < kNormBatch; ++u) {
+            const int s = s0 + 64 * u;
+            if (s >= left) break;
+            const int e = first + min(s + lane, left - 1);
+            int di;
+            wave_rows(rowptr, n_rows, win, e, &di);
+            float v;
+            if (mode == DR_NORM_MEAN) {
+                v = (float)(1.0 / (double)di);
+            } else {
+                const double a = (double)(di > 1 ? di : 1) * (double)(dj[u] > 1 ? dj[u] : 1);
+                v = (float)(1.0 / sqrt(a));
+            }
+            if (s + lane < left) vals[e] = v;
+        }
     }
 }
 
@@ -210,6 +242,7 @@ struct PartSeg {
     int tile0, scan0, col0;            // first workgroup of this relation in the launches of steps 1 and 3 / 2 / 4
 };
 constexpr int kMaxPartSegs = 4;
+constexpr int kPartBatch = 8;      // loads of entries a lane has in flight: a wavefront's stretch is 8 to 12 steps of 64
 struct PartBatch { PartSeg s[kMaxPartSegs]; int n; };
 
 // inclusive scan of one value per thread of the workgroup; every thread gets its own prefix
@@ -236,35 +269,51 @@ __global__ __launch_bounds__(kPartThreads) void part_count_kernel(PartBatch b) {
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].tile0) ++q;
     const PartSeg& g = b.s[q];
     const int tile = blockIdx.x - g.tile0;
+    const PartRange r = part_tile(g.p, g.nnz, tile);        // not empty
+    const int32_t* const col = g.colidx + r.begin;
+    int c[kPartBatch];                                      // the first loads fly while the counters are cleared
+#pragma unroll
+    for (int u = 0; u < kPartBatch; ++u) c[u] = col[min((int)threadIdx.x + u * kPartThreads, r.len - 1)];
     for (int i = threadIdx.x; i < g.p.nb_pad; i += kPartThreads) cnt[i] = 0u;
     __syncthreads();
-    const PartRange r = part_tile(g.p, g.nnz, tile);
-    const int32_t* const col = g.colidx + r.begin;
-    for (int i = threadIdx.x; i < r.len; i += 4 * kPartThreads) {          // four loads in flight
-        int c[4];
+    for (int i = threadIdx.x; i < r.len; i += kPartBatch * kPartThreads) {
+        int next[kPartBatch];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = col[min(i + u * kPartThreads, r.len - 1)];
+        for (int u = 0; u < kPartBatch; ++u) next[u] = col[min(i + (kPartBatch + u) * kPartThreads, r.len - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < kPartBatch; ++u) {
             if (i + u * kPartThreads < r.len) atomicAdd(&cnt[c[u] >> g.p.shift], 1u);
+            c[u] = next[u];
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < g.p.nb_pad; i += kPartThreads) g.hist[(size_t)tile * g.p.nb_pad + i] = cnt[i];
 }
 
-// 64 buckets per workgroup (one per lane); the 16 wavefronts split the tiles
+// 64 buckets per workgroup (one per lane); the 16 wavefronts split the tiles.  There are only a handful of workgroups: the
+// time is that of the chain of loads, so a wavefront requests all its counts at once and keeps them.
+constexpr int kScanPer = kMaxTiles / 16;
 __global__ __launch_bounds__(1024) void part_scan_kernel(PartBatch b) {
     __shared__ uint32_t sum[16][64];
     int q = 0;
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].scan0) ++q;
     const PartSeg& g = b.s[q];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int per = (g.p.n_tiles + 15) / 16;
-    const int t0 = min(wave * per, g.p.n_tiles), t1 = min(t0 + per, g.p.n_tiles);
-    uint32_t* h = g.hist + (blockIdx.x - g.scan0) * 64 + lane;
-    uint32_t s = 0;
-#pragma unroll 8
-    for (int t = t0; t < t1; ++t) s += h[(size_t)t * g.p.nb_pad];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_tiles = g.p.n_tiles, nb_pad = g.p.nb_pad, per = (n_tiles + 15) / 16;       // per <= kScanPer
+    const int t0 = min(wave * per, n_tiles), n = min(per, n_tiles - t0);
+    uint32_t* const h = g.hist + (blockIdx.x - g.scan0) * 64 + lane + (size_t)t0 * nb_pad;
+    uint32_t v[kScanPer], s = 0;
+#pragma unroll
+    for (int j = 0; j < kScanPer; j += 8) {
+#pragma unroll
+        for (int u = j; u < j + 8; ++u) v[u] = 0u;
+        if (j < n) {
+#pragma unroll
+            for (int u = j; u < j + 8; ++u) v[u] = h[(size_t)min(u, n - 1) * nb_pad];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) s += u < n ? v[u] : 0u;
     sum[wave][lane] = s;
     __syncthreads();
     uint32_t run = 0, total = 0;
@@ -273,11 +322,10 @@ __global__ __launch_bounds__(1024) void part_scan_kernel(PartBatch b) {
         run += w < wave ? sum[w][lane] : 0u;
         total += sum[w][lane];
     }
-#pragma unroll 8
-    for (int t = t0; t < t1; ++t) {
-        const uint32_t v = h[(size_t)t * g.p.nb_pad];
-        h[(size_t)t * g.p.nb_pad] = run;
-        run += v;
+#pragma unroll
+    for (int u = 0; u < kScanPer; ++u) {
+        if (u < n) h[(size_t)u * nb_pad] = run;
+        run += v[u];
     }
     if (wave == 0) g.totals[(blockIdx.x - g.scan0) * 64 + lane] = total;
 }
@@ -304,70 +352,82 @@ __global__ __launch_bounds__(kPartThreads) void part_scatter_kernel(PartBatch b)
     const PartSeg& g = b.s[q];
     const int tile = blockIdx.x - g.tile0, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nbp = g.p.nb_pad, shift = g.p.shift;
+    constexpr int kPer = kMaxBuckets / kPartThreads;
+    uint32_t total[kPer], prefix[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x * kPer + u;
+        total[u] = i < nbp ? g.totals[i] : 0u;
+        prefix[u] = i < nbp ? g.hist[(size_t)tile * nbp + i] : 0u;
+    }
     for (int i = threadIdx.x; i < kPartWaves * nbp; i += kPartThreads) cnt[i] = 0u;
     __syncthreads();
     const PartRange r = part_tile_wave(g.p, g.nnz, tile, wave);
     const int32_t* const col = g.colidx + r.begin;
     uint32_t* const mine = cnt + wave * nbp;
-    for (int i = lane; i < r.len; i += 4 * 64) {
-        int c[4];
+    for (int i = lane; i < r.len; i += kPartBatch * 64) {
+        int c[kPartBatch];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = col[min(i + u * 64, r.len - 1)];
+        for (int u = 0; u < kPartBatch; ++u) c[u] = col[min(i + u * 64, r.len - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < kPartBatch; ++u)
             if (i + u * 64 < r.len) atomicAdd(&mine[c[u] >> shift], 1u);
     }
     __syncthreads();
     // first place of (bucket, wavefront): bucket start + what earlier workgroups and earlier wavefronts put there
     {
-        constexpr int kPer = kMaxBuckets / kPartThreads;
-        uint32_t t[kPer], sum = 0;
+        uint32_t sum = 0;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = threadIdx.x * kPer + u;
-            t[u] = i < nbp ? g.totals[i] : 0u;
-            sum += t[u];
-        }
+        for (int u = 0; u < kPer; ++u) sum += total[u];
         uint32_t run = part_scan_inclusive(sum, sm) - sum;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int i = threadIdx.x * kPer + u;
             if (i < nbp) {
-                uint32_t at = run + g.hist[(size_t)tile * nbp + i];
+                uint32_t at = run + prefix[u];
                 for (int w = 0; w < kPartWaves; ++w) {
                     const uint32_t n = cnt[w * nbp + i];
                     cnt[w * nbp + i] = at;
                     at += n;
                 }
             }
-            run += t[u];
+            run += total[u];
         }
     }
     __syncthreads();
     if (r.len <= 0) return;
     const int nbits = 32 - __builtin_clz(max(g.p.nb - 1, 1));
     const bool records = !g.count_only;
-    int row = records ? wave_row_of(g.rowptr, g.n_rows, 0, r.begin) : 0;
-    int c = col[min(lane, r.len - 1)];
-    for (int s = 0; s < r.len; s += 64) {
-        const int i_e = min(s + lane, r.len - 1), e = r.begin + i_e;
-        const bool on = s + lane < r.len;
-        const int c_next = col[min(i_e + 64, r.len - 1)];
-        const uint32_t d = (uint32_t)c >> shift;
-        const unsigned long long m = same_digit(d, nbits, on);
-        const uint32_t at = mine[d];
-        const int before = bits_below(m);
-        __builtin_amdgcn_wave_barrier();                    // one wavefront's LDS accesses run in program order
-        if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
-        __builtin_amdgcn_wave_barrier();
-        if (records) {
-            const int i = wave_rows_from(g.rowptr, g.n_rows, row, e);
-            const float v = g.vals ? g.vals[e] : 0.0f;
-            if (on) g.rec[at + before] = make_int2(i, __float_as_int(v));
-            row = __builtin_amdgcn_readlane(i, 63);
+    RowWindow win{};
+    if (records) win = row_window(g.rowptr, g.n_rows, wave_row_of(g.rowptr, g.n_rows, 0, r.begin));
+    for (int s0 = 0; s0 < r.len; s0 += kPartBatch * 64) {
+        int c[kPartBatch];
+        float v[kPartBatch];
+#pragma unroll
+        for (int u = 0; u < kPartBatch; ++u) {
+            const int i = min(s0 + u * 64 + lane, r.len - 1);
+            c[u] = col[i];
+            v[u] = records && g.vals ? g.vals[r.begin + i] : 0.0f;
         }
-        if (on) g.key[at + before] = c;
-        c = c_next;
+#pragma unroll
+        for (int u = 0; u < kPartBatch; ++u) {
+            const int s = s0 + u * 64;
+            if (s >= r.len) break;
+            const bool on = s + lane < r.len;
+            const uint32_t d = (uint32_t)c[u] >> shift;
+            const unsigned long long m = same_digit(d, nbits, on);
+            const uint32_t at = mine[d];
+            const int before = bits_below(m);
+            __builtin_amdgcn_wave_barrier();                // one wavefront's LDS accesses run in program order
+            if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
+            __builtin_amdgcn_wave_barrier();
+            if (records) {
+                int len;
+                const int i = wave_rows(g.rowptr, g.n_rows, win, r.begin + min(s + lane, r.len - 1), &len);
+                if (on) g.rec[at + before] = make_int2(i, __float_as_int(v[u]));
+            }
+            if (on) g.key[at + before] = c[u];
+        }
     }
 }
 
@@ -397,12 +457,12 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
     uint32_t* const mine = cnt + wave * sub;
     const int32_t* key = g.key + begin + w.begin;
     uint32_t earlier = 0;                                   // records of the bucket in columns before this workgroup's
-    for (int i = lane; i < w.len; i += 4 * 64) {
-        int c[4];
+    for (int i = lane; i < w.len; i += kPartBatch * 64) {
+        int c[kPartBatch];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c[u] = key[min(i + u * 64, w.len - 1)] - first;
+        for (int u = 0; u < kPartBatch; ++u) c[u] = key[min(i + u * 64, w.len - 1)] - first;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < kPartBatch; ++u)
             if (i + u * 64 < w.len) {
                 if (c[u] >= 0 && c[u] < ncol) atomicAdd(&mine[c[u]], 1u);
                 earlier += c[u] < 0 ? 1u : 0u;
@@ -449,21 +509,31 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
     if (first + ncol == g.n_cols && threadIdx.x == 0) g.t_rowptr[g.n_cols] = g.nnz;
     __syncthreads();
     const int2* rec = g.rec + begin + w.begin;
-    for (int s = 0; s < w.len; s += 64) {
-        const int i = min(s + lane, w.len - 1);
-        const int c = key[i] - first;
-        const bool on = s + lane < w.len && c >= 0 && c < ncol;
-        const int2 r = rec[i];
-        const uint32_t d = on ? (uint32_t)c : 0u;
-        const unsigned long long m = same_digit(d, g.p.sub_shift, on);
-        const uint32_t at = mine[d];
-        const int before = bits_below(m);
-        __builtin_amdgcn_wave_barrier();
-        if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
-        __builtin_amdgcn_wave_barrier();
-        if (on) {
-            g.t_colidx[at + before] = r.x;
-            if (g.t_vals) g.t_vals[at + before] = __int_as_float(r.y);
+    for (int s0 = 0; s0 < w.len; s0 += kPartBatch * 64) {
+        int col[kPartBatch];
+        int2 r[kPartBatch];
+#pragma unroll
+        for (int u = 0; u < kPartBatch; ++u) {
+            const int i = min(s0 + u * 64 + lane, w.len - 1);
+            col[u] = key[i] - first;
+            r[u] = rec[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kPartBatch; ++u) {
+            if (s0 + u * 64 >= w.len) break;
+            const int c = col[u];
+            const bool on = s0 + u * 64 + lane < w.len && c >= 0 && c < ncol;
+            const uint32_t d = on ? (uint32_t)c : 0u;
+            const unsigned long long m = same_digit(d, g.p.sub_shift, on);
+            const uint32_t at = mine[d];
+            const int before = bits_below(m);
+            __builtin_amdgcn_wave_barrier();
+            if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
+            __builtin_amdgcn_wave_barrier();
+            if (on) {
+                g.t_colidx[at + before] = r[u].x;
+                if (g.t_vals) g.t_vals[at + before] = __int_as_float(r[u].y);
+            }
         }
     }
 }
