@@ -49,6 +49,14 @@ __device__ __forceinline__ int wave_row_of(const int32_t* __restrict__ rowptr, i
     return lo;
 }
 
+// the same for an edge that is likely to lie within the next 4096 rows: at most 64 rows before the edge's, after one load
+__device__ __forceinline__ int wave_row_ahead(const int32_t* __restrict__ rowptr, int n_rows, int lo, int e) {
+    const long long p = (long long)lo + 64ll * ((threadIdx.x & 63) + 1);
+    const bool below = p < n_rows && rowptr[p < n_rows ? (int)p : lo] <= e;
+    const int n = __popcll(__ballot(below));
+    return n < 64 ? lo + 64 * n : wave_row_of(rowptr, n_rows, lo + 64 * 64, e);
+}
+
 // The row ends a wavefront has at hand, kept from one step to the next: lane l holds the end of row base + l, and of the row
 // 64 further on.  64 row ends serve a dozen steps where rows have a dozen edges; loaded anew for every step they were a
 // dependent load per step, which is what these kernels waited for.
@@ -221,10 +229,14 @@ int launch_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64
 // In steps 3 and 4 a wavefront takes a contiguous stretch of entries, 64 at a time; lanes with the same digit find each
 // other with one ballot per digit bit, so an entry's place is the wavefront's running count of its digit (LDS) plus the
 // number of lower lanes with the same digit: the order of equal digits is kept, and there are no atomics on memory.
-// Bound by memory traffic, 44 bytes per entry: column twice, value, record out and in, result.  (Before: one slot per
-// entry by an atomic cursor and a ranking of every segment afterwards.  The random atomics, one binary search per entry
-// and the ranking of the segments of high-fanout nets took 0.30 / 0.20 / 0.24 ms for the three relations of a
-// 250 000-cell graph with 3.0 / 1.2 / 1.2 M entries.)
+// 44 bytes per entry move: column twice, value, record out and in, result.  Entries are put in order in LDS before they are
+// written (steps 3 and 4): one by one, random columns made a memory transaction of every 4- or 8-byte store, and those bounded
+// both steps.  Edge values and transposes of the three relations, before / after: 250 000 cells (3.0 / 1.2 / 1.2 M entries)
+// 243 / 232 us, 500 000 cells 431 / 334 (with all of this file's changes to step 2 and the row ends), 1.1 M cells 1455 / 1067.
+// What bounds it now: 19 launches of 4 to 33 us one behind the other, each a chain of a dozen waits.
+// (Earlier: one slot per entry by an atomic cursor and a ranking of every segment afterwards.  The random atomics, one binary
+// search per entry and the ranking of the segments of high-fanout nets took 0.30 / 0.20 / 0.24 ms for the three relations of a
+// 250 000-cell graph.)
 // All three relations of a context go through one set of launches.
 // ---------------------------------------------------------------------------------------------------
 
@@ -242,7 +254,7 @@ struct PartSeg {
     int tile0, scan0, col0;            // first workgroup of this relation in the launches of steps 1 and 3 / 2 / 4
 };
 constexpr int kMaxPartSegs = 4;
-constexpr int kPartBatch = 8;      // loads of entries a lane has in flight: a wavefront's stretch is 8 to 12 steps of 64
+constexpr int kPartBatch = 4;      // loads of entries a lane has in flight
 struct PartBatch { PartSeg s[kMaxPartSegs]; int n; };
 
 // inclusive scan of one value per thread of the workgroup; every thread gets its own prefix
@@ -269,20 +281,21 @@ __global__ __launch_bounds__(kPartThreads) void part_count_kernel(PartBatch b) {
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].tile0) ++q;
     const PartSeg& g = b.s[q];
     const int tile = blockIdx.x - g.tile0;
-    const PartRange r = part_tile(g.p, g.nnz, tile);        // not empty
+    const PartRange r = part_tile_wave(g.p, g.nnz, tile, threadIdx.x >> 6);     // may be empty in the last tile: begins past 0 then
+    const int lane = threadIdx.x & 63;
     const int32_t* const col = g.colidx + r.begin;
     int c[kPartBatch];                                      // the first loads fly while the counters are cleared
 #pragma unroll
-    for (int u = 0; u < kPartBatch; ++u) c[u] = col[min((int)threadIdx.x + u * kPartThreads, r.len - 1)];
+    for (int u = 0; u < kPartBatch; ++u) c[u] = col[min(lane + u * 64, r.len - 1)];
     for (int i = threadIdx.x; i < g.p.nb_pad; i += kPartThreads) cnt[i] = 0u;
     __syncthreads();
-    for (int i = threadIdx.x; i < r.len; i += kPartBatch * kPartThreads) {
+    for (int i = lane; i < r.len; i += kPartBatch * 64) {
         int next[kPartBatch];
 #pragma unroll
-        for (int u = 0; u < kPartBatch; ++u) next[u] = col[min(i + (kPartBatch + u) * kPartThreads, r.len - 1)];
+        for (int u = 0; u < kPartBatch; ++u) next[u] = col[min(i + (kPartBatch + u) * 64, r.len - 1)];
 #pragma unroll
         for (int u = 0; u < kPartBatch; ++u) {
-            if (i + u * kPartThreads < r.len) atomicAdd(&cnt[c[u] >> g.p.shift], 1u);
+            if (i + u * 64 < r.len) atomicAdd(&cnt[c[u] >> g.p.shift], 1u);
             c[u] = next[u];
         }
     }
@@ -344,97 +357,109 @@ __device__ __forceinline__ int bits_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__global__ __launch_bounds__(kPartThreads) void part_scatter_kernel(PartBatch b) {
-    extern __shared__ uint32_t cnt[];                       // [kPartWaves][nb_pad] counts, then next free places
-    __shared__ uint32_t sm[kPartWaves];
+// A chunk of the tile is sorted by bucket in LDS and leaves in that order, so that neighbouring lanes write neighbouring records:
+// written straight from the entries' order every lane's record was a transaction of its own, and those were what the kernel
+// took (1.2 M entries into 489 buckets 28 us, whether 8 or 16 wavefronts worked on a tile; without the records 13).
+__host__ __device__ constexpr size_t scatter_lds(int nb_pad) { return 2 * (size_t)kPartWaves * nb_pad + 12 * (size_t)kChunk; }
+using Count16 = uint16_t __attribute__((may_alias));
+__global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch b) {
+    static_assert(kMaxBuckets <= kPartThreads && kChunk % kPartThreads == 0 && kChunk < 65536, "one bucket per thread, 16-bit places");
+    constexpr int kSteps = kChunk / kPartThreads;
+    extern __shared__ __align__(16) uint32_t cnt[];                       // [kPartWaves][nb_pad] 16-bit counts, then places in the chunk
     int q = 0;
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].tile0) ++q;
     const PartSeg& g = b.s[q];
-    const int tile = blockIdx.x - g.tile0, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nbp = g.p.nb_pad, shift = g.p.shift;
-    constexpr int kPer = kMaxBuckets / kPartThreads;
-    uint32_t total[kPer], prefix[kPer];
+    const int tile = blockIdx.x - g.tile0, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bucket = threadIdx.x;
+    const int nbp = g.p.nb_pad, shift = g.p.shift, nbits = 32 - __builtin_clz(max(g.p.nb - 1, 1));
+    const bool records = !g.count_only, have = bucket < nbp;
+    uint32_t* const s_key = cnt + kPartWaves * nbp / 2;      // [kChunk] columns, sorted
+    int2* const s_rec = reinterpret_cast<int2*>(s_key + kChunk);
+    uint32_t* const sm = s_key;                              // [kPartWaves] of the scans, which end before the sorting begins
+    Count16* const place = reinterpret_cast<Count16*>(cnt);
+    Count16* const mine = place + wave * nbp;
+    // where this tile's next record of the thread's bucket goes: bucket start + what earlier tiles put there
+    const uint32_t total = have ? g.totals[bucket] : 0u, prefix = have ? g.hist[(size_t)tile * nbp + bucket] : 0u;
+    uint32_t next = part_scan_inclusive(total, sm) - total + prefix;
+    const PartRange whole = part_tile(g.p, g.nnz, tile);
+    int row0 = 0;
+    for (int at_chunk = 0, k = 0; at_chunk < whole.len; at_chunk += kChunk, ++k) {
+        const PartRange chunk = part_piece(whole, k, kChunk), r = part_piece(chunk, wave, kChunk / kPartWaves);
+        int c[kSteps];
+        float v0 = 0.0f;
+        RowWindow win{};
+        for (int i = threadIdx.x; i < kPartWaves * nbp / 2; i += kPartThreads) cnt[i] = 0u;
+        if (r.len > 0) {
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int i = threadIdx.x * kPer + u;
-        total[u] = i < nbp ? g.totals[i] : 0u;
-        prefix[u] = i < nbp ? g.hist[(size_t)tile * nbp + i] : 0u;
-    }
-    for (int i = threadIdx.x; i < kPartWaves * nbp; i += kPartThreads) cnt[i] = 0u;
-    __syncthreads();
-    const PartRange r = part_tile_wave(g.p, g.nnz, tile, wave);
-    const int32_t* const col = g.colidx + r.begin;
-    uint32_t* const mine = cnt + wave * nbp;
-    for (int i = lane; i < r.len; i += kPartBatch * 64) {
-        int c[kPartBatch];
-#pragma unroll
-        for (int u = 0; u < kPartBatch; ++u) c[u] = col[min(i + u * 64, r.len - 1)];
-#pragma unroll
-        for (int u = 0; u < kPartBatch; ++u)
-            if (i + u * 64 < r.len) atomicAdd(&mine[c[u] >> shift], 1u);
-    }
-    __syncthreads();
-    // first place of (bucket, wavefront): bucket start + what earlier workgroups and earlier wavefronts put there
-    {
-        uint32_t sum = 0;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) sum += total[u];
-        uint32_t run = part_scan_inclusive(sum, sm) - sum;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = threadIdx.x * kPer + u;
-            if (i < nbp) {
-                uint32_t at = run + prefix[u];
-                for (int w = 0; w < kPartWaves; ++w) {
-                    const uint32_t n = cnt[w * nbp + i];
-                    cnt[w * nbp + i] = at;
-                    at += n;
-                }
+            for (int u = 0; u < kSteps; ++u) c[u] = g.colidx[r.begin + min(u * 64 + lane, r.len - 1)];
+            if (records) {
+                if (g.vals) v0 = g.vals[r.begin + min(lane, r.len - 1)];
+                row0 = k == 0 ? wave_row_of(g.rowptr, g.n_rows, 0, r.begin) : wave_row_ahead(g.rowptr, g.n_rows, row0, r.begin);
+                win = row_window(g.rowptr, g.n_rows, row0);
             }
-            run += total[u];
         }
-    }
-    __syncthreads();
-    if (r.len <= 0) return;
-    const int nbits = 32 - __builtin_clz(max(g.p.nb - 1, 1));
-    const bool records = !g.count_only;
-    RowWindow win{};
-    if (records) win = row_window(g.rowptr, g.n_rows, wave_row_of(g.rowptr, g.n_rows, 0, r.begin));
-    for (int s0 = 0; s0 < r.len; s0 += kPartBatch * 64) {
-        int c[kPartBatch];
-        float v[kPartBatch];
+        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kPartBatch; ++u) {
-            const int i = min(s0 + u * 64 + lane, r.len - 1);
-            c[u] = col[i];
-            v[u] = records && g.vals ? g.vals[r.begin + i] : 0.0f;
+        for (int u = 0; u < kSteps; ++u)
+            if (u * 64 + lane < r.len) {
+                const uint32_t d = (uint32_t)c[u] >> shift;
+                atomicAdd(&cnt[(wave * nbp + d) >> 1], 1u << (16 * (d & 1u)));       // nb_pad is even
+            }
+        __syncthreads();
+        uint32_t n = 0;
+        if (have)
+            for (int w = 0; w < kPartWaves; ++w) n += place[w * nbp + bucket];
+        const uint32_t local = part_scan_inclusive(n, sm) - n;
+        if (have) {
+            uint32_t at = local;
+            for (int w = 0; w < kPartWaves; ++w) {
+                const uint32_t m = place[w * nbp + bucket];
+                place[w * nbp + bucket] = (uint16_t)at;
+                at += m;
+            }
         }
-#pragma unroll
-        for (int u = 0; u < kPartBatch; ++u) {
-            const int s = s0 + u * 64;
-            if (s >= r.len) break;
+        __syncthreads();
+        // The columns of the later steps are read again, one step ahead: kept from above they and their unrolled steps take 82
+        // registers, and two workgroups no longer fit a compute unit.
+        int col = c[0];
+#pragma unroll 1
+        for (int s = 0; s < r.len; s += 64) {
+            const int e = r.begin + min(s + lane, r.len - 1), e_next = r.begin + min(s + 64 + lane, r.len - 1);
+            const int col_next = g.colidx[e_next];
+            const float v_next = records && g.vals ? g.vals[e_next] : 0.0f;
             const bool on = s + lane < r.len;
-            const uint32_t d = (uint32_t)c[u] >> shift;
+            const uint32_t d = (uint32_t)col >> shift;
             const unsigned long long m = same_digit(d, nbits, on);
             const uint32_t at = mine[d];
             const int before = bits_below(m);
             __builtin_amdgcn_wave_barrier();                // one wavefront's LDS accesses run in program order
-            if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
+            if (on && before == __popcll(m) - 1) mine[d] = (uint16_t)(at + (uint32_t)before + 1u);
             __builtin_amdgcn_wave_barrier();
             if (records) {
                 int len;
-                const int i = wave_rows(g.rowptr, g.n_rows, win, r.begin + min(s + lane, r.len - 1), &len);
-                if (on) g.rec[at + before] = make_int2(i, __float_as_int(v[u]));
+                const int i = wave_rows(g.rowptr, g.n_rows, win, e, &len);
+                if (on) s_rec[at + before] = make_int2(i, __float_as_int(v0));
             }
-            if (on) g.key[at + before] = c[u];
+            if (on) s_key[at + before] = (uint32_t)col;
+            col = col_next;
+            v0 = v_next;
         }
+        __syncthreads();
+        if (have) cnt[bucket] = next - local;               // the places are used up: from place in the chunk to place in memory
+        next += n;
+        __syncthreads();
+        for (int i = threadIdx.x; i < chunk.len; i += kPartThreads) {
+            const uint32_t key = s_key[i], at = cnt[key >> shift] + (uint32_t)i;
+            g.key[at] = (int32_t)key;
+            if (records) g.rec[at] = s_rec[i];
+        }
+        __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b) {
-    extern __shared__ uint32_t cnt[];                       // [kPartWaves][columns of this workgroup]
+__global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b, int sort_cap) {
+    extern __shared__ __align__(16) uint32_t cnt[];                       // [kPartWaves][columns of this workgroup]; [sort_cap] records
     __shared__ uint32_t sm[kPartWaves];
-    __shared__ uint32_t s_begin, s_before;
+    __shared__ uint32_t s_begin, s_before, s_total;
     int q = 0;
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].col0) ++q;
     const PartSeg& g = b.s[q];
@@ -490,7 +515,9 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
             }
             return;
         }
-        uint32_t run = (uint32_t)begin + s_before + part_scan_inclusive(sum, sm) - sum;
+        const uint32_t incl = part_scan_inclusive(sum, sm);
+        if (threadIdx.x == kPartThreads - 1) s_total = incl;
+        uint32_t run = (uint32_t)begin + s_before + incl - sum;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int i = threadIdx.x * kPer + u;
@@ -508,6 +535,10 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
     }
     if (first + ncol == g.n_cols && threadIdx.x == 0) g.t_rowptr[g.n_cols] = g.nnz;
     __syncthreads();
+    // A bucket that fits is sorted in LDS and leaves in order, coalesced; a larger one is written record by record.
+    int2* const s_out = reinterpret_cast<int2*>(cnt + kPartWaves * sub);
+    const bool sorted = n <= sort_cap;
+    const uint32_t origin = (uint32_t)begin + s_before;     // first place of this workgroup's columns
     const int2* rec = g.rec + begin + w.begin;
     for (int s0 = 0; s0 < w.len; s0 += kPartBatch * 64) {
         int col[kPartBatch];
@@ -531,10 +562,21 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b)
             if (on && before == __popcll(m) - 1) mine[d] = at + (uint32_t)before + 1u;
             __builtin_amdgcn_wave_barrier();
             if (on) {
-                g.t_colidx[at + before] = r[u].x;
-                if (g.t_vals) g.t_vals[at + before] = __int_as_float(r[u].y);
+                if (sorted) {
+                    s_out[at + before - origin] = r[u];
+                } else {
+                    g.t_colidx[at + before] = r[u].x;
+                    if (g.t_vals) g.t_vals[at + before] = __int_as_float(r[u].y);
+                }
             }
         }
+    }
+    if (!sorted) return;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < s_total; i += kPartThreads) {
+        const int2 r = s_out[i];
+        g.t_colidx[origin + i] = r.x;
+        if (g.t_vals) g.t_vals[origin + i] = __int_as_float(r.y);
     }
 }
 
@@ -572,19 +614,24 @@ static int launch_partition(PartBatch& b, hipStream_t s) {
         if ((1 << g.p.sub_shift) > sub) sub = 1 << g.p.sub_shift;
     }
     if (b.n == 0) return DR_OK;
-    const size_t lds3 = 4 * (size_t)kPartWaves * nbp, lds4 = 4 * (size_t)kPartWaves * sub;
+    // Buckets hold 2048 to 4096 entries on average unless there are too many columns for that (kMaxBuckets); 5120 leave room
+    // for their spread, and with the counters of 512 columns two workgroups fit a compute unit.
+    const int sort_cap = sub <= kMaxSub / 2 ? 5120 : 0;
+    const size_t lds3 = scatter_lds(nbp), lds4 = 4 * (size_t)kPartWaves * sub + 8 * (size_t)sort_cap;
     static PerDevice raised;
     int dev = 0, lds_max = 0;
     DRC_HIP(hipGetDevice(&dev));
-    DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // counters of kMaxSub columns and the static words pass 64 KB
+    DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // both pass 64 KB
         *n = 4 * kPartWaves * kMaxSub;
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_scatter_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)scatter_lds(kMaxBuckets)));
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, *n));
         return DR_OK;
     }));
     hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)tiles), dim3(kPartThreads), 0, s, b);
     hipLaunchKernelGGL(part_scan_kernel, dim3((unsigned)scans), dim3(1024), 0, s, b);
     hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);
-    hipLaunchKernelGGL(part_columns_kernel, dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b);
+    hipLaunchKernelGGL(part_columns_kernel, dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }

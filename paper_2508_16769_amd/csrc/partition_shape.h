@@ -15,11 +15,12 @@
 
 namespace drc {
 
-constexpr int kPartThreads = 512, kPartWaves = kPartThreads / 64;
-constexpr int kMaxBuckets = 1024;      // level-1 digits: their counters, one set per wavefront, take 32 KB of LDS
-constexpr int kMaxSub = 2048;          // columns a workgroup of the second level owns: 64 KB of LDS counters
-constexpr int kMinTile = 4096;         // entries a workgroup of the first level takes at least (512 per wavefront)
-constexpr int kMaxTiles = 512;         // two workgroups per compute unit; more would only lengthen the scan of the counts
+constexpr int kPartThreads = 1024, kPartWaves = kPartThreads / 64;
+constexpr int kMaxBuckets = 1024;      // level-1 digits: their counters (16 bits), one set per wavefront, take 32 KB of LDS
+constexpr int kMaxSub = 2048;          // columns a workgroup of the second level owns: 128 KB of LDS counters
+constexpr int kMinTile = 4096;         // entries a workgroup of the first level takes at least (256 per wavefront)
+constexpr int kChunk = kMinTile;       // entries a workgroup of the first level sorts at a time, in LDS
+constexpr int kMaxTiles = 1024;        // a chunk each up to 4.2 M entries; more would only lengthen the scan of the counts
 
 struct PartShape {
     int shift;          // bucket = column >> shift
@@ -30,7 +31,7 @@ struct PartShape {
 
 inline PartShape part_shape(int64_t n_cols, int64_t nnz) {
     PartShape p;
-    // Buckets of about 2048 entries (a second-level workgroup has four 64-entry steps per wavefront), at least 64 columns
+    // Buckets of about 2048 entries (a second-level workgroup has two 64-entry steps per wavefront), at least 64 columns
     // wide and at most kMaxBuckets of them.
     p.shift = 6;
     while (((n_cols + (int64_t(1) << p.shift) - 1) >> p.shift) > kMaxBuckets) ++p.shift;

@@ -144,3 +144,13 @@ def test_as_many_entries_as_accepted():
         e = col + (at - start[col]) * N
         assert torch.equal(got[s:s + step].to(torch.int64), e), s
         assert torch.equal(At.colidx[s:s + step].to(torch.int64), e // d), s
+
+
+@pytest.mark.parametrize("M,N,E,law", [
+    # one bucket of 64 columns at the size up to which it is sorted in LDS
+    (900, 64, 5119, "uniform"), (900, 64, 5120, "uniform"), (900, 64, 5121, "skewed_cols"),
+    # tiles of two chunks, the second partly filled; rows that end far apart between them
+    (300_000, 200_000, 4_300_000, "uniform"), (2_000_000, 200_000, 4_200_001, "tail_rows"),
+])
+def test_transpose_where_sorting_in_lds_changes(M, N, E, law):
+    test_transpose_and_values_exact(M, N, E, law)
