@@ -98,6 +98,12 @@ def test_products_at_tile_edges(D, k_near, k_pins, k_pinned, rows):
         assert np.all(np.abs(got[name] - want) <= 2 * D * 2.0 ** -23 * l1), name
 
 
+@pytest.mark.parametrize("rows", [4096, 4097])
+def test_products_where_workgroups_get_a_second_chunk(rows):
+    """128 and 129 chunks of 32 rows: up to 128, every workgroup of the weight gradients has one chunk."""
+    test_products_at_tile_edges(128, 32, 24, 40, rows)
+
+
 @pytest.mark.parametrize("D", [32, 96, 128])
 def test_ends_of_the_range(D):
     """Infinite operands give the infinities and not-a-numbers of the fp32 products, the largest finite numbers stay finite."""
