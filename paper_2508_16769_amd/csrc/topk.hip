@@ -23,7 +23,7 @@ namespace drc {
 __device__ __forceinline__ uint32_t order_key(float v) {
     uint32_t u = __float_as_uint(v);
     u = (u == 0x80000000u) ? 0u : u;                    // -0.0 ties with +0.0
-    // larger float <=> larger key; all keys > 0.  Negative values flip every bit, the others the sign bit only
+    // larger float <=> larger key; all keys of numbers > 0 (that of the not-a-number 0xffffffff is 0).  Negative values flip every bit, the others the sign bit only
     // (written without a branch: the scalar unit is what bounds this kernel).
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
@@ -339,6 +339,15 @@ template <int L, int SLOTS> struct GroupRow {
                     clo = has_lo ? clo : (float)(D - k);
                     hi = has_hi ? key_of(hif) : most + 1u;
                     chi = has_hi ? chi : (float)-k;
+                    if (__any(most == 0xffffffffu)) {         // a not-a-number of all ones: most + 1 is no key
+                        uint32_t ones = 0xffffffffu;
+                        asm volatile("" : "+v"(ones));        // counted here: hoisted out of the loop, every row would pay
+                        const int c = (int)count(ones) - k;
+                        const bool top = open && most == 0xffffffffu, ge = c >= 0;
+                        lo = top && ge ? 0xffffffffu : lo;    // hi - lo is taken modulo 2^32
+                        hi = top ? (ge ? 0u : (has_hi ? hi : 0xffffffffu)) : hi;
+                        chi = top && !ge && !has_hi ? (float)c : chi;
+                    }
                 }
                 for (; __any(open); ++trip) {
                     uint32_t next = lo + ((hi - lo) >> 1);
@@ -410,24 +419,26 @@ template <int L, int SLOTS> struct GroupRow {
         *total = (all & 0xffu) + (all >> 8 & 0xffu) + (all >> 16 & 0xffu) + (all >> 24);
         return group_before<L>(n, t) + (all << 8) + (all << 16) + (all << 24);     // at most 252: no byte runs over
     }
-    // Of the keys equal to T only the first columns are kept, k in all: the others' keys are cleared.
-    __device__ __forceinline__ void drop_ties(uint32_t T, int k, int t) {
+    // Of the keys equal to T only the first columns are kept, k in all: the others' keys are cleared.  Returns the threshold from
+    // then on: 0, the key of one not-a-number and of what is no column, becomes 1, so that what is cleared lies below it.
+    __device__ __forceinline__ uint32_t drop_ties(uint32_t T, int k, int t) {
         uint32_t above = 0;
 #pragma unroll
         for (int i = 0; i < E; ++i) above += key[i] > T ? 1u : 0u;
         const uint32_t need = (uint32_t)k - group_sum<L>(above);
         uint32_t equal;
-        const uint32_t at = starts(t, [&](int i) { return key[i] == T; }, &equal);
+        const uint32_t at = starts(t, [&](int i) { return key[i] == T; }, &equal), from = max(T, 1u);
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
             uint32_t rank = (at >> (8 * s)) & 0xffu;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool eq = key[4 * s + j] == T;
-                key[4 * s + j] = eq && rank >= need ? 0u : key[4 * s + j];
+                key[4 * s + j] = eq ? (rank < need ? from : 0u) : key[4 * s + j];
                 rank += eq ? 1u : 0u;
             }
         }
+        return from;
     }
     // kept pairs to pairs[0 .. k) of the row; `spare`: a place of this lane's own for what is not kept
     __device__ __forceinline__ void place(uint32_t T, uint32_t at, int t, uint2* pairs, uint2* spare) const {
@@ -474,9 +485,9 @@ __global__ __launch_bounds__(256) void topk_groups_kernel(TopkArgs args) {
     auto select = [&](int k, float* __restrict__ vals, uint16_t* __restrict__ idx, const FirstGuess& guess) {
         bool ties;
         uint32_t at, kept;
-        const uint32_t T = row.threshold(k, t, D, row.guide(t, D, guess), &at, &ties);
+        uint32_t T = row.threshold(k, t, D, row.guide(t, D, guess), &at, &ties);
         if (ties) {
-            row.drop_ties(T, k, t);
+            T = row.drop_ties(T, k, t);
             at = row.starts(t, [&](int i) { return row.key[i] >= T; }, &kept);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // one wavefront's LDS accesses run in program order

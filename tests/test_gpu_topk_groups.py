@@ -82,3 +82,28 @@ def test_alignment_of_inputs_and_outputs(D, k):
         assert np.array_equal(host_idx(idx), wi) and np.array_equal(vals.cpu().numpy(), wv)
         assert bool((vb[shift_v + n * k:] == 7).all()) and bool((vb[:shift_v] == 7).all())
         assert bool((ib[shift_i + n * k:] == 7).all()) and bool((ib[:shift_i] == 7).all())
+
+
+@pytest.mark.parametrize("n", [67, 33_003])
+@pytest.mark.parametrize("D", [32, 36, 64, 100, 128])
+def test_not_a_number_rows_stay_to_themselves(D, n):
+    """Memory filled with 0xFF, and other not-a-numbers whose keys are the ends of the key range, beside ordinary rows: those
+    are exact, and every row keeps k columns of its own (positive not-a-numbers above all, negative ones below all)."""
+    rng = np.random.default_rng(D + n)
+    for k in (1, D // 4, D):
+        say(f"topk not-a-numbers D={D} n={n} k={k}")
+        X = _rows(rng, n, D, "normal")
+        u = X.view(np.uint32)
+        u[1::5] = 0xffffffff
+        part = rng.random((len(u[2::5]), D)) < rng.random((len(u[2::5]), 1))
+        u[2::5][part] = 0xffffffff
+        u[3::10] = 0x7fffffff
+        u[8::10] = rng.choice(np.array([0xffffffff, 0x7fffffff, 0xfffffffe, 0x7f800000, 0], np.uint32), u[8::10].shape)
+        plain = np.where(X == 0, np.uint32(0), u)
+        key = np.where(plain >> 31 != 0, ~plain, plain | np.uint32(0x80000000)).astype(np.int64)
+        cols = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+        vals = torch.full((n, k), 7.0, device="cuda")
+        idx = torch.full((n, k), -1, dtype=torch.int16, device="cuda")
+        P.dr_topk(dev(X), k, vals, idx)
+        assert np.array_equal(host_idx(idx), cols)
+        assert np.array_equal(vals.cpu().numpy().view(np.uint32), np.take_along_axis(u, cols, axis=1))
