@@ -210,15 +210,19 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
 // with k = 32, where under 2 probes and 4 steps do.  (A guess from the rows before instead: 2 to 6 % slower, and no guess at all
 // where the scale changes.)  Rows that are still far after kGuided probes (skewed data) go on with a bracket in key space,
 // halved and interpolated in turn, whose ends are moved to keys of the row, so that few distinct values take few probes; and
-// when the number of keys that would be kept is not k (equal keys were walked over), that search goes on to the end.
+// when the number of keys that would be kept is not k (equal keys were walked over), that search goes on to the end.  A wavefront
+// whose rows needed that from far away begins its later trips where T was, drifting with it, for as long as this serves.
 //   Ties at T are told apart in a branch of their own (by clearing the keys that lose), so the usual row does not pay.
 //   Compaction.  The kept counts of a lane's slots travel as four bytes of one register through one scan over the lanes.  Kept
 // (value, column) pairs are placed in LDS, and the rows' pairs, which lie behind one another in memory, leave as whole
 // 16- and 8-byte stores.
 // At D = 128 bound by HBM: 1.2 M and 0.9 M rows, k = 32, together 372 -> 270 us (5.5 TB/s); 430 000 rows 91 -> 64 us.  At D = 64
 // still by its instructions: 100 000 rows, k = 16, 22 -> 13 us; 3072 rows 5.4 -> 3.9 us; two selections at D = 96, 58 000 rows,
-// 32 -> 18 us.  Other data (250 000 x 128, k = 32): normal 55 -> 41, values rounded to halves 130 -> 91, zeros and ones 115 -> 62,
-// exp(2 N) 63 -> 67, uniform with outliers of 1e6 55 -> 72.
+// 32 -> 18 us.  Other data, one row per wavefront / now (k = 32, D = 128): 1.2 M rows normal 226 -> 197 us,
+// exp(2 N) 270 -> 242 (305 without the trace), uniform with 2 % outliers of 1e6 210 -> 184 (335), Cauchy 254 -> 216 (300), two narrow
+// peaks 253 -> 184 (303); 250 000 rows, values rounded to halves 128 -> 87, zeros and ones 116 -> 64, outliers 53 -> 54, exp(2 N)
+// 65 -> 60.  Where wavefronts have one trip only (65 000 rows at this width) such rows cost more than with a wavefront each:
+// 20 000 rows with outliers 8.5 -> 11.3, Cauchy 9.5 -> 10.0; 45 677 x 100 with outliers 14.3 -> 18.0.
 // ---------------------------------------------------------------------------------------------------
 template <int CTRL> __device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
@@ -260,10 +264,13 @@ __device__ __forceinline__ uint32_t key_of(float v) {       // order_key in thre
     const uint32_t u = __float_as_uint(v + 0.0f);
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
+__device__ __forceinline__ float value_of(uint32_t key) { return __uint_as_float(key ^ (~(uint32_t)((int32_t)key >> 31) | 0x80000000u)); }
 constexpr int kGuided = 3, kWalk = 4;        // guided probes at most; distance from which keys are walked
 constexpr int kGroupBlocks = 2048;           // eight workgroups per compute unit
 constexpr int64_t kFewRows = 32768;
 struct Guide { float at, gap; };            // where T is looked for first, and the distance between neighbouring values there
+// The same from the rows of the trips before.  `lost`: a row had to go on with a bracket from far away.
+struct Trace { Guide g; bool on, lost; };
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 template <int L, int SLOTS> struct GroupRow {
@@ -294,8 +301,11 @@ template <int L, int SLOTS> struct GroupRow {
         *above = ~group_max<L>(~a);
     }
     // k-th largest key, and where each slot's kept keys go (starts)
-    __device__ __forceinline__ uint32_t threshold(int k, int t, int D, const Guide& guide, uint32_t* at, bool* ties) {
-        float lof = -__builtin_inff(), hif = __builtin_inff(), candf = guide.at;
+    // TRACE: 0 none, 1 notes whether one is called for, 2 follows it.
+    template <int TRACE>
+    __device__ __forceinline__ uint32_t threshold(int k, int t, int D, const FirstGuess& f, Trace& trace, uint32_t* at, bool* ties) {
+        Guide g = TRACE == 2 && trace.on ? trace.g : guide(t, D, f);
+        float lof = -__builtin_inff(), hif = __builtin_inff(), candf = g.at;
         float clo = 0.0f, chi = 0.0f;                         // counts less k
         uint32_t cand = key_of(candf);
         int d;                                                // keys at or above cand, less k
@@ -314,7 +324,7 @@ template <int L, int SLOTS> struct GroupRow {
             const float df = (float)d;
             const float width = hif - lof;                    // infinite until both sides have been probed
             const float inside = lof + width * ((clo + 0.5f) * __builtin_amdgcn_rcpf(clo - chi + 1.0f));
-            const float outside = candf + guide.gap * (df + (d >= 0 ? 0.5f : -0.5f)) * (float)(it + 1);
+            const float outside = candf + g.gap * (df + (d >= 0 ? 0.5f : -0.5f)) * (float)(it + 1);
             const float next = fabsf(width) < __builtin_inff() ? inside : outside;
             candf = far ? next : candf;
             cand = key_of(candf);
@@ -323,6 +333,7 @@ template <int L, int SLOTS> struct GroupRow {
         bool open = abs(d) > kWalk;
         for (int reach = kWalk, trip = 0;; reach = 0) {
             if (__any(open)) {
+                const bool lost = TRACE != 0 && reach != 0 && __any(abs(d) > 2 * kWalk);
                 if (hi == 0u) {                               // the probes so far, else the row's least and greatest key
                     uint32_t least = 0xffffffffu, most = 0u;
 #pragma unroll
@@ -370,6 +381,12 @@ template <int L, int SLOTS> struct GroupRow {
                     d = open && met ? 0 : d;                  // nothing to walk: what is kept is counted below
                     open = open && !met && abs(d) > reach;
                 }
+                if (lost && __any(hi - lo > 1u)) {            // the distance of values near T
+                    const float near = (value_of(hi) - value_of(lo)) * __builtin_amdgcn_rcpf(clo - chi);
+                    g.gap = hi - lo > 1u && near < __builtin_inff() ? near : g.gap;
+                    trace.lost = true;
+                    if constexpr (TRACE == 1) trace.g.gap = g.gap;
+                }
             }
             for (int it = 0; it < reach && __any(d != 0); ++it) {
                 uint32_t below, above;
@@ -382,6 +399,7 @@ template <int L, int SLOTS> struct GroupRow {
             *ties = __any(open);
             if (reach == 0 || !*ties) break;
         }
+        if constexpr (TRACE == 2) trace.g = g;
         return cand;
     }
     // Where to begin: as if its values were normally distributed.
@@ -482,10 +500,20 @@ __global__ __launch_bounds__(256) void topk_groups_kernel(TopkArgs args) {
         }
     };
     Row row;
-    auto select = [&](int k, float* __restrict__ vals, uint16_t* __restrict__ idx, const FirstGuess& guess) {
+    Trace trace{};
+    auto select = [&](int k, float* __restrict__ vals, uint16_t* __restrict__ idx, const FirstGuess& guess, auto how) __attribute__((always_inline)) {
+        constexpr int TRACE = decltype(how)::value;
         bool ties;
         uint32_t at, kept;
-        uint32_t T = row.threshold(k, t, D, row.guide(t, D, guess), &at, &ties);
+        uint32_t T = row.template threshold<TRACE>(k, t, D, guess, trace, &at, &ties);
+        if (TRACE == 2 || (TRACE == 1 && trace.lost)) {
+            // Taken up when it is called for, left when it leads astray itself.  Rows with equal values at T leave none: they are as
+            // far from there the next time.
+            const float x = value_of(T), to = trace.on ? trace.g.at + 0.25f * (x - trace.g.at) : x;
+            trace.g.at = fabsf(to) < __builtin_inff() ? to : 0.0f;
+            trace.on = trace.on ? !trace.lost : trace.lost && !ties;
+            trace.lost = false;
+        }
         if (ties) {
             T = row.drop_ties(T, k, t);
             at = row.starts(t, [&](int i) { return row.key[i] >= T; }, &kept);
@@ -518,20 +546,34 @@ __global__ __launch_bounds__(256) void topk_groups_kernel(TopkArgs args) {
     };
     if (row0 >= (uint32_t)n) return;
     load(row0);
-    for (;; row0 += stride) {
+    // true: no row is left; false: the trips to come follow a trace
+    auto trips = [&](auto how) __attribute__((always_inline)) {
+        constexpr int TRACE = decltype(how)::value;
+        for (;; row0 += stride) {
 #pragma unroll
-        for (int i = 0; i < Row::E; ++i) row.v[i] = next[i / 4][i & 3];
-        const bool more = (uint32_t)n - row0 > stride;
-        if (more) load(row0 + stride);                        // in flight while these rows are selected
-        row.make_keys(t, D);
-        const bool ties = select(seg.k, seg.vals, seg.idx, seg.guess);
-        if constexpr (DUAL) {
-            if (seg.vals2) {
-                if (ties) row.make_keys(t, D);
-                select(seg.k2, seg.vals2, seg.idx2, seg.guess2);
+            for (int i = 0; i < Row::E; ++i) row.v[i] = next[i / 4][i & 3];
+            const bool more = (uint32_t)n - row0 > stride;
+            if (more) load(row0 + stride);                    // in flight while these rows are selected
+            row.make_keys(t, D);
+            const bool ties = select(seg.k, seg.vals, seg.idx, seg.guess, how);
+            if constexpr (DUAL) {
+                if (seg.vals2) {
+                    if (ties) row.make_keys(t, D);
+                    select(seg.k2, seg.vals2, seg.idx2, seg.guess2, how);
+                }
             }
+            if (!more) return true;
+            if (TRACE == 1 && trace.on) break;
         }
-        if (!more) break;
+        row0 += stride;
+        return false;
+    };
+    // A trace takes registers (two selections have none to spare) and pays from the second trip on (16 lanes a row have one) where the
+    // search is long; its loop is one of its own because the other's rows would pay for a test and two selects (2 %).
+    if constexpr (!DUAL && L < 16 && SLOTS == 4) {
+        if (!trips(std::integral_constant<int, 1>{})) trips(std::integral_constant<int, 2>{});
+    } else {
+        trips(std::integral_constant<int, 0>{});
     }
 }
 

@@ -107,3 +107,27 @@ def test_not_a_number_rows_stay_to_themselves(D, n):
         P.dr_topk(dev(X), k, vals, idx)
         assert np.array_equal(host_idx(idx), cols)
         assert np.array_equal(vals.cpu().numpy().view(np.uint32), np.take_along_axis(u, cols, axis=1))
+
+
+def _check_on_gpu(X, k, vals, idx):
+    """Against torch's stable sort of the whole rows (finite or infinite values; -0 ties with +0)."""
+    cols = torch.sort(-(X + 0.0), dim=1, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(idx.to(torch.int64), cols)
+    assert torch.equal(vals.view(torch.int32), torch.gather(X, 1, cols).view(torch.int32))
+
+
+@pytest.mark.parametrize("n,D,k", [(280_003, 64, 8), (140_003, 100, 25), (210_011, 128, 32)])
+def test_trips_that_follow_a_trace(n, D, k):
+    """Rows no guess from their moments serves, for two and more trips of a wavefront; then rows of another law and scale."""
+    say(f"topk trace n={n} D={D} k={k}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    X = torch.rand((n, D), device="cuda", generator=gen)
+    big = torch.rand((n, D), device="cuda", generator=gen) < 0.02
+    X = torch.where(big, 1e6 * torch.randn((n, D), device="cuda", generator=gen), X)
+    X[-n // 4:] = torch.exp(3 * torch.randn((n // 4 + 1, D), device="cuda", generator=gen))
+    X[-n // 8:] *= 1e-6
+    X[::11] = torch.round(4 * X[::11])
+    vals, idx = torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int16, device="cuda")
+    P.dr_topk(X, k, vals, idx)
+    _check_on_gpu(X, k, vals, idx)
