@@ -57,7 +57,7 @@ def test_selection_at_the_edges_of_the_lane_groups(D, kind):
 def test_later_trips_of_a_wavefront(n, D, k):
     say(f"topk groups n={n} D={D} k={k}")
     X = _rows(np.random.default_rng(n), n, D, "normal")
-    X[n // 2:] *= 1000.0                                    # the guess learnt on the rows before is of no use here
+    X[n // 2:] *= 1000.0                                    # rows of another scale in the same launch
     wv, wi = _expected(X, k)
     vals, idx = torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int16, device="cuda")
     P.dr_topk(dev(X), k, vals, idx)
@@ -131,3 +131,44 @@ def test_trips_that_follow_a_trace(n, D, k):
     vals, idx = torch.empty((n, k), device="cuda"), torch.empty((n, k), dtype=torch.int16, device="cuda")
     P.dr_topk(X, k, vals, idx)
     _check_on_gpu(X, k, vals, idx)
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "skewed", "hard"])
+@pytest.mark.parametrize("D", [4, 32, 36, 64, 68, 96, 100, 128])
+def test_selection_where_fewer_lanes_share_a_row(D, kind):
+    """From 32768 rows on a row has 4 or 8 lanes; rows that are no whole number of wavefronts, widths that leave lanes without a
+    column, outputs that take no wide stores."""
+    rng = np.random.default_rng(1000 + D)
+    for n, shift in ((32_768, 0), (33_003, 1)):
+        X = dev(_rows(rng, n, D, kind))
+        for k in sorted({1, D // 4 + 1, D}):
+            say(f"topk lanes D={D} n={n} k={k} {kind}")
+            vb, ib = torch.full((n * k + 8,), 7.0, device="cuda"), torch.full((n * k + 8,), 7, dtype=torch.int16, device="cuda")
+            vals, idx = vb[shift:shift + n * k].view(n, k), ib[shift:shift + n * k].view(n, k)
+            P.dr_topk(X, k, vals, idx)
+            _check_on_gpu(X, k, vals, idx)
+            assert bool((vb[shift + n * k:] == 7).all()) and bool((vb[:shift] == 7).all())
+            assert bool((ib[shift + n * k:] == 7).all()) and bool((ib[:shift] == 7).all())
+
+
+@pytest.mark.parametrize("Nc,Nn", [(1_500, 1_001), (30_011, 20_003)])
+@pytest.mark.parametrize("D,ks", [(32, (8, 3, 5)), (64, (16, 7, 24)), (96, (24, 40, 9)), (128, (32, 12, 64))])
+def test_two_selections_of_tied_rows(D, ks, Nc, Nn):
+    """A layer with a width per relation selects twice from every row; clearing the keys that lose a tie in the first selection must
+    not reach the second."""
+    say(f"topk twice D={D} ks={ks} Nc={Nc}")
+    rng = np.random.default_rng(D + Nc)
+
+    def relation(M, N):
+        rowptr = np.arange(M + 1, dtype=np.int32)
+        return P.Csr(M, N, dev(rowptr), dev(rng.integers(0, N, M).astype(np.int32)), torch.ones(M, device="cuda"))
+
+    layer = P.HeteroConv(relation(Nc, Nc), relation(Nn, Nc), relation(Nc, Nn), D, per_relation=ks)
+    saved = layer.alloc_saved()
+    W = {n: torch.zeros((D, D), device="cuda") for n in P.WEIGHT_NAMES}
+    X = {"cell": dev(_rows(rng, Nc, D, "ties")), "net": dev(_rows(rng, Nn, D, "hard"))}
+    X["net"][1::3] = dev(_rows(rng, Nn, D, "ties"))[1::3]
+    layer.heteroconv_fwd(X["cell"], X["net"], W, torch.empty((Nc, D), device="cuda"), torch.empty((Nn, D), device="cuda"), saved)
+    for name, t, k in (("cell", "cell", ks[0]), ("cell_pins", "cell", ks[1]), ("net", "net", ks[2]), ("net_self", "net", ks[1])):
+        _check_on_gpu(X[t], k, saved["vals_" + name], saved["idx_" + name])
+    layer.heteroconv_destroy()
