@@ -296,15 +296,30 @@ template <int KPL> struct Pairs {
     float v[N];
     uint16_t c[N];
     // `k`: stored width of the row; `kk`: pairs of it that count (all, or a prefix of them in the adaptive-K kernels).
-    // PREFIX: pairs at or past kk go to the padding words as well.
+    // PREFIX: pairs at or past kk go to the padding words as well; where the lanes step back (KPL < 0) it is into the prefix, so
+    // that what lies past it is not fetched (250 000 x 12 edges, D = 100, k = 25 with prefixes of 12 and 6: 184 -> 164 us; single pairs
+    // took 166).
     template <bool PREFIX = false>
     __device__ __forceinline__ void load(const float* __restrict__ vals, const uint16_t* __restrict__ idx, uint32_t rowbase,
                                          int t, int k, int kk, int D) {
-        const int first = KPL > 0 ? KPL * t : min(N * t, k - N);
+        const uint16_t padding = (uint16_t)(D + (t & (kBufPad - 1)));
+        if constexpr (PREFIX && (KPL == -1 || KPL == -2)) {        // single pairs: as few loads, and the wide ones' masks spill
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int q = t + kLPE * u;
+                const uint32_t off = rowbase + (uint32_t)min(q, kk - 1);
+                v[u] = vals[off];
+                const uint16_t col = idx[off];
+                c[u] = q < kk ? col : padding;
+            }
+            return;
+        }
+        const int first = KPL > 0 ? KPL * t : min(N * t, PREFIX ? max(kk - N, 0) : k - N);
         load_raw(vals, idx, rowbase, t, first);
 #pragma unroll
         for (int u = 0; u < N; ++u)
-            if ((KPL < 0 && first + u < N * t) || (PREFIX && first + u >= kk)) c[u] = (uint16_t)(D + (t & (kBufPad - 1)));
+            if (KPL < 0 ? first + u < N * t || (PREFIX && u > 0 && u >= kk)        // (the latter where the prefix is shorter than N)
+                        : PREFIX && first + u >= kk) c[u] = padding;
     }
     __device__ __forceinline__ void load_raw(const float* __restrict__ vals, const uint16_t* __restrict__ idx, uint32_t rowbase,
                                              int t, int first) {

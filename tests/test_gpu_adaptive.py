@@ -103,6 +103,28 @@ def test_spmm_fwd_adaptive_parity(case):
     assert_elem_bound(got, H_o, L1, "H")
 
 
+@pytest.mark.parametrize("ks", [(7, 6, 1), (12, 9, 1), (16, 15, 2), (20, 3, 2), (24, 17, 1), (25, 4, 3), (31, 29, 8), (32, 30, 2), (57, 33, 5)])
+def test_prefixes_at_the_ends_of_the_lanes_pairs(ks):
+    """Widths whose pairs are read in runs that step back into the prefix: prefixes shorter than a run, one pair more or less than
+    whole runs; arrays that start at no aligned address, with NaN on either side."""
+    M, N, D = 61, 53, 64
+    say(f"dr_spmm_fwd_adaptive prefixes {ks}")
+    rng = np.random.default_rng(sum(ks))
+    rowptr, colidx, avals = random_csr(rng, M, N, 9, evil_rows=(7,), evil_deg=50)
+    colidx[:2] = 0, N - 1
+    cls = oad.DegreeClasses(3, 6, *ks)
+    ov, oi = oad.topk_ranked(rng.standard_normal((N, D)).astype(np.float32), cls.k1)
+    H_o, L1 = oad.spmm_fwd_adaptive(rowptr, colidx, avals, ov, oi, D, cls)
+    vals = torch.full((N * cls.k1 + 2,), float("nan"), dtype=torch.float32, device="cuda")
+    idx = torch.zeros(N * cls.k1 + 2, dtype=torch.int16, device="cuda")
+    vals[1:-1] = dev(np.asarray(ov), torch.float32).flatten()
+    idx[1:-1] = dev(np.asarray(oi).astype(np.uint16).view(np.int16)).flatten()
+    H = torch.full((M, D), float("nan"), dtype=torch.float32, device="cuda")
+    P.dr_spmm_fwd_adaptive(P.Csr(M, N, dev(rowptr), dev(colidx), dev(avals)), vals[1:-1].view(N, cls.k1), idx[1:-1].view(N, cls.k1), D,
+                           tuple(cls), H)
+    assert_elem_bound(H.cpu().numpy(), H_o, L1, "H")
+
+
 @pytest.mark.parametrize("case", CASES, ids=_ids())
 def test_spmm_bwd_adaptive_parity(case):
     M, N, _, D, _, _, _ = case
