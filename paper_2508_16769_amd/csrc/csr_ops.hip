@@ -1,6 +1,8 @@
 // Per-graph setup kernels: module edge values (mean / symmetric normalisation) and the stable CSR
 // transpose used by the backward pass (paper Alg. 2, stage 1).
 #include "dr_internal.h"
+
+#include <type_traits>
 #include "partition_shape.h"
 
 #include <mutex>
@@ -456,20 +458,23 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
     }
 }
 
+// Counters: a set for each wavefront, or (HALVE) for every second one where the workgroup owns kMaxSub columns; the other wavefronts
+// then only clear and write.
+template <bool HALVE>
 __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b, int sort_cap) {
-    extern __shared__ __align__(16) uint32_t cnt[];                       // [kPartWaves][columns of this workgroup]; [sort_cap] records
+    extern __shared__ __align__(16) uint32_t cnt[];                       // [sets][columns of this workgroup]; [sort_cap] records
     __shared__ uint32_t sm[kPartWaves];
     __shared__ uint32_t s_begin, s_before, s_total;
     int q = 0;
     while (q + 1 < b.n && (int)blockIdx.x >= b.s[q + 1].col0) ++q;
     const PartSeg& g = b.s[q];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sub = 1 << g.p.sub_shift;
+    const int sub = 1 << g.p.sub_shift, sets = HALVE && sub == kMaxSub ? kPartWaves / 2 : kPartWaves;
     const int first = (int)min((long long)(blockIdx.x - g.col0) << g.p.sub_shift, (long long)g.n_cols);    // first column
     const int ncol = min(sub, g.n_cols - first);
     const int bucket = first >> g.p.shift;
     if (ncol <= 0) return;
-    for (int i = threadIdx.x; i < kPartWaves * sub; i += kPartThreads) cnt[i] = 0u;
+    for (int i = threadIdx.x; i < sets * sub; i += kPartThreads) cnt[i] = 0u;
     // records of the bucket: [begin, begin + n)
     uint32_t t = 0;
     for (int i = threadIdx.x; i < bucket; i += kPartThreads) t += g.totals[i];
@@ -478,7 +483,7 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
     if (threadIdx.x == 0) s_before = 0u;
     __syncthreads();
     const int begin = (int)s_begin, n = (int)g.totals[bucket];
-    const PartRange w = part_bucket_wave(n, wave);
+    const PartRange w = part_bucket_wave(n, wave, sets);      // wavefronts without counters: empty
     uint32_t* const mine = cnt + wave * sub;
     const int32_t* key = g.key + begin + w.begin;
     uint32_t earlier = 0;                                   // records of the bucket in columns before this workgroup's
@@ -495,16 +500,16 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
     }
     if (earlier) atomicAdd(&s_before, earlier);
     __syncthreads();
-    // column starts: four consecutive columns per thread
-    {
-        constexpr int kPer = kMaxSub / kPartThreads;
+    // column starts: kPer consecutive columns per thread; the counters become next free places.  False: only counts were asked for.
+    const auto column_starts = [&](auto n_sets) {
+        constexpr int kSets = decltype(n_sets)::value, kPer = kMaxSub / kPartThreads;
         uint32_t col[kPer], sum = 0;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int i = threadIdx.x * kPer + u;
             col[u] = 0u;
             if (i < sub)
-                for (int w = 0; w < kPartWaves; ++w) col[u] += cnt[w * sub + i];
+                for (int w = 0; w < kSets; ++w) col[u] += cnt[w * sub + i];
             sum += col[u];
         }
         if (g.count_only) {
@@ -513,7 +518,7 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
                 const int i = threadIdx.x * kPer + u;
                 if (i < ncol) g.t_rowptr[first + i] = (int32_t)col[u];
             }
-            return;
+            return false;
         }
         const uint32_t incl = part_scan_inclusive(sum, sm);
         if (threadIdx.x == kPartThreads - 1) s_total = incl;
@@ -524,7 +529,7 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
             if (i < ncol) {
                 g.t_rowptr[first + i] = (int32_t)run;
                 uint32_t at = run;
-                for (int w = 0; w < kPartWaves; ++w) {
+                for (int w = 0; w < kSets; ++w) {
                     const uint32_t k = cnt[w * sub + i];
                     cnt[w * sub + i] = at;
                     at += k;
@@ -532,11 +537,14 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
             }
             run += col[u];
         }
-    }
+        return true;
+    };
+    if (!(sets == kPartWaves ? column_starts(std::integral_constant<int, kPartWaves>{})
+                             : column_starts(std::integral_constant<int, kPartWaves / 2>{}))) return;
     if (first + ncol == g.n_cols && threadIdx.x == 0) g.t_rowptr[g.n_cols] = g.nnz;
     __syncthreads();
     // A bucket that fits is sorted in LDS and leaves in order, coalesced; a larger one is written record by record.
-    int2* const s_out = reinterpret_cast<int2*>(cnt + kPartWaves * sub);
+    int2* const s_out = reinterpret_cast<int2*>(cnt + sets * sub);
     const bool sorted = n <= sort_cap;
     const uint32_t origin = (uint32_t)begin + s_before;     // first place of this workgroup's columns
     const int2* rec = g.rec + begin + w.begin;
@@ -602,8 +610,16 @@ static void part_buffers(PartSeg& g, char* w) {
     g.rec = reinterpret_cast<int2*>(w);
 }
 
+// Half the sets of counters where every relation of kMaxSub columns a workgroup has no more than two entries a column: clearing,
+// adding up and rewriting the counters is most of the work there, and with 64 KB two workgroups fit a compute unit.  Transposes, all
+// / half of the sets: 5 M columns, 1 M entries 143 / 91 us; 2 M columns with 1, 4, 6 and 8 M entries 68 / 52, 133 / 118, 186 / 180,
+// 218 / 240; 1.2 M with 14 M 582 / 647.  A column that holds much of all entries makes its workgroup the last one, and half the
+// wavefronts longer (4 M entries in 2 M columns, a third of them in one: 2.1 / 2.8 ms).
+static bool few_per_column(const PartSeg& g) { return g.nnz <= 2 * (int64_t)g.n_cols; }
+
 static int launch_partition(PartBatch& b, hipStream_t s) {
     int tiles = 0, scans = 0, cols = 0, nbp = 0, sub = 0;
+    bool halve = true;
     for (int i = 0; i < b.n; ++i) {
         PartSeg& g = b.s[i];
         g.tile0 = tiles; g.scan0 = scans; g.col0 = cols;
@@ -612,26 +628,29 @@ static int launch_partition(PartBatch& b, hipStream_t s) {
         cols += (int)(((int64_t)g.n_cols + (int64_t(1) << g.p.sub_shift) - 1) >> g.p.sub_shift);
         if (g.p.nb_pad > nbp) nbp = g.p.nb_pad;
         if ((1 << g.p.sub_shift) > sub) sub = 1 << g.p.sub_shift;
+        halve = halve && (1 << g.p.sub_shift < kMaxSub || few_per_column(g));
     }
     if (b.n == 0) return DR_OK;
     // Buckets hold 2048 to 4096 entries on average unless there are too many columns for that (kMaxBuckets); 5120 leave room
     // for their spread, and with the counters of 512 columns two workgroups fit a compute unit.
     const int sort_cap = sub <= kMaxSub / 2 ? 5120 : 0;
-    const size_t lds3 = scatter_lds(nbp), lds4 = 4 * (size_t)kPartWaves * sub + 8 * (size_t)sort_cap;
+    const size_t lds3 = scatter_lds(nbp), lds4 = 4 * (size_t)kPartWaves * (halve && sub == kMaxSub ? sub / 2 : sub) + 8 * (size_t)sort_cap;
     static PerDevice raised;
     int dev = 0, lds_max = 0;
     DRC_HIP(hipGetDevice(&dev));
-    DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // both pass 64 KB
+    DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // all pass 64 KB, the last by its static words
         *n = 4 * kPartWaves * kMaxSub;
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_scatter_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)scatter_lds(kMaxBuckets)));
-        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, *n));
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, *n));
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, *n / 2));
         return DR_OK;
     }));
     hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)tiles), dim3(kPartThreads), 0, s, b);
     hipLaunchKernelGGL(part_scan_kernel, dim3((unsigned)scans), dim3(1024), 0, s, b);
     hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);
-    hipLaunchKernelGGL(part_columns_kernel, dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
+    if (halve && sub == kMaxSub) hipLaunchKernelGGL((part_columns_kernel<true>), dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
+    else hipLaunchKernelGGL((part_columns_kernel<false>), dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
     DRC_HIP(hipGetLastError());
     return DR_OK;
 }

@@ -17,7 +17,7 @@ namespace drc {
 
 constexpr int kPartThreads = 1024, kPartWaves = kPartThreads / 64;
 constexpr int kMaxBuckets = 1024;      // level-1 digits: their counters (16 bits), one set per wavefront, take 32 KB of LDS
-constexpr int kMaxSub = 2048;          // columns a workgroup of the second level owns: 128 KB of LDS counters
+constexpr int kMaxSub = 2048;          // columns a workgroup of the second level owns: 128 KB of LDS counters, one set per wavefront
 constexpr int kMinTile = 4096;         // entries a workgroup of the first level takes at least (256 per wavefront)
 constexpr int kChunk = kMinTile;       // entries a workgroup of the first level sorts at a time, in LDS
 constexpr int kMaxTiles = 1024;        // a chunk each up to 4.2 M entries; more would only lengthen the scan of the counts
@@ -63,9 +63,9 @@ DRC_HOST_DEVICE PartRange part_tile_wave(const PartShape& p, int nnz, int tile, 
     return part_piece(part_tile(p, nnz, tile), wave, p.tile / kPartWaves);
 }
 
-// second level: the stretch of a bucket of n records that one wavefront takes
-DRC_HOST_DEVICE PartRange part_bucket_wave(int n, int wave) {
-    const int per = ((n - 1) / kPartWaves + 64) / 64 * 64;     // n / kPartWaves rounded up, then up to a multiple of 64
+// second level: the stretch of a bucket of n records that one of the `waves` wavefronts takes (empty from there on)
+DRC_HOST_DEVICE PartRange part_bucket_wave(int n, int wave, int waves = kPartWaves) {
+    const int per = ((n - 1) / waves + 64) / 64 * 64;          // n / waves rounded up, then up to a multiple of 64
     return part_piece(PartRange{0, n}, wave, per);
 }
 

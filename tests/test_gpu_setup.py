@@ -154,3 +154,12 @@ def test_as_many_entries_as_accepted():
 ])
 def test_transpose_where_sorting_in_lds_changes(M, N, E, law):
     test_transpose_and_values_exact(M, N, E, law)
+
+
+@pytest.mark.parametrize("M,N,E,law", [
+    # two entries a column and one more: every second wavefront of the second level has counters, then every one
+    (300_000, 1_100_000, 2_200_000, "uniform"), (300_000, 1_100_000, 2_200_001, "uniform"),
+    (300_000, 5_000_000, 1_000_000, "skewed_cols"),
+])
+def test_transpose_of_wide_relations(M, N, E, law):
+    test_transpose_and_values_exact(M, N, E, law)

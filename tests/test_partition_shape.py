@@ -47,6 +47,14 @@ int main() {
         }
         if (g_at != n) return printf("wavefronts cover %lld of a bucket of %lld\n", g_at, n), 1;
     }
+    for (long long n : sizes) {                 // fewer wavefronts take it: those past them get nothing
+        g_at = 0;
+        for (int w = 0; w < kPartWaves; ++w) {
+            const PartRange r = part_bucket_wave((int)n, w, kPartWaves / 2);
+            if (!next(r) || (w >= kPartWaves / 2 && r.len != 0)) return printf("wavefront %d of half of a bucket of %lld\n", w, n), 1;
+        }
+        if (g_at != n) return printf("half the wavefronts cover %lld of a bucket of %lld\n", g_at, n), 1;
+    }
     puts("ok");
     return 0;
 }
