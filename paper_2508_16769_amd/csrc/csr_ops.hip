@@ -364,6 +364,11 @@ __device__ __forceinline__ int bits_below(unsigned long long m) {
 // took (1.2 M entries into 489 buckets 28 us, whether 8 or 16 wavefronts worked on a tile; without the records 13).
 __host__ __device__ constexpr size_t scatter_lds(int nb_pad) { return 2 * (size_t)kPartWaves * nb_pad + 12 * (size_t)kChunk; }
 using Count16 = uint16_t __attribute__((may_alias));
+// RECORDS false: columns only, of which nothing but counts is made, so that any order will do within a bucket and places come from LDS
+// atomics.  Ranked like records, columns that lie near their bucket already took longer than written one by one: symmetric edge
+// values of 1.2 M x 0.9 M with 5 M entries near the diagonal 100 us without the sorting, 121 with it, 97 now; random columns 128,
+// 119, 101.  (A kernel of its own: with both ways in one the registers of the other spilled, transposes 3 to 12 % slower.)
+template <bool RECORDS>
 __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch b) {
     static_assert(kMaxBuckets <= kPartThreads && kChunk % kPartThreads == 0 && kChunk < 65536, "one bucket per thread, 16-bit places");
     constexpr int kSteps = kChunk / kPartThreads;
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
     const PartSeg& g = b.s[q];
     const int tile = blockIdx.x - g.tile0, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bucket = threadIdx.x;
     const int nbp = g.p.nb_pad, shift = g.p.shift, nbits = 32 - __builtin_clz(max(g.p.nb - 1, 1));
-    const bool records = !g.count_only, have = bucket < nbp;
+    const bool have = bucket < nbp;
     uint32_t* const s_key = cnt + kPartWaves * nbp / 2;      // [kChunk] columns, sorted
     int2* const s_rec = reinterpret_cast<int2*>(s_key + kChunk);
     uint32_t* const sm = s_key;                              // [kPartWaves] of the scans, which end before the sorting begins
@@ -386,6 +391,34 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
     int row0 = 0;
     for (int at_chunk = 0, k = 0; at_chunk < whole.len; at_chunk += kChunk, ++k) {
         const PartRange chunk = part_piece(whole, k, kChunk), r = part_piece(chunk, wave, kChunk / kPartWaves);
+        if constexpr (!RECORDS) {
+            int col[kSteps];
+            uint32_t rank[kSteps];
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u) col[u] = g.colidx[chunk.begin + min(u * kPartThreads + (int)threadIdx.x, chunk.len - 1)];
+            if (have) cnt[bucket] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u)
+                if (u * kPartThreads + (int)threadIdx.x < chunk.len) rank[u] = atomicAdd(&cnt[(uint32_t)col[u] >> shift], 1u);
+            __syncthreads();
+            const uint32_t n = have ? cnt[bucket] : 0u, local = part_scan_inclusive(n, sm) - n;
+            if (have) cnt[bucket] = local;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u)
+                if (u * kPartThreads + (int)threadIdx.x < chunk.len) s_key[cnt[(uint32_t)col[u] >> shift] + rank[u]] = (uint32_t)col[u];
+            __syncthreads();
+            if (have) cnt[bucket] = next - local;
+            next += n;
+            __syncthreads();
+            for (int i = threadIdx.x; i < chunk.len; i += kPartThreads) {
+                const uint32_t key = s_key[i];
+                g.key[cnt[key >> shift] + (uint32_t)i] = (int32_t)key;
+            }
+            __syncthreads();
+            continue;
+        }
         int c[kSteps];
         float v0 = 0.0f;
         RowWindow win{};
@@ -393,7 +426,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
         if (r.len > 0) {
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) c[u] = g.colidx[r.begin + min(u * 64 + lane, r.len - 1)];
-            if (records) {
+            if constexpr (RECORDS) {
                 if (g.vals) v0 = g.vals[r.begin + min(lane, r.len - 1)];
                 row0 = k == 0 ? wave_row_of(g.rowptr, g.n_rows, 0, r.begin) : wave_row_ahead(g.rowptr, g.n_rows, row0, r.begin);
                 win = row_window(g.rowptr, g.n_rows, row0);
@@ -409,6 +442,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
         __syncthreads();
         uint32_t n = 0;
         if (have)
+#pragma unroll 4                                            // all sixteen at once take the registers past 64
             for (int w = 0; w < kPartWaves; ++w) n += place[w * nbp + bucket];
         const uint32_t local = part_scan_inclusive(n, sm) - n;
         if (have) {
@@ -427,7 +461,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
         for (int s = 0; s < r.len; s += 64) {
             const int e = r.begin + min(s + lane, r.len - 1), e_next = r.begin + min(s + 64 + lane, r.len - 1);
             const int col_next = g.colidx[e_next];
-            const float v_next = records && g.vals ? g.vals[e_next] : 0.0f;
+            const float v_next = RECORDS && g.vals ? g.vals[e_next] : 0.0f;
             const bool on = s + lane < r.len;
             const uint32_t d = (uint32_t)col >> shift;
             const unsigned long long m = same_digit(d, nbits, on);
@@ -436,7 +470,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
             __builtin_amdgcn_wave_barrier();                // one wavefront's LDS accesses run in program order
             if (on && before == __popcll(m) - 1) mine[d] = (uint16_t)(at + (uint32_t)before + 1u);
             __builtin_amdgcn_wave_barrier();
-            if (records) {
+            if constexpr (RECORDS) {
                 int len;
                 const int i = wave_rows(g.rowptr, g.n_rows, win, e, &len);
                 if (on) s_rec[at + before] = make_int2(i, __float_as_int(v0));
@@ -452,7 +486,7 @@ __global__ __launch_bounds__(kPartThreads, 8) void part_scatter_kernel(PartBatch
         for (int i = threadIdx.x; i < chunk.len; i += kPartThreads) {
             const uint32_t key = s_key[i], at = cnt[key >> shift] + (uint32_t)i;
             g.key[at] = (int32_t)key;
-            if (records) g.rec[at] = s_rec[i];
+            if constexpr (RECORDS) g.rec[at] = s_rec[i];
         }
         __syncthreads();
     }
@@ -640,7 +674,7 @@ static int launch_partition(PartBatch& b, hipStream_t s) {
     DRC_HIP(hipGetDevice(&dev));
     DRC_TRY(raised.get(dev, &lds_max, [](int* n) -> int {    // all pass 64 KB, the last by its static words
         *n = 4 * kPartWaves * kMaxSub;
-        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_scatter_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+        DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_scatter_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)scatter_lds(kMaxBuckets)));
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, *n));
         DRC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&part_columns_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, *n / 2));
@@ -648,7 +682,8 @@ static int launch_partition(PartBatch& b, hipStream_t s) {
     }));
     hipLaunchKernelGGL(part_count_kernel, dim3((unsigned)tiles), dim3(kPartThreads), 0, s, b);
     hipLaunchKernelGGL(part_scan_kernel, dim3((unsigned)scans), dim3(1024), 0, s, b);
-    hipLaunchKernelGGL(part_scatter_kernel, dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);
+    if (b.s[0].count_only) hipLaunchKernelGGL((part_scatter_kernel<false>), dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);
+    else hipLaunchKernelGGL((part_scatter_kernel<true>), dim3((unsigned)tiles), dim3(kPartThreads), lds3, s, b);
     if (halve && sub == kMaxSub) hipLaunchKernelGGL((part_columns_kernel<true>), dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
     else hipLaunchKernelGGL((part_columns_kernel<false>), dim3((unsigned)cols), dim3(kPartThreads), lds4, s, b, sort_cap);
     DRC_HIP(hipGetLastError());
