@@ -67,9 +67,16 @@ template <int D> struct Tile {
 
 // Place of a unit in its plane.  A 16-byte LDS read is served in groups of 16 lanes that mix the rows of two neighbouring
 // units: lanes 0-3, 12-15 and 20-27 of the first 32, and the rest (measured pair by pair), so those two units have to start
-// on the same bank; the units of one row, which a staging wavefront writes together, should not.  A 16-byte gap after every
-// second unit gives both.  (A gap after every unit made every read of a fragment a two-way conflict.)
+// on the same bank; the pairs 2h, 2h + 1 of one row start 16 bytes further on each.  (A gap after every unit made every read of a
+// fragment a two-way conflict.)
 template <int D> __device__ __forceinline__ int unit_at(int unit, int row) { return unit * Tile<D>::BM + (unit >> 1) + row; }
+// The unit that thread t of a row stages.  At D = 128 neighbouring threads take units of different pairs, so that eight of them write
+// to eight different banks: dproj of 250 000 cells and 180 000 nets 131 -> 128 and 73 -> 70 us, forward 131 -> 130.  (Narrower rows
+// have fewer than eight pairs; at D = 96 the forward became 1 % slower.)
+template <int D> __device__ __forceinline__ int unit_of(int t) {
+    constexpr int H = Tile<D>::KU / 2;
+    return D == 128 ? (t < H ? 2 * t : 2 * (t - H) + 1) : t;
+}
 
 // Three bf16 parts of half of each of eight numbers, two at a time (one conversion instruction makes two parts).
 // Half, so that no finite number rounds up to an infinite first part; kUnscale takes a sum of products back.
@@ -126,8 +133,7 @@ __device__ __forceinline__ void put_parts(__bf16* at, int stride, float v) {
 __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// hi += leading products, lo += the five small ones (smallest first), for two tiles of rows at a time: consecutive
-// instructions go to different accumulators
+// hi: sum of the leading products, lo: of the five small ones
 struct Acc { f32x4 hi, lo; };
 // The sum of leading products and small ones.  An infinite or overflowing operand makes the leading sum infinite or
 // not-a-number as in fp32, but its remainder is not-a-number and its small products may be infinities of either sign: the
@@ -294,7 +300,9 @@ template <int D> __device__ __forceinline__ void load_part(const bf16x8* oper, i
         x[rb] = oper[part * Tile<D>::PLANE + unit_at<D>(4 * s + (lane >> 4), rg * 32 + rb * 16 + (lane & 15))];
 }
 // Step STEP's products with NW weights: w[i] the parts of a weight's fragment, c[i] its accumulators for two tiles of rows.
-// MORE: a step follows, whose fragments are at (next, s).
+// MORE: a step follows, whose fragments are at (next, s).  Consecutive instructions go to different accumulators.  The small
+// products are added in the order in which that frees the fragments, x3 y1, x2 y2, x2 y1, x1 y3, x1 y2: one of about 2^-16 comes after
+// one of 2^-8, which costs less than half an ulp of the small sum, 2^-32 of the whole.
 template <int D, int STEP, bool MORE, int NW, int SETS>
 __device__ __forceinline__ void multiply(const bf16x8* const (&w)[NW], Acc (*const (&c)[NW])[2], Frags<SETS>& x, const bf16x8* next, int s,
                                          int rg, int lane) {
@@ -324,6 +332,23 @@ __device__ __forceinline__ void multiply(const bf16x8* const (&w)[NW], Acc (*con
         for (int rb = 0; rb < 2; ++rb) (*c[i])[rb].hi = mfma(w[i][0], x.p0[set][rb], (*c[i])[rb].hi);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (MORE && SETS == 1) load_part<D>(next, 0, s, rg, lane, x.p0[0]);
+}
+// The same without reading ahead, the small products smallest first; the compiler places the reads.
+template <int D, int NW>
+__device__ __forceinline__ void multiply_now(const bf16x8* const (&w)[NW], Acc (*const (&c)[NW])[2], const bf16x8* oper, int s, int rg, int lane) {
+    bf16x8 x[3][2];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) load_part<D>(oper, p, s, rg, lane, x[p]);
+    constexpr int W[5] = {2, 0, 1, 1, 0}, X[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+#pragma unroll
+        for (int j = 0; j < 5; ++j)
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) (*c[i])[rb].lo = mfma(w[i][W[j]], x[X[j]][rb], (*c[i])[rb].lo);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) (*c[i])[rb].hi = mfma(w[i][0], x[0][rb], (*c[i])[rb].hi);
+    }
 }
 template <int D, int SETS> __device__ __forceinline__ void first_frags(const bf16x8* oper, int rg, int lane, Frags<SETS>& x) {
     load_part<D>(oper, 2, 0, rg, lane, x.p2);
@@ -370,7 +395,7 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = wave % T::NB, rg = wave / T::NB;
     const bool relu = a->relu != 0;
-    const int urow = tid / T::KU, unit = tid % T::KU;              // this thread's unit of a dense operand
+    const int urow = tid / T::KU, unit = unit_of<D>(tid % T::KU);              // this thread's unit of a dense operand
     const int prow = tid / T::TPR, ppart = tid % T::TPR;           // past the tile (D = 96): reads nothing, writes nothing
     const bool pairs = wave * 64 < T::BM * T::TPR;                 // whole wavefronts
 
@@ -529,7 +554,7 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
     const int tiles = CELL ? a->cell_tiles : a->net_tiles, n = a->n;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = wave % T::NB, rg = wave / T::NB;
-    const int urow = tid / T::KU, unit = tid % T::KU;
+    const int urow = tid / T::KU, unit = unit_of<D>(tid % T::KU);
     const int prow = tid / T::TPR, ppart = tid % T::TPR;           // past the tile (D = 96): reads nothing, writes nothing
     float* const sC0 = reinterpret_cast<float*>(smem + 4 * T::OPER);          // [2][BM][LDC] self-term products
 
@@ -622,32 +647,55 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
             __builtin_amdgcn_sched_barrier(0);
             // near (or the net's only branch) first, then pinned: the accumulators of both would not fit the registers
             const int ln = opaque(lane), r0 = rg * 32 + (ln & 15), c0 = 16 * nb + 4 * (ln >> 4);
-            Frags<1> x;
-            constexpr int NS = (CELL ? 2 : 1) * T::KS;
             Acc c[2] = {}, cS[2] = {};
-            first_frags<D>(buf, rg, lane, x);
-            steps<NS>([&](auto step) {
-                constexpr int i = decltype(step)::value, s = i % T::KS;
-                const bf16x8* const next = buf + (i + 1) / T::KS * T::OPER;
-                if constexpr (i < T::KS) {
-                    const bf16x8* const w[2] = {w1[s], wS[s]};
-                    Acc(*const acc[2])[2] = {&c, &cS};
-                    multiply<D, i, i + 1 < NS>(w, acc, x, next, (i + 1) % T::KS, rg, lane);
-                } else {
-                    const bf16x8* const w[1] = {w2[s]};
-                    Acc(*const acc[1])[2] = {&c};
-                    multiply<D, i, i + 1 < NS>(w, acc, x, next, (i + 1) % T::KS, rg, lane);
-                }
-                if constexpr (i == T::KS - 1) {
-                    const Buf b1 = block_view(g.dH1 + (size_t)base * D, g.rows - base, D * 4);
+            Acc(*const both[2])[2] = {&c, &cS};
+            Acc(*const one[1])[2] = {&c};
+            const auto near_done = [&]() {
+                const Buf b1 = block_view(g.dH1 + (size_t)base * D, g.rows - base, D * 4);
 #pragma unroll
-                    for (int rb = 0; rb < 2; ++rb) {
-                        *reinterpret_cast<f32x4*>(sC + (r0 + rb * 16) * LDC + c0) = total(cS[rb]);
-                        store4(b1, ((r0 + rb * 16) * D + c0) * 4, total(c[rb]));       // gathered next: these stay in the caches
-                        c[rb] = Acc{};
+                for (int rb = 0; rb < 2; ++rb) {
+                    *reinterpret_cast<f32x4*>(sC + (r0 + rb * 16) * LDC + c0) = total(cS[rb]);
+                    store4(b1, ((r0 + rb * 16) * D + c0) * 4, total(c[rb]));       // gathered next: these stay in the caches
+                    c[rb] = Acc{};
+                }
+            };
+            // Fragments are read ahead where that gains: cells of D = 96 (1.2 M: 449 us, without 455) and, as much as nothing, below.  Beside
+            // the weights of D = 128 they leave the compiler no registers to move reads in, and nets have one product per fragment
+            // less to wait under (backward passes alone, with / without: 1.2 M cells and 0.9 M nets of D = 128 627 / 596 and 317 / 306 us,
+            // nets of D = 96 236 / 230).
+            if constexpr (CELL && D < 128) {
+                Frags<1> x;
+                constexpr int NS = 2 * T::KS;
+                first_frags<D>(buf, rg, lane, x);
+                steps<NS>([&](auto step) {
+                    constexpr int i = decltype(step)::value, s = i % T::KS;
+                    const bf16x8* const next = buf + (i + 1) / T::KS * T::OPER;
+                    if constexpr (i < T::KS) {
+                        const bf16x8* const w[2] = {w1[s], wS[s]};
+                        multiply<D, i, i + 1 < NS>(w, both, x, next, (i + 1) % T::KS, rg, lane);
+                    } else {
+                        const bf16x8* const w[1] = {w2[s]};
+                        multiply<D, i, i + 1 < NS>(w, one, x, next, (i + 1) % T::KS, rg, lane);
+                    }
+                    if constexpr (i == T::KS - 1) near_done();
+                });
+            } else {
+#pragma unroll
+                for (int s = 0; s < T::KS; ++s) {
+                    const bf16x8* const w[2] = {w1[s], wS[s]};
+                    multiply_now<D>(w, both, buf, s, rg, lane);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                near_done();
+                if constexpr (CELL) {
+#pragma unroll
+                    for (int s = 0; s < T::KS; ++s) {
+                        const bf16x8* const w[1] = {w2[s]};
+                        multiply_now<D>(w, one, buf + T::OPER, s, rg, lane);
                     }
                 }
-            });
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if constexpr (CELL) {
                 const Buf b2 = block_view(g.dH2 + (size_t)base * D, g.rows - base, D * 4);
 #pragma unroll
