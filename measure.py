@@ -313,8 +313,8 @@ own streams while the GPU computes; the consumer never waits for the GPU until t
 # (label, substring the dispatched kernel's name must contain) in dispatch order of one forward + backward
 # step with a launch per relation and near^T on staged tiles
 SCHEDULE = (
-    ("dr_topk.net", "topk_rows"), ("dr_spmm_fwd.pinned", "spmm_fwd"),
-    ("dr_topk.cell", "topk_rows"), ("dr_spmm_fwd.pins", "spmm_fwd"), ("dr_spmm_fwd.near", "spmm_fwd"),
+    ("dr_topk.net", "topk_"), ("dr_spmm_fwd.pinned", "spmm_fwd"),
+    ("dr_topk.cell", "topk_"), ("dr_spmm_fwd.pins", "spmm_fwd"), ("dr_spmm_fwd.near", "spmm_fwd"),
     ("proj.cell+merge", "proj_kernel"), ("proj.pins", "proj_kernel"),
     ("wgrad.cell", "wgrad_partial"), ("wgrad.cell.reduce", "wgrad_reduce"),
     ("wgrad.pins", "wgrad_partial"), ("wgrad.pins.reduce", "wgrad_reduce"),
@@ -323,11 +323,11 @@ SCHEDULE = (
 )
 # single-stream dispatch order of `bench.py --only dr --serial` (the timed D-ReLU / DR-SpMM region alone)
 SCHEDULE_DR = (
-    ("dr_topk.cell", "topk_rows"), ("dr_spmm_fwd.near", "spmm_fwd"), ("dr_spmm_bwd.near", "spmm_bwd"),
+    ("dr_topk.cell", "topk_"), ("dr_spmm_fwd.near", "spmm_fwd"), ("dr_spmm_bwd.near", "spmm_bwd"),
     ("dr_spmm_fwd.pins", "spmm_fwd"), ("dr_spmm_bwd.pins", "spmm_bwd"),
-    ("dr_topk.net", "topk_rows"), ("dr_spmm_fwd.pinned", "spmm_fwd"), ("dr_spmm_bwd.pinned", "spmm_bwd"),
+    ("dr_topk.net", "topk_"), ("dr_spmm_fwd.pinned", "spmm_fwd"), ("dr_spmm_bwd.pinned", "spmm_bwd"),
 )
-HOT = ("topk_rows", "spmm_fwd", "spmm_bwd", "proj_kernel", "wgrad_partial", "wgrad_reduce")
+HOT = ("topk_", "spmm_fwd", "spmm_bwd", "proj_kernel", "wgrad_partial", "wgrad_reduce")
 
 
 def per_kernel_kib(path: str, SCHEDULE=SCHEDULE) -> dict:
