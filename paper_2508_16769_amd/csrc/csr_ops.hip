@@ -234,7 +234,8 @@ int launch_csr_normalize_noalloc(int mode, int64_t n_rows, int64_t n_cols, int64
 // 44 bytes per entry move: column twice, value, record out and in, result.  Entries are put in order in LDS before they are
 // written (steps 3 and 4): one by one, random columns made a memory transaction of every 4- or 8-byte store, and those bounded
 // both steps.  Edge values and transposes of the three relations, before / after: 250 000 cells (3.0 / 1.2 / 1.2 M entries)
-// 243 / 232 us, 500 000 cells 431 / 334 (with all of this file's changes to step 2 and the row ends), 1.1 M cells 1455 / 1067.
+// 243 / 232 us (225 with the column counts in any order), 500 000 cells 431 / 334 (with all of this file's changes to step 2 and the
+// row ends), 1.1 M cells 1455 / 1067 (mostly step 3: step 4 sorts in LDS where no relation of the batch has workgroups of 2048 columns).
 // What bounds it now: 19 launches of 4 to 33 us one behind the other, each a chain of a dozen waits.
 // (Earlier: one slot per entry by an atomic cursor and a ranking of every segment afterwards.  The random atomics, one binary
 // search per entry and the ranking of the segments of high-fanout nets took 0.30 / 0.20 / 0.24 ms for the three relations of a
@@ -577,7 +578,8 @@ __global__ __launch_bounds__(kPartThreads) void part_columns_kernel(PartBatch b,
                              : column_starts(std::integral_constant<int, kPartWaves / 2>{}))) return;
     if (first + ncol == g.n_cols && threadIdx.x == 0) g.t_rowptr[g.n_cols] = g.nnz;
     __syncthreads();
-    // A bucket that fits is sorted in LDS and leaves in order, coalesced; a larger one is written record by record.
+    // A bucket that fits is sorted in LDS and leaves in order, coalesced; a larger one, and all of them where the batch's counters leave
+    // no room (sort_cap = 0), is written record by record.
     int2* const s_out = reinterpret_cast<int2*>(cnt + sets * sub);
     const bool sorted = n <= sort_cap;
     const uint32_t origin = (uint32_t)begin + s_before;     // first place of this workgroup's columns

@@ -216,7 +216,8 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(TopkArgs args) {
 //   Compaction.  The kept counts of a lane's slots travel as four bytes of one register through one scan over the lanes.  Kept
 // (value, column) pairs are placed in LDS, and the rows' pairs, which lie behind one another in memory, leave as whole
 // 16- and 8-byte stores.
-// At D = 128 bound by HBM: 1.2 M and 0.9 M rows, k = 32, together 372 -> 270 us (5.5 TB/s); 430 000 rows 91 -> 64 us.  At D = 64
+// At D = 128 the vector units are 93-96 % busy while the rows move at 5.0 TB/s, what a plain copy reaches: 1.2 M and 0.9 M rows,
+// k = 32, together 368 -> 291 us; 430 000 rows 91 -> 64 us.  At D = 64
 // still by its instructions: 100 000 rows, k = 16, 22 -> 13 us; 3072 rows 5.4 -> 3.9 us; two selections at D = 96, 58 000 rows,
 // 32 -> 18 us.  Other data, one row per wavefront / now (k = 32, D = 128): 1.2 M rows normal 226 -> 197 us,
 // exp(2 N) 270 -> 242 (305 without the trace), uniform with 2 % outliers of 1e6 210 -> 184 (335), Cauchy 254 -> 216 (300), two narrow
