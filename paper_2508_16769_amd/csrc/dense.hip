@@ -733,6 +733,10 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs 
 // operand.  The contraction runs over rows, so a unit is eight rows of one column: a thread loads eight dwords down its
 // column.  A wavefront is alone in needing its 16 columns of H, so those go from memory to registers; what all wavefronts
 // need (dZ, and the scattered CBSR) goes through LDS.  Partial sums go to scratch and are added by a second kernel in a fixed order.
+// What bounds it is issue: vector and matrix instructions of a SIMD's two wavefronts take turns for the most part, and a chunk has
+// 144 matrix and about 425 vector instructions per wavefront (cells, D = 128).  1.2 M cells of D = 128: 775 -> 673 us (3.3 TB/s) with
+// 551 -> 425 vector instructions (no cut to finite numbers while all sums are finite), three chains of small products instead of two
+// and one, and matrix instructions issued first; without any loads it takes 504.
 // ---------------------------------------------------------------------------------------------------
 template <int D> struct WTile {
     using T = Tile<D>;
@@ -769,10 +773,8 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
     const int hrow = (4 * kg + (lane >> 4)) * 8, hcol = 16 * mb + (lane & 15);   // this lane's unit of the H operands
 
     f32x4 acc[NP][T::NB];
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int j = 0; j < T::NB; ++j) acc[p][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int* const again = reinterpret_cast<int*>(smem + 6 * W::OPER);     // whether a sum is not finite
+    if (tid == 0) *again = 0;
 
     float y[8], h1[8], h2[8];
     uint32_t mk[8];
@@ -840,8 +842,12 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
         }
     };
     const int chunks = (g->rows + W::CR - 1) / W::CR;
-    const auto walk = [&](auto first) {
-        constexpr bool kFirst = decltype(first)::value;
+    const auto walk = [&](auto first, auto careful) {
+        constexpr bool kFirst = decltype(first)::value, kCareful = decltype(careful)::value;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < T::NB; ++j) acc[p][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         int chunk = wg, cur = 0;
         if (chunk < chunks) {
             load_y(chunk);
@@ -855,8 +861,11 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             const int next = chunk + g->wgs;
             bf16x8* const buf = smem + cur * 3 * W::OPER;
             auto stage_next = [&]() {
+                // matrix instructions go first: cells 700 -> 674 us; nets 357 -> 373 (two products a chunk: they wait for staging)
+                if constexpr (CELL) __builtin_amdgcn_s_setprio(0);
                 commit(next, smem + (cur ^ 1) * 3 * W::OPER);
                 load_y(next + g->wgs);
+                if constexpr (CELL) __builtin_amdgcn_s_setprio(1);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
@@ -867,48 +876,58 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             bf16x8 aS[3];
 #pragma unroll
             for (int p = 0; p < 3; ++p) aS[p] = buf[W::OPER + p * W::PLANE + (hrow >> 3) * D + hcol];
+            // The products of this chunk are summed from zero, leading and small ones apart, and added to the running sum
+            // with one rounding: inside the matrix unit they would be cut off below it, always downwards, which over
+            // many chunks adds up.  (The small sum as the leading one's start costs half of these instructions and is cut off as well:
+            // errors of 2e-7 became 1.5e-6 at 1.1 M rows.)
+            const auto add = [&](f32x4& to, const bf16x8& b, const bf16x8& x, const f32x4& lo) {
+                const f32x4 hi = mfma(b, x, f32x4{0.f, 0.f, 0.f, 0.f});
+                if constexpr (kCareful) to += with_small(hi, lo);
+                else to += hi + lo;
+                asm volatile("" : "+v"(to));          // added here: the compiler would keep all sums to the end of the loop
+            };
 #pragma unroll
             for (int j = 0; j < T::NB; ++j) {
-                // The products of this chunk are summed from zero, leading and small ones apart, and added to the running sum
-                // with one rounding: inside the matrix unit they would be cut off below it, always downwards, which over
-                // many chunks adds up.
                 constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
                 const int ub = (hrow >> 3) * D + 16 * j + (lane & 15);
-                f32x4 lo0 = {0.f, 0.f, 0.f, 0.f}, lo1 = {0.f, 0.f, 0.f, 0.f};
-                bf16x8 b[3];
+                f32x4 lo[3] = {};
+                bf16x8 b[3], b2[3];
 #pragma unroll
-                for (int p = 0; p < 3; ++p) b[p] = buf[p * W::PLANE + ub];
+                for (int p = 0; p < 3; ++p) {
+                    b[p] = buf[p * W::PLANE + ub];
+                    if constexpr (CELL) b2[p] = buf[2 * W::OPER + p * W::PLANE + ub];
+                }
 #pragma unroll
                 for (int i = 0; i < 5; ++i) {
-                    lo0 = mfma(b[BW[i]], a1.p[AW[i]], lo0);
-                    lo1 = mfma(b[BW[i]], aS[AW[i]], lo1);
+                    lo[0] = mfma(b[BW[i]], a1.p[AW[i]], lo[0]);
+                    lo[1] = mfma(b[BW[i]], aS[AW[i]], lo[1]);
+                    if constexpr (CELL) lo[2] = mfma(b2[BW[i]], a2.p[AW[i]], lo[2]);
                 }
-                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                acc[0][j] += with_small(mfma(b[0], a1.p[0], zero), lo0);
-                acc[1][j] += with_small(mfma(b[0], aS[0], zero), lo1);
-                asm volatile("" : "+v"(acc[0][j]), "+v"(acc[1][j]));       // added here: the compiler would keep all sums to the end of the loop
+                add(acc[0][j], b[0], a1.p[0], lo[0]);
+                add(acc[1][j], b[0], aS[0], lo[1]);
+                if constexpr (CELL) add(acc[2][j], b2[0], a2.p[0], lo[2]);
                 __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
-                if constexpr (CELL) {
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) b[p] = buf[2 * W::OPER + p * W::PLANE + ub];
-                    lo0 = lo1 = f32x4{0.f, 0.f, 0.f, 0.f};
-                    lo0 = mfma(b[2], a2.p[0], lo0);
-                    lo1 = mfma(b[1], a2.p[0], lo1);
-                    lo0 = mfma(b[0], a2.p[2], lo0);
-                    lo1 = mfma(b[0], a2.p[1], lo1);
-                    lo0 = mfma(b[1], a2.p[1], lo0);
-                    acc[2][j] += with_small(mfma(b[0], a2.p[0], zero), lo0 + lo1);
-                    asm volatile("" : "+v"(acc[2][j]));
-                    __builtin_amdgcn_sched_barrier(0);
-                }
             }
             load_h(next);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!kFirst) stage_next();
         }
     };
-    if (wave < T::WAVES / 2) walk(yes{});
-    else walk(no{});
+    if (wave < T::WAVES / 2) walk(yes{}, no{});
+    else walk(no{}, no{});
+    // What is not finite stays so in a running sum.  Finite sums therefore have met finite small sums only, which with_small would have
+    // left as they are; with any other, all rows are summed again and with_small decides (twice the time, in the workgroups concerned).
+    bool finite = true;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) finite = finite && __builtin_fabsf(acc[p][j][r]) <= kFloatMax;
+    if (!finite) *again = 1;
+    __syncthreads();
+    __builtin_amdgcn_s_setprio(0);
+    if (*again) walk(no{}, yes{});
     // lane: row 16 mb + (lane & 15) of dW, columns 16 j + 4 (lane >> 4) ..
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -1113,7 +1132,7 @@ size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
 template <int D> static int launch_wgrad_d(WgradArgs& a, hipStream_t s) {
     using T = Tile<D>;
     static PerDevice cache;
-    constexpr size_t lds = sizeof(bf16x8) * 2 * 3 * WTile<D>::OPER;
+    constexpr size_t lds = sizeof(bf16x8) * (2 * 3 * WTile<D>::OPER + 1);
     int res = 0;
     DRC_TRY(resident(&wgrad_partial_kernel<D>, T::THREADS, lds, cache, &res));
     if (res > kWgradMaxWgs) res = kWgradMaxWgs;

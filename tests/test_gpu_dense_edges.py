@@ -216,3 +216,35 @@ def test_as_accurate_as_fp32(D, k, rows, sign):
         want = got[A].T @ B
         err = np.linalg.norm(got[n] - want) / np.linalg.norm(want)
         assert err <= (2.0 ** -24 if sign == "one" else 2.0 ** -23), (n, err)
+
+
+@pytest.mark.parametrize("D", [32, 64, 96, 128])
+@pytest.mark.parametrize("rows", [40, 33_000])
+def test_weight_gradients_with_sums_that_are_not_finite(D, rows):
+    """Workgroups whose sums overflow or meet infinities sum their rows again; the others, and the entries of the same workgroup
+    that stay finite, are as without.  One chunk per workgroup at 40 rows, several at 33 000.  Entries are compared with fp64 products
+    where those stay in range (n * 2^-23 of the L1 norm, as above), with their infinities and not-a-numbers elsewhere."""
+    say(f"dense non-finite weight gradients D={D} rows={rows}")
+    rng = np.random.default_rng(D + rows)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)             # noqa: E731
+    W = {n: f(D, D) for n in P.WEIGHT_NAMES}
+    X_cell, X_net, dYc, dYn = f(rows, D), f(rows, D), f(rows, D), f(rows, D)
+    big = np.finfo(np.float32).max
+    at = rng.permutation(rows)[:6]
+    X_cell[at[0], 3], dYc[at[1], 5], dYc[at[2], 7] = np.inf, -np.inf, np.nan
+    X_net[at[3], 4], dYn[at[4], 6], dYn[at[5], 9] = -np.inf, np.inf, np.nan
+    X_cell[at[3], 11] = X_net[at[0], 11] = big                           # finite, with parts that round up
+    got = _run(rows, rows, D, (D, D, D), rng, X_cell, X_net, W, dYc, dYn, edges=False, dup=True)
+    m = got["mask"] == 1
+    for name, A, B in (("self_near", X_cell, np.where(m, dYc, np.float32(0))), ("self_pins", X_net, dYn)):
+        A, B = A.astype(np.float64), B.astype(np.float64)
+        with np.errstate(invalid="ignore", over="ignore"):
+            want, l1 = A.T @ B, np.abs(A).T @ np.abs(B)
+            off = np.abs(got[name] - want)
+        inside = l1 < big
+        assert inside.any() and np.isnan(want).any() and np.isinf(want).any()
+        assert np.all(off[inside] <= rows * 2.0 ** -23 * l1[inside]), name
+        assert np.array_equal(np.isnan(got[name])[~np.isfinite(l1)], np.isnan(want)[~np.isfinite(l1)]), name
+        inf = np.isinf(want)
+        assert np.array_equal(got[name][inf], want[inf]), name
+    assert np.all(got["pinned"][:, [c for c in range(D) if c not in (5, 7)]] == 0)       # H_pinned is zero
