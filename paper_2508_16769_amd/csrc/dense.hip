@@ -32,7 +32,11 @@
 // as one another, and together little less than their sum.  A matrix instruction takes 16 clocks of the SIMD and keeps vector
 // instructions out for 8 of them; LDS reads come at 256 bytes a clock, writes at 80.  Forward projection of 250 000 cells and
 // 180 000 nets: 204 -> 191 us with fragments read ahead, conflict-free places in LDS and graph descriptors in registers;
-// global memory is no longer what it waits for (without any loads and stores 188).  Not kept: wavefronts with 32 columns and
+// global memory is no longer what it waits for (without any loads and stores 188).  Vector and matrix instructions of a SIMD's two
+// wavefronts take turns for the most part: 191 -> 184 with 385 -> 330 vector instructions per wavefront and tile of cells (the scattered
+// operand in units of eight neighbouring columns, cleared without a loop) and matrix instructions issued first.  Not kept: blocks of
+// 256 rows whose operands stay in registers while the weights pass by in LDS (1.2 M cells 660 -> 758: a barrier every 16 columns, and
+// more splitting in all); wavefronts with 32 columns and
 // all registers of a SIMD (241), and staging spread between the matrix instructions of the same wavefront (201).
 #include "dr_internal.h"
 
@@ -191,17 +195,17 @@ template <int N> __device__ __forceinline__ void pad_stores(float* p) {
 }
 
 // Weight fragments of one 16-column block: output column n = first + (lane & 15), unit 4 s + (lane >> 4) per step.
-// TRANS: B[k][n] = W[n][k].
-template <int D, bool TRANS>
+// TRANS: B[k][n] = W[n][k].  PLAIN: unit u = columns 8u .. 8u+7 (the scattered operand).
+template <int D, bool TRANS, bool PLAIN = false>
 __device__ __forceinline__ void load_weight(const float* __restrict__ W, int first, int lane, bf16x8 (&w)[Tile<D>::KS][3]) {
     const int n = first + (lane & 15);
 #pragma unroll
     for (int s = 0; s < Tile<D>::KS; ++s) {
-        const int k0 = 4 * (4 * s + (lane >> 4));
+        const int u = 4 * s + (lane >> 4);
         float x[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int k = k0 + (j & 3) + (j >> 2) * (D / 2);
+            const int k = PLAIN ? 8 * u + j : 4 * u + (j & 3) + (j >> 2) * (D / 2);
             x[j] = TRANS ? W[(size_t)n * D + k] : W[(size_t)k * D + n];
         }
         const Split8 sp = split8(x);
@@ -258,9 +262,8 @@ __device__ __forceinline__ void load_pairs(PairRegs& r, Buf vals, Buf idx, int k
 // `on` false: goes to the gap behind the last unit
 template <int D> __device__ __forceinline__ void put_pair(bf16x8* plane, bool on, int row, int col, float v) {
     using T = Tile<D>;
-    const int half = col >= D / 2 ? 1 : 0, c = col - half * (D / 2);
-    const int at = on ? unit_at<D>(c >> 2, row) : T::PLANE - 1;
-    put_parts(reinterpret_cast<__bf16*>(plane + at) + (c & 3) + 4 * half, 8 * T::PLANE, v);
+    const int at = on ? unit_at<D>(col >> 3, row) * 8 + (col & 7) : (T::PLANE - 1) * 8;
+    put_parts(reinterpret_cast<__bf16*>(plane) + at, 8 * T::PLANE, v);
 }
 
 // rows past the end hold zeros at column 0
@@ -272,13 +275,18 @@ __device__ __forceinline__ void stage_cbsr(bf16x8* oper, const PairRegs& pr, con
     const int none = opaque(0);
     struct Words { int w[4]; };
     const bf16x8 z = __builtin_bit_cast(bf16x8, Words{none, none, none, none});
-    for (int u = ppart; u < T::KU * 3; u += T::TPR) oper[(u / T::KU) * T::PLANE + unit_at<D>(u % T::KU, row)] = z;
+#pragma unroll
+    for (int u = 0; u < T::KU; u += T::TPR)
+        if (T::KU % T::TPR == 0 || u + ppart < T::KU) {
+#pragma unroll
+            for (int p = 0; p < 3; ++p) oper[p * T::PLANE + unit_at<D>(u + ppart, row)] = z;
+        }
     // the threads of a row sit in one wavefront and LDS executes a wavefront's accesses in order
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int u = 0; u < kPairs; ++u)
-        put_pair<D>(oper, ppart + T::TPR * u < k, row, (int)pr.c[u], pr.v[u]);
+            put_pair<D>(oper, ppart + T::TPR * u < k, row, (int)pr.c[u], pr.v[u]);
     if (k > T::TPR * kPairs && row < rows_left)
         for (int t = ppart + T::TPR * kPairs; t < k; t += T::TPR) put_pair<D>(oper, true, row, idx[(size_t)row * k + t], vals[(size_t)row * k + t]);
 }
@@ -400,7 +408,7 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
     const bool pairs = wave * 64 < T::BM * T::TPR;                 // whole wavefronts
 
     bf16x8 wS[T::KS][3], w1[T::KS][3], w2[T::KS][3];
-    load_weight<D, false>(CELL ? a->w_self_near : a->w_self_pins, 16 * nb, lane, wS);
+    load_weight<D, false, true>(CELL ? a->w_self_near : a->w_self_pins, 16 * nb, lane, wS);
     load_weight<D, false>(CELL ? a->w_neigh_near : a->w_neigh_pins, 16 * nb, lane, w1);
     if constexpr (CELL) load_weight<D, false>(a->w_pinned, 16 * nb, lane, w2);
 
@@ -453,8 +461,10 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
             here = ahead;
             ahead.seek(segs, n, t1 + n_wg);
             auto stage_next = [&]() {
+                __builtin_amdgcn_s_setprio(0);
                 commit(g1, t1, smem + (cur ^ 1) * 3 * T::OPER);
                 prefetch(ahead.g, t1 + n_wg);
+                __builtin_amdgcn_s_setprio(1);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
@@ -497,8 +507,10 @@ __device__ __forceinline__ void proj_fwd_side(const DRC_CONST ProjFwdArgs* a, bf
                     }
                     __builtin_amdgcn_raw_buffer_store_b32(m, bm, at, 0, CP);
                 }
+                if (relu) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = relu ? fmaxf(v[r], 0.0f) : v[r];
+                    for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+                }
                 store4<CP>(by, at * 4, v);
             }
             if constexpr (!kFirst) stage_next();
@@ -842,6 +854,9 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
         }
     };
     const int chunks = (g->rows + W::CR - 1) / W::CR;
+    // Matrix instructions go first: cells 700 -> 674 us; nets 357 -> 373 (two products a chunk: they wait for the staging, as cells do
+    // whose selections do not fit the registers, k = 64: 184 -> 190 us at 250 000 rows).
+    const bool matrix_first = CELL && g->k <= W::TPR * kPairs;
     const auto walk = [&](auto first, auto careful) {
         constexpr bool kFirst = decltype(first)::value, kCareful = decltype(careful)::value;
 #pragma unroll
@@ -861,11 +876,10 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             const int next = chunk + g->wgs;
             bf16x8* const buf = smem + cur * 3 * W::OPER;
             auto stage_next = [&]() {
-                // matrix instructions go first: cells 700 -> 674 us; nets 357 -> 373 (two products a chunk: they wait for staging)
-                if constexpr (CELL) __builtin_amdgcn_s_setprio(0);
+                if (matrix_first) __builtin_amdgcn_s_setprio(0);
                 commit(next, smem + (cur ^ 1) * 3 * W::OPER);
                 load_y(next + g->wgs);
-                if constexpr (CELL) __builtin_amdgcn_s_setprio(1);
+                if (matrix_first) __builtin_amdgcn_s_setprio(1);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
