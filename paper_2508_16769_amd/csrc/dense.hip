@@ -551,15 +551,15 @@ struct ProjBwdSide {
 __device__ __forceinline__ ProjBwdSide fetch(const DRC_CONST ProjBwdSide* s) {
     return ProjBwdSide{s->dY, s->mask, s->dH1, s->dH2, s->idx, s->S, s->rows, s->k, s->tile0};
 }
-struct ProjBwdArgs {
-    ProjBwdSide cell[kMaxGraphs], net[kMaxGraphs];
+template <int G> struct ProjBwdArgs {         // of up to G graphs
+    ProjBwdSide cell[G], net[G];
     const float *w_self_near, *w_neigh_near, *w_pinned, *w_self_pins, *w_neigh_pins;
-    int n, cell_tiles, net_tiles, cell_wgs;
+    int n, cell_tiles, net_tiles, cell_wgs, net_wgs;
 };
-static_assert(sizeof(ProjBwdArgs) < 4096, "kernel arguments");
+static_assert(sizeof(ProjBwdArgs<kMaxGraphs>) < 4096, "kernel arguments");
 
-template <int D, bool CELL>
-__device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf16x8* smem, int wg, int n_wg) {
+template <int D, bool CELL, typename ARGS>
+__device__ __forceinline__ void proj_bwd_side(const DRC_CONST ARGS* a, bf16x8* smem, int wg, int n_wg) {
     using T = Tile<D>;
     constexpr int LDC = D + 4;
     const DRC_CONST ProjBwdSide* const segs = CELL ? a->cell : a->net;
@@ -729,11 +729,11 @@ __device__ __forceinline__ void proj_bwd_side(const DRC_CONST ProjBwdArgs* a, bf
 }
 
 template <int D>
-__global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs a) {
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs<kMaxGraphs> a) {
     extern __shared__ bf16x8 smem8[];
-    const DRC_CONST ProjBwdArgs* const k = kernel_args<ProjBwdArgs>();
+    const DRC_CONST ProjBwdArgs<kMaxGraphs>* const k = kernel_args<ProjBwdArgs<kMaxGraphs>>();
     if ((int)blockIdx.x < k->cell_wgs) proj_bwd_side<D, true>(k, smem8, blockIdx.x, k->cell_wgs);
-    else proj_bwd_side<D, false>(k, smem8, blockIdx.x - k->cell_wgs, gridDim.x - k->cell_wgs);
+    else proj_bwd_side<D, false>(k, smem8, blockIdx.x - k->cell_wgs, k->net_wgs);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -769,8 +769,12 @@ struct WgradSeg {                 // one side of one graph
     float* dW[3];                 // H1's, CBSR's, H2's
     int rows, k, wg0, wgs;
 };
-struct WgradArgs { WgradSeg s[2 * kMaxGraphs]; int n; };
-static_assert(sizeof(WgradArgs) < 4096, "kernel arguments");
+template <int G> struct WgradArgs {           // of up to G graphs
+    WgradSeg s[2 * G];
+    PartialSum* table;            // where the sums to be made are listed; null: wgrad_reduce_kernel follows
+    int n;
+};
+static_assert(sizeof(WgradArgs<kMaxGraphs>) < 4096, "kernel arguments");
 
 template <int D, bool CELL>
 __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* smem, int wg) {
@@ -952,15 +956,43 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(Tile<D>::THREADS, 2) void wgrad_partial_kernel(WgradArgs a) {
-    extern __shared__ bf16x8 smem8[];
+template <int D, typename ARGS> __device__ __forceinline__ void wgrad_workgroup(const DRC_CONST ARGS* k, bf16x8* smem, int wg) {
+    if (k->table && wg == 0 && (int)threadIdx.x < k->n / 2 * kSumsPerGraph) {      // cells and nets in turn
+        const int q = threadIdx.x / kSumsPerGraph, e = threadIdx.x % kSumsPerGraph, prod = e < 3 ? e : e - 3;
+        const DRC_CONST WgradSeg* const g = k->s + 2 * q + (e < 3 ? 0 : 1);
+        const int n = g->wgs * WTile<D>::KG;
+        k->table[threadIdx.x] = PartialSum{g->scratch + (size_t)prod * n * D * D, g->dW[prod], n, D * D};
+    }
     int q = 0;
-    const DRC_CONST WgradArgs* const k = kernel_args<WgradArgs>();
-    while (q + 1 < k->n && (int)blockIdx.x >= k->s[q + 1].wg0) ++q;
+    while (q + 1 < k->n && wg >= k->s[q + 1].wg0) ++q;
     const DRC_CONST WgradSeg* const g = k->s + q;
-    if (g->mask) wgrad_side<D, true>(g, smem8, blockIdx.x - g->wg0);
-    else wgrad_side<D, false>(g, smem8, blockIdx.x - g->wg0);
+    if (g->mask) wgrad_side<D, true>(g, smem, wg - g->wg0);
+    else wgrad_side<D, false>(g, smem, wg - g->wg0);
+}
+template <int D>
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void wgrad_partial_kernel(WgradArgs<kMaxGraphs> a) {
+    extern __shared__ bf16x8 smem8[];
+    wgrad_workgroup<D>(kernel_args<WgradArgs<kMaxGraphs>>(), smem8, blockIdx.x);
+}
+
+// Weight gradients and projections of a backward pass in one launch.  Neither waits for the other, and while either has fewer tiles
+// than the chip has compute units, or ends in a last round that is half empty, the other's workgroups fill it.  Two launches / one,
+// whole layers, us: 2 048 cells, D = 64 60 / 50; 10 000 82 / 76; 60 000 185 / 179; 20 000, D = 128 194 / 187; 250 000 1 182 / 1 172.
+constexpr int kBothGraphs = 12;
+struct DenseBwdArgs {
+    ProjBwdArgs<kBothGraphs> proj;
+    WgradArgs<kBothGraphs> wgrad;
+    int wgrad_wgs;
+};
+static_assert(sizeof(DenseBwdArgs) < 4096, "kernel arguments");
+template <int D>
+__global__ __launch_bounds__(Tile<D>::THREADS, 2) void dense_bwd_kernel(DenseBwdArgs a) {
+    extern __shared__ bf16x8 smem8[];
+    const DRC_CONST DenseBwdArgs* const k = kernel_args<DenseBwdArgs>();
+    const int wg = (int)blockIdx.x - k->wgrad_wgs;
+    if (wg < 0) wgrad_workgroup<D>(&k->wgrad, smem8, blockIdx.x);
+    else if (wg < k->proj.cell_wgs) proj_bwd_side<D, true>(&k->proj, smem8, wg, k->proj.cell_wgs);
+    else proj_bwd_side<D, false>(&k->proj, smem8, wg - k->proj.cell_wgs, k->proj.net_wgs);
 }
 
 // dW[i] = sum over a side's partials in a fixed order: wavefront w of the workgroup sums partials w, w + 16, ... of 64 x 4
@@ -969,7 +1001,7 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void wgrad_partial_kernel(Wgra
 constexpr int kRedWaves = 16;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int D>
-__global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs a) {
+__global__ __launch_bounds__(64 * kRedWaves) void wgrad_reduce_kernel(WgradArgs<kMaxGraphs> a) {
     __shared__ f64x4 part[kRedWaves][64];
     constexpr int kBlocks = D * D / 256;                 // workgroups per product
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1079,29 +1111,21 @@ int launch_proj_fwd(const ProjFwdJob* jobs, int n, const dr_heteroconv_weights& 
     }
 }
 
-template <int D> static int launch_proj_bwd_d(ProjBwdArgs& a, hipStream_t s) {
+template <int D> constexpr size_t dproj_lds() {
+    return sizeof(bf16x8) * 4 * Tile<D>::OPER + sizeof(float) * 2 * Tile<D>::BM * (D + 4);
+}
+// tiles and workgroups, `res` at most
+template <int D, int G> static void plan_proj_bwd(ProjBwdArgs<G>& a, int res) {
     using T = Tile<D>;
-    static PerDevice cache;
-    constexpr size_t lds = sizeof(bf16x8) * 4 * T::OPER + sizeof(float) * 2 * T::BM * (D + 4);
-    int res = 0;
-    DRC_TRY(resident(&dproj_kernel<D>, T::THREADS, lds, cache, &res));
     a.cell_tiles = a.net_tiles = 0;
     for (int i = 0; i < a.n; ++i) {
         a.cell[i].tile0 = a.cell_tiles; a.net[i].tile0 = a.net_tiles;
         a.cell_tiles += (a.cell[i].rows + T::BM - 1) / T::BM;
         a.net_tiles += (a.net[i].rows + T::BM - 1) / T::BM;
     }
-    int nets = 0;
-    share(3ll * a.cell_tiles, 2ll * a.net_tiles, a.cell_tiles, a.net_tiles, res, &a.cell_wgs, &nets);
-    if (a.cell_wgs + nets == 0) return DR_OK;
-    hipLaunchKernelGGL((dproj_kernel<D>), dim3((unsigned)(a.cell_wgs + nets)), dim3(T::THREADS), lds, s, a);
-    DRC_HIP(hipGetLastError());
-    return DR_OK;
+    share(3ll * a.cell_tiles, 2ll * a.net_tiles, a.cell_tiles, a.net_tiles, res, &a.cell_wgs, &a.net_wgs);
 }
-
-int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, hipStream_t s) {
-    if (n > kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "projection of %d graphs in one launch", n);
-    ProjBwdArgs a{};
+template <int G> static void set_proj_bwd(ProjBwdArgs<G>& a, const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& W) {
     a.n = n;
     a.w_self_near = W.self_near; a.w_neigh_near = W.neigh_near; a.w_pinned = W.pinned;
     a.w_self_pins = W.self_pins; a.w_neigh_pins = W.neigh_pins;
@@ -1110,6 +1134,23 @@ int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& 
         a.cell[i] = ProjBwdSide{j.dY_cell, j.mask, j.dH_near, j.dH_pinned, j.idx_near, j.S_cell, (int)j.Nc, j.k_near, 0};
         a.net[i] = ProjBwdSide{j.dY_net, nullptr, j.dH_pins, nullptr, j.idx_self, j.S_net, (int)j.Nn, j.k_self, 0};
     }
+}
+template <int D> static int launch_proj_bwd_d(ProjBwdArgs<kMaxGraphs>& a, hipStream_t s) {
+    using T = Tile<D>;
+    static PerDevice cache;
+    int res = 0;
+    DRC_TRY(resident(&dproj_kernel<D>, T::THREADS, dproj_lds<D>(), cache, &res));
+    plan_proj_bwd<D>(a, res);
+    if (a.cell_wgs + a.net_wgs == 0) return DR_OK;
+    hipLaunchKernelGGL((dproj_kernel<D>), dim3((unsigned)(a.cell_wgs + a.net_wgs)), dim3(T::THREADS), dproj_lds<D>(), s, a);
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& W, int D, hipStream_t s) {
+    if (n > kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "projection of %d graphs in one launch", n);
+    ProjBwdArgs<kMaxGraphs> a{};
+    set_proj_bwd(a, jobs, n, W);
     switch (D) {
         case 32: return launch_proj_bwd_d<32>(a, s);
         case 64: return launch_proj_bwd_d<64>(a, s);
@@ -1143,12 +1184,9 @@ size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
     }
 }
 
-template <int D> static int launch_wgrad_d(WgradArgs& a, hipStream_t s) {
-    using T = Tile<D>;
-    static PerDevice cache;
-    constexpr size_t lds = sizeof(bf16x8) * (2 * 3 * WTile<D>::OPER + 1);
-    int res = 0;
-    DRC_TRY(resident(&wgrad_partial_kernel<D>, T::THREADS, lds, cache, &res));
+template <int D> constexpr size_t wgrad_lds() { return sizeof(bf16x8) * (2 * 3 * WTile<D>::OPER + 1); }
+// workgroups of every side, about `res` in all; returns their number
+template <int D, int G> static int plan_wgrad(WgradArgs<G>& a, int res) {
     if (res > kWgradMaxWgs) res = kWgradMaxWgs;
     int64_t work = 0;
     for (int i = 0; i < a.n; ++i) work += (int64_t)a.s[i].rows * (a.s[i].mask ? 3 : 2);
@@ -1161,27 +1199,76 @@ template <int D> static int launch_wgrad_d(WgradArgs& a, hipStream_t s) {
         g.wg0 = wgs;
         wgs += g.wgs;
     }
-    hipLaunchKernelGGL((wgrad_partial_kernel<D>), dim3((unsigned)wgs), dim3(T::THREADS), lds, s, a);
-    hipLaunchKernelGGL((wgrad_reduce_kernel<D>), dim3((unsigned)(a.n * 3 * (D * D / 256))), dim3(64 * kRedWaves), 0, s, a);
-    DRC_HIP(hipGetLastError());
-    return DR_OK;
+    return wgs;
 }
-
-int launch_wgrads(const WgradJob* jobs, int n, int D, hipStream_t s) {
-    if (n > 2 * kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "weight gradients of %d operands in one launch", n);
-    WgradArgs a{};
+template <int G> static void set_wgrad(WgradArgs<G>& a, const WgradJob* jobs, int n) {
     a.n = n;
     for (int i = 0; i < n; ++i) {
         const WgradJob& j = jobs[i];
         a.s[i] = WgradSeg{j.dY, j.H1, j.H2, j.vals, j.mask, j.idx, static_cast<float*>(j.scratch), {j.dW_H1, j.dW_cbsr, j.dW_H2},
                           (int)j.rows, j.k, 0, 0};
     }
+}
+template <int D> static int launch_wgrad_d(WgradArgs<kMaxGraphs>& a, hipStream_t s) {
+    using T = Tile<D>;
+    static PerDevice cache;
+    int res = 0;
+    DRC_TRY(resident(&wgrad_partial_kernel<D>, T::THREADS, wgrad_lds<D>(), cache, &res));
+    const int wgs = plan_wgrad<D>(a, res);
+    hipLaunchKernelGGL((wgrad_partial_kernel<D>), dim3((unsigned)wgs), dim3(T::THREADS), wgrad_lds<D>(), s, a);
+    if (!a.table) hipLaunchKernelGGL((wgrad_reduce_kernel<D>), dim3((unsigned)(a.n * 3 * (D * D / 256))), dim3(64 * kRedWaves), 0, s, a);
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+static int launch_wgrads_to(const WgradJob* jobs, int n, int D, PartialSum* table, hipStream_t s) {
+    if (n > 2 * kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "weight gradients of %d operands in one launch", n);
+    WgradArgs<kMaxGraphs> a{};
+    set_wgrad(a, jobs, n);
+    a.table = table;
     if (n == 0) return DR_OK;
     switch (D) {
         case 32: return launch_wgrad_d<32>(a, s);
         case 64: return launch_wgrad_d<64>(a, s);
         case 96: return launch_wgrad_d<96>(a, s);
         case 128: return launch_wgrad_d<128>(a, s);
+        default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
+    }
+}
+int launch_wgrads(const WgradJob* jobs, int n, int D, hipStream_t s) { return launch_wgrads_to(jobs, n, D, nullptr, s); }
+
+template <int D> static int launch_dense_bwd_d(const WgradJob* wgrads, const ProjBwdJob* proj, int n, const dr_heteroconv_weights& W,
+                                               PartialSum* table, hipStream_t s) {
+    if (n > kBothGraphs) {
+        DRC_TRY(launch_wgrads_to(wgrads, 2 * n, D, table, s));
+        return launch_proj_bwd(proj, n, W, D, s);
+    }
+    using T = Tile<D>;
+    static PerDevice cache;
+    constexpr size_t lds = dproj_lds<D>() > wgrad_lds<D>() ? dproj_lds<D>() : wgrad_lds<D>();
+    int res = 0;
+    DRC_TRY(resident(&dense_bwd_kernel<D>, T::THREADS, lds, cache, &res));
+    DenseBwdArgs a{};
+    set_proj_bwd(a.proj, proj, n, W);
+    set_wgrad(a.wgrad, wgrads, 2 * n);
+    a.wgrad.table = table;
+    // As many workgroups for either as it would have alone: how a weight gradient is summed does not depend on what shares its launch.
+    plan_proj_bwd<D>(a.proj, res);
+    a.wgrad_wgs = plan_wgrad<D>(a.wgrad, res);
+    hipLaunchKernelGGL((dense_bwd_kernel<D>), dim3((unsigned)(a.wgrad_wgs + a.proj.cell_wgs + a.proj.net_wgs)), dim3(T::THREADS), lds, s, a);
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+int launch_dense_bwd(const WgradJob* wgrads, const ProjBwdJob* proj, int n, const dr_heteroconv_weights& W, int D, PartialSum* table,
+                     PendingSums* pending, hipStream_t s) {
+    if (n > kMaxGraphs) return fail(DR_ERR_INVALID_ARG, "dense gradients of %d graphs in one launch", n);
+    *pending = PendingSums{table, n * kSumsPerGraph, D * D};
+    switch (D) {
+        case 32: return launch_dense_bwd_d<32>(wgrads, proj, n, W, table, s);
+        case 64: return launch_dense_bwd_d<64>(wgrads, proj, n, W, table, s);
+        case 96: return launch_dense_bwd_d<96>(wgrads, proj, n, W, table, s);
+        case 128: return launch_dense_bwd_d<128>(wgrads, proj, n, W, table, s);
         default: return fail(DR_ERR_UNSUPPORTED, "projection width D = %d not in {32,64,96,128}", D);
     }
 }

@@ -63,7 +63,19 @@ struct TopkJob {
     uint16_t* idx2;
 };
 int launch_topks(const TopkJob* jobs, int n, int D, hipStream_t s);
+// A weight gradient whose partial sums wait in scratch memory: dst[at] = 4 * sum over i < n of src[i * count + at], at < count.
+struct PartialSum {
+    const float* src;
+    float* dst;
+    int n, count;
+};
+// Weight gradients that a later launch on the same stream is to sum up; the table is written by the launch that writes the partials.
+struct PendingSums {
+    const PartialSum* table;      // device memory
+    int n, count;                 // n = 0: nothing is pending
+};
 // DR-SpMM.  A job is one relation; jobs of one call may share launches and run side by side.
+constexpr int64_t kSmallLaunch = 8 * 24 * 256;   // rows of a launch up to which a wavefront takes 8 of them
 constexpr int kMaxSegs = 18;     // relations per launch (their descriptors travel as kernel arguments)
 struct SpmmFwdJob {
     const dr_csr* A;
@@ -101,7 +113,8 @@ struct SpmmDenseJob {
     CompactPiece more[2];
 };
 constexpr int kDenseMaxK = 64;   // one window of compact slots
-int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s);    // n <= 64
+// `pending` (may be null): summed up by the last launch of these; what no launch took stays pending.
+int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s, PendingSums* pending = nullptr);    // n <= 64
 int launch_spmm_fwds(const SpmmFwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
 int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s);       // n <= 64
 int launch_spmm_fwd(const dr_csr* A, const float* xs_vals, const uint16_t* xs_idx, int D, int k, float* H,
@@ -231,5 +244,11 @@ struct WgradJob {                 // one node type of one graph; with a mask: ce
 };
 size_t wgrad_scratch_bytes(int64_t rows, int D, int products);
 int launch_wgrads(const WgradJob* jobs, int n, int D, hipStream_t s);      // n <= 2 * kMaxGraphs
+// Weight gradients (cells and nets of each graph in turn) and projections of a backward pass.  The partial sums of the weight gradients
+// are left to launch_spmm_dense, or to launch_pending_sums; `table` has room for kSumsPerGraph entries a graph.
+constexpr int kSumsPerGraph = 5;
+int launch_dense_bwd(const WgradJob* wgrads, const ProjBwdJob* proj, int n, const dr_heteroconv_weights& W, int D, PartialSum* table,
+                     PendingSums* pending, hipStream_t s);
+int launch_pending_sums(const PendingSums& pending, hipStream_t s);
 
 }  // namespace drc

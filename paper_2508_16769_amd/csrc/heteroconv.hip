@@ -1,10 +1,11 @@
 // HeteroConv layer: per-graph context and the forward / backward schedules.  The three relation modules (near, pins,
 // pinned) are independent of one another up to the merge at the cells (paper Section 3.4: independent sub-graph updates
 // launched together).  A step of the layer is ONE launch in which the workgroups of all relations -- and, in a model, of
-// all sub-graphs -- run side by side: a forward is three launches (D-ReLU, DR-SpMM, projections), a backward five (weight
-// gradients and their reduction, projection gradients, transposed DR-SpMM of a placed `near`, the other transposed DR-SpMMs
-// with the dense input gradients).  Three streams joined by events did the same with 24 launches and some 30 event
-// operations; a 2048-cell layer pass then took 0.21 ms, nearly all of it launch and event overhead.
+// all sub-graphs -- run side by side: a forward is three launches (D-ReLU, DR-SpMM, projections), a backward two or three (weight
+// gradients beside projection gradients; transposed DR-SpMM of a placed `near` on staged tiles; the other transposed DR-SpMMs with the
+// dense input gradients, and the sums over the weight gradients' partials behind them).  Three streams joined by events did the
+// same with 24 launches and some 30 event operations; a 2048-cell layer pass then took 0.21 ms, nearly all of it launch and event
+// overhead; with five launches backward 0.067 ms, now 0.050.
 // Everything runs on the caller's stream, in order; the host does not wait inside fwd / bwd, except in the first backward pass
 // of a context that is called on another stream than the one before it (the scratch is the context's).
 #include "dr_internal.h"
@@ -50,6 +51,7 @@ struct dr_heteroconv {
     float* G_pins;      // [Nc,k_pins]   pins piece, only where it needs a buffer of its own
     float* G_pinned;    // [Nn,k_pinned] pinned piece, likewise
     void* wg_scratch[2];   // cells, nets
+    drc::PartialSum* wg_sums;   // [kMaxGraphs * kSumsPerGraph] the sums over that scratch that a pass of several graphs leaves to a later launch
     // The scratch above is one for all backward passes of a context: a pass on another stream than the last one's waits for it.
     // The first change of streams waits on the host; from then on every pass records `end`, and a change waits on the device.
     // (A context that stays on one stream does without the event: it is a packet of its own for the GPU, 3 us of a 70 us layer.
@@ -72,6 +74,15 @@ using namespace drc;
 // Staging the gathered rows of a tile pays from about two edges per staged row on (measured on the 1.2 M-cell `near`
 // relation: 0.64 ms at 2.1, 0.42 ms at 4.7, against 0.67 ms for the plain gather).
 static constexpr double kMinStagingReuse = 2.0;
+
+// Whether a backward pass runs its transposed `near` on the plan's staged tiles.  While wavefronts of 8 rows fit the chip at once
+// (kSmallLaunch), `near` is summed sooner in the launch that writes dX anyway, beside pins, than in a launch of its own that every step has
+// to wait for (backward of 2 048 / 10 000 / 20 000 cells, D = 64, staged / beside pins: 33 / 29, 49 / 44, 60 / 52 us; 33 000: 81 / 87).
+static bool on_staged_tiles(const dr_heteroconv* c) {
+    if (!c->near_plan) return false;
+    const bool beside_pins = c->k_pins == c->k_near && c->k_near <= kDenseMaxK;
+    return !beside_pins || c->Nc + c->Nn > kSmallLaunch;
+}
 
 HeteroDims drc::heteroconv_dims(const dr_heteroconv* c) {
     return HeteroDims{c->Nc, c->Nn, c->D, c->k_near, c->k_pins, c->k_self, c->k_pinned};
@@ -186,6 +197,7 @@ int drc::heteroconv_create_capacity(dr_heteroconv** ctx, int64_t Nc, int64_t Nn,
     if ((rc = dev_alloc(c, (void**)&c->dH_pinned, 4 * (size_t)Nc * D))) return bail(rc);
     if ((rc = dev_alloc(c, &c->wg_scratch[0], wgrad_scratch_bytes(Nc, D, 3)))) return bail(rc);
     if ((rc = dev_alloc(c, &c->wg_scratch[1], wgrad_scratch_bytes(Nn, D, 2)))) return bail(rc);
+    if ((rc = dev_alloc(c, (void**)&c->wg_sums, sizeof(PartialSum) * kMaxGraphs * kSumsPerGraph))) return bail(rc);
     if ((rc = dev_alloc(c, (void**)&c->S_cell, 4 * (size_t)Nc * k_near))) return bail(rc);
     if ((rc = dev_alloc(c, (void**)&c->S_net, 4 * (size_t)Nn * k_self))) return bail(rc);
     if (k_pins != k_near && k_pins > kDenseMaxK && (rc = dev_alloc(c, (void**)&c->G_pins, 4 * (size_t)Nc * k_pins))) return bail(rc);
@@ -594,8 +606,9 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
         jc = SpmmDenseJob{};
         jc.n_rows = c->Nc; jc.dX = L.dX_cell; jc.dH = c->dH;
         const CompactPiece near_piece{q.i_near, c->k_near, c->S_cell, g_near};
-        const bool near_apart = c->near_plan || split || c->k_near > kDenseMaxK;   // near's sum joins the self term in S_cell first
-        if (near_apart && !c->near_plan) first[n_first++] = SpmmBwdJob{&c->At[0], c->dH, q.i_near, c->k_near, c->S_cell, 1};
+        const bool staged = on_staged_tiles(c);
+        const bool near_apart = staged || split || c->k_near > kDenseMaxK;   // near's sum joins the self term in S_cell first
+        if (near_apart && !staged) first[n_first++] = SpmmBwdJob{&c->At[0], c->dH, q.i_near, c->k_near, c->S_cell, 1};
         if (!split) {
             if (c->k_near <= kDenseMaxK) {
                 jc.idx = q.i_near; jc.k = c->k_near; jc.init = c->S_cell; jc.gate = g_near;
@@ -634,15 +647,16 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
     const bool alone = apart && n == 1;
     // The weight gradients come first: what the projections write is then gathered right away.
     if (!alone) {
-        DRC_TRY(launch_wgrads(wj, 2 * n, D, s));
-        if (!need_dx) return DR_OK;
-        DRC_TRY(launch_proj_bwd(pj, n, *W, D, s));
+        if (!need_dx) return launch_wgrads(wj, 2 * n, D, s);
+        PendingSums sums{};
+        DRC_TRY(launch_dense_bwd(wj, pj, n, *W, D, g[0].c->wg_sums, &sums, s));
         for (int i = 0; i < n; ++i)
-            if (g[i].c->near_plan)
+            if (on_staged_tiles(g[i].c))
                 DRC_TRY(launch_spmm_bwd_planned(g[i].c->near_plan, g[i].c->dH, cbsr_sets(g[i].c, g[i].S).i_near, g[i].c->k_near, g[i].c->S_cell, 1, s));
         if (n_first) DRC_TRY(launch_spmm_bwds(first, n_first, D, s));
         if (n_then) DRC_TRY(launch_spmm_bwds(then, n_then, D, s));
-        return launch_spmm_dense(dj, 2 * n, D, s);
+        DRC_TRY(launch_spmm_dense(dj, 2 * n, D, s, &sums));
+        return launch_pending_sums(sums, s);
     }
     dr_heteroconv* c = g[0].c;
     { ScopedTiming tm(c, kWgCell, s); DRC_TRY(launch_wgrads(&wj[0], 1, D, s)); }
@@ -655,7 +669,7 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
     part.Nn = 0;
     { ScopedTiming tm(c, kDhCell, s); DRC_TRY(launch_proj_bwd(&part, 1, *W, D, s)); }
     { ScopedTiming tm(c, kBwdPinned, s); DRC_TRY(launch_spmm_dense(&dj[1], dj[1].At ? 1 : 0, D, s)); }
-    if (c->near_plan) {
+    if (on_staged_tiles(c)) {
         ScopedTiming tm(c, kBwdNear, s);
         DRC_TRY(launch_spmm_bwd_planned(c->near_plan, c->dH, cbsr_sets(c, g[0].S).i_near, c->k_near, c->S_cell, 1, s));
     }

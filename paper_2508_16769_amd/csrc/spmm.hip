@@ -592,7 +592,7 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
 // backward 21 / 26; 20 to 60 edges 51 / 101 and 105 / 114; rows of 1500 among them 39 / 100 and 55 / 98.  Where it does not
 // pay: a forward at D >= 256 or k = 128 with a few edges per row (D = 256, k = 32: 25 / 20, but 81 / 110 with 20 to 60 edges;
 // there is a row buffer per group to clear, whatever the row brings).  A line by what registers and LDS let reside was slower.
-static bool few_rows(int64_t rows) { return rows <= 8ll * 24 * 256; }
+static bool few_rows(int64_t rows) { return rows <= kSmallLaunch; }
 
 static int fwd_kind(const SpmmFwdJob& j) {
     const int k = j.k;
@@ -882,11 +882,66 @@ template <int KPL, int RW, bool DENSE> constexpr int bwd_wave_words(int D) {    
     return kNG * kLPE * KPL + RW * kLPE * KPL / 2 + plan_ints<RW, DENSE>() + (DENSE ? D : 0);
 }
 
+// Partial sums of weight gradients, in workgroups behind those of the rows: 64 entries of one gradient each.  They need a few
+// microseconds of loads one behind the other, which pass under the last rows; as a launch of their own they took 5 to 7
+// (layers of 2 048 to 60 000 cells).  64 bits: up to 256 partials of nearly equal size lose as much in 32-bit sums as everything before.
+constexpr int kSumEntries = kWave;
+__device__ __forceinline__ void sum_partials(const PartialSum* __restrict__ table, int per, int block, double* sums) {
+    const PartialSum p = table[block / per];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int at = (block % per) * kSumEntries + lane;
+    const float* src = p.src + at;
+    double s = 0.0;
+    constexpr int U = 16;
+    int b = wave;
+    for (; b + (U - 1) * kWPB < p.n; b += U * kWPB) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = src[(size_t)(b + u * kWPB) * p.count];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += (double)v[u];
+    }
+    for (; b < p.n; b += 4 * kWPB) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = b + u * kWPB < p.n ? src[(size_t)(b + u * kWPB) * p.count] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += (double)v[u];
+    }
+    sums[wave * kWave + lane] = s;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int w = 1; w < kWPB; ++w) s += sums[w * kWave + lane];
+        p.dst[at] = (float)(4.0 * s);
+    }
+}
+constexpr size_t kSumLds = sizeof(double) * kWPB * kWave;
+__global__ __launch_bounds__(kWPB * kWave) void pending_sums_kernel(const PartialSum* __restrict__ table, int per) {
+    __shared__ double sums[kWPB * kWave];
+    sum_partials(table, per, blockIdx.x, sums);
+}
+int launch_pending_sums(const PendingSums& pending, hipStream_t s) {
+    if (pending.n == 0) return DR_OK;
+    const int per = pending.count / kSumEntries;
+    hipLaunchKernelGGL(pending_sums_kernel, dim3((unsigned)(pending.n * per)), dim3(kWPB * kWave), 0, s, pending.table, per);
+    DRC_HIP(hipGetLastError());
+    return DR_OK;
+}
+
+struct SumTail { const PartialSum* table; int first, per; };      // workgroups from `first` on; table null: none
+
 template <int KPL, int EPI, int RW, bool ADAPT, bool DENSE>
-__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL == 4 ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk) {
+__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL == 4 ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
     extern __shared__ float4 smem4[];
     __shared__ unsigned long long sLong[kWPB];
     constexpr int kWin = kLPE * KPL;                                       // compact slots per pass over the block
+    if constexpr (DENSE) {
+        if (tail.table && (int)blockIdx.x >= tail.first) {
+            sum_partials(tail.table, tail.per, (int)blockIdx.x - tail.first, reinterpret_cast<double*>(smem4));
+            return;
+        }
+    }
     const int local = blockIdx.x / kNumXcd, xcd = blockIdx.x % kNumXcd;
     int sg = 0;
     while (sg + 1 < args.n && local >= args.s[sg + 1].first) ++sg;
@@ -1060,7 +1115,7 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL
 }
 
 template <int KPL, int EPI, bool ADAPT, bool DENSE>
-static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s) {
+static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s, const PendingSums& sums = PendingSums{}) {
     int64_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.s[i].N;
     const bool few = few_rows(rows);
@@ -1073,10 +1128,18 @@ static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s) {
         g.first = first;
         first += g.per_xcd;
     }
-    const size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8, DENSE>(a.D) : bwd_wave_words<KPL, 32, DENSE>(a.D));
-    const dim3 grid((unsigned)(first * kNumXcd)), block(kWPB * kWave);
-    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds, s, a, dk);
-    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, DENSE>), grid, block, lds, s, a, dk);
+    size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8, DENSE>(a.D) : bwd_wave_words<KPL, 32, DENSE>(a.D));
+    SumTail tail{nullptr, first * kNumXcd, 0};
+    int extra = 0;
+    if (DENSE && sums.n) {
+        tail.table = sums.table;
+        tail.per = sums.count / kSumEntries;
+        extra = sums.n * tail.per;
+        lds = lds < kSumLds ? kSumLds : lds;
+    }
+    const dim3 grid((unsigned)(first * kNumXcd + extra)), block(kWPB * kWave);
+    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds, s, a, dk, tail);
+    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, DENSE>), grid, block, lds, s, a, dk, tail);
 }
 
 static int bwd_kind(int k) { return k <= 8 ? 1 : (k <= 16 ? 2 : (k <= 32 ? 4 : 8)); }
@@ -1116,7 +1179,7 @@ int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s) {
 }
 
 // The dense input gradient of several kinds of source rows (k <= kDenseMaxK).
-int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s) {
+int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s, PendingSums* pending) {
     unsigned long long done = 0;
     for (int i = 0; i < n; ++i) {
         if ((done >> i & 1) || jobs[i].n_rows == 0) continue;
@@ -1135,11 +1198,18 @@ int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s) {
             g.init = q.init; g.gate = q.gate;
             g.more[0] = q.more[0]; g.more[1] = q.more[1];
         }
+        bool last = true;
+        for (int r = 0; r < n; ++r) last = last && ((done >> r & 1) || jobs[r].n_rows == 0);
+        PendingSums sums{};
+        if (last && pending) {
+            sums = *pending;
+            pending->n = 0;
+        }
         switch (kind) {
-            case 1: launch_bwd_kernel<1, 4, false, true>(a, DegreeK{}, s); break;
-            case 2: launch_bwd_kernel<2, 4, false, true>(a, DegreeK{}, s); break;
-            case 4: launch_bwd_kernel<4, 2, false, true>(a, DegreeK{}, s); break;
-            default: launch_bwd_kernel<8, 1, false, true>(a, DegreeK{}, s); break;
+            case 1: launch_bwd_kernel<1, 4, false, true>(a, DegreeK{}, s, sums); break;
+            case 2: launch_bwd_kernel<2, 4, false, true>(a, DegreeK{}, s, sums); break;
+            case 4: launch_bwd_kernel<4, 2, false, true>(a, DegreeK{}, s, sums); break;
+            default: launch_bwd_kernel<8, 1, false, true>(a, DegreeK{}, s, sums); break;
         }
     }
     DRC_HIP(hipGetLastError());
