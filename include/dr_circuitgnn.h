@@ -315,9 +315,8 @@ int heteroconv_set_cell_order(dr_heteroconv* ctx, const int32_t* cell_order, int
 /*
  * Relation concurrency (paper Section 3.4).  DR_OVERLAP_ON: a step of the layer is one launch in which the workgroups
  * of near, pins and pinned run side by side.  DR_OVERLAP_OFF: a launch per relation, back to back, in the same dependency
- * order.  DR_OVERLAP_AUTO (default): shared launches while one relation's workgroups leave CUs idle at their tails
- * (max(Nc, Nn) * D < 2^26), a launch per relation beyond that, where every launch fills the chip and a relation finds
- * part of what was just written in the caches.  Takes effect from the next heteroconv_fwd / heteroconv_bwd.
+ * order.  DR_OVERLAP_AUTO (default): shared launches while that gains (max(Nc, Nn) * D < 2^28), a launch per relation
+ * beyond that.  Takes effect from the next heteroconv_fwd / heteroconv_bwd.
  */
 #define DR_OVERLAP_AUTO 0
 #define DR_OVERLAP_ON   1

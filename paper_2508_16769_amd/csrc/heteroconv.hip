@@ -495,14 +495,16 @@ int heteroconv_bwd(dr_heteroconv* c, const float* dY_cell, const float* dY_net, 
 
 }  // extern "C"
 
-// Whether each relation gets launches of its own.  Shared launches pay off while one relation's workgroups leave compute
-// units idle; at 1.2 M cells every launch has tens of thousands of workgroups, and a relation that is gathered right after
-// its D-ReLU was written still finds part of it in the memory-side cache.  Per-kernel timing needs separate launches.
+// Whether each relation gets launches of its own.  Shared launches fill the compute units that the last workgroups of a relation leave
+// idle, and random and grid-local gathers pass side by side.  Whole layers, apart / shared, ms: D = 128, 500 000 cells 2.43 / 2.30,
+// 700 000 3.45 / 3.32, 1.2 M 6.03 / 5.96 (k = 8 5.41 / 5.36), 2 M 9.70 / 9.67; 1.2 M cells of D = 64 2.93 / 2.85, of D = 96
+// 4.99 / 4.86.  The line is where nothing is left of that.  Per-kernel timing needs separate launches.
+constexpr int64_t kApartFrom = int64_t(1) << 28;           // elements of a node type's rows
 bool drc::heteroconv_relations_apart(const dr_heteroconv* c) {
     if (c->profile || c->overlap == DR_OVERLAP_OFF) return true;
     if (c->overlap == DR_OVERLAP_ON) return false;
     const int64_t rows = c->Nc > c->Nn ? c->Nc : c->Nn;
-    return rows * c->D >= kFullLaunch;
+    return rows * c->D >= kApartFrom;
 }
 
 int drc::heteroconv_forward(const LayerFwd* g, int n, const dr_heteroconv_weights* W, hipStream_t s, ForwardOptions opt) {
