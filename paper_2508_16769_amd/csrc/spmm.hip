@@ -468,7 +468,7 @@ struct SpmmFwdArgs { SpmmFwdSeg s[kMaxSegs]; int n, D; };
 constexpr int fwd_waves(int kpl, bool adapt) { return kpl == 16 || kpl == -8 ? 4 : (adapt || kpl < 0 || kpl > 1 ? 5 : 6); }
 
 template <int KPL, int EPI, int RW, bool ADAPT>
-__global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_kernel(SpmmFwdArgs args, DegreeK dk) {
+__device__ __forceinline__ void spmm_fwd_rows(const SpmmFwdArgs& args, const DegreeK& dk) {
     static_assert(!ADAPT || KPL != 0, "the adaptive-K forward needs a path that can mask pairs");
     extern __shared__ float4 smem4[];
     __shared__ unsigned long long sLong[kWPB];
@@ -585,14 +585,48 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_
     }
 }
 
-// Rows per wavefront: 32 fill the groups evenly (a group that finishes takes the next row); with few rows in all, 8 --
-// one per group -- put four times as many wavefronts on the chip and cut the serial chain of a wavefront to one row per
-// group.  The line is about where wavefronts of 8 rows stop fitting the chip at once (256 compute units x 20 to 24
-// wavefronts).  Measured at 40 000 rows, 8 / 32 rows per wavefront, us: D = 128, k = 32, 2 to 8 edges per row forward 15 / 17,
-// backward 21 / 26; 20 to 60 edges 51 / 101 and 105 / 114; rows of 1500 among them 39 / 100 and 55 / 98.  Where it does not
-// pay: a forward at D >= 256 or k = 128 with a few edges per row (D = 256, k = 32: 25 / 20, but 81 / 110 with 20 to 60 edges;
-// there is a row buffer per group to clear, whatever the row brings).  A line by what registers and LDS let reside was slower.
-static bool few_rows(int64_t rows) { return rows <= kSmallLaunch; }
+template <int KPL, int EPI, int RW, bool ADAPT>
+__global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, ADAPT)) void spmm_fwd_kernel(SpmmFwdArgs args, DegreeK dk) {
+    spmm_fwd_rows<KPL, EPI, RW, ADAPT>(args, dk);
+}
+template <int KPL, int EPI>
+__global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, false)) void spmm_fwd_mid_kernel(SpmmFwdArgs args, DegreeK dk) {
+    spmm_fwd_rows<KPL, EPI, 16, false>(args, dk);
+}
+
+// Rows per wavefront.  More of them fill the groups evenly (a group that finishes takes the next row) and are planned at the cost of
+// fewer; fewer of them put more wavefronts on the chip and cut the serial chain of a wavefront (8: one row per group).
+//  * 8 while all wavefronts of a launch are resident at once, 256 compute units x 20 wavefronts; to 49 152 rows where a relation has fewer
+//    rows than columns: nets, whose high-fanout rows are a workgroup's one after the other.  8 / 16 rows, us: 33 000 rows, D = 128,
+//    k = 16, 10 edges per row forward 17.2 / 18.0, backward 17.6 / 18.4; 45 000 rows, k = 32 27.0 / 21.8 and 29.9 / 27.0; 42 000
+//    nets, 42 of them with 200 to 2000 edges, 33 / 45 and 49 / 71.  (8 / 32 rows at 40 000 rows of 20 to 60 edges 51 / 101 and 105 / 114.)
+//  * 16 where the largest relation has no more than 2^19 rows, and for compact sums at any size.  32 / 16 rows, us: near of 60 000 cells,
+//    D = 128, k = 32 forward 34 / 26, backward 41 / 33; 100 000 46 / 41 and 67 / 49; 250 000, k = 8 74 / 61 and 105 / 74; 400 000,
+//    D = 64, k = 16 100 / 92 and 112 / 92; backward of 1.2 M 580 / 530 (near), 430 / 424 (pins), 604 / 586 (pinned).
+//  * 32 above that, where the chip is full anyway (16 / 32: near of 1.2 M cells forward 436 / 412, with 8 edges per row 238 / 222; the
+//    layer's relations together, D = 64, forward 1 308 / 1 283, backward with dense rows 1 536 / 1 518), and for forward rows of less than
+//    nine edges, where a wavefront's plan weighs most, as soon as wavefronts of 16 are not resident at once (16 / 32: pinned, 3.9
+//    edges per row, 80 000 rows 20 / 22, 100 000, k = 8 24 / 21, 250 000 64 / 61; near with 8 edges per row, 250 000 58 / 51, 450 000
+//    98 / 90).  Not for nets, whose rows differ most: 5.5 edges on average, 175 000 nets 75 / 83, 300 000 112 / 118.
+// The adaptive forward keeps 8 and 32 (16 at 250 000 rows: near 91 / 97, pins 86 / 82, pinned 64 / 61).
+// Where 8 do not pay: a forward at D >= 256 or k = 128 with a few edges per row (D = 256, k = 32: 25 / 20 with 32, but 81 / 110 with 20 to
+// 60 edges; there is a row buffer per group to clear, whatever the row brings).
+struct LaunchShape {
+    int64_t rows = 0, most = 0, nnz = 0;
+    bool nets = false;
+    void add(int64_t n_rows, int64_t n_cols, int64_t n) {
+        rows += n_rows;
+        most = n_rows > most ? n_rows : most;
+        nnz += n;
+        nets = nets || n_rows < n_cols;
+    }
+    static constexpr int64_t resident(int rows_per_wave) { return (int64_t)rows_per_wave * 20 * 256; }
+    bool eight() const { return rows <= (nets ? kSmallLaunch : resident(8)); }
+    int forward() const { return eight() ? 8 : (!nets && nnz < 9 * rows ? rows <= resident(16) : most <= int64_t(1) << 19) ? 16 : 32; }
+    int forward_adaptive() const { return rows <= kSmallLaunch ? 8 : 32; }
+    int compact() const { return eight() ? 8 : 16; }
+    int dense() const { return eight() ? 8 : most <= int64_t(1) << 19 ? 16 : 32; }
+};
 
 static int fwd_kind(const SpmmFwdJob& j) {
     const int k = j.k;
@@ -608,11 +642,8 @@ static int fwd_kind(const SpmmFwdJob& j) {
 }
 
 template <int KPL, int EPI, bool ADAPT>
-static void launch_fwd_kernel(SpmmFwdArgs& a, DegreeK dk, hipStream_t s) {
-    int64_t rows = 0;
-    for (int i = 0; i < a.n; ++i) rows += a.s[i].M;
-    const bool few = few_rows(rows);
-    const int rw = few ? 8 : 32;
+static void launch_fwd_kernel(SpmmFwdArgs& a, const LaunchShape& shape, DegreeK dk, hipStream_t s) {
+    const int rw = ADAPT ? shape.forward_adaptive() : shape.forward();
     int first = 0;
     for (int i = 0; i < a.n; ++i) {
         SpmmFwdSeg& g = a.s[i];
@@ -621,10 +652,15 @@ static void launch_fwd_kernel(SpmmFwdArgs& a, DegreeK dk, hipStream_t s) {
         g.first = first;
         first += g.per_xcd;
     }
-    const size_t lds = sizeof(float) * kWPB * ((size_t)kNG * (a.D + kBufPad) + (few ? plan_ints<8>() : plan_ints<32>()));
     const dim3 grid((unsigned)(first * kNumXcd)), block(kWPB * kWave);
-    if (few) hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 8, ADAPT>), grid, block, lds, s, a, dk);
-    else hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 32, ADAPT>), grid, block, lds, s, a, dk);
+    const size_t buffers = sizeof(float) * kWPB * (size_t)kNG * (a.D + kBufPad), plan = sizeof(float) * kWPB;
+    if (rw == 8) {
+        hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 8, ADAPT>), grid, block, buffers + plan * plan_ints<8>(), s, a, dk);
+    } else if (rw == 32) {
+        hipLaunchKernelGGL((spmm_fwd_kernel<KPL, EPI, 32, ADAPT>), grid, block, buffers + plan * plan_ints<32>(), s, a, dk);
+    } else if constexpr (!ADAPT) {
+        hipLaunchKernelGGL((spmm_fwd_mid_kernel<KPL, EPI>), grid, block, buffers + plan * plan_ints<16>(), s, a, dk);
+    }
 }
 
 // Several relations at once: those whose width takes the same kernel share a launch.
@@ -641,25 +677,27 @@ int launch_spmm_fwds(const SpmmFwdJob* jobs, int n, int D, hipStream_t s) {
         const int kind = fwd_kind(j);
         SpmmFwdArgs a{};
         a.D = D;
+        LaunchShape shape;
         for (int r = i; r < n && a.n < kMaxSegs; ++r) {
             const SpmmFwdJob& q = jobs[r];
             if ((done >> r & 1) || q.A->nnz == 0 || fwd_kind(q) != kind) continue;
             done |= 1ull << r;
+            shape.add(q.A->n_rows, q.A->n_cols, q.A->nnz);
             SpmmFwdSeg& g = a.s[a.n++];
             g = SpmmFwdSeg{q.A->rowptr, q.A->colidx, q.A->vals, q.xs_vals, q.xs_idx, q.H, (int)q.A->n_rows, q.k,
                            (D % 4 == 0 && aligned(q.H, 16)) ? 1 : 0, 0, 0, 0};
         }
         switch (kind) {
-            case 1: launch_fwd_kernel<1, 4, false>(a, DegreeK{}, s); break;
-            case 2: launch_fwd_kernel<2, 3, false>(a, DegreeK{}, s); break;
-            case 4: launch_fwd_kernel<4, 2, false>(a, DegreeK{}, s); break;
-            case 8: launch_fwd_kernel<8, 1, false>(a, DegreeK{}, s); break;
-            case 16: launch_fwd_kernel<16, 1, false>(a, DegreeK{}, s); break;
-            case -1: launch_fwd_kernel<-1, 4, false>(a, DegreeK{}, s); break;
-            case -2: launch_fwd_kernel<-2, 3, false>(a, DegreeK{}, s); break;
-            case -3: launch_fwd_kernel<-3, 2, false>(a, DegreeK{}, s); break;
-            case -4: launch_fwd_kernel<-4, 2, false>(a, DegreeK{}, s); break;
-            default: launch_fwd_kernel<0, 1, false>(a, DegreeK{}, s); break;
+            case 1: launch_fwd_kernel<1, 4, false>(a, shape, DegreeK{}, s); break;
+            case 2: launch_fwd_kernel<2, 3, false>(a, shape, DegreeK{}, s); break;
+            case 4: launch_fwd_kernel<4, 2, false>(a, shape, DegreeK{}, s); break;
+            case 8: launch_fwd_kernel<8, 1, false>(a, shape, DegreeK{}, s); break;
+            case 16: launch_fwd_kernel<16, 1, false>(a, shape, DegreeK{}, s); break;
+            case -1: launch_fwd_kernel<-1, 4, false>(a, shape, DegreeK{}, s); break;
+            case -2: launch_fwd_kernel<-2, 3, false>(a, shape, DegreeK{}, s); break;
+            case -3: launch_fwd_kernel<-3, 2, false>(a, shape, DegreeK{}, s); break;
+            case -4: launch_fwd_kernel<-4, 2, false>(a, shape, DegreeK{}, s); break;
+            default: launch_fwd_kernel<0, 1, false>(a, shape, DegreeK{}, s); break;
         }
     }
     DRC_HIP(hipGetLastError());
@@ -679,21 +717,23 @@ int launch_spmm_fwd_adaptive(const dr_csr* A, const float* xr_vals, const uint16
     SpmmFwdArgs a{};
     a.D = D;
     a.n = 1;
+    LaunchShape shape;
+    shape.add(A->n_rows, A->n_cols, A->nnz);
     a.s[0] = SpmmFwdSeg{A->rowptr, A->colidx, A->vals, xr_vals, xr_idx, H, (int)A->n_rows, k, (D % 4 == 0 && aligned(H, 16)) ? 1 : 0, 0, 0, 0};
     // widths that fill the lanes evenly keep the vector loads of the uniform kernel (pairs past the destination's
     // width are redirected after the load); the others take unaligned pairs
     const bool vec = (k == 8) || (k == 16 && aligned(xr_vals, 8) && aligned(xr_idx, 4)) ||
                      ((k == 32 || k == 64) && aligned(xr_vals, 16) && aligned(xr_idx, 8));
     switch (vec ? k / kLPE + 100 : (k + kLPE - 1) / kLPE) {
-        case 101: launch_fwd_kernel<1, 4, true>(a, dk, s); break;
-        case 102: launch_fwd_kernel<2, 3, true>(a, dk, s); break;
-        case 104: launch_fwd_kernel<4, 2, true>(a, dk, s); break;
-        case 108: launch_fwd_kernel<8, 1, true>(a, dk, s); break;
-        case 1: launch_fwd_kernel<-1, 4, true>(a, dk, s); break;
-        case 2: launch_fwd_kernel<-2, 3, true>(a, dk, s); break;
-        case 3: launch_fwd_kernel<-3, 2, true>(a, dk, s); break;
-        case 4: launch_fwd_kernel<-4, 2, true>(a, dk, s); break;
-        default: launch_fwd_kernel<-8, 1, true>(a, dk, s); break;   // k1 <= 64 (checked by the caller)
+        case 101: launch_fwd_kernel<1, 4, true>(a, shape, dk, s); break;
+        case 102: launch_fwd_kernel<2, 3, true>(a, shape, dk, s); break;
+        case 104: launch_fwd_kernel<4, 2, true>(a, shape, dk, s); break;
+        case 108: launch_fwd_kernel<8, 1, true>(a, shape, dk, s); break;
+        case 1: launch_fwd_kernel<-1, 4, true>(a, shape, dk, s); break;
+        case 2: launch_fwd_kernel<-2, 3, true>(a, shape, dk, s); break;
+        case 3: launch_fwd_kernel<-3, 2, true>(a, shape, dk, s); break;
+        case 4: launch_fwd_kernel<-4, 2, true>(a, shape, dk, s); break;
+        default: launch_fwd_kernel<-8, 1, true>(a, shape, dk, s); break;   // k1 <= 64 (checked by the caller)
     }
     DRC_HIP(hipGetLastError());
     return DR_OK;
@@ -932,7 +972,7 @@ int launch_pending_sums(const PendingSums& pending, hipStream_t s) {
 struct SumTail { const PartialSum* table; int first, per; };      // workgroups from `first` on; table null: none
 
 template <int KPL, int EPI, int RW, bool ADAPT, bool DENSE>
-__global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL == 4 ? 5 : 6)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
+__device__ __forceinline__ void spmm_bwd_rows(const SpmmBwdArgs& args, const DegreeK& dk, const SumTail& tail) {
     extern __shared__ float4 smem4[];
     __shared__ unsigned long long sLong[kWPB];
     constexpr int kWin = kLPE * KPL;                                       // compact slots per pass over the block
@@ -1114,12 +1154,19 @@ __global__ __launch_bounds__(kWPB * kWave, KPL == 8 ? 4 : (ADAPT || DENSE || KPL
     }
 }
 
+constexpr int bwd_waves(int kpl, bool adapt, bool dense) { return kpl == 8 ? 4 : (adapt || dense || kpl == 4 ? 5 : 6); }
+template <int KPL, int EPI, int RW, bool ADAPT, bool DENSE>
+__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, ADAPT, DENSE)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
+    spmm_bwd_rows<KPL, EPI, RW, ADAPT, DENSE>(args, dk, tail);
+}
+template <int KPL, int EPI>
+__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, false, true)) void spmm_dense_mid_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
+    spmm_bwd_rows<KPL, EPI, 16, false, true>(args, dk, tail);
+}
+
 template <int KPL, int EPI, bool ADAPT, bool DENSE>
-static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s, const PendingSums& sums = PendingSums{}) {
-    int64_t rows = 0;
-    for (int i = 0; i < a.n; ++i) rows += a.s[i].N;
-    const bool few = few_rows(rows);
-    const int rw = few ? 8 : 32;
+static void launch_bwd_kernel(SpmmBwdArgs& a, const LaunchShape& shape, DegreeK dk, hipStream_t s, const PendingSums& sums = PendingSums{}) {
+    const int rw = DENSE ? shape.dense() : shape.compact();
     int first = 0;
     for (int i = 0; i < a.n; ++i) {
         SpmmBwdSeg& g = a.s[i];
@@ -1128,18 +1175,27 @@ static void launch_bwd_kernel(SpmmBwdArgs& a, DegreeK dk, hipStream_t s, const P
         g.first = first;
         first += g.per_xcd;
     }
-    size_t lds = sizeof(float) * kWPB * (size_t)(few ? bwd_wave_words<KPL, 8, DENSE>(a.D) : bwd_wave_words<KPL, 32, DENSE>(a.D));
     SumTail tail{nullptr, first * kNumXcd, 0};
     int extra = 0;
     if (DENSE && sums.n) {
         tail.table = sums.table;
         tail.per = sums.count / kSumEntries;
         extra = sums.n * tail.per;
-        lds = lds < kSumLds ? kSumLds : lds;
     }
     const dim3 grid((unsigned)(first * kNumXcd + extra)), block(kWPB * kWave);
-    if (few) hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds, s, a, dk, tail);
-    else hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, DENSE>), grid, block, lds, s, a, dk, tail);
+    const auto lds = [&](int words) {
+        const size_t bytes = sizeof(float) * kWPB * (size_t)words;
+        return extra && bytes < kSumLds ? kSumLds : bytes;
+    };
+    if (rw == 8) {
+        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds(bwd_wave_words<KPL, 8, DENSE>(a.D)), s, a, dk, tail);
+    } else if constexpr (!DENSE) {
+        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 16, ADAPT, false>), grid, block, lds(bwd_wave_words<KPL, 16, false>(a.D)), s, a, dk, tail);
+    } else if (rw == 16) {
+        hipLaunchKernelGGL((spmm_dense_mid_kernel<KPL, EPI>), grid, block, lds(bwd_wave_words<KPL, 16, true>(a.D)), s, a, dk, tail);
+    } else {
+        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, true>), grid, block, lds(bwd_wave_words<KPL, 32, true>(a.D)), s, a, dk, tail);
+    }
 }
 
 static int bwd_kind(int k) { return k <= 8 ? 1 : (k <= 16 ? 2 : (k <= 32 ? 4 : 8)); }
@@ -1158,20 +1214,22 @@ int launch_spmm_bwds(const SpmmBwdJob* jobs, int n, int D, hipStream_t s) {
         const int kind = bwd_kind(j.k);
         SpmmBwdArgs a{};
         a.D = D;
+        LaunchShape shape;
         for (int r = i; r < n && a.n < kMaxSegs; ++r) {
             const SpmmBwdJob& q = jobs[r];
             if ((done >> r & 1) || q.At->nnz == 0 || bwd_kind(q.k) != kind) continue;
             done |= 1ull << r;
+            shape.add(q.At->n_rows, q.At->n_cols, q.At->nnz);
             SpmmBwdSeg& g = a.s[a.n++];
             g.rowptr = q.At->rowptr; g.colidx = q.At->colidx; g.avals = q.At->vals;
             g.dH = q.dH; g.xs_idx = q.xs_idx; g.dXs = q.dXs;
             g.N = (int)q.At->n_rows; g.k = q.k; g.accumulate = q.accumulate ? 1 : 0;
         }
         switch (kind) {
-            case 1: launch_bwd_kernel<1, 4, false, false>(a, DegreeK{}, s); break;
-            case 2: launch_bwd_kernel<2, 4, false, false>(a, DegreeK{}, s); break;
-            case 4: launch_bwd_kernel<4, 2, false, false>(a, DegreeK{}, s); break;
-            default: launch_bwd_kernel<8, 1, false, false>(a, DegreeK{}, s); break;
+            case 1: launch_bwd_kernel<1, 4, false, false>(a, shape, DegreeK{}, s); break;
+            case 2: launch_bwd_kernel<2, 4, false, false>(a, shape, DegreeK{}, s); break;
+            case 4: launch_bwd_kernel<4, 2, false, false>(a, shape, DegreeK{}, s); break;
+            default: launch_bwd_kernel<8, 1, false, false>(a, shape, DegreeK{}, s); break;
         }
     }
     DRC_HIP(hipGetLastError());
@@ -1186,10 +1244,12 @@ int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s, Pen
         const int kind = bwd_kind(jobs[i].k);
         SpmmBwdArgs a{};
         a.D = D;
+        LaunchShape shape;
         for (int r = i; r < n && a.n < kMaxSegs; ++r) {
             const SpmmDenseJob& q = jobs[r];
             if ((done >> r & 1) || q.n_rows == 0 || bwd_kind(q.k) != kind) continue;
             done |= 1ull << r;
+            shape.add(q.n_rows, q.At ? q.At->n_cols : 0, 0);
             SpmmBwdSeg& g = a.s[a.n++];
             if (q.At) { g.rowptr = q.At->rowptr; g.colidx = q.At->colidx; g.avals = q.At->vals; }
             if (q.At2) { g.rowptr2 = q.At2->rowptr; g.colidx2 = q.At2->colidx; g.avals2 = q.At2->vals; g.col2_off = q.col2_off; }
@@ -1206,10 +1266,10 @@ int launch_spmm_dense(const SpmmDenseJob* jobs, int n, int D, hipStream_t s, Pen
             pending->n = 0;
         }
         switch (kind) {
-            case 1: launch_bwd_kernel<1, 4, false, true>(a, DegreeK{}, s, sums); break;
-            case 2: launch_bwd_kernel<2, 4, false, true>(a, DegreeK{}, s, sums); break;
-            case 4: launch_bwd_kernel<4, 2, false, true>(a, DegreeK{}, s, sums); break;
-            default: launch_bwd_kernel<8, 1, false, true>(a, DegreeK{}, s, sums); break;
+            case 1: launch_bwd_kernel<1, 4, false, true>(a, shape, DegreeK{}, s, sums); break;
+            case 2: launch_bwd_kernel<2, 4, false, true>(a, shape, DegreeK{}, s, sums); break;
+            case 4: launch_bwd_kernel<4, 2, false, true>(a, shape, DegreeK{}, s, sums); break;
+            default: launch_bwd_kernel<8, 1, false, true>(a, shape, DegreeK{}, s, sums); break;
         }
     }
     DRC_HIP(hipGetLastError());
@@ -1232,15 +1292,17 @@ int launch_spmm_bwd_adaptive(const dr_csr* At, const uint8_t* edge_class, const 
     SpmmBwdArgs a{};
     a.D = D;
     a.n = 1;
+    LaunchShape shape;
+    shape.add(At->n_rows, At->n_cols, At->nnz);
     SpmmBwdSeg& g = a.s[0];
     g.rowptr = At->rowptr; g.colidx = At->colidx; g.avals = At->vals; g.ecls = edge_class;
     g.dH = dH; g.xs_idx = xr_idx; g.dXs = dXr;
     g.N = (int)At->n_rows; g.k = c->k1; g.accumulate = accumulate ? 1 : 0;
     switch (bwd_kind(c->k1)) {
-        case 1: launch_bwd_kernel<1, 4, true, false>(a, dk, s); break;
-        case 2: launch_bwd_kernel<2, 4, true, false>(a, dk, s); break;
-        case 4: launch_bwd_kernel<4, 2, true, false>(a, dk, s); break;
-        default: launch_bwd_kernel<8, 1, true, false>(a, dk, s); break;   // k <= 64: one window of slots (checked by the caller)
+        case 1: launch_bwd_kernel<1, 4, true, false>(a, shape, dk, s); break;
+        case 2: launch_bwd_kernel<2, 4, true, false>(a, shape, dk, s); break;
+        case 4: launch_bwd_kernel<4, 2, true, false>(a, shape, dk, s); break;
+        default: launch_bwd_kernel<8, 1, true, false>(a, shape, dk, s); break;   // k <= 64: one window of slots (checked by the caller)
     }
     DRC_HIP(hipGetLastError());
     return DR_OK;
