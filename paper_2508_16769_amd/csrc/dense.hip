@@ -33,7 +33,7 @@
 // instructions out for 8 of them; LDS reads come at 256 bytes a clock, writes at 80.  Forward projection of 250 000 cells and
 // 180 000 nets: 204 -> 191 us with fragments read ahead, conflict-free places in LDS and graph descriptors in registers;
 // global memory is no longer what it waits for (without any loads and stores 188).  Vector and matrix instructions of a SIMD's two
-// wavefronts take turns for the most part: 191 -> 184 with 385 -> 330 vector instructions per wavefront and tile of cells (the scattered
+// wavefronts take turns for the most part: 202 -> 192 (a launch each) with 385 -> 330 vector instructions per wavefront and tile of cells (the scattered
 // operand in units of eight neighbouring columns, cleared without a loop) and matrix instructions issued first.  Not kept: blocks of
 // 256 rows whose operands stay in registers while the weights pass by in LDS (1.2 M cells 660 -> 758: a barrier every 16 columns, and
 // more splitting in all); wavefronts with 32 columns and
