@@ -1160,7 +1160,7 @@ __global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, ADAPT, DENSE)) void sp
     spmm_bwd_rows<KPL, EPI, RW, ADAPT, DENSE>(args, dk, tail);
 }
 template <int KPL, int EPI>
-__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, false, true)) void spmm_dense_mid_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
+__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, false, true)) void spmm_bwd_mid_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
     spmm_bwd_rows<KPL, EPI, 16, false, true>(args, dk, tail);
 }
 
@@ -1192,7 +1192,7 @@ static void launch_bwd_kernel(SpmmBwdArgs& a, const LaunchShape& shape, DegreeK 
     } else if constexpr (!DENSE) {
         hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 16, ADAPT, false>), grid, block, lds(bwd_wave_words<KPL, 16, false>(a.D)), s, a, dk, tail);
     } else if (rw == 16) {
-        hipLaunchKernelGGL((spmm_dense_mid_kernel<KPL, EPI>), grid, block, lds(bwd_wave_words<KPL, 16, true>(a.D)), s, a, dk, tail);
+        hipLaunchKernelGGL((spmm_bwd_mid_kernel<KPL, EPI>), grid, block, lds(bwd_wave_words<KPL, 16, true>(a.D)), s, a, dk, tail);
     } else {
         hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, true>), grid, block, lds(bwd_wave_words<KPL, 32, true>(a.D)), s, a, dk, tail);
     }

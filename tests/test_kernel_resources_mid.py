@@ -7,7 +7,7 @@ from paper_2508_16769_amd import build
 
 def test_kernels_of_sixteen_rows():
     rep = build.kernel_resources("spmm.hip")
-    mid = {n: r for n, r in rep.items() if "spmm_fwd_mid_kernel" in n or "spmm_dense_mid_kernel" in n or
+    mid = {n: r for n, r in rep.items() if "spmm_fwd_mid_kernel" in n or "spmm_bwd_mid_kernel" in n or
            re.search(r"spmm_bwd_kernelILi\d+ELi\d+ELi16E", n)}
     assert len(mid) == 10 + 4 + 8, sorted(mid)            # forward by pairs per lane, dense backward, compact backward uniform and adaptive
     for name, r in mid.items():
