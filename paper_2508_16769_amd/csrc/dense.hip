@@ -39,6 +39,7 @@
 // more splitting in all); wavefronts with 32 columns and
 // all registers of a SIMD (241), and staging spread between the matrix instructions of the same wavefront (201).
 #include "dr_internal.h"
+#include "wgrad_shape.h"
 
 #include <type_traits>
 
@@ -1160,20 +1161,9 @@ int launch_proj_bwd(const ProjBwdJob* jobs, int n, const dr_heteroconv_weights& 
     }
 }
 
-constexpr int kWgradMaxWgs = 256;                       // one workgroup per compute unit (its tiles take 147 KB of LDS)
-
 template <int D> static int64_t wgrad_chunks(int64_t rows) { return (rows + WTile<D>::CR - 1) / WTile<D>::CR; }
-// at least two chunks per workgroup: the partial sums a workgroup writes weigh as much as the rows of four chunks.  Up to
-// kWgradSingle of them a chunk each all the same: half the chip is idle then, and a second chunk only lengthens the launch
-// (whole layers, two / one chunk: 2048 cells, D = 64 69.8 / 67.8 us; 3000, 128 95.4 / 94.0; 8000, 64 and 128 the same).
-constexpr int kWgradSingle = 128;
-template <int D> static int64_t wgrad_most(int64_t rows) {
-    const int64_t chunks = wgrad_chunks<D>(rows), single = chunks < kWgradSingle ? chunks : kWgradSingle, half = (chunks + 1) / 2;
-    const int64_t n = half > single ? half : single;
-    return n > kWgradMaxWgs ? kWgradMaxWgs : (n < 1 ? 1 : n);
-}
 template <int D> static size_t wgrad_bytes_d(int64_t rows, int products) {
-    return sizeof(float) * products * (size_t)wgrad_most<D>(rows) * WTile<D>::KG * D * D;
+    return sizeof(float) * products * (size_t)wgrad_most(wgrad_chunks<D>(rows)) * WTile<D>::KG * D * D;
 }
 size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
     switch (D) {
@@ -1185,17 +1175,14 @@ size_t wgrad_scratch_bytes(int64_t rows, int D, int products) {
 }
 
 template <int D> constexpr size_t wgrad_lds() { return sizeof(bf16x8) * (2 * 3 * WTile<D>::OPER + 1); }
-// workgroups of every side, about `res` in all; returns their number
+// workgroups of every side; returns their number
 template <int D, int G> static int plan_wgrad(WgradArgs<G>& a, int res) {
-    if (res > kWgradMaxWgs) res = kWgradMaxWgs;
-    int64_t work = 0;
-    for (int i = 0; i < a.n; ++i) work += (int64_t)a.s[i].rows * (a.s[i].mask ? 3 : 2);
+    WgradSide sides[2 * G];
+    for (int i = 0; i < a.n; ++i) sides[i] = WgradSide{a.s[i].rows, a.s[i].mask ? 3 : 2};
     int wgs = 0;
     for (int i = 0; i < a.n; ++i) {
         WgradSeg& g = a.s[i];
-        int64_t n = work ? (int64_t)g.rows * (g.mask ? 3 : 2) * res / work : 1;
-        const int64_t most = wgrad_most<D>(g.rows);
-        g.wgs = (int)(n < 1 ? 1 : (n > most ? most : n));
+        g.wgs = wgrad_share(sides, a.n, i, D, WTile<D>::CR, res, kFullLaunch);
         g.wg0 = wgs;
         wgs += g.wgs;
     }
@@ -1252,7 +1239,8 @@ template <int D> static int launch_dense_bwd_d(const WgradJob* wgrads, const Pro
     set_proj_bwd(a.proj, proj, n, W);
     set_wgrad(a.wgrad, wgrads, 2 * n);
     a.wgrad.table = table;
-    // As many workgroups for either as it would have alone: how a weight gradient is summed does not depend on what shares its launch.
+    // As many workgroups for either as it would have alone: how the weight gradients of a pass are summed does not depend on the
+    // projections beside them.  (It does on the other sides of the pass: they share the workgroups, wgrad_share.)
     plan_proj_bwd<D>(a.proj, res);
     a.wgrad_wgs = plan_wgrad<D>(a.wgrad, res);
     hipLaunchKernelGGL((dense_bwd_kernel<D>), dim3((unsigned)(a.wgrad_wgs + a.proj.cell_wgs + a.proj.net_wgs)), dim3(T::THREADS), lds, s, a);

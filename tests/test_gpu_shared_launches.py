@@ -42,3 +42,32 @@ def test_shared_launches_give_the_bits_of_separate_ones(D, ks, Nc, Nn):
         assert not torch.isnan(b).any()
         assert torch.equal(a, b)
     layer.heteroconv_destroy()
+
+
+def test_large_layers_sum_their_weight_gradients_as_in_launches_of_their_own():
+    """1.2 M cells and 0.9 M nets of 128: either node type gets as many workgroups as alone, so that no running sum gets longer (and
+    less exact) by sharing the launch.  No edges: the gradients of the self terms are what is compared."""
+    D, k, Nc, Nn = 128, 32, 1_200_000, 900_000
+    say(f"shared launches, large: D={D} {Nc} cells {Nn} nets")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    f = lambda *s: torch.randn(*s, device="cuda", generator=gen)         # noqa: E731
+    empty = lambda m, n: P.Csr(m, n, torch.zeros(m + 1, dtype=torch.int32, device="cuda"),     # noqa: E731
+                               torch.empty(0, dtype=torch.int32, device="cuda"), torch.empty(0, device="cuda"))
+    layer = P.HeteroConv(empty(Nc, Nc), empty(Nn, Nc), empty(Nc, Nn), D, k, k)
+    W = {n: f(D, D) for n in P.WEIGHT_NAMES}
+    saved = layer.alloc_saved()
+    X, dY = (f(Nc, D), f(Nn, D)), (f(Nc, D), f(Nn, D))
+    layer.heteroconv_fwd(*X, W, torch.empty_like(X[0]), torch.empty_like(X[1]), saved)
+
+    def backward(mode):
+        layer.heteroconv_set_overlap(mode)
+        dX = torch.full((Nc, D), float("nan"), device="cuda"), torch.full((Nn, D), float("nan"), device="cuda")
+        dW = {n: torch.full((D, D), float("nan"), device="cuda") for n in P.WEIGHT_NAMES}
+        layer.heteroconv_bwd(*dY, W, saved, *dX, dW)
+        return [*dX] + [dW[n] for n in P.WEIGHT_NAMES]
+
+    apart, shared = backward(P.DR_OVERLAP_OFF), backward(P.DR_OVERLAP_AUTO)
+    for a, b in zip(apart, shared):
+        assert not torch.isnan(b).any()
+        assert torch.equal(a, b)
+    layer.heteroconv_destroy()
