@@ -747,9 +747,9 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs<
 // column.  A wavefront is alone in needing its 16 columns of H, so those go from memory to registers; what all wavefronts
 // need (dZ, and the scattered CBSR) goes through LDS.  Partial sums go to scratch and are added by a second kernel in a fixed order.
 // What bounds it is issue: vector and matrix instructions of a SIMD's two wavefronts take turns for the most part, and a chunk has
-// 144 matrix and about 425 vector instructions per wavefront (cells, D = 128).  1.2 M cells of D = 128: 775 -> 673 us (3.3 TB/s) with
-// 551 -> 425 vector instructions (no cut to finite numbers while all sums are finite), three chains of small products instead of two
-// and one, and matrix instructions issued first; without any loads it takes 504.
+// 144 matrix and about 440 vector instructions per wavefront (cells, D = 128).  1.2 M cells of D = 128: 775 -> 673 us (3.3 TB/s) with
+// 551 -> 440 vector instructions (small sums are cut to finite numbers only where an operand calls for it), three chains of small
+// products instead of two and one, and matrix instructions issued first; without any loads it takes 504.
 // ---------------------------------------------------------------------------------------------------
 template <int D> struct WTile {
     using T = Tile<D>;
@@ -777,6 +777,29 @@ template <int G> struct WgradArgs {           // of up to G graphs
 };
 static_assert(sizeof(WgradArgs<kMaxGraphs>) < 4096, "kernel arguments");
 
+// The small sums are cut to finite numbers (as with_small does) in chunks that hold a number of kWide or more: below it a small sum
+// is less than 32 * 5 * 2^(2 * 62 - 9) and finite.  A not-a-number needs no cut: it makes the leading sum one as well.  Cut always, 96
+// of 500 vector instructions, 1.2 M cells and 250 000 take 0.7 and 1.6 % longer (backward passes 2 512 / 2 500, 532 / 523 us); left to a
+// second walk of the workgroups whose sums are not finite, a single infinity cost 2 500 -> 2 790 and 523 -> 640.
+constexpr float kWide = 4611686018427387904.0f;         // 2^62
+// the largest of m >= 0, |a| and |b|, not-a-numbers aside
+__device__ __forceinline__ float largest(float m, float a, float b) {
+    float v;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(v) : "v"(m), "v"(a), "v"(b));
+    return v;
+}
+__device__ __forceinline__ float largest(const float (&x)[8], float m = 0.0f) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) m = largest(m, x[j], x[j + 1]);
+    return m;
+}
+__device__ __forceinline__ f32x4 cut_to_finite(const f32x4& x) {
+    f32x4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = __builtin_amdgcn_fmed3f(x[r], -kFloatMax, kFloatMax);
+    return v;
+}
+
 template <int D, bool CELL>
 __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* smem, int wg) {
     using T = Tile<D>;
@@ -790,8 +813,9 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
     const int hrow = (4 * kg + (lane >> 4)) * 8, hcol = 16 * mb + (lane & 15);   // this lane's unit of the H operands
 
     f32x4 acc[NP][T::NB];
-    int* const again = reinterpret_cast<int*>(smem + 6 * W::OPER);     // whether a sum is not finite
-    if (tid == 0) *again = 0;
+    int* const wide = reinterpret_cast<int*>(smem + 6 * W::OPER);      // per LDS buffer: the last chunk in it with a number of kWide or more
+    if (tid < 2) wide[tid] = -1;
+    __syncthreads();
 
     float y[8], h1[8], h2[8];
     uint32_t mk[8];
@@ -823,7 +847,14 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
 #pragma unroll
         for (int p = 0; p < 3; ++p) oper[p * W::PLANE + tid] = s.p[p];          // unit (rgi, col) sits at rgi * D + col = tid
     };
-    auto commit = [&](int chunk, bf16x8* buf) {
+    auto commit = [&](int chunk, int to) {
+        bf16x8* const buf = smem + to * 3 * W::OPER;
+        float most = largest(y);
+        if (pairs) {
+#pragma unroll
+            for (int u = 0; u < kPairs; u += 2) most = largest(most, pr.v[u], pr.v[u + 1]);
+        }
+        if (most >= kWide) wide[to] = chunk;
         const Split8 sp = split8(y);
         if constexpr (CELL) {
             const Split8 s1 = select8(sp, [&](int j) { return mk[j] == 1u; }), s2 = select8(sp, [&](int j) { return mk[j] == 0u; });
@@ -854,16 +885,19 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
                 if (ppart + W::TPR * u < g->k) put_one((int)pr.c[u], pr.v[u]);      // rows past the end: a zero at column 0
             const int row = chunk * W::CR + prow;
             if (g->k > W::TPR * kPairs && row < g->rows)
-                for (int p = ppart + W::TPR * kPairs; p < g->k; p += W::TPR)
-                    put_one(g->idx[(size_t)row * g->k + p], g->vals[(size_t)row * g->k + p]);
+                for (int p = ppart + W::TPR * kPairs; p < g->k; p += W::TPR) {
+                    const float v = g->vals[(size_t)row * g->k + p];
+                    if (__builtin_fabsf(v) >= kWide) wide[to] = chunk;
+                    put_one(g->idx[(size_t)row * g->k + p], v);
+                }
         }
     };
     const int chunks = (g->rows + W::CR - 1) / W::CR;
     // Matrix instructions go first: cells 700 -> 674 us; nets 357 -> 373 (two products a chunk: they wait for the staging, as cells do
     // whose selections do not fit the registers, k = 64: 184 -> 190 us at 250 000 rows).
     const bool matrix_first = CELL && g->k <= W::TPR * kPairs;
-    const auto walk = [&](auto first, auto careful) {
-        constexpr bool kFirst = decltype(first)::value, kCareful = decltype(careful)::value;
+    const auto walk = [&](auto first) {
+        constexpr bool kFirst = decltype(first)::value;
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
@@ -872,7 +906,7 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
         if (chunk < chunks) {
             load_y(chunk);
             if constexpr (!kFirst) load_h(chunk);
-            commit(chunk, smem);
+            commit(chunk, 0);
             load_y(chunk + g->wgs);
             if constexpr (kFirst) load_h(chunk);          // the order in which the loop issues them
         }
@@ -882,15 +916,19 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             bf16x8* const buf = smem + cur * 3 * W::OPER;
             auto stage_next = [&]() {
                 if (matrix_first) __builtin_amdgcn_s_setprio(0);
-                commit(next, smem + (cur ^ 1) * 3 * W::OPER);
+                commit(next, cur ^ 1);
                 load_y(next + g->wgs);
                 if (matrix_first) __builtin_amdgcn_s_setprio(1);
             };
             if constexpr (kFirst) stage_next();
             __builtin_amdgcn_sched_barrier(0);
+            float most = largest(h1);
+            if constexpr (CELL) most = largest(h2, most);
             const Split8 a1 = split8(h1);
             Split8 a2;
             if constexpr (CELL) a2 = split8(h2);
+            // H is a wavefront's own, what is staged is everybody's
+            const bool cut = __builtin_amdgcn_readfirstlane(wide[cur]) == chunk || __builtin_amdgcn_ballot_w64(most >= kWide) != 0;
             __builtin_amdgcn_sched_barrier(0);
             bf16x8 aS[3];
 #pragma unroll
@@ -899,12 +937,6 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             // with one rounding: inside the matrix unit they would be cut off below it, always downwards, which over
             // many chunks adds up.  (The small sum as the leading one's start costs half of these instructions and is cut off as well:
             // errors of 2e-7 became 1.5e-6 at 1.1 M rows.)
-            const auto add = [&](f32x4& to, const bf16x8& b, const bf16x8& x, const f32x4& lo) {
-                const f32x4 hi = mfma(b, x, f32x4{0.f, 0.f, 0.f, 0.f});
-                if constexpr (kCareful) to += with_small(hi, lo);
-                else to += hi + lo;
-                asm volatile("" : "+v"(to));          // added here: the compiler would keep all sums to the end of the loop
-            };
 #pragma unroll
             for (int j = 0; j < T::NB; ++j) {
                 constexpr int BW[5] = {2, 0, 1, 1, 0}, AW[5] = {0, 2, 1, 0, 1};
@@ -922,9 +954,20 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
                     lo[1] = mfma(b[BW[i]], aS[AW[i]], lo[1]);
                     if constexpr (CELL) lo[2] = mfma(b2[BW[i]], a2.p[AW[i]], lo[2]);
                 }
-                add(acc[0][j], b[0], a1.p[0], lo[0]);
-                add(acc[1][j], b[0], aS[0], lo[1]);
-                if constexpr (CELL) add(acc[2][j], b2[0], a2.p[0], lo[2]);
+                const f32x4 zero = {};
+                f32x4 hi[3];
+                hi[0] = mfma(b[0], a1.p[0], zero);
+                hi[1] = mfma(b[0], aS[0], zero);
+                if constexpr (CELL) hi[2] = mfma(b2[0], a2.p[0], zero);
+                if (cut) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) lo[p] = cut_to_finite(lo[p]);
+                }
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    acc[p][j] += hi[p] + lo[p];
+                    asm volatile("" : "+v"(acc[p][j]));       // added here: the compiler would keep all sums to the end of the loop
+                }
                 __builtin_amdgcn_sched_barrier(0);    // one column block's operands at a time: more do not fit the registers
             }
             load_h(next);
@@ -932,21 +975,9 @@ __device__ __forceinline__ void wgrad_side(const DRC_CONST WgradSeg* g, bf16x8* 
             if constexpr (!kFirst) stage_next();
         }
     };
-    if (wave < T::WAVES / 2) walk(yes{}, no{});
-    else walk(no{}, no{});
-    // What is not finite stays so in a running sum.  Finite sums therefore have met finite small sums only, which with_small would have
-    // left as they are; with any other, all rows are summed again and with_small decides (twice the time, in the workgroups concerned).
-    bool finite = true;
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int j = 0; j < T::NB; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) finite = finite && __builtin_fabsf(acc[p][j][r]) <= kFloatMax;
-    if (!finite) *again = 1;
-    __syncthreads();
+    if (wave < T::WAVES / 2) walk(yes{});
+    else walk(no{});
     __builtin_amdgcn_s_setprio(0);
-    if (*again) walk(no{}, yes{});
     // lane: row 16 mb + (lane & 15) of dW, columns 16 j + 4 (lane >> 4) ..
 #pragma unroll
     for (int p = 0; p < NP; ++p) {

@@ -221,8 +221,8 @@ def test_as_accurate_as_fp32(D, k, rows, sign):
 @pytest.mark.parametrize("D", [32, 64, 96, 128])
 @pytest.mark.parametrize("rows", [40, 33_000])
 def test_weight_gradients_with_sums_that_are_not_finite(D, rows):
-    """Workgroups whose sums overflow or meet infinities sum their rows again; the others, and the entries of the same workgroup
-    that stay finite, are as without.  One chunk per workgroup at 40 rows, several at 33 000.  Entries are compared with fp64 products
+    """Sums that overflow or meet infinities are infinities and not-a-numbers as in fp32; the others of the same workgroup are as
+    without.  One chunk per workgroup at 40 rows, several at 33 000.  Entries are compared with fp64 products
     where those stay in range (n * 2^-23 of the L1 norm, as above), with their infinities and not-a-numbers elsewhere."""
     say(f"dense non-finite weight gradients D={D} rows={rows}")
     rng = np.random.default_rng(D + rows)
