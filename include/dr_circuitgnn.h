@@ -304,9 +304,9 @@ int heteroconv_destroy(dr_heteroconv* ctx);
  * placement).  cell_order: device array of Nc cell ids, a permutation, in which cells that lie close to each other in
  * the layout sit next to each other (e.g. sorted along a Z-order curve of their coordinates); NULL = the cells' own
  * order.  The layer's backward then runs the transposed `near` DR-SpMM through dr_spmm_plan / dr_spmm_bwd_planned (dH
- * rows of a tile of cells staged in LDS) -- provided the plan can be made and reuses a staged row at least twice on
- * average; *staged (may be NULL) reports whether it does.  Graphs of up to 49152 cells and nets together are faster without and
- * run the plain kernel all the same.  No result changes with the order.  Builds the plan on the
+ * rows of a tile of cells staged in LDS) -- provided the plan can be made, reuses a staged row at least twice on average,
+ * and the graph has more than 49152 cells and nets together or k_pins differs from k_near (a smaller graph with one cell width
+ * is faster without); *staged (may be NULL) reports whether it will.  No result changes with the order.  Builds the plan on the
  * host (waits for `stream` and for the context's transposes); call it once per bound graph, outside the timed loop.
  * A later re-binding of the context drops the plan.
  */

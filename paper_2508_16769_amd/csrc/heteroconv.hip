@@ -75,13 +75,11 @@ using namespace drc;
 // relation: 0.64 ms at 2.1, 0.42 ms at 4.7, against 0.67 ms for the plain gather).
 static constexpr double kMinStagingReuse = 2.0;
 
-// Whether a backward pass runs its transposed `near` on the plan's staged tiles.  While wavefronts of 8 rows fit the chip at once
-// (kSmallLaunch), `near` is summed sooner in the launch that writes dX anyway, beside pins, than in a launch of its own that every step has
-// to wait for (backward of 2 048 / 10 000 / 20 000 cells, D = 64, staged / beside pins: 33 / 29, 49 / 44, 60 / 52 us; 33 000: 81 / 87).
-static bool on_staged_tiles(const dr_heteroconv* c) {
-    if (!c->near_plan) return false;
-    const bool beside_pins = c->k_pins == c->k_near && c->k_near <= kDenseMaxK;
-    return !beside_pins || c->Nc + c->Nn > kSmallLaunch;
+// Whether the launch that writes dX sums the transposed `near` sooner than a launch of its own on staged tiles, which every step has to
+// wait for: beside pins (one cell width), while wavefronts of 8 rows fit the chip at once (kSmallLaunch).  Backward of 2 048 / 10 000 /
+// 20 000 cells, D = 64, staged / beside pins: 33 / 29, 49 / 44, 60 / 52 us; 33 000: 81 / 87.
+static bool near_beside_pins(const dr_heteroconv* c) {
+    return c->k_pins == c->k_near && c->k_near <= kDenseMaxK && c->Nc + c->Nn <= kSmallLaunch;
 }
 
 HeteroDims drc::heteroconv_dims(const dr_heteroconv* c) {
@@ -321,7 +319,9 @@ int heteroconv_set_cell_order(dr_heteroconv* ctx, const int32_t* cell_order, int
     int64_t n_tiles = 0;
     double reuse = 0.0;
     DRC_TRY(dr_spmm_plan_info(plan, &n_tiles, &reuse));
-    if (reuse < kMinStagingReuse) {                    // nothing to gain from staging: rows of a tile share too few neighbours
+    // Nothing to gain from staging: rows of a tile share too few neighbours, or the graph is small.  (The plan was made all the same: it
+    // is what refuses an order that is no permutation.)
+    if (reuse < kMinStagingReuse || near_beside_pins(ctx)) {
         spmm_plan_destroy(plan);
         return DR_OK;
     }
@@ -608,7 +608,7 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
         jc = SpmmDenseJob{};
         jc.n_rows = c->Nc; jc.dX = L.dX_cell; jc.dH = c->dH;
         const CompactPiece near_piece{q.i_near, c->k_near, c->S_cell, g_near};
-        const bool staged = on_staged_tiles(c);
+        const bool staged = c->near_plan != nullptr;
         const bool near_apart = staged || split || c->k_near > kDenseMaxK;   // near's sum joins the self term in S_cell first
         if (near_apart && !staged) first[n_first++] = SpmmBwdJob{&c->At[0], c->dH, q.i_near, c->k_near, c->S_cell, 1};
         if (!split) {
@@ -653,7 +653,7 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
         PendingSums sums{};
         DRC_TRY(launch_dense_bwd(wj, pj, n, *W, D, g[0].c->wg_sums, &sums, s));
         for (int i = 0; i < n; ++i)
-            if (on_staged_tiles(g[i].c))
+            if (g[i].c->near_plan)
                 DRC_TRY(launch_spmm_bwd_planned(g[i].c->near_plan, g[i].c->dH, cbsr_sets(g[i].c, g[i].S).i_near, g[i].c->k_near, g[i].c->S_cell, 1, s));
         if (n_first) DRC_TRY(launch_spmm_bwds(first, n_first, D, s));
         if (n_then) DRC_TRY(launch_spmm_bwds(then, n_then, D, s));
@@ -671,7 +671,7 @@ static int backward_pass(const LayerBwd* g, int n, const dr_heteroconv_weights* 
     part.Nn = 0;
     { ScopedTiming tm(c, kDhCell, s); DRC_TRY(launch_proj_bwd(&part, 1, *W, D, s)); }
     { ScopedTiming tm(c, kBwdPinned, s); DRC_TRY(launch_spmm_dense(&dj[1], dj[1].At ? 1 : 0, D, s)); }
-    if (on_staged_tiles(c)) {
+    if (c->near_plan) {
         ScopedTiming tm(c, kBwdNear, s);
         DRC_TRY(launch_spmm_bwd_planned(c->near_plan, c->dH, cbsr_sets(c, g[0].S).i_near, c->k_near, c->S_cell, 1, s));
     }

@@ -143,6 +143,36 @@ def test_layer_backward_with_a_cell_order_equals_the_layer_without():
     layer.heteroconv_destroy()
 
 
+def test_a_cell_order_of_a_small_graph():
+    """Small graphs with one cell width keep the plain kernel, and heteroconv_set_cell_order says so; with a width of its own `near`
+    is staged.  An order that is no permutation is refused either way."""
+    g = make_graph("tiny", seed=0)
+    rels = [P.device_relation(g.near, P.DR_NORM_MEAN), P.device_relation(g.pins, P.DR_NORM_MEAN),
+            P.device_relation(g.pinned, P.DR_NORM_SYM)]
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    f = lambda *s: torch.randn(*s, device="cuda", generator=gen)         # noqa: E731
+    W = {n: f(64, 64) for n in P.WEIGHT_NAMES}
+    X, dY = (f(g.Nc, 64), f(g.Nn, 64)), (f(g.Nc, 64), f(g.Nn, 64))
+    for ks, staged in (((16, 16, 16), False), ((16, 8, 16), True)):
+        layer = P.HeteroConv(*rels, 64, per_relation=ks)
+        saved = layer.alloc_saved()
+        layer.heteroconv_fwd(*X, W, f(g.Nc, 64), f(g.Nn, 64), saved)
+
+        def backward():
+            dX, dW = (f(g.Nc, 64), f(g.Nn, 64)), {n: f(64, 64) for n in P.WEIGHT_NAMES}
+            layer.heteroconv_bwd(*dY, W, saved, *dX, dW)
+            return [*dX, *dW.values()]
+        plain = backward()
+        assert layer.heteroconv_set_cell_order(dev(g.cell_order)) is staged
+        for a, b in zip(plain, backward()):              # at most 32 destinations a cell: the same order of sums
+            assert torch.equal(a, b)
+        assert np.bincount(g.near.colidx, minlength=g.Nc).max() <= 32
+        with pytest.raises(P.DrError) as e:
+            layer.heteroconv_set_cell_order(dev(np.zeros(g.Nc, np.int32)))
+        assert e.value.code == P.DR_ERR_INVALID_ARG
+        layer.heteroconv_destroy()
+
+
 def test_plan_refusals():
     rng = np.random.default_rng(0)
     lib = P.load()
