@@ -9,6 +9,7 @@
 #include <cstdio>
 
 #include "dr_circuitgnn.h"
+#include "launch_shape.h"
 #include "per_device.h"
 
 namespace drc {
@@ -75,7 +76,6 @@ struct PendingSums {
     int n, count;                 // n = 0: nothing is pending
 };
 // DR-SpMM.  A job is one relation; jobs of one call may share launches and run side by side.
-constexpr int64_t kSmallLaunch = 8 * 24 * 256;   // rows of a launch up to which a wavefront takes 8 of them
 constexpr int kMaxSegs = 18;     // relations per launch (their descriptors travel as kernel arguments)
 struct SpmmFwdJob {
     const dr_csr* A;

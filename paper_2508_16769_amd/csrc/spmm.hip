@@ -594,40 +594,6 @@ __global__ __launch_bounds__(kWPB * kWave, fwd_waves(KPL, false)) void spmm_fwd_
     spmm_fwd_rows<KPL, EPI, 16, false>(args, dk);
 }
 
-// Rows per wavefront.  More of them fill the groups evenly (a group that finishes takes the next row) and are planned at the cost of
-// fewer; fewer of them put more wavefronts on the chip and cut the serial chain of a wavefront (8: one row per group).
-//  * 8 while all wavefronts of a launch are resident at once, 256 compute units x 20 wavefronts; to 49 152 rows where a relation has fewer
-//    rows than columns: nets, whose high-fanout rows are a workgroup's one after the other.  8 / 16 rows, us: 33 000 rows, D = 128,
-//    k = 16, 10 edges per row forward 17.2 / 18.0, backward 17.6 / 18.4; 45 000 rows, k = 32 27.0 / 21.8 and 29.9 / 27.0; 42 000
-//    nets, 42 of them with 200 to 2000 edges, 33 / 45 and 49 / 71.  (8 / 32 rows at 40 000 rows of 20 to 60 edges 51 / 101 and 105 / 114.)
-//  * 16 where the largest relation has no more than 2^19 rows, and for compact sums at any size.  32 / 16 rows, us: near of 60 000 cells,
-//    D = 128, k = 32 forward 34 / 26, backward 41 / 33; 100 000 46 / 41 and 67 / 49; 250 000, k = 8 74 / 61 and 105 / 74; 400 000,
-//    D = 64, k = 16 100 / 92 and 112 / 92; backward of 1.2 M 580 / 530 (near), 430 / 424 (pins), 604 / 586 (pinned).
-//  * 32 above that, where the chip is full anyway (16 / 32: near of 1.2 M cells forward 436 / 412, with 8 edges per row 238 / 222; the
-//    layer's relations together, D = 64, forward 1 308 / 1 283, backward with dense rows 1 536 / 1 518), and for forward rows of less than
-//    nine edges, where a wavefront's plan weighs most, as soon as wavefronts of 16 are not resident at once (16 / 32: pinned, 3.9
-//    edges per row, 80 000 rows 20 / 22, 100 000, k = 8 24 / 21, 250 000 64 / 61; near with 8 edges per row, 250 000 58 / 51, 450 000
-//    98 / 90).  Not for nets, whose rows differ most: 5.5 edges on average, 175 000 nets 75 / 83, 300 000 112 / 118.
-// The adaptive forward keeps 8 and 32 (16 at 250 000 rows: near 91 / 97, pins 86 / 82, pinned 64 / 61).
-// Where 8 do not pay: a forward at D >= 256 or k = 128 with a few edges per row (D = 256, k = 32: 25 / 20 with 32, but 81 / 110 with 20 to
-// 60 edges; there is a row buffer per group to clear, whatever the row brings).
-struct LaunchShape {
-    int64_t rows = 0, most = 0, nnz = 0;
-    bool nets = false;
-    void add(int64_t n_rows, int64_t n_cols, int64_t n) {
-        rows += n_rows;
-        most = n_rows > most ? n_rows : most;
-        nnz += n;
-        nets = nets || n_rows < n_cols;
-    }
-    static constexpr int64_t resident(int rows_per_wave) { return (int64_t)rows_per_wave * 20 * 256; }
-    bool eight() const { return rows <= (nets ? kSmallLaunch : resident(8)); }
-    int forward() const { return eight() ? 8 : (!nets && nnz < 9 * rows ? rows <= resident(16) : most <= int64_t(1) << 19) ? 16 : 32; }
-    int forward_adaptive() const { return rows <= kSmallLaunch ? 8 : 32; }
-    int compact() const { return eight() ? 8 : 16; }
-    int dense() const { return eight() ? 8 : most <= int64_t(1) << 19 ? 16 : 32; }
-};
-
 static int fwd_kind(const SpmmFwdJob& j) {
     const int k = j.k;
     int kpl = 0;
@@ -1159,14 +1125,14 @@ template <int KPL, int EPI, int RW, bool ADAPT, bool DENSE>
 __global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, ADAPT, DENSE)) void spmm_bwd_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
     spmm_bwd_rows<KPL, EPI, RW, ADAPT, DENSE>(args, dk, tail);
 }
-template <int KPL, int EPI>
-__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, false, true)) void spmm_bwd_mid_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
-    spmm_bwd_rows<KPL, EPI, 16, false, true>(args, dk, tail);
+template <int KPL, int EPI, bool ADAPT, bool DENSE>
+__global__ __launch_bounds__(kWPB * kWave, bwd_waves(KPL, ADAPT, DENSE)) void spmm_bwd_mid_kernel(SpmmBwdArgs args, DegreeK dk, SumTail tail) {
+    spmm_bwd_rows<KPL, EPI, 16, ADAPT, DENSE>(args, dk, tail);
 }
 
 template <int KPL, int EPI, bool ADAPT, bool DENSE>
 static void launch_bwd_kernel(SpmmBwdArgs& a, const LaunchShape& shape, DegreeK dk, hipStream_t s, const PendingSums& sums = PendingSums{}) {
-    const int rw = DENSE ? shape.dense() : shape.compact();
+    const int rw = DENSE ? shape.dense(a.D) : shape.compact(a.D);
     int first = 0;
     for (int i = 0; i < a.n; ++i) {
         SpmmBwdSeg& g = a.s[i];
@@ -1189,12 +1155,10 @@ static void launch_bwd_kernel(SpmmBwdArgs& a, const LaunchShape& shape, DegreeK 
     };
     if (rw == 8) {
         hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 8, ADAPT, DENSE>), grid, block, lds(bwd_wave_words<KPL, 8, DENSE>(a.D)), s, a, dk, tail);
-    } else if constexpr (!DENSE) {
-        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 16, ADAPT, false>), grid, block, lds(bwd_wave_words<KPL, 16, false>(a.D)), s, a, dk, tail);
     } else if (rw == 16) {
-        hipLaunchKernelGGL((spmm_bwd_mid_kernel<KPL, EPI>), grid, block, lds(bwd_wave_words<KPL, 16, true>(a.D)), s, a, dk, tail);
-    } else {
-        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, true>), grid, block, lds(bwd_wave_words<KPL, 32, true>(a.D)), s, a, dk, tail);
+        hipLaunchKernelGGL((spmm_bwd_mid_kernel<KPL, EPI, ADAPT, DENSE>), grid, block, lds(bwd_wave_words<KPL, 16, DENSE>(a.D)), s, a, dk, tail);
+    } else if constexpr (DENSE || KPL < 8) {      // (compact: rows of D <= 32 only, k <= 32 then)
+        hipLaunchKernelGGL((spmm_bwd_kernel<KPL, EPI, 32, ADAPT, DENSE>), grid, block, lds(bwd_wave_words<KPL, 32, DENSE>(a.D)), s, a, dk, tail);
     }
 }
 

@@ -581,8 +581,9 @@ def test_batched_model_with_one_k_per_edge_type():
         c.heteroconv_destroy()
 
 
-@pytest.mark.parametrize("n_graphs,by_itself", [(18, ()), (16, ()), (4, (1,)), (3, (0, 2))],
-                         ids=["more_than_one_launch_takes", "one_full_launch", "one_by_itself", "first_and_last_by_themselves"])
+@pytest.mark.parametrize("n_graphs,by_itself", [(18, ()), (16, ()), (13, ()), (12, ()), (4, (1,)), (3, (0, 2))],
+                         ids=["more_than_one_launch_takes", "one_full_launch", "gradients_in_two_launches", "gradients_in_one_launch",
+                              "one_by_itself", "first_and_last_by_themselves"])
 def test_shared_launches_equal_a_launch_per_subgraph(n_graphs, by_itself):
     """Sub-graphs whose launches are shared against the same sub-graphs with launches of their own: the last layer's
     selections, predictions and gradients per cell are the same numbers, sums over rows agree up to their order."""

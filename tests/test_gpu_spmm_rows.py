@@ -1,4 +1,4 @@
-"""DR-SpMM where its row dispatch changes: the row counts at which a wavefront goes from 8 rows to 32, and row lengths at
+"""DR-SpMM where its row dispatch changes: the row counts at which a wavefront goes from 8 rows to 16 and 32, and row lengths at
 which a row passes from one lane group to a wavefront (32) and to a whole workgroup (256)."""
 import numpy as np
 import pytest
@@ -11,7 +11,8 @@ from gpu_util import assert_elem_bound, assert_row_bound, dev, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,D,k", [(33, 32, 8), (1000, 100, 25), (49_152, 64, 16), (49_153, 64, 16), (49_153, 64, 40)])
+@pytest.mark.parametrize("M,D,k", [(33, 32, 8), (1000, 100, 25), (49_152, 64, 16), (49_153, 64, 16), (49_153, 64, 40),
+                                   (40_960, 64, 16), (40_961, 64, 16), (102_401, 32, 8)])
 def test_row_lengths_at_the_dispatch_edges(M, D, k):
     say(f"spmm rows M={M} D={D} k={k}")
     rng = np.random.default_rng(M + k)
