@@ -327,7 +327,7 @@ SCHEDULE_DR = (
     ("dr_spmm_fwd.pins", "spmm_fwd"), ("dr_spmm_bwd.pins", "spmm_bwd"),
     ("dr_topk.net", "topk_"), ("dr_spmm_fwd.pinned", "spmm_fwd"), ("dr_spmm_bwd.pinned", "spmm_bwd"),
 )
-HOT = ("topk_", "spmm_fwd", "spmm_bwd", "proj_kernel", "wgrad_partial", "wgrad_reduce")
+HOT = ("topk_", "spmm_fwd", "spmm_bwd", "proj_kernel", "wgrad_partial", "wgrad_reduce", "dense_bwd")
 
 
 def per_kernel_kib(path: str, SCHEDULE=SCHEDULE) -> dict:
