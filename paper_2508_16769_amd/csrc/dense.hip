@@ -14,8 +14,8 @@
 // rounding, which an fp32 multiply-add commits for every term anyway.  The leading products x1 y1 and the five small ones
 // have accumulators of their own: the small sum is added once, with one rounding, and it can be left out where the leading
 // one is not finite, so that infinite and overflowing products are what they are in fp32 (with_small).
-// Six bf16 products run at 250 .. 300 TFLOP/s of fp32 work, above what memory feeds these kernels, so they are bound by HBM
-// now: every operand is read once for all the products it takes part in.
+// Six bf16 products run at 250 .. 300 TFLOP/s of fp32 work.  Every operand is read once for all the products it takes part in: memory
+// is then no longer what these kernels wait for, but the issue of vector and matrix instructions is (below).
 //
 // Layouts.  The 16x16x32 instruction takes eight consecutive contraction indices per lane, as one 16-byte register
 // group.  LDS holds the operand tile in exactly those units, one plane per part.  The contraction index is permuted
@@ -87,7 +87,8 @@ template <int D> __device__ __forceinline__ int unit_of(int t) {
 // Half, so that no finite number rounds up to an infinite first part; kUnscale takes a sum of products back.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-constexpr float kScale = 0.5f, kUnscale = 4.0f;
+constexpr float kScale = 0.5f;
+static_assert(kScale * kScale * kUnscale == 1.0f);
 struct Split8 { bf16x8 p[3]; };
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
@@ -1028,7 +1029,7 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void dense_bwd_kernel(DenseBwd
 }
 
 // dW[i] = sum over a side's partials in a fixed order: wavefront w of the workgroup sums partials w, w + 16, ... of 64 x 4
-// consecutive entries, then the 16 sums are added in order.  In 64 bits: up to 256 partials of nearly equal size lose as much
+// consecutive entries, then the 16 sums are added in order.  In 64 bits: up to 1024 partials of nearly equal size lose as much
 // in 32-bit sums as everything before.  One launch for all products of all sides and graphs.
 constexpr int kRedWaves = 16;
 typedef double f64x4 __attribute__((ext_vector_type(4)));

@@ -64,7 +64,9 @@ struct TopkJob {
     uint16_t* idx2;
 };
 int launch_topks(const TopkJob* jobs, int n, int D, hipStream_t s);
-// A weight gradient whose partial sums wait in scratch memory: dst[at] = 4 * sum over i < n of src[i * count + at], at < count.
+// The dense products halve their operands: kUnscale takes a sum of products back.
+constexpr float kUnscale = 4.0f;
+// A weight gradient whose partial sums wait in scratch memory: dst[at] = kUnscale * sum over i < n of src[i * count + at], at < count.
 struct PartialSum {
     const float* src;
     float* dst;

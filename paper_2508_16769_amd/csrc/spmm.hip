@@ -890,7 +890,8 @@ template <int KPL, int RW, bool DENSE> constexpr int bwd_wave_words(int D) {    
 
 // Partial sums of weight gradients, in workgroups behind those of the rows: 64 entries of one gradient each.  They need a few
 // microseconds of loads one behind the other, which pass under the last rows; as a launch of their own they took 5 to 7
-// (layers of 2 048 to 60 000 cells).  64 bits: up to 256 partials of nearly equal size lose as much in 32-bit sums as everything before.
+// (layers of 2 048 to 60 000 cells).  64 bits: up to 1024 partials (256 workgroups of 4 at D = 32) of nearly equal size lose as much in
+// 32-bit sums as everything before.
 constexpr int kSumEntries = kWave;
 __device__ __forceinline__ void sum_partials(const PartialSum* __restrict__ table, int per, int block, double* sums) {
     const PartialSum p = table[block / per];
@@ -919,7 +920,7 @@ __device__ __forceinline__ void sum_partials(const PartialSum* __restrict__ tabl
     if (wave == 0) {
 #pragma unroll
         for (int w = 1; w < kWPB; ++w) s += sums[w * kWave + lane];
-        p.dst[at] = (float)(4.0 * s);
+        p.dst[at] = (float)((double)kUnscale * s);
     }
 }
 constexpr size_t kSumLds = sizeof(double) * kWPB * kWave;
