@@ -24,7 +24,8 @@ constexpr int64_t kSmallLaunch = 8 * 24 * 256;   // rows of a launch with nets u
 //    280 000 77 / 78; 6.6 edges, hubs among them, 86 000 41 / 41, 144 000 53 / 62, 288 000 100 / 101.
 //    Forward, relations sharing a launch (whole passes).  Up to 163 840 rows 16 gain at any degree: training steps of two sub-graphs 590 /
 //    601, layers of 60 000 cells 125 / 128 to 355 / 363.  Up to 409 600 from six edges per row on: training on six sub-graphs of 6.3 edges
-//    1 320 / 1 338, of 5.6 edges 1 189 / 1 172; layers of 130 000 cells 538 / 551.  Above that from seven and a half on: training on eight
+//    1 320 / 1 338, of 5.6 edges 1 189 / 1 172; layers of 130 000 cells 538 / 551 (from nine on without nets, as in a model's last layer: the
+//    launch of eight sub-graphs, 320 000 rows of 6.8 edges, 82 / 80).  Above that from seven and a half on: training on eight
 //    sub-graphs of 6.3 edges 1 603 / 1 585, layers of 300 000 cells of 7.6 1 220 / 1 234, of 7.0 527 / 516 (D = 32, 64) and 1 078 / 1 074.
 //    Backward with dense rows: D = 32 layers of 130 000 / 180 000 / 250 000 / 450 000 cells 259 / 265, 340 / 333, 348 / 342, 753 / 729; D = 64
 //    250 000 / 450 000 552 / 549, 1 129 / 1 111, training on eight sub-graphs 858 / 867; D = 128 up to 2^19 rows as fast or faster (1 087 / 1 094).
@@ -49,8 +50,8 @@ struct LaunchShape {
     int forward() const {
         if (eight()) return 8;
         if (most > int64_t(1) << 19) return 32;
-        if (relations > 1) return rows <= resident(32) || (nnz >= 6 * rows && rows <= resident(80)) || 2 * nnz >= 15 * rows ? 16 : 32;
         const bool few = nnz < (nets ? 6 : 9) * rows;
+        if (relations > 1) return rows <= resident(32) || (!few && (rows <= resident(80) || 2 * nnz >= 15 * rows)) ? 16 : 32;
         return !few || rows <= resident(16) || (nets && rows > resident(32)) ? 16 : 32;
     }
     int forward_adaptive() const { return rows <= kSmallLaunch ? 8 : 32; }

@@ -59,6 +59,10 @@ int main() {
     EXPECT(layer(8 * 20000, 8 * 14000, 8 * 200000, 8 * 70000).forward(), 32);
     EXPECT(layer(8 * 20000, 8 * 14000, 8 * 160000, 8 * 70000).forward(), 32);
     EXPECT(layer(250000, 180000, 3000000, 1180000).forward(), 16);
+    // the last layer of a model: no nets
+    EXPECT(shape({{46000, 46000, 460000}, {46000, 32000, 160000}}).forward(), 16);
+    EXPECT(shape({{160000, 160000, 1600000}, {160000, 112000, 560000}}).forward(), 32);
+    EXPECT(shape({{160000, 160000, 9 * 320000}, {160000, 112000, 0}}).forward(), 16);
     EXPECT(layer(524288, 100000, 12 * 524288, 1500000).forward(), 16);
     EXPECT(layer(524289, 100000, 12 * 524289, 1500000).forward(), 32);
     // dense backward: narrow rows (250 000 cells, D = 32: 348 us with 16 rows, 342 with 32) and 2^19 rows
