@@ -33,7 +33,7 @@
 // instructions out for 8 of them; LDS reads come at 256 bytes a clock, writes at 80.  Forward projection of 250 000 cells and
 // 180 000 nets: 204 -> 191 us with fragments read ahead, conflict-free places in LDS and graph descriptors in registers;
 // global memory is no longer what it waits for (without any loads and stores 188).  Vector and matrix instructions of a SIMD's two
-// wavefronts take turns for the most part: 202 -> 192 (a launch each) with 385 -> 330 vector instructions per wavefront and tile of cells (the scattered
+// wavefronts take turns for the most part: 202 -> 192 (a launch each) with 382 -> 296 vector instructions per wavefront and tile of cells (the scattered
 // operand in units of eight neighbouring columns, cleared without a loop) and matrix instructions issued first.  Not kept: blocks of
 // 256 rows whose operands stay in registers while the weights pass by in LDS (1.2 M cells 660 -> 758: a barrier every 16 columns, and
 // more splitting in all); wavefronts with 32 columns and
@@ -748,8 +748,8 @@ __global__ __launch_bounds__(Tile<D>::THREADS, 2) void dproj_kernel(ProjBwdArgs<
 // column.  A wavefront is alone in needing its 16 columns of H, so those go from memory to registers; what all wavefronts
 // need (dZ, and the scattered CBSR) goes through LDS.  Partial sums go to scratch and are added by a second kernel in a fixed order.
 // What bounds it is issue: vector and matrix instructions of a SIMD's two wavefronts take turns for the most part, and a chunk has
-// 144 matrix and about 440 vector instructions per wavefront (cells, D = 128).  1.2 M cells of D = 128: 775 -> 673 us (3.3 TB/s) with
-// 551 -> 440 vector instructions (small sums are cut to finite numbers only where an operand calls for it), three chains of small
+// 144 matrix and 469 vector instructions per wavefront (counters; cells, D = 128).  1.2 M cells of D = 128: 775 -> 673 us (3.3 TB/s) with
+// 576 -> 469 vector instructions (small sums are cut to finite numbers only where an operand calls for it), three chains of small
 // products instead of two and one, and matrix instructions issued first; without any loads it takes 504.
 // ---------------------------------------------------------------------------------------------------
 template <int D> struct WTile {
@@ -779,8 +779,8 @@ template <int G> struct WgradArgs {           // of up to G graphs
 static_assert(sizeof(WgradArgs<kMaxGraphs>) < 4096, "kernel arguments");
 
 // The small sums are cut to finite numbers (as with_small does) in chunks that hold a number of kWide or more: below it a small sum
-// is less than 32 * 5 * 2^(2 * 62 - 9) and finite.  A not-a-number needs no cut: it makes the leading sum one as well.  Cut always, 96
-// of 500 vector instructions, 1.2 M cells and 250 000 take 0.7 and 1.6 % longer (backward passes 2 512 / 2 500, 532 / 523 us); left to a
+// is less than 32 * 5 * 2^(2 * 62 - 9) and finite.  A not-a-number needs no cut: it makes the leading sum one as well.  Cut always (96
+// vector instructions, 18 to find out), 1.2 M cells and 250 000 take 0.7 and 1.6 % longer (backward passes 2 512 / 2 500, 532 / 523 us); left to a
 // second walk of the workgroups whose sums are not finite, a single infinity cost 2 500 -> 2 790 and 523 -> 640.
 constexpr float kWide = 4611686018427387904.0f;         // 2^62
 // the largest of m >= 0, |a| and |b|, not-a-numbers aside

@@ -1,5 +1,7 @@
 """The backward's shared launches -- weight gradients beside projections, their partial sums behind the last rows of the transposed
-DR-SpMM -- against a launch of its own for every step: the same bits, whatever the widths leave to which launch."""
+DR-SpMM -- against a launch of its own for every step: the same bits, whatever the widths leave to which launch.  (Small layers, where a
+workgroup has one chunk of rows either way, and one of which either side fills the chip; in between the sides share workgroups and the
+weight gradients differ by the order of their sums, tests/test_gpu_rows_per_wavefront.py.)"""
 import numpy as np
 import pytest
 import torch
