@@ -150,7 +150,9 @@ int launch_spmm_bwd_planned(const dr_spmm_plan* p, const float* dH, const uint16
                             hipStream_t s);
 
 constexpr int kMaxGraphs = 16;    // graphs per launch (their descriptors travel as kernel arguments)
-constexpr int64_t kFullLaunch = int64_t(1) << 26;   // elements of a node type's rows from which on sub-graphs of a batch share no launches
+// elements of a node type's rows from which on it fills the chip: sub-graphs of a batch share no launches, and cells and nets no workgroups
+// for their weight gradients
+constexpr int64_t kFullLaunch = int64_t(1) << 26;
 
 // shape of a layer context (heteroconv.hip owns the struct)
 struct HeteroDims {

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 # rows, columns, most edges of a row, bounds of edges per row (20 % of the rows are empty)
 SHAPES = [(40_960, 3_000, 11, 0, 9), (40_961, 3_000, 11, 0, 9), (49_152, 50_001, 5, 0, 6), (49_153, 50_001, 5, 0, 6),
-          (81_920, 900, 14, 0, 9), (81_921, 900, 14, 0, 9), (81_921, 900, 28, 9, 99), (81_921, 90_000, 5, 0, 6), (90_000, 99_000, 18, 6, 99)]
+          (81_920, 900, 14, 0, 9), (81_921, 900, 14, 0, 9), (81_921, 900, 3, 0, 9), (82_017, 900, 14, 0, 9),
+          (81_921, 900, 28, 9, 99), (81_921, 90_000, 5, 0, 6), (90_000, 99_000, 18, 6, 99)]
 LARGE = [(102_400, 800, 8, 0, 6), (102_401, 800, 8, 0, 6), (102_401, 800, 18, 6, 9), (163_840, 170_000, 5, 0, 6), (163_841, 170_000, 5, 0, 6),
          (524_288, 70, 28, 9, 99), (524_289, 70, 28, 9, 99), (524_289, 70, 12, 0, 6)]
 CASES = [(s, w) for s in SHAPES for w in ((32, 8), (64, 25), (128, 32))] + [(s, w) for s in LARGE for w in ((32, 8), (32, 16))] + [(LARGE[5], (64, 25))]
