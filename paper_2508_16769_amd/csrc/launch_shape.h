@@ -21,7 +21,8 @@ constexpr int64_t kSmallLaunch = 8 * 24 * 256;   // rows of a launch with nets u
 //    degrees at D = 64 and less lose up to a tenth past 300 000 rows: 350 000, k = 16 109 / 101.)  Less than nine: 80 000 rows 26 / 25,
 //    120 000 31 / 25, 250 000, D = 64 45 / 39, so 32 as soon as wavefronts of 16 are not resident at once.  Nets differ most among their rows
 //    and gain again when wavefronts of 32 are not resident either: 5 edges 84 000 nets 29 / 25, 112 000 35 / 32, 175 000 50 / 52,
-//    280 000 77 / 78; 6.6 edges, hubs among them, 86 000 41 / 41, 144 000 53 / 62, 288 000 100 / 101.
+//    280 000 77 / 78; 6.6 edges, hubs among them, 86 000 41 / 41, 144 000 53 / 62, 288 000 100 / 101.  Rows wider than 128 have larger row
+//    buffers and fewer wavefronts resident: 60 000 rows of 3.5 edges, k = 32 D = 256 26 / 21, D = 512, k = 48 61 / 54; of 8 edges, D = 256 23 / 20.
 //    Forward, relations sharing a launch (whole passes).  Up to 163 840 rows 16 gain at any degree: training steps of two sub-graphs 590 /
 //    601, layers of 60 000 cells 125 / 128 to 355 / 363.  Up to 409 600 from six edges per row on: training on six sub-graphs of 6.3 edges
 //    1 320 / 1 338, of 5.6 edges 1 189 / 1 172; layers of 130 000 cells 538 / 551 (from nine on without nets, as in a model's last layer: the
@@ -45,14 +46,19 @@ struct LaunchShape {
         ++relations;
         nets = nets || n_rows < n_cols;
     }
-    static constexpr int64_t resident(int rows_per_wave) { return (int64_t)rows_per_wave * 20 * 256; }
+    // rows of as many wavefronts as fit 256 compute units at once: 20 each by their registers, fewer where four wavefronts' row buffers
+    // of 8 x (D + 4) words and plans take more than a fifth of 160 KB
+    static constexpr int64_t resident(int rows_per_wave, int D = 128) {
+        const int groups = (160 << 10) / (16 * (8 * (D + 4) + 564));
+        return (int64_t)rows_per_wave * 4 * (groups < 5 ? (groups < 1 ? 1 : groups) : 5) * 256;
+    }
     bool eight() const { return rows <= (nets ? kSmallLaunch : resident(8)); }
-    int forward() const {
+    int forward(int D) const {
         if (eight()) return 8;
         if (most > int64_t(1) << 19) return 32;
         const bool few = nnz < (nets ? 6 : 9) * rows;
-        if (relations > 1) return rows <= resident(32) || (!few && (rows <= resident(80) || 2 * nnz >= 15 * rows)) ? 16 : 32;
-        return !few || rows <= resident(16) || (nets && rows > resident(32)) ? 16 : 32;
+        if (relations > 1) return rows <= resident(32, D) || (!few && (rows <= resident(80, D) || 2 * nnz >= 15 * rows)) ? 16 : 32;
+        return !few || rows <= resident(16, D) || (nets && rows > resident(32, D)) ? 16 : 32;
     }
     int forward_adaptive() const { return rows <= kSmallLaunch ? 8 : 32; }
     int compact(int D) const { return eight() ? 8 : D <= 32 && nnz < 6 * rows && rows > resident(20) ? 32 : 16; }

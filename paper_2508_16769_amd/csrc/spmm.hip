@@ -609,7 +609,7 @@ static int fwd_kind(const SpmmFwdJob& j) {
 
 template <int KPL, int EPI, bool ADAPT>
 static void launch_fwd_kernel(SpmmFwdArgs& a, const LaunchShape& shape, DegreeK dk, hipStream_t s) {
-    const int rw = ADAPT ? shape.forward_adaptive() : shape.forward();
+    const int rw = ADAPT ? shape.forward_adaptive() : shape.forward(a.D);
     int first = 0;
     for (int i = 0; i < a.n; ++i) {
         SpmmFwdSeg& g = a.s[i];

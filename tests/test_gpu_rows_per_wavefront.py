@@ -18,6 +18,7 @@ SHAPES = [(40_960, 3_000, 11, 0, 9), (40_961, 3_000, 11, 0, 9), (49_152, 50_001,
 LARGE = [(102_400, 800, 8, 0, 6), (102_401, 800, 8, 0, 6), (102_401, 800, 18, 6, 9), (163_840, 170_000, 5, 0, 6), (163_841, 170_000, 5, 0, 6),
          (524_288, 70, 28, 9, 99), (524_289, 70, 28, 9, 99), (524_289, 70, 12, 0, 6)]
 CASES = [(s, w) for s in SHAPES for w in ((32, 8), (64, 25), (128, 32))] + [(s, w) for s in LARGE for w in ((32, 8), (32, 16))] + [(LARGE[5], (64, 25))]
+CASES += [((M, 900, 8, 0, 9), (256, 32)) for M in (49_152, 49_153)]      # wide rows: fewer wavefronts resident
 
 
 @pytest.mark.parametrize("shape,width", CASES, ids=[f"{s[0]}x{s[1]}_deg{s[2]}_D{w[0]}_k{w[1]}" for s, w in CASES])
